@@ -356,44 +356,45 @@ hipError_t attention_dispatch<bf16>(const bf16* q, const int* row_pos, const int
 
 template <typename T>
 hipError_t gemm_any(const T* a, const T* wt, const T* wt2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
-                    float* partial, hipStream_t st, const int* m_live = nullptr);
+                    float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 template <>
 hipError_t gemm_any<float>(const float* a, const float* wt, const float* wt2, void* c, int m, int n, int k, int ldc,
-                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live) {
-  return launch_gemm<float>(a, wt, wt2, c, m, n, k, ldc, epi, st, m_live);
+                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live, int m_expected) {
+  return launch_gemm<float>(a, wt, wt2, c, m, n, k, ldc, epi, st, m_live, m_expected);
 }
 template <>
 hipError_t gemm_any<bf16>(const bf16* a, const bf16* wt, const bf16* wt2, void* c, int m, int n, int k, int ldc,
-                          GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live) {
-  return launch_gemm_bf16(a, wt, wt2, c, m, n, k, ldc, epi, partial, st, m_live);
+                          GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
+  return launch_gemm_bf16(a, wt, wt2, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
 }
 template <typename T>
 hipError_t gemm_qkv_any(const T* a, const T* wq, int nq, const T* wk, const T* wv, int nkv, float* c, int m, int k,
-                        float* partial, hipStream_t st, const int* m_live);
+                        float* partial, hipStream_t st, const int* m_live, int m_expected);
 template <>
 hipError_t gemm_qkv_any<float>(const float* a, const float* wq, int nq, const float* wk, const float* wv, int nkv,
-                               float* c, int m, int k, float*, hipStream_t st, const int* m_live) {
-  return launch_gemm_qkv<float>(a, wq, nq, wk, wv, nkv, c, m, k, st, m_live);
+                               float* c, int m, int k, float*, hipStream_t st, const int* m_live, int m_expected) {
+  return launch_gemm_qkv<float>(a, wq, nq, wk, wv, nkv, c, m, k, st, m_live, m_expected);
 }
 template <>
 hipError_t gemm_qkv_any<bf16>(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                              int m, int k, float* partial, hipStream_t st, const int* m_live) {
-  return launch_gemm_qkv_bf16(a, wq, nq, wk, wv, nkv, c, m, k, partial, st, m_live);
+                              int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected) {
+  return launch_gemm_qkv_bf16(a, wq, nq, wk, wv, nkv, c, m, k, partial, st, m_live, m_expected);
 }
 
 // Partial-attention slots the sparse phase (and the phase after it) may use when the threshold selector decides the
 // row counts on the device: planned for a nominal selection of a fifth of every segment, with room for twice that;
 // a selection that needs more attends unsplit.
-struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int cap[PH_COUNT]; };
+struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int cap[PH_COUNT]; int rows[PH_COUNT]; };
 ThresholdSplit plan_threshold_split(const ReqTable& base, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos, bool bf16_model) {
   ThresholdSplit ts;
-  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.cap[p] = 0; }
+  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.cap[p] = 0; ts.rows[p] = 0; }
   if (!bf16_model) return ts;
   for (int p = PH_C; p <= PH_D; ++p) {
     ReqTable t = base;
     for (int b = 0; b < t.n_req; ++b)
       if (t.r[b].k > 0) t.r[b].k = std::max(1, t.r[b].S / 5);
     fill_phase_table(&t, p, nullptr, tile_rows);
+    ts.rows[p] = t.total_rows;
     AttnSplit sp = choose_phase_split(&t, n_kv_heads, n_q_heads, tile_rows, max_pos);
     if (sp.n_chunks <= 1) continue;
     for (int b = 0; b < t.n_req; ++b)
@@ -430,6 +431,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
   // Row counts of the phase: exact on the host, or (threshold selector, from the sparse phase on) an upper bound
   // that sizes the grids while the kernels read the live counts from the device table.
   auto live = [&](int ph) -> const int* { return on_device[ph] ? &(w.tables + ph)->total_rows : nullptr; };
+  int expected_rows[PH_COUNT] = {0, 0, 0, 0};   // of a phase whose count is on the device: what the GEMM tiles are chosen for
   auto enter_phase = [&](Phase ph) -> rc_status {
     if (!on_device[ph]) {
       fill_phase_table(&tabs[ph], ph, cur >= 0 ? &tabs[cur] : nullptr, tile_rows);
@@ -500,6 +502,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
           for (int p = PH_C; p <= PH_D; ++p) {
             fill_phase_table(&tabs[p], p, &tabs[phase_before], tile_rows);
             splits[p] = ts.sp[p];
+            expected_rows[p] = ts.rows[p];
             if (attention_partial_floats(splits[p].total_slots, d.n_q_heads) > w.attn_part_floats) splits[p] = attention_no_split();
             // work items of the attention grid, as an upper bound over every possible selection: all tiles whole, or
             // the tiles that stay whole plus as many (tile, chunk) pairs as there are slots
@@ -527,12 +530,13 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     const int rows = tabs[cur].total_rows;
     if (rows == 0) continue;
     const int* m_live = live(cur);
+    const int rows_expected = m_live ? expected_rows[cur] : rows;
     if (l == job.capture_layer) RC_LAUNCH(PC_ROWS, launch_capture_rows<T>(w.tables + cur, rows, w.h[hbuf], w.row_req, D, st));
 
     float* h = w.h[hbuf];
     RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_attn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
     RC_LAUNCH(PC_GEMM_QKV, gemm_qkv_any<T>((const T*)w.a, (const T*)lw.wq, nq, (const T*)lw.wk, (const T*)lw.wv, nkv,
-                                              w.qkv, rows, D, w.gemm_part, st, m_live));
+                                              w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
     // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
     RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
                                   (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
@@ -551,10 +555,10 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     if (job.any_inf)
       RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.max_pos, job.inf,
                                                       w.inf_scratch, scores_from_attention, st));
-    RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live));
+    RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
     RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_ffn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
-    RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live));
-    RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live));
+    RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
+    RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
   }
 
   // first-token logits from the last position of each request
@@ -698,7 +702,7 @@ rc_status rc_model_create(const rc_model_desc* desc, const rc_layer_w* layers, c
 }
 
 rc_status rc_tune_set(int32_t key, int32_t value) {
-  if (key == RC_TUNE_GEMM_TILE && (value == 0 || value == 1 || value == 2 || value == 3 || value == 5 || value == 6 || value == 7)) {
+  if (key == RC_TUNE_GEMM_TILE && (value == 0 || value == 1 || value == 2 || value == 3 || (value >= 5 && value <= 13))) {
     set_gemm_tile(value);
     return RC_OK;
   }

@@ -282,11 +282,11 @@ hipError_t launch_rmsnorm(const float* h, const T* gain, T* out, int rows, int d
 
 enum GemmEpilogue : int { EPI_STORE_F32 = 0, EPI_STORE_T = 1, EPI_ADD_F32 = 2, EPI_SWIGLU_T = 3 };
 // C[M][ldc] (op)= A[M][K] * W[N][K]^T ; W2 only for EPI_SWIGLU_T (gate = W, up = W2)
-// m_live (optional, device): the live row count when m is only an upper bound (rows selected on the device);
+// m_live (optional, device): the live row count when m is only an upper bound (rows selected on the device); m_expected: the row count to plan for then (0: m)
 // the launch then covers m rows' worth of tiles and workgroups past the live rows leave at once
 template <typename T>
 hipError_t launch_gemm(const T* a, const T* w, const T* w2, void* c, int m, int n, int k, int ldc,
-                       GemmEpilogue epi, hipStream_t st, const int* m_live = nullptr);
+                       GemmEpilogue epi, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 
 // few-row variant (M <= 32, weights streamed once); columns < ns1 come from w, < ns2 from w2, the rest from w3
 bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2);
@@ -297,19 +297,19 @@ hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2,
 // C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T
 template <typename T>
 hipError_t launch_gemm_qkv(const T* a, const T* wq, int nq, const T* wk, const T* wv, int nkv, float* c, int m,
-                           int k, hipStream_t st, const int* m_live = nullptr);
+                           int k, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.
 size_t gemm_partial_bytes();
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live = nullptr);
+                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                                int m, int k, float* partial, hipStream_t st, const int* m_live = nullptr);
+                                int m, int k, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 void set_gemm_xcd_remap(int on);
 int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool with_partial, int* n_blocks_out);
 void set_gemm_thin_tiles(int on);   // 1: a ragged last tile row of at most 64 rows goes to the thin tile body
-void set_gemm_tile(int t);  // 0: by shape; 1-3 register-staged tiles; 5-7 direct-to-LDS tiles (bf16 MFMA GEMM)
+void set_gemm_tile(int t);  // 0: by shape; 1-3 register-staged tiles; 5-13 direct-to-LDS tiles (bf16 MFMA GEMM)
 
 template <typename T>
 hipError_t launch_rope_scatter(const float* qkv, int n_rows, const int* row_pos, const int* row_req,

@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "common.h"
+#include "gemm_pipe.h"
 
 namespace rc {
 
@@ -310,6 +311,16 @@ __device__ inline void store_tile16(const f32x4 (&acc)[FM][FN], void* __restrict
   }
 }
 
+// raw accumulators of a K part, register-major so that consecutive lanes write consecutive 16-byte groups
+template <int FM, int FN, int NT>
+__device__ inline void store_partial(const f32x4 (&acc)[FM][FN], float* __restrict__ partial, int part_slot, int tid) {
+  f32x4* dst = reinterpret_cast<f32x4*>(partial) + (size_t)part_slot * (FM * FN) * NT + tid;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) dst[(size_t)(i * FN + j) * NT] = acc[i][j];
+}
+
 // One output tile (or one K part of it): the work of a workgroup once it knows its tile.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool DUAL>
 __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const bf16* __restrict__ w,
@@ -444,18 +455,28 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
   }
 
   if (part_slot >= 0) {
-    // raw accumulators, register-major so that consecutive lanes write consecutive floats
-    constexpr int NT = NW * 64;
-    float* dst = partial + (size_t)part_slot * (FM * FN * 4) * NT + tid;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dst[(size_t)((i * FN + j) * 4 + e) * NT] = acc[i][j][e];
+    store_partial<FM, FN, NW * 64>(acc, partial, part_slot, tid);
     return;
   }
   store_tile16<FM, FN, WTM, WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane);
+}
+
+// The same on the pipelined main loop of gemm_pipe.h; partial sums in the layout of gemm_tile_body.
+template <typename T, bool DUAL>
+__device__ __forceinline__ void gemm_pipe_body(const bf16* __restrict__ a, const bf16* __restrict__ w,
+                                               const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
+                                               void* __restrict__ c, int m, int n, int k, int ldc, int epi, int m0, int n0,
+                                               int k_begin, int k_end, int part_slot, float* __restrict__ partial) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  f32x4 acc[T::FM][T::FN];
+  gemm_pipe_loop<T, DUAL>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (part_slot >= 0) {
+    store_partial<T::FM, T::FN, 512>(acc, partial, part_slot, tid);
+    return;
+  }
+  store_tile16<T::FM, T::FN, T::WTM, T::WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wave / T::WN, wave % T::WN, lane);
 }
 
 // What the launch's grid does.  Workgroups [0, n_full_wgs) each own one of the first full_tiles output tiles
@@ -515,12 +536,31 @@ __device__ __host__ inline BlockWork block_work(const GridPlan& g, int bid, int 
   return bw;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool DUAL, int OCC, bool THIN>
-__global__ void __launch_bounds__(WAVES_M * WAVES_N * 64, OCC)
+// Tile types of the direct-to-LDS kernels: the pipelined ones (eight wavefronts) and the 128x128 tile of four wavefronts.
+struct Tile128 {
+  static constexpr int WM = 2, WN = 2, FM = 4, FN = 4, WTM = 64, WTN = 64, BM = 128, BN = 128, NT = 256;
+  static constexpr int LDS_BYTES = 2 * (BM + BN) * 128;
+  static constexpr int OCC = 2, WAVES_PER_SIMD = 2;
+  static constexpr bool DUAL_OK = true;
+  template <bool DUAL, typename... Args> static __device__ __forceinline__ void body(Args... args) {
+    gemm_tile_body<128, 128, 2, 2, DUAL>(args...);
+  }
+};
+template <int WM_, int WN_, int FM0_, int FM1_, int FN0_, int FN1_, int OCC_ = 1>
+struct TilePipe : PipeTile<WM_, WN_, FM0_, FM1_, FN0_, FN1_> {
+  static constexpr int NT = 512, OCC = OCC_, WAVES_PER_SIMD = 2 * OCC_;
+  static constexpr bool DUAL_OK = FN0_ == FN1_;
+  template <bool DUAL, typename... Args> static __device__ __forceinline__ void body(Args... args) {
+    gemm_pipe_body<PipeTile<WM_, WN_, FM0_, FM1_, FN0_, FN1_>, DUAL>(args...);
+  }
+};
+
+template <typename T, bool DUAL, bool THIN>
+__global__ void __launch_bounds__(T::NT, T::WAVES_PER_SIMD)
 gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
                     const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
                     int epi, GridPlan plan, float* __restrict__ partial, const int* __restrict__ m_live) {
-  constexpr int BN_OUT = DUAL ? BN / 2 : BN;
+  constexpr int BM = T::BM, BN = T::BN, BN_OUT = DUAL ? BN / 2 : BN;
   if (m_live) {
     // The row count lives on the device (rows selected by a threshold) and the host's m only sized the grid.  The
     // schedule is rebuilt here for the live count, in its plain form: every tile whole, by one workgroup, ids
@@ -534,35 +574,32 @@ gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, cons
     if ((plan.per_xcd > 0 && j >= per_xcd) || logical >= total) return;
     int tile_m, tile_n;
     tile_of(make_tile_order(tiles_m, tiles_n), logical, &tile_m, &tile_n);
-    gemm_tile_body<BM, BN, WAVES_M, WAVES_N, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, tile_m * BM, tile_n * BN_OUT,
-                                                   0, k, -1, partial);
+    T::template body<DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, tile_m * BM, tile_n * BN_OUT, 0, k, -1, partial);
     return;
   }
   const BlockWork bw = block_work(plan, (int)blockIdx.x, k);
   if (bw.kind == 0) return;
   if constexpr (THIN) {
     if (bw.kind == 2) {
-      gemm_tile_body<64, BN, 1, WAVES_M * WAVES_N, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
+      gemm_tile_body<64, BN, 1, T::NT / 64, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
                                                          bw.tile_n * BN_OUT, 0, k, -1, partial);
       return;
     }
   }
-  gemm_tile_body<BM, BN, WAVES_M, WAVES_N, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
-                                                 bw.tile_n * BN_OUT, bw.k_begin, bw.k_end, bw.part_slot, partial);
+  T::template body<DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM, bw.tile_n * BN_OUT, bw.k_begin,
+                         bw.k_end, bw.part_slot, partial);
 }
 
 // Sum of the K-split parts of the tail tiles (fixed order: part 0, 1, ...) followed by the epilogue.  One
 // workgroup per (tile, accumulator (i, j)); thread t owns the same (wavefront, lane) as thread t of the GEMM
 // kernel, so all reads of a part are coalesced.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool DUAL>
-__global__ void __launch_bounds__(WAVES_M * WAVES_N * 64)
+template <typename T, bool DUAL>
+__global__ void __launch_bounds__(T::NT)
 gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, TileOrder order, int full_tiles /* of `order` */,
                   int split, const float* __restrict__ partial) {
-  constexpr int NW = WAVES_M * WAVES_N, NT = NW * 64;
-  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  constexpr int FM = WTM / 16, FN = WTN / 16;
+  constexpr int NT = T::NT, BM = T::BM, WTM = T::WTM, WTN = T::WTN, FM = T::FM, FN = T::FN;
   constexpr int FN_OUT = DUAL ? FN / 2 : FN;
-  constexpr int BN_OUT = DUAL ? BN / 2 : BN;
+  constexpr int BN_OUT = DUAL ? T::BN / 2 : T::BN;
   constexpr int PER_TILE = FM * FN_OUT;
   const int t = (int)blockIdx.x / PER_TILE;
   const int rest = (int)blockIdx.x % PER_TILE;
@@ -570,18 +607,15 @@ gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, TileOrde
   int tile_m, tile_n;
   tile_of(order, full_tiles + t, &tile_m, &tile_n);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int wm = wave / T::WN, wn = wave % T::WN;
   // the sums land in a one-accumulator "tile" so that the epilogue code is the GEMM kernel's own
   f32x4 one[1][DUAL ? 2 : 1];
 #pragma unroll
   for (int e = 0; e < 4; ++e) { one[0][0][e] = 0.f; if (DUAL) one[0][DUAL ? 1 : 0][e] = 0.f; }
   for (int p = 0; p < split; ++p) {
-    const float* src = partial + (size_t)(t * split + p) * (FM * FN * 4) * NT + tid;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      one[0][0][e] += src[(size_t)((i * FN + j) * 4 + e) * NT];
-      if (DUAL) one[0][DUAL ? 1 : 0][e] += src[(size_t)((i * FN + j + FN_OUT) * 4 + e) * NT];
-    }
+    const f32x4* src = reinterpret_cast<const f32x4*>(partial) + (size_t)(t * split + p) * (FM * FN) * NT + tid;
+    one[0][0] += src[(size_t)(i * FN + j) * NT];
+    if (DUAL) one[0][DUAL ? 1 : 0] += src[(size_t)(i * FN + j + FN_OUT) * NT];
   }
   // row/column origin of accumulator (i, j) of this wavefront
   const int m_org = tile_m * BM + wm * WTM + i * 16;
@@ -589,9 +623,17 @@ gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, TileOrde
   store_tile16<1, DUAL ? 2 : 1, 16, DUAL ? 32 : 16, DUAL>(one, c, m, n, ldc, epi, m_org, n_org, 0, 0, lane);
 }
 
-// Rough time model (microseconds, measured on MI355X) used to choose the tile and the K-split of the tail:
-// one K step of a full round costs kStep256 with 256x256 tiles, kStep192 with 256x192 tiles (one workgroup per
-// CU each) and kStep128 with 128x128 tiles (two per CU); summing one tile part in the fix-up costs kFixPart.
+// ------------------------------------------------------------------ the K partition of a product
+// Which outputs are summed over K in one go and which in parts.  This is part of the result's definition: another
+// partition changes the last bit of float sums, bf16 rounding turns that into whole rounding steps and a stack of
+// decoder layers carries them to about 1e-2 of the logits.  So the partition is a function of the product's sizes
+// alone (rows, columns, K, epilogue, compute units), and the tile types below, which only decide who computes what,
+// all give the same bits.
+//
+// The rule: 256x256, 256x192 (where they cover N exactly) or 128x128 tiles, whichever a rough time model prices lowest
+// (microseconds; one K step of a full round costs kStep256, kStep192 (one workgroup per CU) or kStep128 (two per CU),
+// summing one tile part in the fix-up kFixPart).  Full rounds of 256-row tiles are summed whole; the remaining tiles,
+// too few to fill the chip, in parts.  128x128 tiles are always summed whole.
 static constexpr float kStep256 = 1.9f, kStep192 = 1.55f, kStep128 = 1.2f, kFixPart = 0.1f, kFixLaunch = 6.f;
 
 struct SplitPlan { int rem, split; float cost; };
@@ -626,7 +668,8 @@ static int num_cus() {
   return n;
 }
 
-size_t gemm_partial_bytes() { return (size_t)256 * 256 * 256 * sizeof(float) + 4096; }   // 256 tile parts
+static constexpr size_t kPartialFloats = (size_t)256 * 256 * 256;   // 256 parts of the largest tile
+size_t gemm_partial_bytes() { return kPartialFloats * sizeof(float) + 4096; }
 
 // Schedule of a launch of 256-row tiles: which tiles run whole, which are cut along K, and whether the ragged
 // last tile row goes to the thin body.  A thin tile is priced at kThinCost of a full one.
@@ -702,42 +745,86 @@ static GridPlan make_grid_plan(int m, int tiles_n, int bm, int ksteps, int slots
   return g;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int OCC>
-static hipError_t launch_dl(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c,
-                            int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                            const int* m_live) {
-  if (m_live) partial = nullptr;   // the kernel rebuilds the plain schedule for the live row count
+// ------------------------------------------------------------------ tile types
+// step_lo / step_hi: microseconds of one K step (64) when a quarter / all of the workgroup slots are busy (the clock
+// falls as more of the chip multiplies), fixed: prologue, first loads and epilogue of a round.  All constants are a
+// least-squares fit of log(time) to 250 launches (all tile types, 40 to 5120 rows, N x K of 4096 x 4096, 6144 x 4096,
+// 4096 x 14336 and the gate/up pair 2 x 14336 x 4096, random operands, weights from memory; residual 10 %); choosing by
+// it is on average 2.5 % behind the fastest type of each shape.
+struct TileInfo { int code, bm, bn, occ; bool dual; float step_lo, step_hi, fixed; };
+static constexpr TileInfo kTiles[] = {
+    {5, 256, 256, 1, true, 1.09f, 1.49f, 3.9f},  {7, 256, 192, 1, false, 0.86f, 1.11f, 3.3f},
+    {8, 192, 256, 1, true, 0.83f, 1.18f, 4.6f},  {11, 192, 192, 1, false, 0.68f, 0.88f, 4.1f},
+    {9, 128, 256, 1, true, 0.61f, 0.86f, 3.3f},  {10, 128, 128, 2, true, 0.40f, 1.01f, 1.5f},
+    {12, 64, 128, 3, true, 0.32f, 1.19f, 3.3f},  {13, 64, 256, 2, true, 0.53f, 1.42f, 3.5f},
+};
+static constexpr float kFixLaunchUs = 1.5f;         // a fix-up launch
+static constexpr float kPartBytesPerUs = 6.3e6f;    // K parts are written, then read
+static constexpr float kWeightBytesPerUs = 4.2e6f;  // the whole weight matrix from memory
+
+// one K step with a share f of the slots busy; hbm: microseconds below which the weight slices do not arrive from
+// memory (they are shared by the tile rows of a column, so only launches of one or two tile rows feel it)
+static float step_us(const TileInfo& t, float f, int tiles_m) {
+  const float mfma = t.step_lo + (t.step_hi - t.step_lo) * std::max(f - 0.25f, -0.1f) / 0.75f;
+  const float hbm = (float)(t.bn * t.occ) / 256.f * (0.17f + 1.46f * f) / (float)tiles_m;
+  return std::max(mfma, hbm);
+}
+
+// time of a launch of tile type t whose tiles are all summed in `split` parts of kpp K steps
+static float tile_cost(const TileInfo& t, int m, int tiles_n, int ksteps, int n_cus, int split, int kpp) {
+  const int tiles_m = (m + t.bm - 1) / t.bm, slots = n_cus * t.occ, wgs = tiles_m * tiles_n * split;
+  const int rounds = wgs / slots, last = wgs % slots;
+  float c = (float)rounds * (kpp * step_us(t, 1.f, tiles_m) + t.fixed);
+  if (last > 0) c += kpp * step_us(t, (float)last / slots, tiles_m) + t.fixed;
+  if (split > 1) c += kFixLaunchUs + (float)wgs * t.bm * t.bn * 8.f / kPartBytesPerUs;
+  return std::max(c, (float)tiles_n * t.bn * ksteps * BK * 2.f / kWeightBytesPerUs + t.fixed);
+}
+
+// the grid of a launch whose tiles are all summed in `split` parts of kpp K steps
+static GridPlan uniform_grid_plan(int m, int tiles_n, int bm, int ksteps, int split, int kpp, int* n_blocks, int* rem_tiles) {
+  GridPlan g = {};
+  const int tiles_m = (m + bm - 1) / bm;
+  g.order = make_tile_order(tiles_m, tiles_n);
+  g.full_tiles = split > 1 ? 0 : tiles_m * tiles_n;
+  g.per_xcd = (g.full_tiles + XCDS - 1) / XCDS;
+  g.n_full_wgs = g.per_xcd * XCDS;
+  g.split = split;
+  g.kpp = kpp;
+  *rem_tiles = split > 1 ? tiles_m * tiles_n : 0;
+  *n_blocks = g.n_full_wgs + *rem_tiles * split;
+  if (!g_xcd_remap) g.per_xcd = 0;
+  return g;
+}
+
+template <typename T, bool THIN>
+static hipError_t launch_dl(const GridPlan& plan, int n_blocks, int rem_tiles, const bf16* a, const bf16* w, const bf16* w2,
+                            const bf16* w3, int ns1, int ns2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
+                            float* partial, hipStream_t st, const int* m_live) {
+  constexpr int NT = T::NT;
   const bool dual = epi == EPI_SWIGLU_T;
-  const int bn_out = dual ? BN / 2 : BN;
-  const int tiles_n = (n + bn_out - 1) / bn_out;
-  // Full rounds of one tile per workgroup slot; the remainder (less than one round) is cut along K so
-  // that it also fills the chip.  Only with a partial buffer, and only for the one-workgroup-per-CU tiles.
-  constexpr bool THIN = BM == 256 && BN == 256 && OCC == 1;
-  int n_blocks = 0, rem_tiles = 0;
-  const GridPlan plan = make_grid_plan(m, tiles_n, BM, k / BK, num_cus() * OCC, BN == 192 ? kStep192 : kStep256,
-                                       partial != nullptr && OCC == 1, THIN && m_live == nullptr, &n_blocks, &rem_tiles);
   const int normal_full = plan.full_tiles - plan.n_thin;
   const dim3 grid((unsigned)n_blocks);
-  constexpr int NT = WAVES_M * WAVES_N * 64;
-  constexpr size_t lds_bytes = 2 * (size_t)(BM + BN) * 128;
+  constexpr size_t lds_bytes = T::LDS_BYTES;
   hipError_t e = hipSuccess;
-  if (dual) {
-    auto kern = gemm_mfma_dl_kernel<BM, BN, WAVES_M, WAVES_N, true, OCC, THIN>;
+  if constexpr (T::DUAL_OK) if (dual) {
+    auto kern = gemm_mfma_dl_kernel<T, true, THIN>;
     static std::atomic<unsigned long long> told{0};
     e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
     if (e != hipSuccess) return e;
     kern<<<grid, NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
     if (rem_tiles > 0)
-      gemm_fixup_kernel<BM, BN, WAVES_M, WAVES_N, true><<<rem_tiles * (BM / WAVES_M / 16) * (BN / WAVES_N / 32), NT, 0, st>>>(
+      gemm_fixup_kernel<T, true><<<rem_tiles * T::FM * (T::FN / 2), NT, 0, st>>>(
           c, m, n, ldc, (int)epi, plan.order, normal_full, plan.split, partial);
-  } else {
-    auto kern = gemm_mfma_dl_kernel<BM, BN, WAVES_M, WAVES_N, false, OCC, THIN>;
+    return hipGetLastError();
+  }
+  {
+    auto kern = gemm_mfma_dl_kernel<T, false, THIN>;
     static std::atomic<unsigned long long> told{0};
     e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
     if (e != hipSuccess) return e;
     kern<<<grid, NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
     if (rem_tiles > 0)
-      gemm_fixup_kernel<BM, BN, WAVES_M, WAVES_N, false><<<rem_tiles * (BM / WAVES_M / 16) * (BN / WAVES_N / 16), NT, 0, st>>>(
+      gemm_fixup_kernel<T, false><<<rem_tiles * T::FM * T::FN, NT, 0, st>>>(
           c, m, n, ldc, (int)epi, plan.order, normal_full, plan.split, partial);
   }
   return hipGetLastError();
@@ -760,22 +847,22 @@ int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool wi
     const BlockWork bw = block_work(g, bid, k);
     if (bw.kind == 0) continue;
     if (bw.tile_m < 0 || bw.tile_m >= tiles_m || bw.tile_n < 0 || bw.tile_n >= tiles_n) { ++errors; continue; }
-    const size_t t = (size_t)bw.tile_m * tiles_n + bw.tile_n;
+    const size_t u = (size_t)bw.tile_m * tiles_n + bw.tile_n;
     if (bw.kind == 2 && (bw.tile_m != tiles_m - 1 || m - (tiles_m - 1) * bm > kThinRows || bw.part_slot >= 0)) ++errors;
     if (bw.part_slot < 0) {
-      if (bw.k_begin != 0 || bw.k_end != k || covered[t] != 0) ++errors;
-      covered[t] = 1;
-      next_k[t] = k;
+      if (bw.k_begin != 0 || bw.k_end != k || covered[u] != 0) ++errors;
+      covered[u] = 1;
+      next_k[u] = k;
     } else {
       // parts arrive in block order = part order
-      if (covered[t] == 1 || bw.k_begin != next_k[t] || bw.k_end <= bw.k_begin || bw.k_end > k) ++errors;
-      covered[t] = 2;
-      next_k[t] = bw.k_end;
+      if (covered[u] == 1 || bw.k_begin != next_k[u] || bw.k_end <= bw.k_begin || bw.k_end > k) ++errors;
+      covered[u] = 2;
+      next_k[u] = bw.k_end;
       slots.push_back(bw.part_slot);
     }
   }
-  for (size_t t = 0; t < covered.size(); ++t)
-    if (covered[t] == 0 || next_k[t] != k) ++errors;
+  for (size_t u = 0; u < covered.size(); ++u)
+    if (covered[u] == 0 || next_k[u] != k) ++errors;
   // part slots are 0, 1, ... without gaps and fit the partial buffer
   for (size_t i = 0; i < slots.size(); ++i)
     if (slots[i] != (int)i) ++errors;
@@ -783,7 +870,7 @@ int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool wi
   return errors;
 }
 
-static int g_gemm_tile = 0;   // 0: by shape; 1-3: register-staged 128x256 / 256x256 / 128x128; 5-7: direct-to-LDS 256x256 / 128x128 / 256x192
+static int g_gemm_tile = 0;   // 0: by shape; 1-3: register-staged 128x256 / 256x256 / 128x128; 5-13: direct-to-LDS (kTiles; 6: Tile128)
 void set_gemm_tile(int t) { g_gemm_tile = t; }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int OCC>
@@ -806,71 +893,117 @@ static hipError_t launch_cfg(const bf16* a, const bf16* w, const bf16* w2, const
   return hipGetLastError();
 }
 
+// Direct-to-LDS kernels (K a multiple of 64): the K partition by the rule above, then the tile type.  A product that is
+// summed the same way everywhere (whole, or all in the same parts) goes to the tile type with the cheapest
+// schedule; one with whole and cut tiles runs on the tiles its partition is made of.
+static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
+                              void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
+                              const int* m_live, int m_expected) {
+  const bool dual = epi == EPI_SWIGLU_T;
+  const int ksteps = k / BK, cus = num_cus();
+  if (dual && (tile == 7 || tile == 11)) tile = 8;   // forced, but the column halves of these two cannot be gate and up
+  auto cols = [&](int bn) { const int o = dual ? bn / 2 : bn; return (n + o - 1) / o; };
+  // which of 256x256 (5), 128x128 (6) and 256x192 (7) the partition is made of
+  int part = tile == 5 || tile == 6 || tile == 7 ? tile : 0;
+  if (part == 0) {
+    const long t6 = (long)((m + 127) / 128) * cols(128);
+    const int slots6 = 2 * cus;
+    const float cost5 = plan_launch(m, cols(256), 256, ksteps, cus, kStep256, partial != nullptr, true).cost;
+    const long last6 = t6 % slots6;
+    const float cost6 = (t6 / slots6) * ksteps * kStep128 +
+                        (last6 == 0 ? 0.f : (last6 * 2 <= slots6 ? 0.65f : 1.f) * ksteps * kStep128);
+    part = cost5 <= cost6 ? 5 : 6;
+    if (!dual && n % 192 == 0) {
+      const float cost7 = plan_launch(m, n / 192, 256, ksteps, cus, kStep192, partial != nullptr, false).cost;
+      if (cost7 < std::min(cost5, cost6)) part = 7;
+    }
+  }
+  int n_blocks = 0, rem_tiles = 0, split = 1, kpp = ksteps;
+  GridPlan plan = {};
+  bool uniform = true;
+  if (part != 6) {
+    plan = make_grid_plan(m, cols(part == 7 ? 192 : 256), 256, ksteps, cus, part == 7 ? kStep192 : kStep256,
+                          partial != nullptr, part == 5 && m_live == nullptr, &n_blocks, &rem_tiles);
+    if (rem_tiles > 0 && plan.split > 1) {
+      uniform = plan.full_tiles == 0;
+      split = plan.split;
+      kpp = plan.kpp;
+    }
+  }
+  int type = part;
+  if (uniform && part != tile) {
+    float best = 0.f;
+    type = 0;
+    for (const TileInfo& t : kTiles) {
+      if (dual && !t.dual) continue;
+      if (split > 1 && (size_t)((m + t.bm - 1) / t.bm) * cols(t.bn) * split * t.bm * t.bn > kPartialFloats) continue;
+      const float cost = tile_cost(t, m_expected, cols(t.bn), ksteps, cus, split, kpp);
+      if (type == 0 || cost < best) { type = t.code; best = cost; }
+    }
+    if (tile >= 8) type = tile;
+    for (const TileInfo& t : kTiles)
+      if (t.code == type) plan = uniform_grid_plan(m, cols(t.bn), t.bm, ksteps, split, kpp, &n_blocks, &rem_tiles);
+  } else if (part == 6) {
+    plan = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &n_blocks, &rem_tiles);
+  }
+#define RC_DL(CODE, THIN, ...) \
+  case CODE: return launch_dl<__VA_ARGS__, THIN>(plan, n_blocks, rem_tiles, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live)
+  switch (type) {
+    RC_DL(5, true, TilePipe<2, 4, 4, 4, 2, 2>);
+    RC_DL(6, false, Tile128);
+    RC_DL(7, false, TilePipe<2, 4, 4, 4, 2, 1>);
+    RC_DL(8, false, TilePipe<4, 2, 2, 1, 4, 4>);
+    RC_DL(9, false, TilePipe<2, 4, 2, 2, 2, 2>);
+    RC_DL(10, false, TilePipe<2, 4, 2, 2, 1, 1, 2>);
+    RC_DL(11, false, TilePipe<4, 2, 2, 1, 4, 2>);
+    RC_DL(12, false, TilePipe<2, 4, 2, 0, 1, 1, 3>);
+    RC_DL(13, false, TilePipe<1, 8, 4, 0, 1, 1, 2>);
+    default: return hipErrorInvalidValue;
+  }
+#undef RC_DL
+}
+
 static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c,
                            int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                           const int* m_live) {
+                           const int* m_live, int m_expected) {
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
   if (tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2))
     return launch_gemm_skinny_bf16(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
-  if (m_live) partial = nullptr;   // live row count on the device: plain schedule, priced as such
-  if (tile == 0) {
-    if (k % BK != 0) {
-      tile = 3;
-    } else {
-      // 256x256 tiles (one workgroup per CU, K-split tail) against 128x128 tiles (two per CU), by the time model
-      const bool dual = epi == EPI_SWIGLU_T;
-      const int ksteps = k / BK;
-      const long t6 = (long)((m + 127) / 128) * ((n + (dual ? 63 : 127)) / (dual ? 64 : 128));
-      const int slots6 = 2 * num_cus();
-      const float cost5 = plan_launch(m, (n + (dual ? 127 : 255)) / (dual ? 128 : 256), 256, ksteps, num_cus(), kStep256,
-                                      partial != nullptr, true).cost;
-      const long last6 = t6 % slots6;
-      const float cost6 = (t6 / slots6) * ksteps * kStep128 +
-                          (last6 == 0 ? 0.f : (last6 * 2 <= slots6 ? 0.65f : 1.f) * ksteps * kStep128);
-      tile = cost5 <= cost6 ? 5 : 6;
-      // 256x192 tiles where they cover N exactly (the fused q|k|v projection: 6144 = 32 x 192): a launch of a
-      // few hundred rows then has a third more tiles to spread over the CUs
-      if (!dual && n % 192 == 0) {
-        const float cost7 = plan_launch(m, n / 192, 256, ksteps, num_cus(), kStep192, partial != nullptr, false).cost;
-        if (cost7 < std::min(cost5, cost6)) tile = 7;
-      }
-    }
-  }
-  if (tile >= 5 && (k % BK) != 0) tile = 3;   // the direct-load kernels need whole K steps
-  switch (tile) {
-    case 5: return launch_dl<256, 256, 4, 2, 1>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live);
-    case 6: return launch_dl<128, 128, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, nullptr, st, m_live);
-    case 7: return launch_dl<256, 192, 4, 2, 1>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live);
+  if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
+  if ((tile == 0 || tile >= 5) && k % BK == 0)
+    return dispatch_dl(tile, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live,
+                       m_live && m_expected > 0 ? std::min(m, m_expected) : m);
+  switch (tile) {   // the direct-load kernels need whole K steps
+    case 1: return launch_cfg<128, 256, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
     case 2: return launch_cfg<256, 256, 4, 2, 1>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
-    case 3: return launch_cfg<128, 128, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
-    default: return launch_cfg<128, 256, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
+    default: return launch_cfg<128, 128, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
   }
 }
 
 template <>
 hipError_t launch_gemm<bf16>(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                             GemmEpilogue epi, hipStream_t st, const int* m_live) {
-  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, nullptr, st, m_live);
+                             GemmEpilogue epi, hipStream_t st, const int* m_live, int m_expected) {
+  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, nullptr, st, m_live, m_expected);
 }
 
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live) {
-  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live);
+                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
+  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
 }
 
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                                int m, int k, float* partial, hipStream_t st, const int* m_live) {
+                                int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected) {
   const int n = nq + 2 * nkv;
-  return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, partial, st, m_live);
+  return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, partial, st, m_live, m_expected);
 }
 
 // q | k | v projections of the same rows as one GEMM over the concatenated output columns
 template <>
 hipError_t launch_gemm_qkv<bf16>(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
-                                 float* c, int m, int k, hipStream_t st, const int* m_live) {
+                                 float* c, int m, int k, hipStream_t st, const int* m_live, int m_expected) {
   const int n = nq + 2 * nkv;
-  return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, nullptr, st, m_live);
+  return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, nullptr, st, m_live, m_expected);
 }
 
 }  // namespace rc

@@ -95,13 +95,13 @@ hipError_t launch_gemm_simt(const T* a, const T* w, const T* w2, void* c, int m,
 
 template <>
 hipError_t launch_gemm<float>(const float* a, const float* w, const float* w2, void* c, int m, int n, int k,
-                              int ldc, GemmEpilogue epi, hipStream_t st, const int* m_live) {
+                              int ldc, GemmEpilogue epi, hipStream_t st, const int* m_live, int) {
   return launch_gemm_simt<float>(a, w, w2, c, m, n, k, ldc, epi, st, m_live);
 }
 
 template <>
 hipError_t launch_gemm_qkv<float>(const float* a, const float* wq, int nq, const float* wk, const float* wv, int nkv,
-                                  float* c, int m, int k, hipStream_t st, const int* m_live) {
+                                  float* c, int m, int k, hipStream_t st, const int* m_live, int) {
   const int n = nq + 2 * nkv;
   hipError_t e = launch_gemm_simt<float>(a, wq, nullptr, c, m, nq, k, n, EPI_STORE_F32, st, m_live);
   if (e != hipSuccess) return e;
