@@ -3,6 +3,7 @@
 // decides which rows are active in which layer and enqueues launches.
 #include <algorithm>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -418,13 +419,12 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
   const KvGeom gd = geom_of(*job.dst, d);
   const bool has_seg = job.max_seg > 0;
   const bool by_threshold = job.selector == RC_SELECT_THRESHOLD;
+  constexpr bool kFloat = std::is_same<T, float>::value;   // float models: norms, rotary + scatter and gather inside the GEMMs
 
   ReqTable tabs[PH_COUNT];
   AttnSplit splits[PH_COUNT];
   bool on_device[PH_COUNT] = {false, false, false, false};   // table already written (and finalized) on the device
   for (int p = 0; p < PH_COUNT; ++p) tabs[p] = job.base;
-
-  RC_LAUNCH(PC_TABLES, launch_rope_table(w.rope_tab, job.max_pos, d.head_dim / 2, (double)d.rope_base, st));
 
   int cur = -1;   // phase whose rows are live in w.h[hbuf]
   int hbuf = 0;
@@ -442,11 +442,17 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
         splits[ph] = attention_no_split();
       }
       if (splits[ph].n_chunks <= 1) assign_split_slots(&tabs[ph], tile_rows, kKvTile, 1 << 24, 1, 0);   // items = tiles
-      RC_LAUNCH(PC_TABLES, launch_upload_table(tabs[ph], w.tables + ph, st));
     }
     const int nb = cur >= 0 ? 1 - hbuf : hbuf;
-    RC_LAUNCH(PC_ROWS, launch_build_rows<T>(w.tables + ph, tabs[ph].total_rows, w.h[hbuf], w.h[nb], w.row_pos, w.row_req,
-                                job.sel_idx, D, st));
+    if (on_device[ph]) {
+      RC_LAUNCH(PC_ROWS, launch_build_rows<T>(w.tables + ph, tabs[ph].total_rows, w.h[hbuf], w.h[nb], w.row_pos, w.row_req,
+                                  job.sel_idx, D, st));
+    } else {
+      RopeFill rope = {};
+      if (cur < 0) rope = {w.rope_tab, has_seg && job.takeover ? w.delta_tab : nullptr, d.head_dim / 2, job.takeover, (double)d.rope_base, 0, 0, 0};
+      RC_LAUNCH(PC_ROWS, launch_enter_phase<T>(tabs[ph], w.tables + ph, w.h[hbuf], w.h[nb], w.row_pos, w.row_req, job.sel_idx, D,
+                                               rope, st));
+    }
     hbuf = nb;
     cur = ph;
     return RC_OK;
@@ -461,7 +467,6 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     // Layers that recompute rows later simply overwrite them.
     if (l == 0 && has_seg && job.takeover) {
       const KvGeom gs = geom_of(*job.src, d);
-      RC_LAUNCH(PC_TABLES, launch_delta_table(w.delta_tab, w.tables + cur, n_req, d.head_dim / 2, (double)d.rope_base, st));
       for (int l0 = 0; l0 < d.n_layers; l0 += kRerotateLayers) {
         const int nl = std::min(kRerotateLayers, d.n_layers - l0);
         RerotatePtrs ptrs;
@@ -482,8 +487,13 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       for (int b = 0; b < n_req; ++b) any = any || job.base.r[b].k > 0;
       if (any) {
         const int rows_b = tabs[cur].total_rows;
-        RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h[hbuf], (const T*)lw.g_attn, (T*)w.a, rows_b, D, d.rms_eps, st));
-        RC_LAUNCH(PC_GEMM_VFRESH, gemm_any<T>((const T*)w.a, (const T*)lw.wv, nullptr, w.vfresh, rows_b, nkv, D, nkv, EPI_STORE_T, w.gemm_part, st));
+        if constexpr (kFloat) {
+          RC_LAUNCH(PC_GEMM_VFRESH, launch_gemm_f32_normed(w.h[hbuf], (const float*)lw.g_attn, d.rms_eps, nullptr, (const float*)lw.wv,
+                                                           nullptr, (float*)w.vfresh, rows_b, nkv, D, EPI_STORE_F32, st));
+        } else {
+          RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h[hbuf], (const T*)lw.g_attn, (T*)w.a, rows_b, D, d.rms_eps, st));
+          RC_LAUNCH(PC_GEMM_VFRESH, gemm_any<T>((const T*)w.a, (const T*)lw.wv, nullptr, w.vfresh, rows_b, nkv, D, nkv, EPI_STORE_T, w.gemm_part, st));
+        }
         float* sc = job.scores_out ? job.scores_out : w.scores;
         RC_LAUNCH(PC_SCORE, launch_vdev_score<T>((const T*)w.vfresh, nkv, (const T*)job.dst->v_pool[l], gd, w.tables + cur,
                                     n_req, job.max_seg, sc, st));
@@ -534,13 +544,20 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     if (l == job.capture_layer) RC_LAUNCH(PC_ROWS, launch_capture_rows<T>(w.tables + cur, rows, w.h[hbuf], w.row_req, D, st));
 
     float* h = w.h[hbuf];
-    RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_attn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
-    RC_LAUNCH(PC_GEMM_QKV, gemm_qkv_any<T>((const T*)w.a, (const T*)lw.wq, nq, (const T*)lw.wk, (const T*)lw.wv, nkv,
-                                              w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
-    // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
-    RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
-                                  (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
-                                  job.k_pre_pool ? (T*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st));
+    if constexpr (kFloat) {
+      RC_LAUNCH(PC_GEMM_QKV, launch_gemm_f32_qkv_rope(h, (const float*)lw.g_attn, d.rms_eps, (const float*)lw.wq, (const float*)lw.wk,
+                                                      (const float*)lw.wv, rows, D, w.row_pos, w.row_req, w.tables + cur, w.rope_tab,
+                                                      (float*)w.q, (float*)job.dst->k_pool[l], (float*)job.dst->v_pool[l],
+                                                      job.k_pre_pool ? (float*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st, m_live));
+    } else {
+      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_attn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
+      RC_LAUNCH(PC_GEMM_QKV, gemm_qkv_any<T>((const T*)w.a, (const T*)lw.wq, nq, (const T*)lw.wk, (const T*)lw.wv, nkv,
+                                                w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
+      // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
+      RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
+                                    (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
+                                    job.k_pre_pool ? (T*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st));
+    }
     // influence accumulation (decoding): the bf16 matrix-core attention kernel hands out its scores; the other
     // paths compute them in a pass of their own
     const bool scores_from_attention = job.any_inf && d.dtype == RC_BF16 && d.n_q_heads / d.n_kv_heads <= 8;
@@ -556,17 +573,28 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.max_pos, job.inf,
                                                       w.inf_scratch, scores_from_attention, st));
     RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
-    RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_ffn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
-    RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
+    if constexpr (kFloat) {
+      RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_f32_normed(h, (const float*)lw.g_ffn, d.rms_eps, nullptr, (const float*)lw.w_gate,
+                                                        (const float*)lw.w_up, (float*)w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
+    } else {
+      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_ffn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
+      RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
+    }
     RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
   }
 
   // first-token logits from the last position of each request
-  RC_LAUNCH(PC_ROWS, launch_gather_last(w.tables + cur, n_req, w.h[hbuf], w.h_last, D, st));
-  RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h_last, (const T*)job.m->g_final, (T*)w.a_last, n_req, D, d.rms_eps, st));
-  RC_LAUNCH(PC_GEMM_LM_HEAD, gemm_any<T>((const T*)w.a_last, (const T*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, d.vocab,
-                        EPI_STORE_F32, w.gemm_part, st));
-  return RC_OK;
+  if constexpr (kFloat) {
+    RC_LAUNCH(PC_GEMM_LM_HEAD, launch_gemm_f32_normed(w.h[hbuf], (const float*)job.m->g_final, d.rms_eps, w.tables + cur, (const float*)job.m->w_lm,
+                                                      nullptr, job.logits, n_req, d.vocab, D, EPI_STORE_F32, st));
+    return RC_OK;
+  } else {
+    RC_LAUNCH(PC_ROWS, launch_gather_last(w.tables + cur, n_req, w.h[hbuf], w.h_last, D, st));
+    RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h_last, (const T*)job.m->g_final, (T*)w.a_last, n_req, D, d.rms_eps, st));
+    RC_LAUNCH(PC_GEMM_LM_HEAD, gemm_any<T>((const T*)w.a_last, (const T*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, d.vocab,
+                          EPI_STORE_F32, w.gemm_part, st));
+    return RC_OK;
+  }
 }
 
 rc_status check_seq_fits(const rc_paged_kv* kv, int seq, int len) {

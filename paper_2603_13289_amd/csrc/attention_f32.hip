@@ -1,0 +1,151 @@
+// K6 for the float configuration: causal grouped-query attention of arbitrary query rows over a paged cache on
+// v_mfma_f32_16x16x4_f32.
+//
+// A workgroup serves 16 query rows of one request and one query head; its eight (head size 128: four)
+// wavefronts take every eighth block of 16 keys, each with a running softmax of its own, and are merged through LDS at the end.  Per key block a wavefront computes
+//   S^T[key][q] = K[key][:] . Q[q][:]      lane holds query lane % 16, keys 4 (lane / 16) + 0..3
+//   O^T[d][q]  += V^T[d][key] P[key][q]    P's operand is S^T's result register as it stands
+// Bound by latency: float models have a few hundred keys, so the chain of one wavefront is a handful of blocks; the next
+// block's keys are requested before the current one is used.  Measured, 384 rows x 4 heads x up to 384 keys:
+// 147 us with one wavefront per (row, head) on the vector ALUs, 9 us now.
+#include "common.h"
+
+namespace rc {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4a;
+
+template <int DH>
+__global__ void __launch_bounds__(DH == 64 ? 512 : 256)
+attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, const ReqTable* __restrict__ table,
+                int fixed_seq, int total_rows, const float* __restrict__ k_pool, const float* __restrict__ v_pool, KvGeom g,
+                int n_q_heads, float* __restrict__ out) {
+  constexpr int NB = DH / 16, NW = DH == 64 ? 8 : 4;   // wavefronts: what 32 KB of partial results allow
+  __shared__ float lds_o[NW][DH][16];
+  __shared__ float2 lds_ml[NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, qi = lane & 15, kq = lane >> 4;
+  const int head = blockIdx.y, kvh = head / (n_q_heads / g.n_kv_heads);
+  int r0 = blockIdx.x * 16, n_valid, seq = fixed_seq;
+  if (table) {   // the tile-th group of 16 rows, counted request by request
+    int tile = blockIdx.x, b = 0;
+    for (; b < table->n_req; ++b) {
+      const int t = (table->r[b].n_rows + 15) / 16;
+      if (tile < t) break;
+      tile -= t;
+    }
+    if (b == table->n_req) return;   // uniform: the grid is an upper bound
+    r0 = table->r[b].row_base + tile * 16;
+    n_valid = min(16, table->r[b].n_rows - tile * 16);
+    seq = table->r[b].dst_seq;
+  } else {
+    n_valid = min(16, total_rows - r0);
+  }
+  const bool q_ok = qi < n_valid;
+  const int my_pos = q_ok ? row_pos[r0 + qi] : -1;
+  int last_pos = my_pos;   // the group's largest position
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
+  const float scale = 1.4426950408889634f / sqrtf((float)DH);   // scores in log2 units
+  const float* qrow = q + ((size_t)(r0 + (q_ok ? qi : 0)) * n_q_heads + head) * DH;
+  f32x4a fq[NB], fk[NB], acc[NB];
+#pragma unroll
+  for (int t = 0; t < NB; ++t) {
+    fq[t] = q_ok ? *reinterpret_cast<const f32x4a*>(qrow + 16 * t + 4 * kq) * scale : f32x4a{0.f, 0.f, 0.f, 0.f};
+    acc[t] = f32x4a{0.f, 0.f, 0.f, 0.f};
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  const int n_blocks = last_pos / 16 + 1;
+  auto fetch_k = [&](int kb) {
+    const float* krow = k_pool + kv_row_offset(g, seq, min(kb * 16 + qi, last_pos), kvh);
+#pragma unroll
+    for (int t = 0; t < NB; ++t) fk[t] = *reinterpret_cast<const f32x4a*>(krow + 16 * t + 4 * kq);
+  };
+  if (wave < n_blocks) fetch_k(wave);
+  for (int kb = wave; kb < n_blocks; kb += NW) {
+    float fv[NB][4];   // V[key 4 kq + c][d]: the operand of instruction c
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float* vrow = v_pool + kv_row_offset(g, seq, min(kb * 16 + 4 * kq + c, last_pos), kvh) + qi;
+#pragma unroll
+      for (int t = 0; t < NB; ++t) fv[t][c] = vrow[16 * t];
+    }
+    f32x4a s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int t = 0; t < NB; t += 2)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(fk[t][c], fq[t][c], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(fk[t + 1][c], fq[t + 1][c], s1, 0, 0, 0);
+      }
+    if (kb + NW < n_blocks) fetch_k(kb + NW);
+    s0 += s1;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (kb * 16 + 4 * kq + e > my_pos) s0[e] = -INFINITY;
+      mx = fmaxf(mx, s0[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx), m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = exp2f(m_run - m_use);
+    float ps = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s0[e] = exp2f(s0[e] - m_use);
+      ps += s0[e];
+    }
+    l_run = l_run * corr + ps;
+    m_run = m_new;
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      acc[t] *= corr;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[t][c], s0[c], acc[t], 0, 0, 0);
+    }
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (kq == 0) lds_ml[wave][qi] = make_float2(m_run, l_run);
+#pragma unroll
+  for (int t = 0; t < NB; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) lds_o[wave][16 * t + 4 * kq + e][qi] = acc[t][e];
+  __syncthreads();
+  // NT / 16 threads per row, thread c of them the elements c, c + NT / 16, ...
+  constexpr int NT = 64 * NW, PER = NT / 16;
+  const int row = tid / PER;
+  if (row >= n_valid) return;
+  float m = -INFINITY, l = 0.f, f[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) m = fmaxf(m, lds_ml[w][row].x);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    f[w] = exp2f(lds_ml[w][row].x - m);
+    l += lds_ml[w][row].y * f[w];
+  }
+  float* orow = out + ((size_t)(r0 + row) * n_q_heads + head) * DH;
+#pragma unroll
+  for (int d0 = 0; d0 < DH; d0 += PER) {
+    const int d = d0 + tid % PER;
+    float o = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) o = fmaf(lds_o[w][d][row], f[w], o);
+    orow[d] = o / l;
+  }
+}
+
+template <>
+hipError_t launch_attention<float>(const float* q, const int* row_pos, const int* row_req, const ReqTable* table,
+                                   int fixed_seq, int total_rows, int total_tiles, const float* k_pool,
+                                   const float* v_pool, KvGeom g, int n_q_heads, float* out, hipStream_t st) {
+  (void)row_req;
+  if (total_rows <= 0) return hipSuccess;
+  // 16-row groups: at most two per query tile (32 rows) of the table
+  const unsigned groups = table ? (unsigned)(2 * total_tiles) : (unsigned)((total_rows + 15) / 16);
+  const dim3 grid(groups, (unsigned)n_q_heads);
+  if (g.head_dim == 64) attn_f32_kernel<64><<<grid, 512, 0, st>>>(q, row_pos, table, fixed_seq, total_rows, k_pool, v_pool, g, n_q_heads, out);
+  else attn_f32_kernel<128><<<grid, 256, 0, st>>>(q, row_pos, table, fixed_seq, total_rows, k_pool, v_pool, g, n_q_heads, out);
+  return hipGetLastError();
+}
+
+}  // namespace rc

@@ -1,6 +1,6 @@
-// K6 for the float configuration: causal grouped-query attention of arbitrary query rows over a paged
+// K6 for bf16 models with more than eight query heads per KV head: causal grouped-query attention of arbitrary query rows over a paged
 // cache on the vector ALUs.  One wavefront (= one workgroup) per (query row, query head); keys are
-// consumed 64 at a time with a running softmax.  bf16 models use the MFMA kernel instead.
+// consumed 64 at a time with a running softmax.  Narrower groups use the matrix-core kernel instead.
 #include "common.h"
 
 namespace rc {
@@ -77,20 +77,9 @@ hipError_t launch_attention_simt(const T* q, const int* row_pos, const int* row_
                                                                         k_pool, v_pool, g, n_q_heads, out);
   return hipGetLastError();
 }
-template hipError_t launch_attention_simt<float>(const float*, const int*, const int*, const ReqTable*, int, int,
-                                                 const float*, const float*, KvGeom, int, float*, hipStream_t);
 template hipError_t launch_attention_simt<bf16>(const bf16*, const int*, const int*, const ReqTable*, int, int,
                                                 const bf16*, const bf16*, KvGeom, int, bf16*, hipStream_t);
 
-
-template <>
-hipError_t launch_attention<float>(const float* q, const int* row_pos, const int* row_req, const ReqTable* table,
-                                   int fixed_seq, int total_rows, int total_tiles, const float* k_pool,
-                                   const float* v_pool, KvGeom g, int n_q_heads, float* out, hipStream_t st) {
-  (void)total_tiles;
-  return launch_attention_simt<float>(q, row_pos, row_req, table, fixed_seq, total_rows, k_pool, v_pool, g,
-                                      n_q_heads, out, st);
-}
 
 int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads) {
   (void)dtype; (void)n_q_heads; (void)n_kv_heads;

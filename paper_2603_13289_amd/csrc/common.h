@@ -268,6 +268,16 @@ template <typename T>
 hipError_t launch_rerotate(const RerotatePtrs& ptrs, int n_layers, KvGeom gs, KvGeom gd, const ReqTable* table,
                            int n_req, int max_seg, const float2* rope_tab, const float2* delta_tab, hipStream_t st);
 
+// what enter_phase fills besides the phase's rows at the start of a call (tab == nullptr: nothing)
+struct RopeFill {
+  float2 *tab, *delta_tab;   // delta_tab may be nullptr
+  int half, takeover;
+  double base;
+  int per_request, lo, hi;   // set by the launcher
+};
+template <typename T>
+hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, int* row_pos,
+                              int* row_req, const int* sel_idx, int d, RopeFill rope, hipStream_t st);
 template <typename T>
 hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new,
                              int* row_pos, int* row_req, const int* sel_idx, int d, hipStream_t st);
@@ -287,6 +297,17 @@ enum GemmEpilogue : int { EPI_STORE_F32 = 0, EPI_STORE_T = 1, EPI_ADD_F32 = 2, E
 template <typename T>
 hipError_t launch_gemm(const T* a, const T* w, const T* w2, void* c, int m, int n, int k, int ldc,
                        GemmEpilogue epi, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+
+// Float models: what surrounds a product is done inside it.  h is RMS-normalised with `gain` on the way in; last_of:
+// row b of the product is the last live row of request b.
+hipError_t launch_gemm_f32_normed(const float* h, const float* gain, float eps, const ReqTable* last_of, const float* w,
+                                  const float* w2, float* c, int m, int n, int k, GemmEpilogue epi, hipStream_t st,
+                                  const int* m_live = nullptr);
+hipError_t launch_gemm_f32_qkv_rope(const float* h, const float* gain, float eps, const float* wq, const float* wk,
+                                    const float* wv, int m, int k, const int* row_pos, const int* row_req,
+                                    const ReqTable* table, const float2* rope_tab, float* q_out, float* k_pool, float* v_pool,
+                                    float* k_pre_pool, KvGeom geom, int n_q_heads, hipStream_t st,
+                                    const int* m_live = nullptr);
 
 // few-row variant (M <= 32, weights streamed once); columns < ns1 come from w, < ns2 from w2, the rest from w3
 bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2);

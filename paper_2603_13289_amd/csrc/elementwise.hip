@@ -1,5 +1,7 @@
 // Bandwidth-bound stages of the selective-recompute prefill: rotary re-rotation of reused keys,
 // active-row bookkeeping, RMSNorm, rotary + paged scatter of fresh K/V, Eq. (1) scoring.
+#include <algorithm>
+
 #include "common.h"
 
 namespace rc {
@@ -51,14 +53,22 @@ hipError_t launch_finalize_tables(ReqTable* tabs, const int* sel_cnt, int tile_r
 // ------------------------------------------------------------------ rotary tables
 // tab[pos][i] = (cos, sin)(pos * base^(-2i/dh)), evaluated in double so that positions in the tens
 // of thousands keep full float accuracy.
-__global__ void rope_table_kernel(float2* tab, int n_pos, int half, double base) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_pos * half) return;
-  const int pos = idx / half, i = idx - pos * half;
+__device__ inline float2 rope_entry(int pos, int i, int half, double base) {
   const double theta = pow(base, -(double)i / (double)half);   // -2i/dh with dh = 2*half
   double s, c;
   sincos((double)pos * theta, &s, &c);
-  tab[idx] = make_float2((float)c, (float)s);
+  return make_float2((float)c, (float)s);
+}
+// positions [rope_first, rope_end) of a request whose table entries a call reads: its rows, and, when it takes a
+// segment over, the segment's new positions
+__device__ __host__ inline int rope_first(const ReqDev& r, int takeover) { return takeover || r.P > 0 ? r.pos0 : r.pos0 + r.S; }
+__device__ __host__ inline int rope_end(const ReqDev& r) { return r.pos0 + r.P + r.S + r.nsuf; }
+
+__global__ void rope_table_kernel(float2* tab, int n_pos, int half, double base) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= n_pos * half) return;
+  const int pos = idx / half;
+  tab[idx] = rope_entry(pos, idx - pos * half, half, base);
 }
 
 hipError_t launch_rope_table(float2* tab, int n_pos, int half, double base, hipStream_t st) {
@@ -72,11 +82,8 @@ hipError_t launch_rope_table(float2* tab, int n_pos, int half, double base, hipS
 __global__ void delta_table_kernel(float2* tab, const ReqTable* table, int n_req, int half, double base) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n_req * half) return;
-  const int b = idx / half, i = idx - b * half;
-  const double theta = pow(base, -(double)i / (double)half);
-  double s, c;
-  sincos((double)table->r[b].rot_delta * theta, &s, &c);
-  tab[idx] = make_float2((float)c, (float)s);
+  const int b = idx / half;
+  tab[idx] = rope_entry(table->r[b].rot_delta, idx - b * half, half, base);
 }
 
 hipError_t launch_delta_table(float2* tab, const ReqTable* table, int n_req, int half, double base,
@@ -149,14 +156,13 @@ template hipError_t launch_rerotate<bf16>(const RerotatePtrs&, int, KvGeom, KvGe
 // Builds the compact residual-stream buffer of a new phase: one workgroup per destination row.
 // Rows of a request are ordered by position: prefix, active segment rows, suffix.
 template <typename T>
-__global__ void __launch_bounds__(kThreads)
-build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ h_old, float* __restrict__ h_new,
-                  int* __restrict__ row_pos, int* __restrict__ row_req, const int* __restrict__ sel_idx, int d) {
-  const int r = blockIdx.x;
-  if (r >= table->total_rows) return;   // the grid may be sized for an upper bound of the row count
+__device__ __forceinline__ void build_row(const ReqTable& table, int r, const float* __restrict__ h_old,
+                                          float* __restrict__ h_new, int* __restrict__ row_pos, int* __restrict__ row_req,
+                                          const int* __restrict__ sel_idx, int d) {
+  if (r >= table.total_rows) return;   // the grid may be sized for an upper bound of the row count
   int b = 0;
-  while (b + 1 < table->n_req && r >= table->r[b].row_base + table->r[b].n_rows) ++b;
-  const ReqDev& rq = table->r[b];
+  while (b + 1 < table.n_req && r >= table.r[b].row_base + table.r[b].n_rows) ++b;
+  const ReqDev& rq = table.r[b];
   const int i = r - rq.row_base;
   int pos, flags = 0;
   const T* src_t = nullptr;      // input tensor row (T)
@@ -198,6 +204,80 @@ build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ 
     for (int c = threadIdx.x; c < d; c += kThreads) dst[c] = to_f32(src_t[c]);
   }
 }
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads)
+build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ h_old, float* __restrict__ h_new,
+                  int* __restrict__ row_pos, int* __restrict__ row_req, const int* __restrict__ sel_idx, int d) {
+  build_row<T>(*table, blockIdx.x, h_old, h_new, row_pos, row_req, sel_idx, d);
+}
+
+// A phase whose row counts the host knows, in one launch: its table travels as a kernel argument (no host-to-device copy,
+// no pinned staging buffer), workgroup 0 leaves it in device memory for the kernels that follow, workgroups 1.. build the
+// rows.  At the start of a call the same launch also fills the rotary tables (independent work; a launch of its
+// own costs 4.8 us behind another, whatever it does): workgroups past the rows take the positions the call uses.
+template <typename T>
+__global__ void __launch_bounds__(kThreads)
+enter_phase_kernel(ReqTable t, ReqTable* dst, const float* __restrict__ h_old, float* __restrict__ h_new,
+                   int* __restrict__ row_pos, int* __restrict__ row_req, const int* __restrict__ sel_idx, int d, RopeFill rope) {
+  const int bid = blockIdx.x;
+  if (bid == 0) {
+    const int* s = reinterpret_cast<const int*>(&t);
+    int* o = reinterpret_cast<int*>(dst);
+    for (int i = threadIdx.x; i < (int)(sizeof(ReqTable) / sizeof(int)); i += kThreads) o[i] = s[i];
+    if (rope.delta_tab) {
+      for (int i = threadIdx.x; i < t.n_req * rope.half; i += kThreads)
+        rope.delta_tab[i] = rope_entry(t.r[i / rope.half].rot_delta, i % rope.half, rope.half, rope.base);
+    }
+    return;
+  }
+  if (bid <= t.total_rows) {
+    build_row<T>(t, bid - 1, h_old, h_new, row_pos, row_req, sel_idx, d);
+    return;
+  }
+  const long idx = (long)(bid - 1 - t.total_rows) * kThreads + threadIdx.x;
+  int pos = (int)(idx / rope.half);
+  const int i = (int)(idx - (long)pos * rope.half);
+  if (rope.per_request) {   // position numbers run through the requests' own ranges
+    int b = 0;
+    for (; b < t.n_req; ++b) {
+      const int lo = rope_first(t.r[b], rope.takeover), n = rope_end(t.r[b]) - lo;
+      if (pos < n) { pos += lo; break; }
+      pos -= n;
+    }
+    if (b == t.n_req) return;
+  } else {
+    pos += rope.lo;
+    if (pos >= rope.hi) return;
+  }
+  rope.tab[(size_t)pos * rope.half + i] = rope_entry(pos, i, rope.half, rope.base);
+}
+
+template <typename T>
+hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, int* row_pos,
+                              int* row_req, const int* sel_idx, int d, RopeFill rope, hipStream_t st) {
+  long items = 0;
+  if (rope.tab) {
+    long sum = 0;
+    rope.lo = 1 << 30;
+    rope.hi = 0;
+    for (int b = 0; b < table.n_req; ++b) {
+      const int lo = rope_first(table.r[b], rope.takeover), hi = rope_end(table.r[b]);
+      sum += hi - lo;
+      rope.lo = std::min(rope.lo, lo);
+      rope.hi = std::max(rope.hi, hi);
+    }
+    rope.per_request = sum < rope.hi - rope.lo;
+    items = (rope.per_request ? sum : rope.hi - rope.lo) * rope.half;
+  }
+  const unsigned grid = 1u + (unsigned)table.total_rows + (unsigned)((items + kThreads - 1) / kThreads);
+  enter_phase_kernel<T><<<grid, kThreads, 0, st>>>(table, dev_slot, h_old, h_new, row_pos, row_req, sel_idx, d, rope);
+  return hipGetLastError();
+}
+template hipError_t launch_enter_phase<float>(const ReqTable&, ReqTable*, const float*, float*, int*, int*, const int*, int,
+                                              RopeFill, hipStream_t);
+template hipError_t launch_enter_phase<bf16>(const ReqTable&, ReqTable*, const float*, float*, int*, int*, const int*, int,
+                                             RopeFill, hipStream_t);
 
 template <typename T>
 hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new,

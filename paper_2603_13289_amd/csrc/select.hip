@@ -43,7 +43,7 @@ __device__ inline int block_exclusive_scan(int v, int* lds /* kSelWaves + 1 ints
 }
 
 __device__ __forceinline__ void topk_body(const float* __restrict__ score, int n, int k, int* __restrict__ idx_out) {
-  __shared__ int hist[256];
+  __shared__ int hist[256], hist_inc[256];
   __shared__ int scan_lds[kSelWaves + 1];
   __shared__ uint32_t s_prefix;
   __shared__ int s_need;
@@ -60,14 +60,28 @@ __device__ __forceinline__ void topk_body(const float* __restrict__ score, int n
       if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      int run = 0, d = 255;
-      for (; d > 0; --d) {
-        if (run + hist[d] >= need) break;
-        run += hist[d];
+    // from the top: digit 255 - t of thread t; the digit that holds the need-th element is the one whose running
+    // count reaches `need` (the last digit takes it whatever the count)
+    if (threadIdx.x < 256) {
+      const int lane = threadIdx.x & 63, v = hist[255 - threadIdx.x];
+      int inc = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
       }
-      s_prefix = prefix | ((uint32_t)d << shift);
-      s_need = need - run;
+      if (lane == 63) scan_lds[threadIdx.x >> 6] = inc;
+      hist_inc[threadIdx.x] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      int before = hist_inc[threadIdx.x] - hist[255 - threadIdx.x];
+      for (int i = 0; i < (int)(threadIdx.x >> 6); ++i) before += scan_lds[i];
+      const int v = hist[255 - threadIdx.x];
+      if (before < need && (before + v >= need || threadIdx.x == 255)) {
+        s_prefix = prefix | ((255u - threadIdx.x) << shift);
+        s_need = need - before;
+      }
     }
     __syncthreads();
     prefix = s_prefix;
