@@ -9,7 +9,7 @@
 //
 // A wavefront keeps two register sets of U steps and refills one while the other is multiplied, so loads are always
 // in flight.  Loading a group of four steps, waiting for it and multiplying it left memory idle between groups:
-// gate/up of 1 x 28672 x 4096 47.0 -> 43.7 us (5.4 TB/s); decoding one sequence on the 7B shape 4.49 -> 4.39 ms, sixteen
+// gate/up of 1 x 28672 x 4096 47.0 -> 43.7 us (5.4 TB/s, one workgroup to a CU); decoding one sequence on the 7B shape 4.49 -> 4.39 ms, sixteen
 // 7.70 -> 7.02 ms (their activation rows come from the L2, which the old loop waited for as well).
 #include <type_traits>
 
@@ -21,16 +21,18 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8s;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4s;
 
 static constexpr int kSkinnyWaves = 8;
-// Products of up to two workgroups per CU take register sets of eight steps instead of four (128 KB in flight per
+// Products of at most one workgroup per CU (256) take register sets of eight steps instead of four (128 KB in flight per
 // workgroup): there are too few wavefronts to hide the latency otherwise.  They need two full sets in a wavefront's
-// share of K; shorter ones (K below 4096) have nothing to pipeline and ran 2-3 us slower with the wide set.
-static constexpr int kSkinnyDeepGroups = 512;
+// share of K: shorter ones (K below 4096) have nothing to pipeline.  With more workgroups, two have to fit a CU:
+// sets of four steps in at most 128 registers (the line at 512 workgroups and 130 registers: a decoding step of one
+// sequence 4.10 ms, of sixteen 7.07; as it is 4.02 and 6.94).
+static constexpr int kSkinnyDeepGroups = 256;
 
 __device__ inline float silu_s(float x) { return x / (1.0f + __expf(-x)); }
 
 // DUAL: gate and up weights of the same columns.  TWO: more than 16 rows.  U: K steps of a register set.
 template <bool DUAL, bool TWO, int U>
-__global__ void __launch_bounds__(kSkinnyWaves * 64)
+__global__ void __launch_bounds__(kSkinnyWaves * 64, U == 8 || (DUAL && TWO) ? 2 : 4)
 gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
                    const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
                    int epi, const int* __restrict__ m_live) {
