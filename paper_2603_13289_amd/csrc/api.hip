@@ -212,39 +212,11 @@ float price_split(const ReqTable* t, int n_kv_heads, int n_q_heads, int tile_row
   return cost;
 }
 
-// The decode kernel takes phases whose requests have one row at most.
-bool decode_kernel_applies(const ReqTable* t, int n_kv_heads, int n_q_heads) {
-  for (int b = 0; b < t->n_req; ++b)
-    if (t->r[b].n_rows > 1) return false;
-  return n_q_heads / n_kv_heads <= kDecodeMaxGroup;
-}
-
-// Chunks of the decode kernel, whose workgroups do a 64-key tile in half a step of their four wavefronts: two rounds of
-// the three workgroups that a compute unit holds even ragged sequences out, and two tiles give every wavefront one step.
-// A merge costs a launch, about as much as the steps of 16 tiles.
-constexpr int kDecodeWgs = 1536;
-constexpr int kDecodeWholeTiles = 16;
-int decode_chunk_tiles(const ReqTable* t, int n_kv_heads) {
-  long tiles = 0, longest = 0;
-  for (int b = 0; b < t->n_req; ++b) {
-    if (t->r[b].n_rows < 1) continue;
-    const int n = est_row_pos(t->r[b], 0) / kKvTile + 1;
-    tiles += n;
-    longest = std::max<long>(longest, n);
-  }
-  if (longest <= kDecodeWholeTiles) return 0;
-  return (int)std::max<long>(2, (tiles * n_kv_heads + kDecodeWgs - 1) / kDecodeWgs);
-}
-
-AttnSplit choose_phase_split(const ReqTable* t, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos, bool may_decode) {
+AttnSplit choose_phase_split(const ReqTable* t, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos) {
   int chunk_tiles = 0;
-  const bool decode = may_decode && decode_kernel_applies(t, n_kv_heads, n_q_heads);
   const int forced = attention_forced_chunk_tiles();
   if (forced > 0) {
     chunk_tiles = forced;
-  } else if (decode) {
-    chunk_tiles = decode_chunk_tiles(t, n_kv_heads);
-    if (chunk_tiles == 0) return attention_no_split(1);
   } else {
     // query-head groups of up to four wavefronts run two workgroups per compute unit, wider ones one
     const int slots = (n_q_heads / n_kv_heads <= 4 ? 2 : 1) * 256;
@@ -264,16 +236,16 @@ AttnSplit choose_phase_split(const ReqTable* t, int n_kv_heads, int n_q_heads, i
   }
   const int max_tiles = (max_pos + kKvTile - 1) / kKvTile;
   const int n_chunks = (max_tiles + chunk_tiles - 1) / chunk_tiles;
-  if (n_chunks <= 1) return attention_no_split(decode ? 1 : 32);
-  AttnSplit sp = {n_chunks, chunk_tiles, chunk_tiles, 0, decode ? 1 : 32};
+  if (n_chunks <= 1) return attention_no_split();
+  AttnSplit sp = {n_chunks, chunk_tiles, chunk_tiles, 0};
   return sp;
 }
 
 // the whole plan of a phase whose row counts the host knows: decision, then slots (no capacity limit)
 AttnSplit plan_phase_split(ReqTable* t, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos) {
-  AttnSplit sp = choose_phase_split(t, n_kv_heads, n_q_heads, tile_rows, max_pos, true);
+  AttnSplit sp = choose_phase_split(t, n_kv_heads, n_q_heads, tile_rows, max_pos);
   sp.total_slots = assign_split_slots(t, tile_rows, kKvTile, sp.long_thr, sp.n_chunks, 1 << 30);
-  if (sp.total_slots == 0) return attention_no_split(sp.slot_rows);
+  if (sp.total_slots == 0) return attention_no_split();
   return sp;
 }
 
@@ -413,10 +385,10 @@ hipError_t gemm_qkv_any<bf16>(const bf16* a, const bf16* wq, int nq, const bf16*
 // Partial-attention slots the sparse phase (and the phase after it) may use when the threshold selector decides the
 // row counts on the device: planned for a nominal selection of a fifth of every segment, with room for twice that;
 // a selection that needs more attends unsplit.
-struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int rows[PH_COUNT]; };
+struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int cap[PH_COUNT]; int rows[PH_COUNT]; };
 ThresholdSplit plan_threshold_split(const ReqTable& base, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos, bool bf16_model) {
   ThresholdSplit ts;
-  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.rows[p] = 0; }
+  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.cap[p] = 0; ts.rows[p] = 0; }
   if (!bf16_model) return ts;
   for (int p = PH_C; p <= PH_D; ++p) {
     ReqTable t = base;
@@ -424,7 +396,7 @@ ThresholdSplit plan_threshold_split(const ReqTable& base, int n_kv_heads, int n_
       if (t.r[b].k > 0) t.r[b].k = std::max(1, t.r[b].S / 5);
     fill_phase_table(&t, p, nullptr, tile_rows);
     ts.rows[p] = t.total_rows;
-    AttnSplit sp = choose_phase_split(&t, n_kv_heads, n_q_heads, tile_rows, max_pos, false);
+    AttnSplit sp = choose_phase_split(&t, n_kv_heads, n_q_heads, tile_rows, max_pos);
     if (sp.n_chunks <= 1) continue;
     for (int b = 0; b < t.n_req; ++b)
       if (t.r[b].k > 0) t.r[b].k = std::min(t.r[b].S, 2 * t.r[b].k);
@@ -433,6 +405,7 @@ ThresholdSplit plan_threshold_split(const ReqTable& base, int n_kv_heads, int n_
     if (cap <= 0) continue;
     sp.total_slots = cap;
     ts.sp[p] = sp;
+    ts.cap[p] = cap;
   }
   return ts;
 }
@@ -464,9 +437,9 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       fill_phase_table(&tabs[ph], ph, cur >= 0 ? &tabs[cur] : nullptr, tile_rows);
       splits[ph] = d.dtype == RC_BF16 ? plan_phase_split(&tabs[ph], d.n_kv_heads, d.n_q_heads, tile_rows, job.max_pos)
                                       : attention_no_split();
-      if (attention_partial_floats(splits[ph], d.n_q_heads) > w.attn_part_floats) {
+      if (attention_partial_floats(splits[ph].total_slots, d.n_q_heads) > w.attn_part_floats) {
         // the plan was made for other row counts than the workspace was sized for: attend unsplit
-        splits[ph] = attention_no_split(splits[ph].slot_rows);
+        splits[ph] = attention_no_split();
       }
       if (splits[ph].n_chunks <= 1) assign_split_slots(&tabs[ph], tile_rows, kKvTile, 1 << 24, 1, 0);   // items = tiles
     }
@@ -540,7 +513,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
             fill_phase_table(&tabs[p], p, &tabs[phase_before], tile_rows);
             splits[p] = ts.sp[p];
             expected_rows[p] = ts.rows[p];
-            if (attention_partial_floats(splits[p], d.n_q_heads) > w.attn_part_floats) splits[p] = attention_no_split();
+            if (attention_partial_floats(splits[p].total_slots, d.n_q_heads) > w.attn_part_floats) splits[p] = attention_no_split();
             // work items of the attention grid, as an upper bound over every possible selection: all tiles whole, or
             // the tiles that stay whole plus as many (tile, chunk) pairs as there are slots
             assign_split_slots(&tabs[p], tile_rows, kKvTile, splits[p].long_thr, splits[p].n_chunks, 1 << 30);
@@ -701,13 +674,13 @@ size_t attn_part_need(const Job& job) {
   if (by_threshold) ts = plan_threshold_split(job.base, d.n_kv_heads, d.n_q_heads, tile_rows, job.max_pos, true);
   for (int p = 0; p < PH_COUNT; ++p) {
     if (by_threshold && p >= PH_C) {
-      need = std::max(need, attention_partial_floats(ts.sp[p], d.n_q_heads));
+      need = std::max(need, attention_partial_floats(ts.cap[p], d.n_q_heads));
       continue;
     }
     ReqTable t = job.base;
     fill_phase_table(&t, p, nullptr, tile_rows);
     const AttnSplit sp = plan_phase_split(&t, d.n_kv_heads, d.n_q_heads, tile_rows, job.max_pos);
-    need = std::max(need, attention_partial_floats(sp, d.n_q_heads));
+    need = std::max(need, attention_partial_floats(sp.total_slots, d.n_q_heads));
   }
   return need;
 }
@@ -1170,7 +1143,7 @@ static AttnSplit plan_stage_split(int tiles, int n_kv_heads, int capacity) {
   }
   const int n_chunks = ((capacity + kKvTile - 1) / kKvTile + chunk_tiles - 1) / chunk_tiles;
   if (n_chunks <= 1) return attention_no_split();
-  AttnSplit sp = {n_chunks, chunk_tiles, thr, tiles * n_chunks, 32};
+  AttnSplit sp = {n_chunks, chunk_tiles, thr, tiles * n_chunks};
   return sp;
 }
 
@@ -1179,7 +1152,7 @@ size_t rc_sparse_attention_workspace_bytes(int32_t n, int32_t n_q_heads, const r
   const int tile_rows = attention_tile_rows(cache->dtype, n_q_heads, cache->n_kv_heads);
   const int tiles = (n + tile_rows - 1) / tile_rows;
   const AttnSplit sp = plan_stage_split(tiles, cache->n_kv_heads, cache->max_blocks_per_seq * cache->block_size);
-  return align_up(sizeof(float) * attention_partial_floats(sp, n_q_heads));
+  return align_up(sizeof(float) * attention_partial_floats(sp.total_slots, n_q_heads));
 }
 
 rc_status rc_sparse_attention(const void* q, const int32_t* q_pos, int32_t n, int32_t n_q_heads,

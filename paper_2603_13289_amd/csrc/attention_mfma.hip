@@ -463,8 +463,6 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   }
 }
 
-#include "attention_decode.h"
-
 // Merge of the KV chunks of one (row, head): one wavefront each, two head-dim elements per lane.
 // Only rows of split tiles take part; chunk c holds keys for a row iff its first key position is <=
 // the row's position.
@@ -488,7 +486,7 @@ attn_merge_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_r
     r = rq.row_base + local;
     const int lt = local / BQ;
     split_tile = lt - rq.long_tile_start;
-    ql = sp.slot_rows > 1 ? local % BQ : 0;
+    ql = local % BQ;
     part_base = rq.part_base;
     tile_last_row = min(rq.row_base + (lt + 1) * BQ, rq.row_base + rq.n_rows) - 1;
   } else {
@@ -502,8 +500,8 @@ attn_merge_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_r
   const int n_kv_tiles = row_pos[tile_last_row] / BKV + 1;
   if (split_tile < 0 || n_kv_tiles <= sp.long_thr) return;   // this row's tile was done by one workgroup
   const int nc = min(sp.n_chunks, row_pos[r] / (sp.chunk_tiles * BKV) + 1);
-  const size_t slot0 = ((size_t)(part_base + split_tile * sp.n_chunks) * n_q_heads + head) * sp.slot_rows + ql;
-  const size_t cstride = (size_t)n_q_heads * sp.slot_rows;
+  const size_t slot0 = ((size_t)(part_base + split_tile * sp.n_chunks) * n_q_heads + head) * BQ + ql;
+  const size_t cstride = (size_t)n_q_heads * BQ;
   // Pass 1, one chunk per lane (64 at a time): the common reference exponent.  Pass 2: every lane needs every
   // chunk's weight, so the (m, l) pairs are read again (they are cached) and the partial outputs of four chunks are
   // requested before the first is used.  The sums run in chunk order.
@@ -553,8 +551,8 @@ int attention_forced_chunk_tiles() { return g_force_chunk_tiles; }
 // rows the slots of one KV chunk of successive query tiles lie a multiple of 1 MiB apart whenever the chunk count is
 // even, and the workgroups that finish together (same chunk, neighbouring tiles) then write to the same memory
 // channels (measured: even chunk counts ran the split layers up to twice as slow).
-size_t attention_partial_floats(const AttnSplit& sp, int n_q_heads) {
-  return (size_t)sp.total_slots * n_q_heads * sp.slot_rows * (PROW + 2);
+size_t attention_partial_floats(int total_slots, int n_q_heads) {
+  return (size_t)total_slots * n_q_heads * BQ * (PROW + 2);
 }
 
 template <int G>
@@ -587,18 +585,9 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
                                  hipStream_t st, float* scores, int scores_len, int merge_rows) {
   if (total_rows <= 0) return hipSuccess;
   const int G = n_q_heads / g.n_kv_heads;
-  if (!part || sp.total_slots <= 0) sp = attention_no_split(sp.slot_rows);
-  hipError_t e = hipSuccess;
-  if (table && sp.slot_rows == 1) {
-    float2* ml = reinterpret_cast<float2*>(part + (size_t)sp.total_slots * n_q_heads * PROW);
-    const dim3 grid((unsigned)((long)total_tiles * g.n_kv_heads));
-    if (scores)
-      attn_decode_kernel<true><<<grid, 64 * kDecWaves, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, ml, scores, scores_len,
-                                                                influence_pairs(scores, total_rows, n_q_heads, scores_len));
-    else
-      attn_decode_kernel<false><<<grid, 64 * kDecWaves, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, ml, nullptr, 0, nullptr);
-    e = hipGetLastError();
-  } else switch (G) {
+  if (!part || sp.total_slots <= 0) sp = attention_no_split();
+  hipError_t e;
+  switch (G) {
 #define RC_ATTN_CASE(GG) \
     case GG: e = launch_g<GG>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool, v_pool, g, out, sp, part, scores, scores_len, st); break;
     RC_ATTN_CASE(1) RC_ATTN_CASE(2) RC_ATTN_CASE(3) RC_ATTN_CASE(4)
@@ -610,7 +599,7 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
                                          n_q_heads, out, st);
   }
   if (e != hipSuccess || sp.n_chunks == 1) return e;
-  const float2* part_ml = reinterpret_cast<const float2*>(part + (size_t)sp.total_slots * n_q_heads * sp.slot_rows * PROW);
+  const float2* part_ml = reinterpret_cast<const float2*>(part + (size_t)sp.total_slots * n_q_heads * BQ * PROW);
   // with a table, merge_rows (the rows of the tiles that may be split, or an upper bound) sizes the merge grid
   const int items = (table ? merge_rows : total_rows) * n_q_heads;
   if (items <= 0) return hipSuccess;

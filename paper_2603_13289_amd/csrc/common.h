@@ -357,13 +357,11 @@ int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads);  // query row
 // A query tile whose KV range spans more than long_thr tiles is cut into chunks of chunk_tiles tiles;
 // n_chunks is the grid's chunk dimension (1: no split at all), total_slots the (tile, chunk) slots of
 // partial results the plan may touch.
-// slot_rows: query rows per slot; 32 (the tile kernel), or 1: every request has at most one row and the decode kernel runs.
-struct AttnSplit { int n_chunks, chunk_tiles, long_thr, total_slots, slot_rows; };
-constexpr int kDecodeMaxGroup = 8;   // query heads per KV head the decode kernel takes
-inline AttnSplit attention_no_split(int slot_rows = 32) { AttnSplit sp = {1, 1 << 24, 1 << 24, 0, slot_rows}; return sp; }
+struct AttnSplit { int n_chunks, chunk_tiles, long_thr, total_slots; };
+inline AttnSplit attention_no_split() { AttnSplit sp = {1, 1 << 24, 1 << 24, 0}; return sp; }
 int attention_forced_chunk_tiles();
 void set_attention_chunk_tiles(int t);  // 0: by shape; > 0: forced KV tiles per chunk
-size_t attention_partial_floats(const AttnSplit& sp, int n_q_heads);
+size_t attention_partial_floats(int total_slots, int n_q_heads);
 hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                  int fixed_seq, int total_rows, int total_tiles, const bf16* k_pool,
                                  const bf16* v_pool, KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part,
