@@ -275,9 +275,11 @@ RC_API rc_status rc_profile_read(float* ms, int32_t* launches);
 
 /* Tuning knobs (process-global).  RC_TUNE_GEMM_TILE: kernel / workgroup tile of the bf16 projection GEMM,
  * 0 = chosen per shape (default); register-staged tiles 1 = 128x256, 2 = 256x256, 3 = 128x128;
- * direct-to-LDS tiles 5 = 256x256 (with the K-split tail), 6 = 128x128, 7 = 256x192 (K-split tail), and, summing over K
- * exactly as the default does, 8 = 192x256, 9 = 128x256, 10 = 128x128 (two per compute unit), 11 = 192x192, 12 = 64x128,
- * 13 = 64x256. */
+ * direct-to-LDS tiles 5 = 256x256 (with the K-split tail), 6 = 128x128, 7 = 256x192 (K-split tail; the gate/up
+ * epilogue runs 8 instead), and, summing over K as the default does for more than 32 rows, 8 = 192x256, 9 = 128x256,
+ * 10 = 128x128 (two per compute unit), 11 = 192x192 (gate/up: 8), 12 = 64x128, 13 = 64x256.  8 to 13 are a wish: products
+ * that the default sums partly whole and partly in parts keep the tiles of that partition, and a type whose padded
+ * parts would not fit the workspace leaves the choice to the library. */
 #define RC_TUNE_GEMM_TILE 1
 /* RC_TUNE_ATTN_CHUNK_TILES: KV tiles (of 64 keys) per attention workgroup when a query tile's KV range is
  * split; 0 = chosen per shape (default), a value beyond the context length disables the split. */
@@ -290,9 +292,10 @@ RC_API rc_status rc_profile_read(float* ms, int32_t* launches);
 RC_API rc_status rc_tune_set(int32_t key, int32_t value);
 
 /* Host-only self-check of the bf16 GEMM's launch schedule (no GPU needed): builds the grid the library would launch
- * for C[m][n] = A[m][k] W^T with direct-to-LDS tile `tile` (5, 6 or 7, see RC_TUNE_GEMM_TILE) on a device of n_cus
- * compute units, walks every workgroup id and counts violations of "every output tile is covered exactly once, by
- * one workgroup over the whole K range or by K parts that partition it in order".  swiglu != 0: the gate/up
+ * for C[m][n] = A[m][k] W^T under RC_TUNE_GEMM_TILE = `tile` (0 or 5 to 13; few-row products, which 0 sends to a kernel of
+ * their own, as if they were not) on a device of n_cus compute units, walks every workgroup id and counts violations of "every
+ * output tile is covered exactly once, by one workgroup over the whole K range or by K parts that partition it in
+ * order, and the parts fit the workspace".  swiglu != 0: the gate/up
  * epilogue (half as many output columns per tile); with_workspace != 0: the K-split tail is allowed.
  * *n_blocks (optional) receives the grid size.  Returns the number of violations, or -1 for bad arguments. */
 RC_API int32_t rc_gemm_plan_check(int32_t m, int32_t n, int32_t k, int32_t swiglu, int32_t tile, int32_t n_cus,

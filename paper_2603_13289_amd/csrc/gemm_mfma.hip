@@ -830,46 +830,6 @@ static hipError_t launch_dl(const GridPlan& plan, int n_blocks, int rem_tiles, c
   return hipGetLastError();
 }
 
-// Host-side check of a launch's grid: every output tile must be covered exactly once, by one whole-K workgroup or by
-// K parts that partition [0, k) in part order; thin tiles only in the last tile row and only for at most 64 live rows.
-// Returns the number of violations; *n_blocks_out receives the grid size.  tile: 5, 6 or 7; n_cus: CUs to plan for.
-int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool with_partial, int* n_blocks_out) {
-  const int bm = tile == 6 ? 128 : 256, bn = tile == 6 ? 128 : (tile == 7 ? 192 : 256), occ = tile == 6 ? 2 : 1;
-  const int bn_out = dual ? bn / 2 : bn;
-  const int tiles_m = (m + bm - 1) / bm, tiles_n = (n + bn_out - 1) / bn_out;
-  int n_blocks = 0, rem_tiles = 0;
-  const GridPlan g = make_grid_plan(m, tiles_n, bm, k / BK, n_cus * occ, tile == 7 ? kStep192 : kStep256,
-                                    with_partial && occ == 1, tile == 5, &n_blocks, &rem_tiles);
-  if (n_blocks_out) *n_blocks_out = n_blocks;
-  int errors = 0;
-  std::vector<int> covered((size_t)tiles_m * tiles_n, 0), next_k((size_t)tiles_m * tiles_n, 0), slots;
-  for (int bid = 0; bid < n_blocks; ++bid) {
-    const BlockWork bw = block_work(g, bid, k);
-    if (bw.kind == 0) continue;
-    if (bw.tile_m < 0 || bw.tile_m >= tiles_m || bw.tile_n < 0 || bw.tile_n >= tiles_n) { ++errors; continue; }
-    const size_t u = (size_t)bw.tile_m * tiles_n + bw.tile_n;
-    if (bw.kind == 2 && (bw.tile_m != tiles_m - 1 || m - (tiles_m - 1) * bm > kThinRows || bw.part_slot >= 0)) ++errors;
-    if (bw.part_slot < 0) {
-      if (bw.k_begin != 0 || bw.k_end != k || covered[u] != 0) ++errors;
-      covered[u] = 1;
-      next_k[u] = k;
-    } else {
-      // parts arrive in block order = part order
-      if (covered[u] == 1 || bw.k_begin != next_k[u] || bw.k_end <= bw.k_begin || bw.k_end > k) ++errors;
-      covered[u] = 2;
-      next_k[u] = bw.k_end;
-      slots.push_back(bw.part_slot);
-    }
-  }
-  for (size_t u = 0; u < covered.size(); ++u)
-    if (covered[u] == 0 || next_k[u] != k) ++errors;
-  // part slots are 0, 1, ... without gaps and fit the partial buffer
-  for (size_t i = 0; i < slots.size(); ++i)
-    if (slots[i] != (int)i) ++errors;
-  if (slots.size() > 256) ++errors;
-  return errors;
-}
-
 static int g_gemm_tile = 0;   // 0: by shape; 1-3: register-staged 128x256 / 256x256 / 128x128; 5-13: direct-to-LDS (kTiles; 6: Tile128)
 void set_gemm_tile(int t) { g_gemm_tile = t; }
 
@@ -893,14 +853,17 @@ static hipError_t launch_cfg(const bf16* a, const bf16* w, const bf16* w2, const
   return hipGetLastError();
 }
 
-// Direct-to-LDS kernels (K a multiple of 64): the K partition by the rule above, then the tile type.  A product that is
-// summed the same way everywhere (whole, or all in the same parts) goes to the tile type with the cheapest
-// schedule; one with whole and cut tiles runs on the tiles its partition is made of.
-static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
-                              void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                              const int* m_live, int m_expected) {
-  const bool dual = epi == EPI_SWIGLU_T;
-  const int ksteps = k / BK, cus = num_cus();
+// The launch of a direct-to-LDS product: tile type (the codes of kTiles; 6: Tile128), grid, tiles that are summed in K parts.
+struct DlPlan { int type; GridPlan grid; int n_blocks, rem_tiles; };
+
+static bool parts_fit(int bm, int bn, int tiles, int split) { return (size_t)tiles * split * bm * bn <= kPartialFloats; }
+
+// The K partition by the rule above, then the tile type.  A product that is summed the same way everywhere (whole, or
+// all in the same parts) goes to the tile type with the cheapest schedule; one with whole and cut tiles runs on the tiles
+// its partition is made of.  A type whose padded tiles in `split` parts exceed the partial buffer is not taken, asked
+// for or not: the number of parts comes from 256-row tiles, and 193 rows padded to 2 x 192 hold half as much again.
+static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool with_partial, bool device_rows, int m_expected) {
+  const int ksteps = k / BK;
   if (dual && (tile == 7 || tile == 11)) tile = 8;   // forced, but the column halves of these two cannot be gate and up
   auto cols = [&](int bn) { const int o = dual ? bn / 2 : bn; return (n + o - 1) / o; };
   // which of 256x256 (5), 128x128 (6) and 256x192 (7) the partition is made of
@@ -908,47 +871,96 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
   if (part == 0) {
     const long t6 = (long)((m + 127) / 128) * cols(128);
     const int slots6 = 2 * cus;
-    const float cost5 = plan_launch(m, cols(256), 256, ksteps, cus, kStep256, partial != nullptr, true).cost;
+    const float cost5 = plan_launch(m, cols(256), 256, ksteps, cus, kStep256, with_partial, true).cost;
     const long last6 = t6 % slots6;
     const float cost6 = (t6 / slots6) * ksteps * kStep128 +
                         (last6 == 0 ? 0.f : (last6 * 2 <= slots6 ? 0.65f : 1.f) * ksteps * kStep128);
     part = cost5 <= cost6 ? 5 : 6;
     if (!dual && n % 192 == 0) {
-      const float cost7 = plan_launch(m, n / 192, 256, ksteps, cus, kStep192, partial != nullptr, false).cost;
+      const float cost7 = plan_launch(m, n / 192, 256, ksteps, cus, kStep192, with_partial, false).cost;
       if (cost7 < std::min(cost5, cost6)) part = 7;
     }
   }
-  int n_blocks = 0, rem_tiles = 0, split = 1, kpp = ksteps;
-  GridPlan plan = {};
+  DlPlan p = {part, {}, 0, 0};
+  int split = 1, kpp = ksteps;
   bool uniform = true;
   if (part != 6) {
-    plan = make_grid_plan(m, cols(part == 7 ? 192 : 256), 256, ksteps, cus, part == 7 ? kStep192 : kStep256,
-                          partial != nullptr, part == 5 && m_live == nullptr, &n_blocks, &rem_tiles);
-    if (rem_tiles > 0 && plan.split > 1) {
-      uniform = plan.full_tiles == 0;
-      split = plan.split;
-      kpp = plan.kpp;
+    p.grid = make_grid_plan(m, cols(part == 7 ? 192 : 256), 256, ksteps, cus, part == 7 ? kStep192 : kStep256,
+                            with_partial, part == 5 && !device_rows, &p.n_blocks, &p.rem_tiles);
+    if (p.rem_tiles > 0 && p.grid.split > 1) {
+      uniform = p.grid.full_tiles == 0;
+      split = p.grid.split;
+      kpp = p.grid.kpp;
     }
   }
-  int type = part;
   if (uniform && part != tile) {
     float best = 0.f;
-    type = 0;
+    p.type = 0;
     for (const TileInfo& t : kTiles) {
       if (dual && !t.dual) continue;
-      if (split > 1 && (size_t)((m + t.bm - 1) / t.bm) * cols(t.bn) * split * t.bm * t.bn > kPartialFloats) continue;
+      if (split > 1 && !parts_fit(t.bm, t.bn, ((m + t.bm - 1) / t.bm) * cols(t.bn), split)) continue;
+      if (t.code == tile) { p.type = t.code; break; }
       const float cost = tile_cost(t, m_expected, cols(t.bn), ksteps, cus, split, kpp);
-      if (type == 0 || cost < best) { type = t.code; best = cost; }
+      if (p.type == 0 || cost < best) { p.type = t.code; best = cost; }
     }
-    if (tile >= 8) type = tile;
     for (const TileInfo& t : kTiles)
-      if (t.code == type) plan = uniform_grid_plan(m, cols(t.bn), t.bm, ksteps, split, kpp, &n_blocks, &rem_tiles);
+      if (t.code == p.type) p.grid = uniform_grid_plan(m, cols(t.bn), t.bm, ksteps, split, kpp, &p.n_blocks, &p.rem_tiles);
   } else if (part == 6) {
-    plan = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &n_blocks, &rem_tiles);
+    p.grid = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &p.n_blocks, &p.rem_tiles);
   }
+  return p;
+}
+
+// Host-side check of a launch: every output tile must be covered exactly once, by one whole-K workgroup or by K parts
+// that partition [0, k) in part order and fit the partial buffer; thin tiles only in the last row of 256x256 tiles and only for
+// at most 64 live rows.  Returns the number of violations; *n_blocks_out receives the grid size.  tile: 0 or a direct-to-LDS
+// code; n_cus: CUs to plan for.
+int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool with_partial, int* n_blocks_out) {
+  const DlPlan p = plan_dl(tile, m, n, k, dual, n_cus, with_partial, false, m);
+  int bm = 128, bn = 128;   // code 6
+  for (const TileInfo& t : kTiles)
+    if (t.code == p.type) { bm = t.bm; bn = t.bn; }
+  const int bn_out = dual ? bn / 2 : bn;
+  const int tiles_m = (m + bm - 1) / bm, tiles_n = (n + bn_out - 1) / bn_out;
+  if (n_blocks_out) *n_blocks_out = p.n_blocks;
+  int errors = 0;
+  std::vector<int> covered((size_t)tiles_m * tiles_n, 0), next_k((size_t)tiles_m * tiles_n, 0), slots;
+  for (int bid = 0; bid < p.n_blocks; ++bid) {
+    const BlockWork bw = block_work(p.grid, bid, k);
+    if (bw.kind == 0) continue;
+    if (bw.tile_m < 0 || bw.tile_m >= tiles_m || bw.tile_n < 0 || bw.tile_n >= tiles_n) { ++errors; continue; }
+    const size_t u = (size_t)bw.tile_m * tiles_n + bw.tile_n;
+    if (bw.kind == 2 && (p.type != 5 || bw.tile_m != tiles_m - 1 || m - (tiles_m - 1) * bm > kThinRows || bw.part_slot >= 0)) ++errors;
+    if (bw.part_slot < 0) {
+      if (bw.k_begin != 0 || bw.k_end != k || covered[u] != 0) ++errors;
+      covered[u] = 1;
+      next_k[u] = k;
+    } else {
+      // parts arrive in block order = part order
+      if (covered[u] == 1 || bw.k_begin != next_k[u] || bw.k_end <= bw.k_begin || bw.k_end > k) ++errors;
+      covered[u] = 2;
+      next_k[u] = bw.k_end;
+      slots.push_back(bw.part_slot);
+    }
+  }
+  for (size_t u = 0; u < covered.size(); ++u)
+    if (covered[u] == 0 || next_k[u] != k) ++errors;
+  // part slots are 0, 1, ... without gaps and fit the partial buffer; the fix-up pass visits exactly the cut tiles
+  for (size_t i = 0; i < slots.size(); ++i)
+    if (slots[i] != (int)i) ++errors;
+  if (!parts_fit(bm, bn, (int)slots.size(), 1)) ++errors;
+  if (p.rem_tiles > 0 ? slots.size() != (size_t)p.rem_tiles * p.grid.split : !slots.empty()) ++errors;
+  return errors;
+}
+
+// Direct-to-LDS kernels (K a multiple of 64).
+static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
+                              void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
+                              const int* m_live, int m_expected) {
+  const DlPlan p = plan_dl(tile, m, n, k, epi == EPI_SWIGLU_T, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
 #define RC_DL(CODE, THIN, ...) \
-  case CODE: return launch_dl<__VA_ARGS__, THIN>(plan, n_blocks, rem_tiles, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live)
-  switch (type) {
+  case CODE: return launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, p.rem_tiles, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live)
+  switch (p.type) {
     RC_DL(5, true, TilePipe<2, 4, 4, 4, 2, 2>);
     RC_DL(6, false, Tile128);
     RC_DL(7, false, TilePipe<2, 4, 4, 4, 2, 1>);

@@ -30,6 +30,18 @@ def test_coverage_over_a_sweep_of_row_counts(n_cus):
                 assert err == 0, (m, n, k, swiglu, tile, n_cus)
 
 
+@pytest.mark.parametrize("tile", [0, 8, 9, 10, 11, 12, 13])
+def test_every_tile_type_covers_the_output_and_fits_the_workspace(tile):
+    """The tile types that share one K partition: at 193 to 256 rows, 192-row tiles cut in 16 parts would hold half as
+    much again as the workspace does."""
+    rows = (1, 33, 61, 64, 65, 100, 192, 193, 200, 256, 257, 400, 449, 600, 1025, 1639, 2500, 5120)
+    shapes = ((6144, 4096), (4096, 4096), (1024, 4096), (4096, 14336), (7168, 5120), (5120, 27648), (777, 448))
+    for m, (n, k), swiglu, ws in itertools.product(rows, shapes, (False, True), (True, False)):
+        assert rc.rc_gemm_plan_check(m, n, k, swiglu, tile, 256, ws)[0] == 0, (m, n, k, swiglu, ws)
+    for n_cus, m in itertools.product((8, 64, 304), range(1, 420, 19)):
+        assert rc.rc_gemm_plan_check(m, 768, 1024, False, tile, n_cus, True)[0] == 0, (n_cus, m)
+
+
 def test_thin_tiles_are_used_for_a_one_row_remainder():
     """1024 + 1 rows against a wide N: the schedule with the thin last tile row needs fewer workgroups than
     five full tile rows would."""
