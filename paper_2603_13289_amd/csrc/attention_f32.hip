@@ -8,6 +8,8 @@
 // Bound by latency: float models have a few hundred keys, so the chain of one wavefront is a handful of blocks; the next
 // block's keys are requested before the current one is used.  Measured, 384 rows x 4 heads x up to 384 keys:
 // 147 us with one wavefront per (row, head) on the vector ALUs, 9 us now.
+#include <climits>
+
 #include "common.h"
 
 namespace rc {
@@ -15,7 +17,7 @@ namespace rc {
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4a;
 
 template <int DH>
-__global__ void __launch_bounds__(DH == 64 ? 512 : 256)
+__global__ void __launch_bounds__(DH == 64 ? 512 : 256, DH == 64 ? 4 : 2)
 attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, const ReqTable* __restrict__ table,
                 int fixed_seq, int total_rows, const float* __restrict__ k_pool, const float* __restrict__ v_pool, KvGeom g,
                 int n_q_heads, float* __restrict__ out) {
@@ -41,9 +43,12 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
   }
   const bool q_ok = qi < n_valid;
   const int my_pos = q_ok ? row_pos[r0 + qi] : -1;
-  int last_pos = my_pos;   // the group's largest position
+  int last_pos = my_pos, first_pos = q_ok ? my_pos : INT_MAX;   // the group's largest and smallest position
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
+  for (int o = 1; o < 16; o <<= 1) {
+    last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
+    first_pos = min(first_pos, __shfl_xor(first_pos, o, 64));
+  }
   const float scale = 1.4426950408889634f / sqrtf((float)DH);   // scores in log2 units
   const float* qrow = q + ((size_t)(r0 + (q_ok ? qi : 0)) * n_q_heads + head) * DH;
   f32x4a fq[NB], fk[NB], acc[NB];
@@ -96,11 +101,44 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
     }
     l_run = l_run * corr + ps;
     m_run = m_new;
+    // Keys that only some rows of the group see have weight 0 for the others, and a value there that is not finite must not
+    // reach them (0 x inf): such values (rare) leave the product and are added row by row to the rows that see them.
+    // The test itself costs up to 2 % (2000 rows x 4 heads: 66.6 -> 67.7 us).
+    bool odd = false;
+    if (kb * 16 + 15 > first_pos) {
+      float z = 0.f;
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) z = fmaf(fv[t][c], 0.f, z);
+      odd = __any(z != z);
+      if (odd) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) fv[t][c] = isfinite(fv[t][c]) ? fv[t][c] : 0.f;
+      }
+    }
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       acc[t] *= corr;
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[t][c], s0[c], acc[t], 0, 0, 0);
+    }
+    if (odd) {
+#pragma unroll 1
+      for (int j = 0; j < 16; ++j) {
+        const int key = kb * 16 + j;
+        const float mine = (j & 2) ? ((j & 1) ? s0[3] : s0[2]) : ((j & 1) ? s0[1] : s0[0]);
+        const float p = __shfl(mine, qi + 16 * (j >> 2), 64);
+        if (key > my_pos) continue;
+        const float* vrow = v_pool + kv_row_offset(g, seq, key, kvh) + 4 * kq;
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!isfinite(vrow[16 * t + e])) acc[t][e] += p * vrow[16 * t + e];
+      }
     }
   }
   l_run += __shfl_xor(l_run, 16, 64);
