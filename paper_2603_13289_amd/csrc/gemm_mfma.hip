@@ -561,6 +561,7 @@ gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, cons
                     const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
                     int epi, GridPlan plan, float* __restrict__ partial, const int* __restrict__ m_live) {
   constexpr int BM = T::BM, BN = T::BN, BN_OUT = DUAL ? BN / 2 : BN;
+  BlockWork bw = {1, 0, 0, 0, k, -1};   // one call of the tile body for both cases: with two, its loop ran out of registers
   if (m_live) {
     // The row count lives on the device (rows selected by a threshold) and the host's m only sized the grid.  The
     // schedule is rebuilt here for the live count, in its plain form: every tile whole, by one workgroup, ids
@@ -572,13 +573,11 @@ gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, cons
     const int x = (int)blockIdx.x % XCDS, j = (int)blockIdx.x / XCDS;
     const int logical = plan.per_xcd > 0 ? x * per_xcd + j : (int)blockIdx.x;
     if ((plan.per_xcd > 0 && j >= per_xcd) || logical >= total) return;
-    int tile_m, tile_n;
-    tile_of(make_tile_order(tiles_m, tiles_n), logical, &tile_m, &tile_n);
-    T::template body<DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, tile_m * BM, tile_n * BN_OUT, 0, k, -1, partial);
-    return;
+    tile_of(make_tile_order(tiles_m, tiles_n), logical, &bw.tile_m, &bw.tile_n);
+  } else {
+    bw = block_work(plan, (int)blockIdx.x, k);
+    if (bw.kind == 0) return;
   }
-  const BlockWork bw = block_work(plan, (int)blockIdx.x, k);
-  if (bw.kind == 0) return;
   if constexpr (THIN) {
     if (bw.kind == 2) {
       gemm_tile_body<64, BN, 1, T::NT / 64, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,

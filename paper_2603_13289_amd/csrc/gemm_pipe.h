@@ -11,7 +11,9 @@
 //     loads therefore stay in flight for 1.5 K steps and are counted (s_waitcnt vmcnt(n), never 0 in the loop).
 //   * Two barriers per K step, before phases 0 and 2.
 // LDS reads are inline assembly, because the compiler would otherwise wait for all direct-to-LDS loads before every
-// LDS read; each phase starts with a wait that names the fragments it is about to use.
+// LDS read; each phase starts with a wait that names the fragments it is about to use.  The compiler takes a fragment as
+// there from its read on, so between the two it must neither move nor spill it: no tile type may run out of registers
+// (tests/test_gemm_code.py reads the generated code for both; a spill would also wait for every load in flight).
 // Measured on 5120 x 28672 x 4096 with random operands: 1370-1390 TFLOP/s against 1200-1210 for a loop with one
 // barrier and one full wait per K step (1710 with operands of zeros, which draw less power).
 #pragma once
@@ -229,9 +231,17 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
   step(i0, i1, k0);
   if (k0 + 64 < k_end) {
     step(i1, i2, k0 + 64);
-  } else {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the reads and loads of the empty step
+  } else {   // the loads and reads of the empty step, whose registers are not free before this
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int i = 0; i < FM0; ++i) asm volatile("" ::"v"(fa[0][s][i]));
+#pragma unroll
+      for (int j = 0; j < FN0; ++j) asm volatile("" ::"v"(fb[1][s][j]));
+    }
   }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // nothing left to wait for; says so on every path of the code
 #undef RC_LDS_READ
 #undef RC_FENCE
 }
