@@ -7,7 +7,7 @@
 // Float models are small (hundreds of rows and columns), where a launch costs what it takes to start it, to fetch its
 // operands once and to drain: the small variant gives every 16 x 16 output block to a workgroup of four wavefronts that
 // share its K range, so that thousands of wavefronts have a few loads each, all in flight.  Products with enough 64 x 64
-// tiles to fill the chip use the big variant (32 x 32 per wavefront, whole K).
+// tiles to fill the chip use the big variant (32 x 32 or 64 x 64 per wavefront, whole K).
 //
 // What would be launches of their own around a product is done inside it: the RMS norm of the input rows (gain applied
 // to the operand, 1 / rms to the finished sums), rotary + paged scatter behind the q|k|v projection, the gather of
@@ -195,28 +195,31 @@ gemm_f32_rope_kernel(F32Gemm g, F32Rope p) {
   }
 }
 
-// 64 x 64 outputs per workgroup (DUAL: 64 x 32 of each matrix), 32 x 32 per wavefront, one step of loads ahead
-template <bool DUAL>
+// 32 F x 32 F outputs per workgroup (DUAL: half as many columns of each matrix), 16 F x 16 F per wavefront, one step of loads
+// ahead.  Bound by the operands' way from the L2 and L1, so products with enough tiles take F = 4, which loads half as much
+// per output: 4096 x 4096 x 4096 1880 -> 1267 us, 5120 x 4096 x 1024 590 -> 411 us against F = 2 (108 TFLOP/s; a 64 x 64
+// vector-ALU tile with its operands in LDS: 1723 and 537 us).
+template <bool DUAL, int F>
 __global__ void __launch_bounds__(256)
 gemm_f32_big_kernel(F32Gemm g) {
-  constexpr int BN = DUAL ? 32 : 64;
-  const int m = live_count(g.m, g.m_live), m0 = blockIdx.y * 64, n0 = blockIdx.x * BN;
+  constexpr int BM = 32 * F, BN = DUAL ? 16 * F : 32 * F;
+  const int m = live_count(g.m, g.m_live), m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
   if (m0 >= m) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, kq = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
-  const float *arow[2], *wrow[2];
+  const float *arow[F], *wrow[F];   // DUAL: the first half of the column blocks is the gate, the second the up projection
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    arow[i] = f32_a_row(g, m0 + wm * 32 + i * 16 + r, m);
-    if (DUAL) wrow[i] = (i ? g.w2 : g.w) + (size_t)min(n0 + wn * 16 + r, g.n - 1) * g.k;
-    else wrow[i] = f32_w_row(g, n0 + wn * 32 + i * 16 + r);
+  for (int i = 0; i < F; ++i) {
+    arow[i] = f32_a_row(g, m0 + (wm * F + i) * 16 + r, m);
+    if (DUAL) wrow[i] = (i >= F / 2 ? g.w2 : g.w) + (size_t)min(n0 + (wn * (F / 2) + i % (F / 2)) * 16 + r, g.n - 1) * g.k;
+    else wrow[i] = f32_w_row(g, n0 + (wn * F + i) * 16 + r);
   }
-  f32x4m acc[2][2] = {}, fa[2], fw[2], fg, na[2], nw[2], ng;
-  float ss[2] = {0.f, 0.f};
+  f32x4m acc[F][F] = {}, fa[F], fw[F], fg, na[F], nw[F], ng;
+  float ss[F] = {};
   auto fetch = [&](int t) {
     const int k0 = 16 * t + 4 * kq;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < F; ++i) {
       na[i] = load_k4(arow[i], k0, g.k);
       nw[i] = load_k4(wrow[i], k0, g.k);
     }
@@ -226,54 +229,68 @@ gemm_f32_big_kernel(F32Gemm g) {
   fetch(0);
   for (int t = 0; t < nt; ++t) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) { fa[i] = na[i]; fw[i] = nw[i]; }
+    for (int i = 0; i < F; ++i) { fa[i] = na[i]; fw[i] = nw[i]; }
     fg = ng;
     if (t + 1 < nt) fetch(t + 1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float av[2];
+      float av[F];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < F; ++i) {
         av[i] = fa[i][e];
         if (g.gain) { ss[i] = fmaf(av[i], av[i], ss[i]); av[i] *= fg[e]; }
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], av[i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], av[i], acc[i][j], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < F; ++i) {
     if (g.gain) {
       float s = ss[i];
       s += __shfl_xor(s, 16, 64);
       s += __shfl_xor(s, 32, 64);
       const float inv = 1.0f / sqrtf(s / (float)g.k + g.eps);
-      acc[i][0] *= inv;
-      acc[i][1] *= inv;
-    }
-    const int row = m0 + wm * 32 + i * 16 + r;
-    if (DUAL) {
-      f32x4m v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = silu_f(acc[i][0][e]) * acc[i][1][e];
-      f32_store(g, row, n0 + wn * 16 + 4 * kq, v, m);
-    } else {
-      f32_store(g, row, n0 + wn * 32 + 4 * kq, acc[i][0], m);
-      f32_store(g, row, n0 + wn * 32 + 16 + 4 * kq, acc[i][1], m);
+      for (int j = 0; j < F; ++j) acc[i][j] *= inv;
+    }
+    const int row = m0 + (wm * F + i) * 16 + r;
+#pragma unroll
+    for (int j = 0; j < (DUAL ? F / 2 : F); ++j) {
+      const int col = n0 + (wn * (DUAL ? F / 2 : F) + j) * 16 + 4 * kq;
+      f32x4m v = acc[i][j];
+      if (DUAL) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = silu_f(acc[i][j][e]) * acc[i][j + F / 2][e];
+      }
+      f32_store(g, row, col, v, m);
     }
   }
+}
+
+template <int F>
+static void launch_f32_big(const F32Gemm& g, hipStream_t st) {
+  const bool dual = g.epi == EPI_SWIGLU_T;
+  const int bn = dual ? 16 * F : 32 * F;
+  const dim3 grid((unsigned)((g.n + bn - 1) / bn), (unsigned)((g.m + 32 * F - 1) / (32 * F)));
+  if (dual) gemm_f32_big_kernel<true, F><<<grid, 256, 0, st>>>(g);
+  else gemm_f32_big_kernel<false, F><<<grid, 256, 0, st>>>(g);
 }
 
 static hipError_t launch_f32(const F32Gemm& g, hipStream_t st) {
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
   const bool dual = g.epi == EPI_SWIGLU_T;
-  const long tiles = (long)((g.m + 63) / 64) * ((g.n + (dual ? 31 : 63)) / (dual ? 32 : 64));
-  if (tiles >= 512) {   // two workgroups per compute unit
-    const dim3 grid((unsigned)((g.n + (dual ? 31 : 63)) / (dual ? 32 : 64)), (unsigned)((g.m + 63) / 64));
-    if (dual) gemm_f32_big_kernel<true><<<grid, 256, 0, st>>>(g);
-    else gemm_f32_big_kernel<false><<<grid, 256, 0, st>>>(g);
+  // output tiles of side x side (dual: of both matrices together)
+  auto tiles = [&](long side) { const long bn = dual ? side / 2 : side; return ((g.m + side - 1) / side) * ((g.n + bn - 1) / bn); };
+  // The large tile from two workgroups per compute unit on, with K from 1024 on from one (700 x 8192 x 688, 384 tiles: 118 us
+  // against 101 with the 64 tile; 1000 x 4096 x 4096, 256 tiles: 363 against 474), if it adds at most a quarter of
+  // padding to the 64 tile's (64 rows: two thirds slower).
+  if (tiles(128) >= (g.k >= 1024 ? 256 : 512) && 16 * tiles(128) <= 5 * tiles(64)) {
+    launch_f32_big<4>(g, st);
+  } else if (tiles(64) >= 512) {   // two workgroups per compute unit
+    launch_f32_big<2>(g, st);
   } else {
     const dim3 grid((unsigned)((g.n + 15) / 16), (unsigned)((g.m + 15) / 16));
     if (dual) gemm_f32_small_kernel<true><<<grid, 256, 0, st>>>(g);
