@@ -22,6 +22,7 @@
 // all row tiles of the same few weight-column tiles: a weight tile is then fetched from HBM once
 // per XCD-L2 instead of once per row tile.
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "common.h"
@@ -745,27 +746,33 @@ static GridPlan make_grid_plan(int m, int tiles_n, int bm, int ksteps, int slots
 }
 
 // ------------------------------------------------------------------ tile types
-// step_lo / step_hi: microseconds of one K step (64) when a quarter / all of the workgroup slots are busy (the clock
-// falls as more of the chip multiplies), fixed: prologue, first loads and epilogue of a round.  All constants are a
-// least-squares fit of log(time) to 250 launches (all tile types, 40 to 5120 rows, N x K of 4096 x 4096, 6144 x 4096,
-// 4096 x 14336 and the gate/up pair 2 x 14336 x 4096, random operands, weights from memory; residual 10 %); choosing by
-// it is on average 2.5 % behind the fastest type of each shape.
+// step_lo / step_hi: microseconds of one K step (64) when a quarter / all of the workgroup slots are busy, extended in a
+// straight line (the clock falls as more of the chip multiplies; where several workgroups share a compute unit, the units
+// that hold most of them decide), fixed: prologue, first loads and epilogue of a round.  The constants are chosen for the
+// types they pick: least squares of log(time) over 4300 launches (all types in turn, 33 to 5120 rows, the q|k|v, output,
+// gate/up and down products of models of 512, 2048, 4096 and 5120 columns, random operands), then moved to where the picked
+// type loses least.  On average it is 0.7 % behind the fastest type of each of 625 shapes with weights from memory (5 % of
+// them: more than 4 %, at worst 14 %).  Constants fitted to the 4096-column products alone, without the step in the number of
+// workgroups to a compute unit, were 2.9 % (16 %, 32 %) behind: gate/up of 200 x 27648 x 5120 167 us for 133,
+// 777 x 6144 x 4096 65 for 51.
 struct TileInfo { int code, bm, bn, occ; bool dual; float step_lo, step_hi, fixed; };
 static constexpr TileInfo kTiles[] = {
-    {5, 256, 256, 1, true, 1.09f, 1.49f, 3.9f},  {7, 256, 192, 1, false, 0.86f, 1.11f, 3.3f},
-    {8, 192, 256, 1, true, 0.83f, 1.18f, 4.6f},  {11, 192, 192, 1, false, 0.68f, 0.88f, 4.1f},
-    {9, 128, 256, 1, true, 0.61f, 0.86f, 3.3f},  {10, 128, 128, 2, true, 0.40f, 1.01f, 1.5f},
-    {12, 64, 128, 3, true, 0.32f, 1.19f, 3.3f},  {13, 64, 256, 2, true, 0.53f, 1.42f, 3.5f},
+    {5, 256, 256, 1, true, 1.01f, 1.23f, 5.34f},  {7, 256, 192, 1, false, 0.70f, 1.11f, 2.44f},
+    {8, 192, 256, 1, true, 0.99f, 1.03f, 2.60f},  {11, 192, 192, 1, false, 0.78f, 0.89f, 2.12f},
+    {9, 128, 256, 1, true, 0.69f, 0.85f, 1.60f},  {10, 128, 128, 2, true, 0.07f, 1.12f, 2.03f},
+    {12, 64, 128, 3, true, 0.03f, 1.27f, 0.68f},  {13, 64, 256, 2, true, 0.02f, 1.46f, 2.05f},
 };
-static constexpr float kFixLaunchUs = 1.5f;         // a fix-up launch
-static constexpr float kPartBytesPerUs = 6.3e6f;    // K parts are written, then read
-static constexpr float kWeightBytesPerUs = 4.2e6f;  // the whole weight matrix from memory
+static constexpr float kFixLaunchUs = 3.10f;          // a fix-up launch
+static constexpr float kPartBytesPerUs = 8.79e6f;     // K parts are written, then read
+static constexpr float kWeightBytesPerUs = 12.11e6f;  // the whole weight matrix from memory
 
-// one K step with a share f of the slots busy; hbm: microseconds below which the weight slices do not arrive from
-// memory (they are shared by the tile rows of a column, so only launches of one or two tile rows feel it)
-static float step_us(const TileInfo& t, float f, int tiles_m) {
-  const float mfma = t.step_lo + (t.step_hi - t.step_lo) * std::max(f - 0.25f, -0.1f) / 0.75f;
-  const float hbm = (float)(t.bn * t.occ) / 256.f * (0.17f + 1.46f * f) / (float)tiles_m;
+// one K step with `wgs` workgroups on the chip; hbm: microseconds below which the weight slices do not arrive from
+// memory (the tile rows of a column share them, but do not ask for them at the same time)
+static float step_us(const TileInfo& t, int wgs, int n_cus, int tiles_m) {
+  const float f = (float)wgs / (float)(n_cus * t.occ);
+  const float busy = t.occ == 1 ? f : (float)((wgs + n_cus - 1) / n_cus) / (float)t.occ;
+  const float mfma = t.step_lo + (t.step_hi - t.step_lo) * std::max(busy - 0.25f, -0.1f) / 0.75f;
+  const float hbm = (float)(t.bn * t.occ) / 256.f * (0.15f + 0.80f * f) * std::pow((float)tiles_m, -0.25f);
   return std::max(mfma, hbm);
 }
 
@@ -773,8 +780,8 @@ static float step_us(const TileInfo& t, float f, int tiles_m) {
 static float tile_cost(const TileInfo& t, int m, int tiles_n, int ksteps, int n_cus, int split, int kpp) {
   const int tiles_m = (m + t.bm - 1) / t.bm, slots = n_cus * t.occ, wgs = tiles_m * tiles_n * split;
   const int rounds = wgs / slots, last = wgs % slots;
-  float c = (float)rounds * (kpp * step_us(t, 1.f, tiles_m) + t.fixed);
-  if (last > 0) c += kpp * step_us(t, (float)last / slots, tiles_m) + t.fixed;
+  float c = (float)rounds * (kpp * step_us(t, slots, n_cus, tiles_m) + t.fixed);
+  if (last > 0) c += kpp * step_us(t, last, n_cus, tiles_m) + t.fixed;
   if (split > 1) c += kFixLaunchUs + (float)wgs * t.bm * t.bn * 8.f / kPartBytesPerUs;
   return std::max(c, (float)tiles_n * t.bn * ksteps * BK * 2.f / kWeightBytesPerUs + t.fixed);
 }
