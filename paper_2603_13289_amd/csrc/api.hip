@@ -257,7 +257,7 @@ struct Workspace {
   int* row_pos;
   int* row_req;
   float* h[2];
-  void* a;       // normalised activations [R][d] of T
+  bf16* a;       // normalised activations [R][d]; this, qkv, h_last and a_last: bf16 models only, float ones never store them
   float* qkv;    // [R][Hq*dh + 2*Hkv*dh]
   void* q;       // rotated queries [R][Hq*dh] of T
   void* o;       // attention output [R][Hq*dh] of T
@@ -265,7 +265,7 @@ struct Workspace {
   void* vfresh;  // [R][Hkv*dh] of T
   float* scores;
   float* h_last;
-  void* a_last;
+  bf16* a_last;
   float* attn_part;   // partial attention results when a layer's KV range is split into chunks
   float* gemm_part;   // accumulators of K-split tail tiles of the bf16 GEMMs
   float* inf_scratch; // attention scores of the decoding rows (influence accumulation)
@@ -293,18 +293,19 @@ Workspace carve(void* base, const rc_model_desc& d, int max_rows, int max_pos, i
   w.row_req = (int*)take(sizeof(int) * R);
   w.h[0] = (float*)take(sizeof(float) * R * d.d_model);
   w.h[1] = (float*)take(sizeof(float) * R * d.d_model);
-  w.a = take(es * R * d.d_model);
-  w.qkv = (float*)take(sizeof(float) * R * (nq + 2 * nkv));
+  const bool is_bf16 = d.dtype == RC_BF16;
+  w.a = is_bf16 ? (bf16*)take(es * R * d.d_model) : nullptr;
+  w.qkv = is_bf16 ? (float*)take(sizeof(float) * R * (nq + 2 * nkv)) : nullptr;
   w.q = take(es * R * nq);
   w.o = take(es * R * nq);
   w.act = take(es * R * d.d_ffn);
   w.vfresh = take(es * R * nkv);
   w.scores = (float*)take(sizeof(float) * (size_t)(sum_seg > 0 ? sum_seg : 1));
-  w.h_last = (float*)take(sizeof(float) * (size_t)n_req * d.d_model);
-  w.a_last = take(es * (size_t)n_req * d.d_model);
+  w.h_last = is_bf16 ? (float*)take(sizeof(float) * (size_t)n_req * d.d_model) : nullptr;
+  w.a_last = is_bf16 ? (bf16*)take(es * (size_t)n_req * d.d_model) : nullptr;
   w.attn_part = (float*)take(sizeof(float) * (attn_part_floats > 0 ? attn_part_floats : 1));
   w.attn_part_floats = attn_part_floats;
-  w.gemm_part = (float*)take(d.dtype == RC_BF16 ? gemm_partial_bytes() : 256);
+  w.gemm_part = (float*)take(is_bf16 ? gemm_partial_bytes() : 256);
   w.inf_scratch = (float*)take(sizeof(float) * (inf_floats > 0 ? inf_floats : 1));
   w.bytes = off;
   return w;
@@ -360,28 +361,14 @@ hipError_t gemm_any(const T* a, const T* wt, const T* wt2, void* c, int m, int n
                     float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 template <>
 hipError_t gemm_any<float>(const float* a, const float* wt, const float* wt2, void* c, int m, int n, int k, int ldc,
-                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live, int m_expected) {
-  return launch_gemm<float>(a, wt, wt2, c, m, n, k, ldc, epi, st, m_live, m_expected);
+                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live, int) {
+  return launch_gemm_f32(a, wt, wt2, c, m, n, k, ldc, epi, st, m_live);
 }
 template <>
 hipError_t gemm_any<bf16>(const bf16* a, const bf16* wt, const bf16* wt2, void* c, int m, int n, int k, int ldc,
                           GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
   return launch_gemm_bf16(a, wt, wt2, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
 }
-template <typename T>
-hipError_t gemm_qkv_any(const T* a, const T* wq, int nq, const T* wk, const T* wv, int nkv, float* c, int m, int k,
-                        float* partial, hipStream_t st, const int* m_live, int m_expected);
-template <>
-hipError_t gemm_qkv_any<float>(const float* a, const float* wq, int nq, const float* wk, const float* wv, int nkv,
-                               float* c, int m, int k, float*, hipStream_t st, const int* m_live, int m_expected) {
-  return launch_gemm_qkv<float>(a, wq, nq, wk, wv, nkv, c, m, k, st, m_live, m_expected);
-}
-template <>
-hipError_t gemm_qkv_any<bf16>(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                              int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected) {
-  return launch_gemm_qkv_bf16(a, wq, nq, wk, wv, nkv, c, m, k, partial, st, m_live, m_expected);
-}
-
 // Partial-attention slots the sparse phase (and the phase after it) may use when the threshold selector decides the
 // row counts on the device: planned for a nominal selection of a fifth of every segment, with room for twice that;
 // a selection that needs more attends unsplit.
@@ -491,7 +478,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
           RC_LAUNCH(PC_GEMM_VFRESH, launch_gemm_f32_normed(w.h[hbuf], (const float*)lw.g_attn, d.rms_eps, nullptr, (const float*)lw.wv,
                                                            nullptr, (float*)w.vfresh, rows_b, nkv, D, EPI_STORE_F32, st));
         } else {
-          RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h[hbuf], (const T*)lw.g_attn, (T*)w.a, rows_b, D, d.rms_eps, st));
+          RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(w.h[hbuf], (const bf16*)lw.g_attn, w.a, rows_b, D, d.rms_eps, st));
           RC_LAUNCH(PC_GEMM_VFRESH, gemm_any<T>((const T*)w.a, (const T*)lw.wv, nullptr, w.vfresh, rows_b, nkv, D, nkv, EPI_STORE_T, w.gemm_part, st));
         }
         float* sc = job.scores_out ? job.scores_out : w.scores;
@@ -550,9 +537,9 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
                                                       (float*)w.q, (float*)job.dst->k_pool[l], (float*)job.dst->v_pool[l],
                                                       job.k_pre_pool ? (float*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st, m_live));
     } else {
-      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_attn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
-      RC_LAUNCH(PC_GEMM_QKV, gemm_qkv_any<T>((const T*)w.a, (const T*)lw.wq, nq, (const T*)lw.wk, (const T*)lw.wv, nkv,
-                                                w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
+      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
+      RC_LAUNCH(PC_GEMM_QKV, launch_gemm_qkv_bf16(w.a, (const bf16*)lw.wq, nq, (const bf16*)lw.wk, (const bf16*)lw.wv, nkv,
+                                                  w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
       // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
       RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
                                     (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
@@ -577,7 +564,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_f32_normed(h, (const float*)lw.g_ffn, d.rms_eps, nullptr, (const float*)lw.w_gate,
                                                         (const float*)lw.w_up, (float*)w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
     } else {
-      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(h, (const T*)lw.g_ffn, (T*)w.a, rows, D, d.rms_eps, st, m_live));
+      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
       RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
     }
     RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
@@ -590,7 +577,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     return RC_OK;
   } else {
     RC_LAUNCH(PC_ROWS, launch_gather_last(w.tables + cur, n_req, w.h[hbuf], w.h_last, D, st));
-    RC_LAUNCH(PC_RMSNORM, launch_rmsnorm<T>(w.h_last, (const T*)job.m->g_final, (T*)w.a_last, n_req, D, d.rms_eps, st));
+    RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(w.h_last, (const bf16*)job.m->g_final, w.a_last, n_req, D, d.rms_eps, st));
     RC_LAUNCH(PC_GEMM_LM_HEAD, gemm_any<T>((const T*)w.a_last, (const T*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, d.vocab,
                           EPI_STORE_F32, w.gemm_part, st));
     return RC_OK;
@@ -1222,7 +1209,7 @@ rc_status rc_gemm_rows(int32_t dtype, const void* a, const void* w, float* c, in
     RC_HIP(launch_gemm_bf16((const bf16*)a, (const bf16*)w, nullptr, c, m, n, k, n, EPI_STORE_F32,
                             reinterpret_cast<float*>(workspace), st));
   else
-    RC_HIP(launch_gemm<float>((const float*)a, (const float*)w, nullptr, c, m, n, k, n, EPI_STORE_F32, st));
+    RC_HIP(launch_gemm_f32((const float*)a, (const float*)w, nullptr, c, m, n, k, n, EPI_STORE_F32, st));
   return RC_OK;
 }
 

@@ -595,7 +595,7 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
 #undef RC_ATTN_CASE
     default:  // wider groups: one wavefront per (row, head) on the vector ALUs
       if (scores) return hipErrorInvalidValue;
-      return launch_attention_simt<bf16>(q, row_pos, row_req, table, fixed_seq, total_rows, k_pool, v_pool, g,
+      return launch_attention_simt(q, row_pos, row_req, table, fixed_seq, total_rows, k_pool, v_pool, g,
                                          n_q_heads, out, st);
   }
   if (e != hipSuccess || sp.n_chunks == 1) return e;

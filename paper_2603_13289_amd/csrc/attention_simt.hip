@@ -1,16 +1,15 @@
-// K6 for bf16 models with more than eight query heads per KV head: causal grouped-query attention of arbitrary query rows over a paged
-// cache on the vector ALUs.  One wavefront (= one workgroup) per (query row, query head); keys are
+// K6 for bf16 models with more than eight query heads per KV head: causal grouped-query attention of arbitrary query
+// rows over a paged cache on the vector ALUs.  One wavefront (= one workgroup) per (query row, query head); keys are
 // consumed 64 at a time with a running softmax.  Narrower groups use the matrix-core kernel instead.
 #include "common.h"
 
 namespace rc {
 
-template <typename T>
 __global__ void __launch_bounds__(64)
-attn_simt_kernel(const T* __restrict__ q, const int* __restrict__ row_pos, const int* __restrict__ row_req,
-                 const ReqTable* __restrict__ table, int fixed_seq, const T* __restrict__ k_pool,
-                 const T* __restrict__ v_pool, KvGeom g, int n_q_heads, T* __restrict__ out) {
-  constexpr int VEC = Vec16<T>::N;
+attn_simt_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, const int* __restrict__ row_req,
+                 const ReqTable* __restrict__ table, int fixed_seq, const bf16* __restrict__ k_pool,
+                 const bf16* __restrict__ v_pool, KvGeom g, int n_q_heads, bf16* __restrict__ out) {
+  constexpr int VEC = Vec16<bf16>::N;
   __shared__ float q_s[128];
   __shared__ float p_s[64];
   const int lane = threadIdx.x;
@@ -20,7 +19,7 @@ attn_simt_kernel(const T* __restrict__ q, const int* __restrict__ row_pos, const
   const int dh = g.head_dim;
   const int pos = row_pos[r];
   const int seq = table ? table->r[row_req[r] & kRowReqMask].dst_seq : fixed_seq;
-  const T* qrow = q + ((size_t)r * n_q_heads + hq) * dh;
+  const bf16* qrow = q + ((size_t)r * n_q_heads + hq) * dh;
   for (int c = lane; c < dh; c += 64) q_s[c] = to_f32(qrow[c]);
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)dh);
@@ -29,11 +28,11 @@ attn_simt_kernel(const T* __restrict__ q, const int* __restrict__ row_pos, const
     const int t = t0 + lane;
     float s = -INFINITY;
     if (t <= pos) {
-      const T* krow = k_pool + kv_row_offset(g, seq, t, kvh);
+      const bf16* krow = k_pool + kv_row_offset(g, seq, t, kvh);
       float d = 0.f;
       for (int c = 0; c < dh; c += VEC) {
         float kv[VEC];
-        Vec16<T>::load(krow + c, kv);
+        Vec16<bf16>::load(krow + c, kv);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) d = fmaf(q_s[c + e], kv[e], d);
       }
@@ -56,30 +55,26 @@ attn_simt_kernel(const T* __restrict__ q, const int* __restrict__ row_pos, const
     acc[1] *= corr;
     const int nt = min(64, pos - t0 + 1);
     for (int tt = 0; tt < nt; ++tt) {
-      const T* vrow = v_pool + kv_row_offset(g, seq, t0 + tt, kvh);
+      const bf16* vrow = v_pool + kv_row_offset(g, seq, t0 + tt, kvh);
       const float pw = p_s[tt];
       if (lane < dh) acc[0] = fmaf(pw, to_f32(vrow[lane]), acc[0]);
       if (lane + 64 < dh) acc[1] = fmaf(pw, to_f32(vrow[lane + 64]), acc[1]);
     }
     __syncthreads();
   }
-  T* orow = out + ((size_t)r * n_q_heads + hq) * dh;
-  if (lane < dh) orow[lane] = from_f32<T>(acc[0] / l);
-  if (lane + 64 < dh) orow[lane + 64] = from_f32<T>(acc[1] / l);
+  bf16* orow = out + ((size_t)r * n_q_heads + hq) * dh;
+  if (lane < dh) orow[lane] = from_f32<bf16>(acc[0] / l);
+  if (lane + 64 < dh) orow[lane + 64] = from_f32<bf16>(acc[1] / l);
 }
 
-template <typename T>
-hipError_t launch_attention_simt(const T* q, const int* row_pos, const int* row_req, const ReqTable* table,
-                                 int fixed_seq, int total_rows, const T* k_pool, const T* v_pool, KvGeom g,
-                                 int n_q_heads, T* out, hipStream_t st) {
+hipError_t launch_attention_simt(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
+                                 int fixed_seq, int total_rows, const bf16* k_pool, const bf16* v_pool, KvGeom g,
+                                 int n_q_heads, bf16* out, hipStream_t st) {
   if (total_rows <= 0) return hipSuccess;
-  attn_simt_kernel<T><<<(unsigned)(total_rows * n_q_heads), 64, 0, st>>>(q, row_pos, row_req, table, fixed_seq,
+  attn_simt_kernel<<<(unsigned)(total_rows * n_q_heads), 64, 0, st>>>(q, row_pos, row_req, table, fixed_seq,
                                                                         k_pool, v_pool, g, n_q_heads, out);
   return hipGetLastError();
 }
-template hipError_t launch_attention_simt<bf16>(const bf16*, const int*, const int*, const ReqTable*, int, int,
-                                                const bf16*, const bf16*, KvGeom, int, bf16*, hipStream_t);
-
 
 int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads) {
   (void)dtype; (void)n_q_heads; (void)n_kv_heads;

@@ -286,17 +286,16 @@ hipError_t launch_capture_rows(const ReqTable* table, int total_rows, const floa
                                int d, hipStream_t st);
 
 // m_live (optional, device): the live row count when `rows` is only an upper bound
-template <typename T>
-hipError_t launch_rmsnorm(const float* h, const T* gain, T* out, int rows, int d, float eps, hipStream_t st,
+hipError_t launch_rmsnorm(const float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
                           const int* m_live = nullptr);
 
 enum GemmEpilogue : int { EPI_STORE_F32 = 0, EPI_STORE_T = 1, EPI_ADD_F32 = 2, EPI_SWIGLU_T = 3 };
 // C[M][ldc] (op)= A[M][K] * W[N][K]^T ; W2 only for EPI_SWIGLU_T (gate = W, up = W2)
-// m_live (optional, device): the live row count when m is only an upper bound (rows selected on the device); m_expected: the row count to plan for then (0: m)
-// the launch then covers m rows' worth of tiles and workgroups past the live rows leave at once
-template <typename T>
-hipError_t launch_gemm(const T* a, const T* w, const T* w2, void* c, int m, int n, int k, int ldc,
-                       GemmEpilogue epi, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+// m_live (optional, device): the live row count when m is only an upper bound (rows selected on the device); the launch
+// then covers m rows' worth of tiles and workgroups past the live rows leave at once.  m_expected: the row count to plan
+// for then (0: m).
+hipError_t launch_gemm_f32(const float* a, const float* w, const float* w2, void* c, int m, int n, int k, int ldc,
+                           GemmEpilogue epi, hipStream_t st, const int* m_live = nullptr);
 
 // Float models: what surrounds a product is done inside it.  h is RMS-normalised with `gain` on the way in; last_of:
 // row b of the product is the last live row of request b.
@@ -315,16 +314,12 @@ hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2,
                                    void* c, int m, int n, int k, int ldc, GemmEpilogue epi, hipStream_t st,
                                    const int* m_live = nullptr);
 
-// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T
-template <typename T>
-hipError_t launch_gemm_qkv(const T* a, const T* wq, int nq, const T* wk, const T* wv, int nkv, float* c, int m,
-                           int k, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
-
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.
 size_t gemm_partial_bytes();
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
                             GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
                                 int m, int k, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
 void set_gemm_xcd_remap(int on);
@@ -344,10 +339,9 @@ template <typename T>
 hipError_t launch_attention(const T* q, const int* row_pos, const int* row_req, const ReqTable* table,
                             int fixed_seq, int total_rows, int total_tiles, const T* k_pool, const T* v_pool,
                             KvGeom g, int n_q_heads, T* out, hipStream_t st);
-template <typename T>
-hipError_t launch_attention_simt(const T* q, const int* row_pos, const int* row_req, const ReqTable* table,
-                                 int fixed_seq, int total_rows, const T* k_pool, const T* v_pool, KvGeom g,
-                                 int n_q_heads, T* out, hipStream_t st);
+hipError_t launch_attention_simt(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
+                                 int fixed_seq, int total_rows, const bf16* k_pool, const bf16* v_pool, KvGeom g,
+                                 int n_q_heads, bf16* out, hipStream_t st);
 int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads);  // query rows per attention tile
 
 // bf16 attention with an optional split of every query tile's KV range into chunks (partial results

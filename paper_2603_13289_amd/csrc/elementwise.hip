@@ -350,9 +350,8 @@ __device__ inline void load4(const bf16* p, float* v) {
 // One workgroup per row; the row stays in registers between the sum of squares and the scaling when it is
 // at most kNormKeep floats per thread (d <= 8192), else it is read again.
 constexpr int kNormKeep = 8;
-template <typename T>
 __global__ void __launch_bounds__(kThreads)
-rmsnorm_kernel(const float* __restrict__ h, const T* __restrict__ gain, T* __restrict__ out, int d, float eps,
+rmsnorm_kernel(const float* __restrict__ h, const bf16* __restrict__ gain, bf16* __restrict__ out, int d, float eps,
                const int* __restrict__ m_live) {
   __shared__ float red[kThreads / 64];
   if (m_live && (int)blockIdx.x >= *m_live) return;
@@ -381,7 +380,7 @@ rmsnorm_kernel(const float* __restrict__ h, const T* __restrict__ gain, T* __res
   }
   ss = block_sum(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  T* o = out + (size_t)blockIdx.x * d;
+  bf16* o = out + (size_t)blockIdx.x * d;
 #pragma unroll
   for (int u = 0; u < kNormKeep; ++u) {
     const int c = (threadIdx.x + u * kThreads) * 4;
@@ -399,15 +398,12 @@ rmsnorm_kernel(const float* __restrict__ h, const T* __restrict__ gain, T* __res
   }
 }
 
-template <typename T>
-hipError_t launch_rmsnorm(const float* h, const T* gain, T* out, int rows, int d, float eps, hipStream_t st,
+hipError_t launch_rmsnorm(const float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
                           const int* m_live) {
   if (rows <= 0) return hipSuccess;
-  rmsnorm_kernel<T><<<rows, kThreads, 0, st>>>(h, gain, out, d, eps, m_live);
+  rmsnorm_kernel<<<rows, kThreads, 0, st>>>(h, gain, out, d, eps, m_live);
   return hipGetLastError();
 }
-template hipError_t launch_rmsnorm<float>(const float*, const float*, float*, int, int, float, hipStream_t, const int*);
-template hipError_t launch_rmsnorm<bf16>(const float*, const bf16*, bf16*, int, int, float, hipStream_t, const int*);
 
 // ------------------------------------------------------------------ rotary on fresh q/k + K7: paged scatter
 // One workgroup per live row.  qkv is the float output of the three projections laid out

@@ -299,9 +299,8 @@ static hipError_t launch_f32(const F32Gemm& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <>
-hipError_t launch_gemm<float>(const float* a, const float* w, const float* w2, void* c, int m, int n, int k,
-                              int ldc, GemmEpilogue epi, hipStream_t st, const int* m_live, int) {
+hipError_t launch_gemm_f32(const float* a, const float* w, const float* w2, void* c, int m, int n, int k, int ldc,
+                           GemmEpilogue epi, hipStream_t st, const int* m_live) {
   return launch_f32(F32Gemm{a, w, w2, nullptr, n, n, nullptr, 0.f, nullptr, (float*)c, m, n, k, ldc, (int)epi, m_live}, st);
 }
 

@@ -999,29 +999,16 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
   }
 }
 
-template <>
-hipError_t launch_gemm<bf16>(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                             GemmEpilogue epi, hipStream_t st, const int* m_live, int m_expected) {
-  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, nullptr, st, m_live, m_expected);
-}
-
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
                             GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
   return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
 }
 
+// q | k | v projections of the same rows as one GEMM over the concatenated output columns
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
                                 int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected) {
   const int n = nq + 2 * nkv;
   return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, partial, st, m_live, m_expected);
-}
-
-// q | k | v projections of the same rows as one GEMM over the concatenated output columns
-template <>
-hipError_t launch_gemm_qkv<bf16>(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
-                                 float* c, int m, int k, hipStream_t st, const int* m_live, int m_expected) {
-  const int n = nq + 2 * nkv;
-  return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, nullptr, st, m_live, m_expected);
 }
 
 }  // namespace rc
