@@ -755,9 +755,11 @@ static GridPlan make_grid_plan(int m, int tiles_n, int bm, int ksteps, int slots
 // them: more than 4 %, at worst 14 %).  Constants fitted to the 4096-column products alone, without the step in the number of
 // workgroups to a compute unit, were 2.9 % (16 %, 32 %) behind: gate/up of 200 x 27648 x 5120 167 us for 133,
 // 777 x 6144 x 4096 65 for 51.
+// 256x192 at 1.08 and not the fit's 1.11: 192-row tiles that cover as much in the one round are then not preferred to it
+// (2500 x 4096 x 14336 244 -> 239 us, 2039 x 5120 x 27648 466 -> 453; 1801 x 5120 x 27648 loses 441 -> 451).
 struct TileInfo { int code, bm, bn, occ; bool dual; float step_lo, step_hi, fixed; };
 static constexpr TileInfo kTiles[] = {
-    {5, 256, 256, 1, true, 1.01f, 1.23f, 5.34f},  {7, 256, 192, 1, false, 0.70f, 1.11f, 2.44f},
+    {5, 256, 256, 1, true, 1.01f, 1.23f, 5.34f},  {7, 256, 192, 1, false, 0.70f, 1.08f, 2.44f},
     {8, 192, 256, 1, true, 0.99f, 1.03f, 2.60f},  {11, 192, 192, 1, false, 0.78f, 0.89f, 2.12f},
     {9, 128, 256, 1, true, 0.69f, 0.85f, 1.60f},  {10, 128, 128, 2, true, 0.07f, 1.12f, 2.03f},
     {12, 64, 128, 3, true, 0.03f, 1.27f, 0.68f},  {13, 64, 256, 2, true, 0.02f, 1.46f, 2.05f},
