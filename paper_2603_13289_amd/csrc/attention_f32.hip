@@ -1,13 +1,14 @@
 // K6 for the float configuration: causal grouped-query attention of arbitrary query rows over a paged cache on
 // v_mfma_f32_16x16x4_f32.
 //
-// A workgroup serves 16 query rows of one request and one query head; its eight (head size 128: four)
-// wavefronts take every eighth block of 16 keys, each with a running softmax of its own, and are merged through LDS at the end.  Per key block a wavefront computes
+// A workgroup serves 16 query rows of one request and one query head; its eight (head size 128: four) wavefronts take
+// every eighth (fourth) block of 16 keys, each with a running softmax of its own, and are merged through LDS at the end.
+// Per key block a wavefront computes
 //   S^T[key][q] = K[key][:] . Q[q][:]      lane holds query lane % 16, keys 4 (lane / 16) + 0..3
 //   O^T[d][q]  += V^T[d][key] P[key][q]    P's operand is S^T's result register as it stands
 // Bound by latency: float models have a few hundred keys, so the chain of one wavefront is a handful of blocks; the next
-// block's keys are requested before the current one is used.  Measured, 384 rows x 4 heads x up to 384 keys:
-// 147 us with one wavefront per (row, head) on the vector ALUs, 9 us now.
+// block's keys are requested before the current one is used.  Measured in a call, 384 rows x 4 heads of 64 x up to 384
+// keys: 146 us with one wavefront per (row, head) on the vector ALUs, 15.7 us now.
 #include <climits>
 
 #include "common.h"

@@ -364,7 +364,7 @@ rmsnorm_kernel(const float* __restrict__ h, const bf16* __restrict__ gain, bf16*
     const int c = (threadIdx.x + u * kThreads) * 4;
     if (c < d) {
       keep[u] = *reinterpret_cast<const float4*>(x + c);
-      load4(gain + c, gv[u]);   // asked for with the row, not after the sum: a single row 5.1 -> 4.4 us
+      load4(gain + c, gv[u]);   // asked for with the row, not after the sum: a single row of a decoding step 4.7 -> 4.5 us
     }
   }
 #pragma unroll

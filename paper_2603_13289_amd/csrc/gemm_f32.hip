@@ -11,8 +11,8 @@
 //
 // What would be launches of their own around a product is done inside it: the RMS norm of the input rows (gain applied
 // to the operand, 1 / rms to the finished sums), rotary + paged scatter behind the q|k|v projection, the gather of
-// each request's last row before the LM head.  Measured, 384 x 256 x 256: 31 us with a 64 x 64 vector-ALU tile (24 workgroups),
-// 5 us now, of which 4.5 us are the launch.
+// each request's last row before the LM head.  Measured in a call against a 64 x 64 vector-ALU tile (24 workgroups):
+// 384 x 256 x 256 22.0 -> 4.7 us, 384 x 256 x 688 53.5 -> 6.5 us; an empty launch takes about 4 us.
 #include "common.h"
 
 namespace rc {

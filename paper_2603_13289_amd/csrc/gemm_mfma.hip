@@ -626,9 +626,10 @@ gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, TileOrde
 // ------------------------------------------------------------------ the K partition of a product
 // Which outputs are summed over K in one go and which in parts.  This is part of the result's definition: another
 // partition changes the last bit of float sums, bf16 rounding turns that into whole rounding steps and a stack of
-// decoder layers carries them to about 1e-2 of the logits.  So the partition is a function of the product's sizes
-// alone (rows, columns, K, epilogue, compute units), and the tile types below, which only decide who computes what,
-// all give the same bits.
+// decoder layers carries them to about 1e-2 of the logits.  So the partition is a function of the product's sizes (rows,
+// columns, K, epilogue, compute units) and of what the caller hands over (without a workspace, or with the row count on
+// the device, every output is summed whole), never of the tile types below, which only decide who computes what and
+// all give the same bits.  Products of at most 32 rows may go to the few-row kernel, which adds eight shares of K.
 //
 // The rule: 256x256, 256x192 (where they cover N exactly) or 128x128 tiles, whichever a rough time model prices lowest
 // (microseconds; one K step of a full round costs kStep256, kStep192 (one workgroup per CU) or kStep128 (two per CU),

@@ -8,9 +8,9 @@
 // order and the epilogue is applied.  Rows 16..31 use a second accumulator.
 //
 // A wavefront keeps two register sets of U steps and refills one while the other is multiplied, so loads are always
-// in flight.  Loading a group of four steps, waiting for it and multiplying it left memory idle between groups:
-// gate/up of 1 x 28672 x 4096 47.0 -> 43.7 us (5.4 TB/s, one workgroup to a CU); decoding one sequence on the 7B shape 4.49 -> 4.39 ms, sixteen
-// 7.70 -> 7.02 ms (their activation rows come from the L2, which the old loop waited for as well).
+// in flight.  Loading a group of four steps, waiting for it and multiplying it left memory idle between groups: gate/up of
+// 1 x 28672 x 4096 in a decoding step 47.4 -> 42.4 us (5.5 TB/s), of 16 rows 62.5 -> 47.7 us (their activation rows come from
+// the L2, which the old loop waited for as well).
 #include <type_traits>
 
 #include "common.h"
@@ -25,7 +25,7 @@ static constexpr int kSkinnyWaves = 8;
 // workgroup): there are too few wavefronts to hide the latency otherwise.  They need two full sets in a wavefront's
 // share of K: shorter ones (K below 4096) have nothing to pipeline.  With more workgroups, two have to fit a CU:
 // sets of four steps in at most 128 registers (the line at 512 workgroups and 130 registers: a decoding step of one
-// sequence 4.10 ms, of sixteen 7.07; as it is 4.02 and 6.94).
+// sequence on the 7B shape 4.23 ms, of sixteen 7.97; as it is 4.17 and 7.88).
 static constexpr int kSkinnyDeepGroups = 256;
 
 __device__ inline float silu_s(float x) { return x / (1.0f + __expf(-x)); }
