@@ -333,17 +333,18 @@ struct Job {
   bool takeover = true;           // false: the segment rows already sit in dst (a decoding step)
   bool any_inf = false;
   InfluencePtrs inf;
+  int score_len() const { return (max_pos + 3) & ~3; }   // floats between the rows of attention scores: whole 16-byte groups
 };
 
 template <typename T>
 hipError_t attention_dispatch(const T* q, const int* row_pos, const int* row_req, const ReqTable* table,
                               int total_rows, int total_tiles, const T* k_pool, const T* v_pool, KvGeom g,
                               int n_q_heads, T* out, AttnSplit sp, float* part, hipStream_t st, float* scores,
-                              int scores_len, int merge_rows);
+                              int scores_len, int merge_rows, bool one_row);
 template <>
 hipError_t attention_dispatch<float>(const float* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                      int total_rows, int total_tiles, const float* k_pool, const float* v_pool,
-                                     KvGeom g, int n_q_heads, float* out, AttnSplit, float*, hipStream_t st, float*, int, int) {
+                                     KvGeom g, int n_q_heads, float* out, AttnSplit, float*, hipStream_t st, float*, int, int, bool) {
   return launch_attention<float>(q, row_pos, row_req, table, 0, total_rows, total_tiles, k_pool, v_pool, g,
                                  n_q_heads, out, st);
 }
@@ -351,9 +352,9 @@ template <>
 hipError_t attention_dispatch<bf16>(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                     int total_rows, int total_tiles, const bf16* k_pool, const bf16* v_pool,
                                     KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part, hipStream_t st,
-                                    float* scores, int scores_len, int merge_rows) {
+                                    float* scores, int scores_len, int merge_rows, bool one_row) {
   return launch_attention_bf16(q, row_pos, row_req, table, 0, total_rows, total_tiles, k_pool, v_pool, g, n_q_heads,
-                               out, sp, part, st, scores, scores_len, merge_rows);
+                               out, sp, part, st, scores, scores_len, merge_rows, one_row);
 }
 
 template <typename T>
@@ -410,6 +411,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
 
   ReqTable tabs[PH_COUNT];
   AttnSplit splits[PH_COUNT];
+  bool one_row[PH_COUNT] = {false, false, false, false};     // no request has more than one live row
   bool on_device[PH_COUNT] = {false, false, false, false};   // table already written (and finalized) on the device
   for (int p = 0; p < PH_COUNT; ++p) tabs[p] = job.base;
 
@@ -429,6 +431,8 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
         splits[ph] = attention_no_split();
       }
       if (splits[ph].n_chunks <= 1) assign_split_slots(&tabs[ph], tile_rows, kKvTile, 1 << 24, 1, 0);   // items = tiles
+      one_row[ph] = true;
+      for (int b = 0; b < n_req; ++b) one_row[ph] = one_row[ph] && tabs[ph].r[b].n_rows <= 1;
     }
     const int nb = cur >= 0 ? 1 - hbuf : hbuf;
     if (on_device[ph]) {
@@ -550,14 +554,14 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     const bool scores_from_attention = job.any_inf && d.dtype == RC_BF16 && d.n_q_heads / d.n_kv_heads <= 8;
     if (job.any_inf && !scores_from_attention)
       RC_LAUNCH(PC_INFLUENCE, launch_influence_scores<T>((const T*)w.q, w.row_pos, w.row_req, w.tables + cur, rows,
-                                                         (const T*)job.dst->k_pool[l], gd, d.n_q_heads, job.max_pos,
+                                                         (const T*)job.dst->k_pool[l], gd, d.n_q_heads, job.score_len(),
                                                          w.inf_scratch, st));
     RC_LAUNCH(PC_ATTENTION, attention_dispatch<T>((const T*)w.q, w.row_pos, w.row_req, w.tables + cur, rows,
                                  tabs[cur].total_items, (const T*)job.dst->k_pool[l],
                                  (const T*)job.dst->v_pool[l], gd, d.n_q_heads, (T*)w.o, splits[cur], w.attn_part, st,
-                                 scores_from_attention ? w.inf_scratch : nullptr, job.max_pos, tabs[cur].total_merge_rows));
+                                 scores_from_attention ? w.inf_scratch : nullptr, job.score_len(), tabs[cur].total_merge_rows, one_row[cur]));
     if (job.any_inf)
-      RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.max_pos, job.inf,
+      RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.score_len(), job.inf,
                                                       w.inf_scratch, scores_from_attention, st));
     RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
     if constexpr (kFloat) {
@@ -915,7 +919,7 @@ static rc_status prepare_decode(const rc_model* m, const rc_decode_req* reqs, in
 }
 
 static size_t decode_inf_floats(const Job& job) {
-  return job.any_inf ? influence_scratch_floats(job.base.n_req, job.m->d.n_q_heads, job.max_pos) : 0;
+  return job.any_inf ? influence_scratch_floats(job.base.n_req, job.m->d.n_q_heads, job.score_len()) : 0;
 }
 
 size_t rc_decode_workspace_bytes(const rc_model* m, const rc_decode_req* reqs, int32_t n_req) {

@@ -463,6 +463,8 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   }
 }
 
+#include "attention_decode.h"
+
 // Merge of the KV chunks of one (row, head): one wavefront each, two head-dim elements per lane.
 // Only rows of split tiles take part; chunk c holds keys for a row iff its first key position is <=
 // the row's position.
@@ -582,12 +584,21 @@ static hipError_t launch_g(const bf16* q, const int* row_pos, const ReqTable* ta
 hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                  int fixed_seq, int total_rows, int total_tiles, const bf16* k_pool,
                                  const bf16* v_pool, KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part,
-                                 hipStream_t st, float* scores, int scores_len, int merge_rows) {
+                                 hipStream_t st, float* scores, int scores_len, int merge_rows, bool one_row) {
   if (total_rows <= 0) return hipSuccess;
   const int G = n_q_heads / g.n_kv_heads;
   if (!part || sp.total_slots <= 0) sp = attention_no_split();
   hipError_t e;
-  switch (G) {
+  if (table && one_row && G <= 8) {
+    const unsigned grid = (unsigned)total_tiles * (unsigned)g.n_kv_heads;
+    float2* part_ml = reinterpret_cast<float2*>(part + (size_t)sp.total_slots * n_q_heads * BQ * PROW);
+    if (scores)
+      attn_decode_kernel<true><<<grid, 128, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, scores,
+                                                     scores_len, influence_pairs(scores, total_rows, n_q_heads, scores_len));
+    else
+      attn_decode_kernel<false><<<grid, 128, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, nullptr, 0, nullptr);
+    e = hipGetLastError();
+  } else switch (G) {
 #define RC_ATTN_CASE(GG) \
     case GG: e = launch_g<GG>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool, v_pool, g, out, sp, part, scores, scores_len, st); break;
     RC_ATTN_CASE(1) RC_ATTN_CASE(2) RC_ATTN_CASE(3) RC_ATTN_CASE(4)

@@ -351,6 +351,7 @@ int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads);  // query row
 // A query tile whose KV range spans more than long_thr tiles is cut into chunks of chunk_tiles tiles;
 // n_chunks is the grid's chunk dimension (1: no split at all), total_slots the (tile, chunk) slots of
 // partial results the plan may touch.
+// one_row (with a table whose counts the host knows): no request has more than one live row.
 struct AttnSplit { int n_chunks, chunk_tiles, long_thr, total_slots; };
 inline AttnSplit attention_no_split() { AttnSplit sp = {1, 1 << 24, 1 << 24, 0}; return sp; }
 int attention_forced_chunk_tiles();
@@ -359,7 +360,8 @@ size_t attention_partial_floats(int total_slots, int n_q_heads);
 hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                  int fixed_seq, int total_rows, int total_tiles, const bf16* k_pool,
                                  const bf16* v_pool, KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part,
-                                 hipStream_t st, float* scores = nullptr, int scores_len = 0, int merge_rows = 0);
+                                 hipStream_t st, float* scores = nullptr, int scores_len = 0, int merge_rows = 0,
+                                 bool one_row = false);
 
 template <typename T>
 hipError_t launch_vdev_score(const T* v_fresh, int fresh_row_stride, const T* v_pool, KvGeom g,
