@@ -256,8 +256,9 @@ struct Workspace {
   float2* delta_tab;
   int* row_pos;
   int* row_req;
+  unsigned* row_dst;   // pool row of the row's place in the destination cache, KV head 0
   float* h[2];
-  bf16* a;       // normalised activations [R][d]; this, qkv, h_last and a_last: bf16 models only, float ones never store them
+  bf16* a;       // normalised activations [R][d]; this, qkv, row_dst, h_last and a_last: bf16 models only, float ones never store them
   float* qkv;    // [R][Hq*dh + 2*Hkv*dh]
   void* q;       // rotated queries [R][Hq*dh] of T
   void* o;       // attention output [R][Hq*dh] of T
@@ -294,6 +295,7 @@ Workspace carve(void* base, const rc_model_desc& d, int max_rows, int max_pos, i
   w.h[0] = (float*)take(sizeof(float) * R * d.d_model);
   w.h[1] = (float*)take(sizeof(float) * R * d.d_model);
   const bool is_bf16 = d.dtype == RC_BF16;
+  w.row_dst = is_bf16 ? (unsigned*)take(sizeof(unsigned) * R) : nullptr;
   w.a = is_bf16 ? (bf16*)take(es * R * d.d_model) : nullptr;
   w.qkv = is_bf16 ? (float*)take(sizeof(float) * R * (nq + 2 * nkv)) : nullptr;
   w.q = take(es * R * nq);
@@ -415,6 +417,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
   bool on_device[PH_COUNT] = {false, false, false, false};   // table already written (and finalized) on the device
   for (int p = 0; p < PH_COUNT; ++p) tabs[p] = job.base;
 
+  const RowInfo row_info = {w.row_pos, w.row_req, w.row_dst, gd};
   int cur = -1;   // phase whose rows are live in w.h[hbuf]
   int hbuf = 0;
   // Row counts of the phase: exact on the host, or (threshold selector, from the sparse phase on) an upper bound
@@ -436,13 +439,12 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     }
     const int nb = cur >= 0 ? 1 - hbuf : hbuf;
     if (on_device[ph]) {
-      RC_LAUNCH(PC_ROWS, launch_build_rows<T>(w.tables + ph, tabs[ph].total_rows, w.h[hbuf], w.h[nb], w.row_pos, w.row_req,
+      RC_LAUNCH(PC_ROWS, launch_build_rows<T>(w.tables + ph, tabs[ph].total_rows, w.h[hbuf], w.h[nb], row_info,
                                   job.sel_idx, D, st));
     } else {
       RopeFill rope = {};
       if (cur < 0) rope = {w.rope_tab, has_seg && job.takeover ? w.delta_tab : nullptr, d.head_dim / 2, job.takeover, (double)d.rope_base, 0, 0, 0};
-      RC_LAUNCH(PC_ROWS, launch_enter_phase<T>(tabs[ph], w.tables + ph, w.h[hbuf], w.h[nb], w.row_pos, w.row_req, job.sel_idx, D,
-                                               rope, st));
+      RC_LAUNCH(PC_ROWS, launch_enter_phase<T>(tabs[ph], w.tables + ph, w.h[hbuf], w.h[nb], row_info, job.sel_idx, D, rope, st));
     }
     hbuf = nb;
     cur = ph;
@@ -541,13 +543,23 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
                                                       (float*)w.q, (float*)job.dst->k_pool[l], (float*)job.dst->v_pool[l],
                                                       job.k_pre_pool ? (float*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st, m_live));
     } else {
-      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
-      RC_LAUNCH(PC_GEMM_QKV, launch_gemm_qkv_bf16(w.a, (const bf16*)lw.wq, nq, (const bf16*)lw.wk, (const bf16*)lw.wv, nkv,
-                                                  w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
-      // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
-      RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
-                                    (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
-                                    job.k_pre_pool ? (T*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st));
+      const NormIn norm = {h, (const bf16*)lw.g_attn, d.rms_eps, {0, 1, 2, 3}};
+      const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D, nq, nq + nkv);
+      const bool normed = few && gemm_skinny_norm_fits(rows, D);
+      if (!normed) RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
+      if (few) {
+        const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
+                              job.k_pre_pool ? (bf16*)job.k_pre_pool[l] : nullptr, gd.block_size};
+        RC_LAUNCH(PC_GEMM_QKV, launch_gemm_skinny_qkv_rope(w.a, normed ? norm : NormIn{}, (const bf16*)lw.wq, nq, (const bf16*)lw.wk,
+                                                           (const bf16*)lw.wv, nkv, rows, D, rope, st, m_live));
+      } else {
+        RC_LAUNCH(PC_GEMM_QKV, launch_gemm_qkv_bf16(w.a, (const bf16*)lw.wq, nq, (const bf16*)lw.wk, (const bf16*)lw.wv, nkv,
+                                                    w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
+        // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
+        RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
+                                      (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
+                                      job.k_pre_pool ? (T*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st));
+      }
     }
     // influence accumulation (decoding): the bf16 matrix-core attention kernel hands out its scores; the other
     // paths compute them in a pass of their own
@@ -568,8 +580,13 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_f32_normed(h, (const float*)lw.g_ffn, d.rms_eps, nullptr, (const float*)lw.w_gate,
                                                         (const float*)lw.w_up, (float*)w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
     } else {
-      RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
-      RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
+      if (gemm_takes_few_rows(rows, F, D, F, F) && gemm_skinny_norm_fits(rows, D)) {
+        const NormIn norm = {h, (const bf16*)lw.g_ffn, d.rms_eps, {0, 1, 2, 3}};
+        RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_skinny_normed(norm, (const bf16*)lw.w_gate, (const bf16*)lw.w_up, w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
+      } else {
+        RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
+        RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
+      }
     }
     RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
   }
@@ -580,6 +597,13 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
                                                       nullptr, job.logits, n_req, d.vocab, D, EPI_STORE_F32, st));
     return RC_OK;
   } else {
+    // the host knows where the last rows are unless they are rows of a phase counted on the device
+    if (!on_device[cur] && gemm_takes_few_rows(n_req, d.vocab, D, d.vocab, d.vocab) && gemm_skinny_norm_fits(n_req, D)) {
+      NormIn norm = {w.h[hbuf], (const bf16*)job.m->g_final, d.rms_eps, {0, 0, 0, 0}};
+      for (int b = 0; b < n_req; ++b) norm.row[b] = tabs[cur].r[b].n_rows > 0 ? tabs[cur].r[b].row_base + tabs[cur].r[b].n_rows - 1 : -1;
+      RC_LAUNCH(PC_GEMM_LM_HEAD, launch_gemm_skinny_normed(norm, (const bf16*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, EPI_STORE_F32, st, nullptr));
+      return RC_OK;
+    }
     RC_LAUNCH(PC_ROWS, launch_gather_last(w.tables + cur, n_req, w.h[hbuf], w.h_last, D, st));
     RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(w.h_last, (const bf16*)job.m->g_final, w.a_last, n_req, D, d.rms_eps, st));
     RC_LAUNCH(PC_GEMM_LM_HEAD, gemm_any<T>((const T*)w.a_last, (const T*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, d.vocab,

@@ -78,6 +78,14 @@ template <> struct Vec16<bf16> {
   }
 };
 
+// ss + |v|^2, every operation spelled out: kernels that normalise the same row have to get the same sum, and what the compiler
+// contracts depends on the code around
+__device__ inline float add_squares(float ss, float4 v) {
+#pragma clang fp contract(off)
+  const float t = __builtin_fmaf(v.w, v.w, __builtin_fmaf(v.z, v.z, __builtin_fmaf(v.x, v.x, v.y * v.y)));
+  return ss + t;
+}
+
 // ------------------------------------------------------------------ paged cache geometry
 struct KvGeom {
   int n_blocks, block_size;
@@ -268,6 +276,8 @@ template <typename T>
 hipError_t launch_rerotate(const RerotatePtrs& ptrs, int n_layers, KvGeom gs, KvGeom gd, const ReqTable* table,
                            int n_req, int max_seg, const float2* rope_tab, const float2* delta_tab, hipStream_t st);
 
+// What a phase's kernels know of its rows: position, request (with flags) and (bf16) pool row of KV head 0 in the destination cache g.
+struct RowInfo { int *pos, *req; unsigned* dst; KvGeom g; };
 // what enter_phase fills besides the phase's rows at the start of a call (tab == nullptr: nothing)
 struct RopeFill {
   float2 *tab, *delta_tab;   // delta_tab may be nullptr
@@ -276,11 +286,11 @@ struct RopeFill {
   int per_request, lo, hi;   // set by the launcher
 };
 template <typename T>
-hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, int* row_pos,
-                              int* row_req, const int* sel_idx, int d, RopeFill rope, hipStream_t st);
+hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, RowInfo rows,
+                              const int* sel_idx, int d, RopeFill rope, hipStream_t st);
 template <typename T>
-hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new,
-                             int* row_pos, int* row_req, const int* sel_idx, int d, hipStream_t st);
+hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new, RowInfo rows,
+                             const int* sel_idx, int d, hipStream_t st);
 template <typename T>
 hipError_t launch_capture_rows(const ReqTable* table, int total_rows, const float* h, const int* row_req,
                                int d, hipStream_t st);
@@ -308,11 +318,28 @@ hipError_t launch_gemm_f32_qkv_rope(const float* h, const float* gain, float eps
                                     float* k_pre_pool, KvGeom geom, int n_q_heads, hipStream_t st,
                                     const int* m_live = nullptr);
 
+// Rows that a product normalises on its way in: rows row[..] of h (float, k wide; < 0: a row of zeros) times gain, bf16.
+// h == nullptr: not asked for.
+constexpr int kNormRows = 4;
+struct NormIn { const float* h; const bf16* gain; float eps; int row[kNormRows]; };
+// Where the q|k|v product leaves its rows when rotary and scatter are part of it: q rotated, k rotated (and, with k_pre_pool,
+// as it was) and v in the cache rows that row_dst names (pool row of KV head 0; the other heads follow block_size apart).
+constexpr unsigned kRowNoDst = 0xffffffffu;   // a row that leaves the cache writes to its twin
+struct RopeOut { const int* row_pos; const unsigned* row_dst; const float2* tab; bf16 *q, *k_pool, *v_pool, *k_pre_pool; int block_size; };
+
 // few-row variant (M <= 32, weights streamed once); columns < ns1 come from w, < ns2 from w2, the rest from w3
 bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2);
 hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
                                    void* c, int m, int n, int k, int ldc, GemmEpilogue epi, hipStream_t st,
                                    const int* m_live = nullptr);
+
+bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2);   // as above, and no tile type is forced
+// the same with the RMS norm of the rows inside (gemm_skinny_norm_fits), and the q|k|v product (heads of 128) with rotary and scatter
+bool gemm_skinny_norm_fits(int m, int k);
+hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf16* w2, void* c, int m, int n, int k,
+                                     GemmEpilogue epi, hipStream_t st, const int* m_live);
+hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
+                                       int m, int k, const RopeOut& rope, hipStream_t st, const int* m_live);
 
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.

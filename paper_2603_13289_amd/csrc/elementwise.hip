@@ -1,6 +1,7 @@
 // Bandwidth-bound stages of the selective-recompute prefill: rotary re-rotation of reused keys,
 // active-row bookkeeping, RMSNorm, rotary + paged scatter of fresh K/V, Eq. (1) scoring.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -157,8 +158,8 @@ template hipError_t launch_rerotate<bf16>(const RerotatePtrs&, int, KvGeom, KvGe
 // Rows of a request are ordered by position: prefix, active segment rows, suffix.
 template <typename T>
 __device__ __forceinline__ void build_row(const ReqTable& table, int r, const float* __restrict__ h_old,
-                                          float* __restrict__ h_new, int* __restrict__ row_pos, int* __restrict__ row_req,
-                                          const int* __restrict__ sel_idx, int d) {
+                                          float* __restrict__ h_new, const RowInfo& rows, const int* __restrict__ sel_idx,
+                                          int d) {
   if (r >= table.total_rows) return;   // the grid may be sized for an upper bound of the row count
   int b = 0;
   while (b + 1 < table.n_req && r >= table.r[b].row_base + table.r[b].n_rows) ++b;
@@ -193,8 +194,9 @@ __device__ __forceinline__ void build_row(const ReqTable& table, int r, const fl
     else src_t = reinterpret_cast<const T*>(rq.x_suffix) + (size_t)si * d;
   }
   if (threadIdx.x == 0) {
-    row_pos[r] = pos;
-    row_req[r] = b | flags;
+    rows.pos[r] = pos;
+    rows.req[r] = b | flags;
+    if (std::is_same<T, bf16>::value) rows.dst[r] = flags & kRowNoCacheWrite ? kRowNoDst : (unsigned)(kv_row_offset(rows.g, rq.dst_seq, pos, 0) / rows.g.head_dim);
   }
   float* dst = h_new + (size_t)r * d;
   if (src_f) {
@@ -207,9 +209,9 @@ __device__ __forceinline__ void build_row(const ReqTable& table, int r, const fl
 
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
-build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ h_old, float* __restrict__ h_new,
-                  int* __restrict__ row_pos, int* __restrict__ row_req, const int* __restrict__ sel_idx, int d) {
-  build_row<T>(*table, blockIdx.x, h_old, h_new, row_pos, row_req, sel_idx, d);
+build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ h_old, float* __restrict__ h_new, RowInfo rows,
+                  const int* __restrict__ sel_idx, int d) {
+  build_row<T>(*table, blockIdx.x, h_old, h_new, rows, sel_idx, d);
 }
 
 // A phase whose row counts the host knows, in one launch: its table travels as a kernel argument (no host-to-device copy,
@@ -218,8 +220,8 @@ build_rows_kernel(const ReqTable* __restrict__ table, const float* __restrict__ 
 // own costs 4.8 us behind another, whatever it does): workgroups past the rows take the positions the call uses.
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
-enter_phase_kernel(ReqTable t, ReqTable* dst, const float* __restrict__ h_old, float* __restrict__ h_new,
-                   int* __restrict__ row_pos, int* __restrict__ row_req, const int* __restrict__ sel_idx, int d, RopeFill rope) {
+enter_phase_kernel(ReqTable t, ReqTable* dst, const float* __restrict__ h_old, float* __restrict__ h_new, RowInfo rows,
+                   const int* __restrict__ sel_idx, int d, RopeFill rope) {
   const int bid = blockIdx.x;
   if (bid == 0) {
     const int* s = reinterpret_cast<const int*>(&t);
@@ -232,7 +234,7 @@ enter_phase_kernel(ReqTable t, ReqTable* dst, const float* __restrict__ h_old, f
     return;
   }
   if (bid <= t.total_rows) {
-    build_row<T>(t, bid - 1, h_old, h_new, row_pos, row_req, sel_idx, d);
+    build_row<T>(t, bid - 1, h_old, h_new, rows, sel_idx, d);
     return;
   }
   const long idx = (long)(bid - 1 - t.total_rows) * kThreads + threadIdx.x;
@@ -254,8 +256,8 @@ enter_phase_kernel(ReqTable t, ReqTable* dst, const float* __restrict__ h_old, f
 }
 
 template <typename T>
-hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, int* row_pos,
-                              int* row_req, const int* sel_idx, int d, RopeFill rope, hipStream_t st) {
+hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const float* h_old, float* h_new, RowInfo rows,
+                              const int* sel_idx, int d, RopeFill rope, hipStream_t st) {
   long items = 0;
   if (rope.tab) {
     long sum = 0;
@@ -271,25 +273,23 @@ hipError_t launch_enter_phase(const ReqTable& table, ReqTable* dev_slot, const f
     items = (rope.per_request ? sum : rope.hi - rope.lo) * rope.half;
   }
   const unsigned grid = 1u + (unsigned)table.total_rows + (unsigned)((items + kThreads - 1) / kThreads);
-  enter_phase_kernel<T><<<grid, kThreads, 0, st>>>(table, dev_slot, h_old, h_new, row_pos, row_req, sel_idx, d, rope);
+  enter_phase_kernel<T><<<grid, kThreads, 0, st>>>(table, dev_slot, h_old, h_new, rows, sel_idx, d, rope);
   return hipGetLastError();
 }
-template hipError_t launch_enter_phase<float>(const ReqTable&, ReqTable*, const float*, float*, int*, int*, const int*, int,
-                                              RopeFill, hipStream_t);
-template hipError_t launch_enter_phase<bf16>(const ReqTable&, ReqTable*, const float*, float*, int*, int*, const int*, int,
-                                             RopeFill, hipStream_t);
+template hipError_t launch_enter_phase<float>(const ReqTable&, ReqTable*, const float*, float*, RowInfo, const int*, int, RopeFill,
+                                              hipStream_t);
+template hipError_t launch_enter_phase<bf16>(const ReqTable&, ReqTable*, const float*, float*, RowInfo, const int*, int, RopeFill,
+                                             hipStream_t);
 
 template <typename T>
-hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new,
-                             int* row_pos, int* row_req, const int* sel_idx, int d, hipStream_t st) {
+hipError_t launch_build_rows(const ReqTable* table, int total_rows, const float* h_old, float* h_new, RowInfo rows,
+                             const int* sel_idx, int d, hipStream_t st) {
   if (total_rows <= 0) return hipSuccess;
-  build_rows_kernel<T><<<total_rows, kThreads, 0, st>>>(table, h_old, h_new, row_pos, row_req, sel_idx, d);
+  build_rows_kernel<T><<<total_rows, kThreads, 0, st>>>(table, h_old, h_new, rows, sel_idx, d);
   return hipGetLastError();
 }
-template hipError_t launch_build_rows<float>(const ReqTable*, int, const float*, float*, int*, int*, const int*,
-                                             int, hipStream_t);
-template hipError_t launch_build_rows<bf16>(const ReqTable*, int, const float*, float*, int*, int*, const int*,
-                                            int, hipStream_t);
+template hipError_t launch_build_rows<float>(const ReqTable*, int, const float*, float*, RowInfo, const int*, int, hipStream_t);
+template hipError_t launch_build_rows<bf16>(const ReqTable*, int, const float*, float*, RowInfo, const int*, int, hipStream_t);
 
 // hidden states entering a layer, written out per request in T (what the cache manager keeps)
 template <typename T>
@@ -370,13 +370,10 @@ rmsnorm_kernel(const float* __restrict__ h, const bf16* __restrict__ gain, bf16*
 #pragma unroll
   for (int u = 0; u < kNormKeep; ++u) {
     const int c = (threadIdx.x + u * kThreads) * 4;
-    if (c < d) {
-      ss += keep[u].x * keep[u].x + keep[u].y * keep[u].y + keep[u].z * keep[u].z + keep[u].w * keep[u].w;
-    }
+    if (c < d) ss = add_squares(ss, keep[u]);
   }
   for (int c = (threadIdx.x + kNormKeep * kThreads) * 4; c < d; c += kThreads * 4) {
-    const float4 v = *reinterpret_cast<const float4*>(x + c);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    ss = add_squares(ss, *reinterpret_cast<const float4*>(x + c));
   }
   ss = block_sum(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);

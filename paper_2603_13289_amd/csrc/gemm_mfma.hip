@@ -984,12 +984,14 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
 #undef RC_DL
 }
 
+bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2) { return g_gemm_tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2); }
+
 static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c,
                            int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
                            const int* m_live, int m_expected) {
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
-  if (tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2))
+  if (gemm_takes_few_rows(m, n, k, ns1, ns2))
     return launch_gemm_skinny_bf16(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
   if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
   if ((tile == 0 || tile >= 5) && k % BK == 0)

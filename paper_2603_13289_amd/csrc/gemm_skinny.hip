@@ -28,21 +28,48 @@ static constexpr int kSkinnyWaves = 8;
 // sequence on the 7B shape 4.23 ms, of sixteen 7.97; as it is 4.17 and 7.88).
 static constexpr int kSkinnyDeepGroups = 256;
 
+// Rows that a workgroup normalises for itself: at most four, of at most 5120 elements (registers), in at most 48 KB of LDS (with
+// the partial tiles two workgroups fit a compute unit).
+static constexpr int kNormRowMax = 5120;
+static constexpr size_t kNormLds = 48 * 1024;
+__device__ __host__ inline int norm_pitch(int k) { return 2 * k + 16; }   // bytes; rows start in different LDS banks
+bool gemm_skinny_norm_fits(int m, int k) {
+  return m <= kNormRows && k <= kNormRowMax && (size_t)m * norm_pitch(k) <= kNormLds;
+}
+
+// a barrier that waits for the LDS accesses before it, not for loads in flight as __syncthreads may
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ inline float silu_s(float x) { return x / (1.0f + __expf(-x)); }
 
 // DUAL: gate and up weights of the same columns.  TWO: more than 16 rows.  U: K steps of a register set.
-template <bool DUAL, bool TWO, int U>
+// NORM: the rows, at most 2 NORM of them, are RMS-normalised on the way in (NormIn), in the order of rmsnorm_kernel, so that the
+// operand has the same bits.  Every workgroup does it for itself, into LDS, while its first weights are on their way: what a row of
+// 4096 costs (16 KB from the L2, a reduction) hides behind them and the launch of the norm kernel goes.
+// One row, K = 4096: q|k|v 12.0 + norm 4.7 + rotary 5.5 -> 14.3 us, gate/up 42.2 + 4.7 -> 43.0, LM head (32768) 43 + norm and
+// gather 10.3 -> 46.3.  More than four rows keep the norm's own launch: every workgroup would read and hold them all.
+// ROPE: the columns are q, k and v heads of 128 (RopeOut); a workgroup has columns 8 j .. 8 j + 7 of both halves of a head, i.e.
+// eight whole rotary pairs, and its epilogue does what rope_scatter_kernel does with a row, in the same arithmetic.
+template <bool DUAL, bool TWO, int U, int NORM, bool ROPE>
 __global__ void __launch_bounds__(kSkinnyWaves * 64, U == 8 || (DUAL && TWO) ? 2 : 4)
 gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
                    const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
-                   int epi, const int* __restrict__ m_live) {
-  __shared__ float part[kSkinnyWaves][4][64][4];   // [wave][tile: gate/rows 0-15, gate/16-31, up/0-15, up/16-31][lane][e]
+                   int epi, const int* __restrict__ m_live, NormIn norm, RopeOut rope) {
+  static_assert(!(NORM > 0 && TWO) && !(DUAL && ROPE), "");
+  constexpr int TILES = (DUAL ? 2 : 1) * (TWO ? 2 : 1), UP = TWO ? 2 : 1;   // tiles: gate rows 0-15 (16-31), up rows 0-15 (16-31)
+  __shared__ float part[kSkinnyWaves][TILES][64][4];   // [wave][tile][lane][e]
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_rows[];   // NORM: [m][k] bf16, rows norm_pitch(k) bytes apart
+  __shared__ float norm_red[NORM > 0 ? NORM : 1][kSkinnyWaves];
+  __shared__ float2 lds_cs[ROPE ? 32 : 1][8];
+  __shared__ unsigned lds_dst[ROPE ? 32 : 1];
   m = live_count(m, m_live);
   if (m <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = (int)blockIdx.x * 16;
-  const int col = n0 + (lane & 15);
+  // ROPE: columns 0-7 and 8-15 of the tile are partners, half a head apart
+  const int head = (int)blockIdx.x >> 3, dim = ((int)blockIdx.x & 7) * 8 + (lane & 7) + 64 * ((lane >> 3) & 1);
+  const int col = ROPE ? head * 128 + dim : n0 + (lane & 15);
   const int kw = k / kSkinnyWaves;
   const size_t koff = (size_t)wave * kw + 8 * (lane >> 4);
   const bf16* pw;
@@ -55,8 +82,9 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
   }
   const bf16* pa0 = a + (size_t)min(lane & 15, m - 1) * k + koff;
   const bf16* pa1 = a + (size_t)min(16 + (lane & 15), m - 1) * k + koff;
+  const unsigned char* la0 = lds_rows + (size_t)min(lane & 15, m - 1) * norm_pitch(k) + 2 * koff;
   f32x4s g0 = {0.f, 0.f, 0.f, 0.f}, g1 = g0, u0 = g0, u1 = g0;
-  bf16x8s fb[2][U], fu[2][DUAL ? U : 1], fa0[2][U], fa1[2][TWO ? U : 1];
+  bf16x8s fb[2][U], fu[2][DUAL ? U : 1], fa0[2][NORM > 0 ? 1 : U], fa1[2][TWO ? U : 1];
   const int steps = kw / 32;
   auto load = [&](auto set, int first, auto ragged) {   // ragged: some steps of the set may lie past the last one
     constexpr int S = decltype(set)::value;
@@ -66,62 +94,158 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
       const int o = 32 * (first + i);
       fb[S][i] = *reinterpret_cast<const bf16x8s*>(pw + o);
       if constexpr (DUAL) fu[S][i] = *reinterpret_cast<const bf16x8s*>(pu + o);
-      fa0[S][i] = *reinterpret_cast<const bf16x8s*>(pa0 + o);
+      if constexpr (NORM == 0) fa0[S][i] = *reinterpret_cast<const bf16x8s*>(pa0 + o);
       if constexpr (TWO) fa1[S][i] = *reinterpret_cast<const bf16x8s*>(pa1 + o);
     }
   };
-  auto multiply = [&](auto set, int live) {
+  auto multiply = [&](auto set, int live, int first) {
     constexpr int S = decltype(set)::value;
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       if (i >= live) continue;
-      g0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[S][i], fb[S][i], g0, 0, 0, 0);
+      bf16x8s f;
+      if constexpr (NORM > 0) f = *reinterpret_cast<const bf16x8s*>(la0 + 64 * (first + i));
+      else f = fa0[S][i];
+      g0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, fb[S][i], g0, 0, 0, 0);
       if constexpr (TWO) g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[S][i], fb[S][i], g1, 0, 0, 0);
       if constexpr (DUAL) {
-        u0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[S][i], fu[S][i], u0, 0, 0, 0);
+        u0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, fu[S][i], u0, 0, 0, 0);
         if constexpr (TWO) u1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[S][i], fu[S][i], u1, 0, 0, 0);
       }
     }
   };
+
+  // NORM: wavefronts 0-3 take row 0 (and 2), 4-7 row 1 (and 3); threads and order of the sum as in rmsnorm_kernel.  No condition
+  // around the loads: elements past the row repeat its last ones, rows past the last one repeat it.
+  constexpr int NK = NORM > 0 ? kNormRowMax / 1024 : 1, NP = NORM > 0 ? NORM : 1;
+  float4 keep[NP][NK];
+  uint2 gain[NK];
+  const int nt = tid & 255;
+  auto norm_load = [&]() {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const float* x = norm.h + (size_t)max(norm.row[min(2 * p + (wave >> 2), m - 1)], 0) * k;
+#pragma unroll
+      for (int u = 0; u < NK; ++u) keep[p][u] = *reinterpret_cast<const float4*>(x + min((nt + u * 256) * 4, k - 4));
+    }
+#pragma unroll
+    for (int u = 0; u < NK; ++u) gain[u] = *reinterpret_cast<const uint2*>(norm.gain + min((nt + u * 256) * 4, k - 4));
+  };
+  auto norm_rows = [&]() {
+    float ss[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const bool dead = norm.row[min(2 * p + (wave >> 2), m - 1)] < 0;   // uniform
+      ss[p] = 0.f;
+#pragma unroll
+      for (int u = 0; u < NK; ++u) {
+        float4& x = keep[p][u];
+        // not touched, and so not waited for, ahead of this point: the weights are asked for first
+        asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w));
+        if (dead || (nt + u * 256) * 4 >= k) x = make_float4(0.f, 0.f, 0.f, 0.f);
+        ss[p] = add_squares(ss[p], x);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ss[p] += __shfl_xor(ss[p], o, 64);
+      if (lane == 0) norm_red[p][wave] = ss[p];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s += norm_red[p][(wave & 4) + i];
+      const float r = 1.0f / sqrtf(s / (float)k + norm.eps);
+      const int row = 2 * p + (wave >> 2);
+#pragma unroll
+      for (int u = 0; u < NK; ++u) {
+        const int e = (nt + u * 256) * 4;
+        const float4 x = keep[p][u];
+        uint2 pk;
+        pk.x = (uint32_t)f32_to_bf16(x.x * r * __uint_as_float(gain[u].x << 16)).v |
+               ((uint32_t)f32_to_bf16(x.y * r * __uint_as_float(gain[u].x & 0xffff0000u)).v << 16);
+        pk.y = (uint32_t)f32_to_bf16(x.z * r * __uint_as_float(gain[u].y << 16)).v |
+               ((uint32_t)f32_to_bf16(x.w * r * __uint_as_float(gain[u].y & 0xffff0000u)).v << 16);
+        if (row < m && e < k) *reinterpret_cast<uint2*>(lds_rows + (size_t)row * norm_pitch(k) + 2 * e) = pk;
+      }
+    }
+    lds_barrier();
+  };
+  // ROPE: thread 8 r + p fetches the angle of pair p of the tile for row r, and the row's place in the cache; they wait in LDS for
+  // the epilogue.  Every wavefront asks: a load that only some have in flight would make the compiler wait for all.
+  int rope_pos;
+  unsigned rope_dst;
+  float2 rope_cs;
+  auto rope_load = [&]() {
+    if constexpr (ROPE) {
+      const int r = min(tid >> 3, m - 1);
+      rope_pos = rope.row_pos[r];
+      rope_dst = rope.row_dst[r];
+    }
+  };
+  auto rope_angles = [&]() {
+    if constexpr (ROPE) rope_cs = rope.tab[(size_t)rope_pos * 64 + ((int)blockIdx.x & 7) * 8 + (tid & 7)];
+  };
+
   const std::integral_constant<int, 0> s0;
   const std::integral_constant<int, 1> s1;
   const std::false_type whole;
   const std::true_type tail;
+  constexpr bool kRopeEarly = !TWO;   // with two row tiles the registers are needed: behind the main loop
+  if constexpr (kRopeEarly) rope_load();
+  if constexpr (NORM > 0) norm_load();
+  __builtin_amdgcn_sched_barrier(0);
   int at = 0;
   if (steps >= 2 * U) {
     load(s0, 0, whole);
     __builtin_amdgcn_sched_barrier(0);
-    load(s1, U, whole);
+    if constexpr (NORM == 0 || !DUAL) load(s1, U, whole);   // registers: behind the norm
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kRopeEarly) rope_angles();
+    if constexpr (NORM > 0) norm_rows();
+    if constexpr (NORM > 0 && DUAL) load(s1, U, whole);
     __builtin_amdgcn_sched_barrier(0);
     // no condition inside: a load that may or may not be in flight would make the compiler wait for all of them
     for (; at + 4 * U <= steps; at += 2 * U) {
-      multiply(s0, U);
+      multiply(s0, U, at);
       __builtin_amdgcn_sched_barrier(0);
       load(s0, at + 2 * U, whole);
       __builtin_amdgcn_sched_barrier(0);
-      multiply(s1, U);
+      multiply(s1, U, at + U);
       __builtin_amdgcn_sched_barrier(0);
       load(s1, at + 3 * U, whole);
       __builtin_amdgcn_sched_barrier(0);
     }
-    multiply(s0, U);
+    multiply(s0, U, at);
     if (at + 2 * U < steps) load(s0, at + 2 * U, tail);
-    multiply(s1, U);
+    multiply(s1, U, at + U);
     at += 2 * U;
   } else {
     load(s0, 0, tail);
+    if constexpr (kRopeEarly) rope_angles();
+    if constexpr (NORM > 0) norm_rows();
   }
   if (at < steps) {
     if (at + U < steps) load(s1, at + U, tail);
-    multiply(s0, steps - at);
-    if (at + U < steps) multiply(s1, steps - at - U);
+    multiply(s0, steps - at, at);
+    if (at + U < steps) multiply(s1, steps - at - U, at + U);
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     part[wave][0][lane][e] = g0[e];
-    if (TWO) part[wave][1][lane][e] = g1[e];
-    if (DUAL) part[wave][2][lane][e] = u0[e];
-    if (DUAL && TWO) part[wave][3][lane][e] = u1[e];
+    if constexpr (TWO) part[wave][1][lane][e] = g1[e];
+    if constexpr (DUAL) part[wave][UP][lane][e] = u0[e];
+    if constexpr (DUAL && TWO) part[wave][UP + 1][lane][e] = u1[e];
+  }
+  if constexpr (ROPE) {
+    if constexpr (!kRopeEarly) {
+      rope_load();
+      rope_angles();
+    }
+    if (tid < 256) {
+      lds_cs[tid >> 3][tid & 7] = rope_cs;
+      if ((tid & 7) == 0) lds_dst[tid >> 3] = rope_dst;
+    }
   }
   __syncthreads();
   // wavefront 0 finishes rows 0-15, wavefront 1 rows 16-31
@@ -131,8 +255,30 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       gs[e] += part[p][wave][lane][e];
-      if (DUAL) us[e] += part[p][2 + wave][lane][e];
+      if constexpr (DUAL) us[e] += part[p][UP + wave][lane][e];
     }
+  }
+  if constexpr (ROPE) {
+    const bool is_q = col < ns1, is_v = col >= ns2;   // uniform
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float other = __shfl_xor(gs[e], 8, 64);
+      const int row = wave * 16 + 4 * (lane >> 4) + e;
+      if (row >= m) continue;
+      const float2 cs = lds_cs[row][lane & 7];
+      const unsigned dst = lds_dst[row];
+      float v = gs[e];
+      if (!is_v) v = dim < 64 ? fmaf(v, cs.x, -(other * cs.y)) : fmaf(v, cs.x, other * cs.y);
+      if (is_q) {
+        rope.q[(size_t)row * ns1 + col] = f32_to_bf16(v);
+      } else if (dst != kRowNoDst) {
+        const int kvh = head - (is_v ? ns2 : ns1) / 128;
+        const size_t o = ((size_t)dst + (size_t)kvh * rope.block_size) * 128 + dim;
+        (is_v ? rope.v_pool : rope.k_pool)[o] = f32_to_bf16(v);
+        if (!is_v && rope.k_pre_pool) rope.k_pre_pool[o] = f32_to_bf16(gs[e]);
+      }
+    }
+    return;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -155,8 +301,8 @@ hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2,
                                    const int* m_live) {
   const dim3 grid((unsigned)(n / 16));
   auto go = [&](auto dual, auto two, auto u) {
-    gemm_skinny_kernel<decltype(dual)::value, decltype(two)::value, decltype(u)::value>
-        <<<grid, kSkinnyWaves * 64, 0, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, m_live);
+    gemm_skinny_kernel<decltype(dual)::value, decltype(two)::value, decltype(u)::value, 0, false>
+        <<<grid, kSkinnyWaves * 64, 0, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, m_live, NormIn{}, RopeOut{});
   };
   auto rows = [&](auto dual, auto u) {
     if (m > 16) go(dual, std::true_type{}, u);
@@ -167,6 +313,39 @@ hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2,
   if (epi == EPI_SWIGLU_T) rows(std::true_type{}, u4);
   else if (n <= 16 * kSkinnyDeepGroups && k >= kSkinnyWaves * 32 * 16) rows(std::false_type{}, u8);
   else rows(std::false_type{}, u4);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf16* w2, void* c, int m, int n, int k,
+                                     GemmEpilogue epi, hipStream_t st, const int* m_live) {
+  const dim3 grid((unsigned)(n / 16));
+  auto go = [&](auto dual, auto passes) {
+    gemm_skinny_kernel<decltype(dual)::value, false, 4, decltype(passes)::value, false>
+        <<<grid, kSkinnyWaves * 64, (size_t)m * norm_pitch(k), st>>>(nullptr, w, w2, nullptr, n, n, c, m, n, k, n, (int)epi, m_live, norm,
+                                                                    RopeOut{});
+  };
+  auto rows = [&](auto dual) {
+    if (m > 2) go(dual, std::integral_constant<int, 2>{});
+    else go(dual, std::integral_constant<int, 1>{});
+  };
+  if (epi == EPI_SWIGLU_T) rows(std::true_type{});
+  else rows(std::false_type{});
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
+                                       int m, int k, const RopeOut& rope, hipStream_t st, const int* m_live) {
+  const int n = nq + 2 * nkv;
+  const dim3 grid((unsigned)(n / 16));
+  auto go = [&](auto two, auto passes) {
+    gemm_skinny_kernel<false, decltype(two)::value, 4, decltype(passes)::value, true>
+        <<<grid, kSkinnyWaves * 64, norm.h ? (size_t)m * norm_pitch(k) : 0, st>>>(a, wq, wk, wv, nq, nq + nkv, nullptr, m, n, k, n,
+                                                                                 (int)EPI_STORE_T, m_live, norm, rope);
+  };
+  if (norm.h && m > 2) go(std::false_type{}, std::integral_constant<int, 2>{});
+  else if (norm.h) go(std::false_type{}, std::integral_constant<int, 1>{});
+  else if (m > 16) go(std::true_type{}, std::integral_constant<int, 0>{});
+  else go(std::false_type{}, std::integral_constant<int, 0>{});
   return hipGetLastError();
 }
 
