@@ -361,16 +361,16 @@ hipError_t attention_dispatch<bf16>(const bf16* q, const int* row_pos, const int
 
 template <typename T>
 hipError_t gemm_any(const T* a, const T* wt, const T* wt2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
-                    float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+                    float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0, GemmRest* rest = nullptr);
 template <>
 hipError_t gemm_any<float>(const float* a, const float* wt, const float* wt2, void* c, int m, int n, int k, int ldc,
-                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live, int) {
+                           GemmEpilogue epi, float*, hipStream_t st, const int* m_live, int, GemmRest*) {
   return launch_gemm_f32(a, wt, wt2, c, m, n, k, ldc, epi, st, m_live);
 }
 template <>
 hipError_t gemm_any<bf16>(const bf16* a, const bf16* wt, const bf16* wt2, void* c, int m, int n, int k, int ldc,
-                          GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
-  return launch_gemm_bf16(a, wt, wt2, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
+                          GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected, GemmRest* rest) {
+  return launch_gemm_bf16(a, wt, wt2, c, m, n, k, ldc, epi, partial, st, m_live, m_expected, rest);
 }
 // Partial-attention slots the sparse phase (and the phase after it) may use when the threshold selector decides the
 // row counts on the device: planned for a nominal selection of a fifth of every segment, with room for twice that;
@@ -451,6 +451,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     return RC_OK;
   };
 
+  GemmRest rest = {};   // K parts of the last down projection, when the next layer's norm adds them up
   for (int l = 0; l < d.n_layers; ++l) {
     const rc_layer_w& lw = job.m->layers[l];
     const Phase ph = phase_of_layer(l, job.l_start, job.l_det, job.l_end);
@@ -546,7 +547,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       const NormIn norm = {h, (const bf16*)lw.g_attn, d.rms_eps, {0, 1, 2, 3}};
       const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D, nq, nq + nkv);
       const bool normed = few && gemm_skinny_norm_fits(rows, D);
-      if (!normed) RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
+      if (!normed) RC_LAUNCH(PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
       if (few) {
         const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
                               job.k_pre_pool ? (bf16*)job.k_pre_pool[l] : nullptr, gd.block_size};
@@ -575,7 +576,10 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     if (job.any_inf)
       RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.score_len(), job.inf,
                                                       w.inf_scratch, scores_from_attention, st));
-    RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
+    rest.tiles = 0;
+    const bool rest_ok = !kFloat && D <= kRestNormMax && !gemm_skinny_norm_fits(rows, D);
+    RC_LAUNCH(PC_GEMM_O, gemm_any<T>((const T*)w.o, (const T*)lw.wo, nullptr, h, rows, D, nq, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected,
+                                     rest_ok ? &rest : nullptr));
     if constexpr (kFloat) {
       RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_f32_normed(h, (const float*)lw.g_ffn, d.rms_eps, nullptr, (const float*)lw.w_gate,
                                                         (const float*)lw.w_up, (float*)w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
@@ -584,11 +588,15 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
         const NormIn norm = {h, (const bf16*)lw.g_ffn, d.rms_eps, {0, 1, 2, 3}};
         RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_skinny_normed(norm, (const bf16*)lw.w_gate, (const bf16*)lw.w_up, w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
       } else {
-        RC_LAUNCH(PC_RMSNORM, launch_rmsnorm(h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
+        RC_LAUNCH(PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
         RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
       }
     }
-    RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected));
+    rest.tiles = 0;
+    // the next layer starts with the norm of these rows, unless another phase or the record of hidden states reads them first
+    const bool norm_next = l + 1 < d.n_layers && phase_of_layer(l + 1, job.l_start, job.l_det, job.l_end) == ph && l + 1 != job.capture_layer;
+    RC_LAUNCH(PC_GEMM_DOWN, gemm_any<T>((const T*)w.act, (const T*)lw.w_down, nullptr, h, rows, D, F, D, EPI_ADD_F32, w.gemm_part, st, m_live, rows_expected,
+                                        rest_ok && norm_next ? &rest : nullptr));
   }
 
   // first-token logits from the last position of each request

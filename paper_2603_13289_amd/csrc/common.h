@@ -344,8 +344,17 @@ hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const 
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.
 size_t gemm_partial_bytes();
+// K parts that a product has left in the scratch buffer: `tiles` of its tiles (0: none) in `split` parts each
+struct GemmRest { int tiles, tiles_m, tiles_n, bands, full, split, bm, bn; const float* partial; };
+// rest (residual add only): the parts are not added up; launch_rest_rmsnorm does it, before anything else reads C or writes the
+// scratch buffer.
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0,
+                            GemmRest* rest = nullptr);
+// h += the parts, then out = RMS norm of h times gain (d <= kRestNormMax)
+constexpr int kRestNormMax = 8192;
+hipError_t launch_rest_rmsnorm(const GemmRest& rest, float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
+                               const int* m_live);
 // C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
                                 int m, int k, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);

@@ -247,6 +247,31 @@ gemm_mfma_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const b
 // four consecutive output columns per lane, stored with one 16-byte (f32) or 8-byte (bf16) access.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// four consecutive outputs at element o of C, `left` of them inside the row
+__device__ __forceinline__ void store_quad(void* __restrict__ c, size_t o, const float (&v)[4], int epi, bool f32_out, bool vec, int left) {
+  if (vec) {
+    if (f32_out) {
+      float4* dst = reinterpret_cast<float4*>(reinterpret_cast<float*>(c) + o);
+      float4 t = make_float4(v[0], v[1], v[2], v[3]);
+      if (epi == EPI_ADD_F32) { const float4 old = *dst; t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w; }
+      *dst = t;
+    } else {
+      union { bf16 h[4]; uint2 u; } pk;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pk.h[e] = f32_to_bf16(v[e]);
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(c) + o) = pk.u;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e >= left) continue;
+      if (!f32_out) reinterpret_cast<bf16*>(c)[o + e] = f32_to_bf16(v[e]);
+      else if (epi == EPI_ADD_F32) reinterpret_cast<float*>(c)[o + e] += v[e];
+      else reinterpret_cast<float*>(c)[o + e] = v[e];
+    }
+  }
+}
+
 template <int FM, int FN, int WTM, int WTN, bool DUAL>
 __device__ inline void store_tile16(const f32x4 (&acc)[FM][FN], void* __restrict__ c, int m, int n, int ldc, int epi,
                                     int m0, int n0, int wm, int wn, int lane) {
@@ -287,39 +312,28 @@ __device__ inline void store_tile16(const f32x4 (&acc)[FM][FN], void* __restrict
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = DUAL ? silu_mf(acc[i][j][e]) * acc[i][j + FN_OUT][e] : acc[i][j][e];
-      if (vec_ok && col + 3 < n) {
-        if (f32_out) {
-          float4* dst = reinterpret_cast<float4*>(reinterpret_cast<float*>(c) + o);
-          float4 t = make_float4(v[0], v[1], v[2], v[3]);
-          if (epi == EPI_ADD_F32) { const float4 old = *dst; t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w; }
-          *dst = t;
-        } else {
-          union { bf16 h[4]; uint2 u; } pk;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) pk.h[e] = f32_to_bf16(v[e]);
-          *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(c) + o) = pk.u;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (col + e >= n) continue;
-          if (!f32_out) reinterpret_cast<bf16*>(c)[o + e] = f32_to_bf16(v[e]);
-          else if (epi == EPI_ADD_F32) reinterpret_cast<float*>(c)[o + e] += v[e];
-          else reinterpret_cast<float*>(c)[o + e] = v[e];
-        }
-      }
+      store_quad(c, o, v, epi, f32_out, vec_ok && col + 3 < n, n - col);
     }
   }
 }
 
-// raw accumulators of a K part, register-major so that consecutive lanes write consecutive 16-byte groups
-template <int FM, int FN, int NT>
-__device__ inline void store_partial(const f32x4 (&acc)[FM][FN], float* __restrict__ partial, int part_slot, int tid) {
-  f32x4* dst = reinterpret_cast<f32x4*>(partial) + (size_t)part_slot * (FM * FN) * NT + tid;
+// The accumulators of a K part, as rows of BN floats (DUAL: the tile's gate columns, then its up columns) of the part's BM x BN
+// block: whoever adds the parts up reads whole rows.  Rows past the product's last one are left out.
+template <int FM, int FN, int BM, int BN, int WTM, int WTN, bool DUAL>
+__device__ inline void store_partial(const f32x4 (&acc)[FM][FN], float* __restrict__ partial, int part_slot, int rows, int wm, int wn,
+                                     int lane) {
+  constexpr int FH = FN / 2;
+  float* const base = partial + (size_t)part_slot * BM * BN + 4 * (lane >> 4);
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int i = 0; i < FM; ++i) {
+    const int row = wm * WTM + i * 16 + (lane & 15);
+    if (row >= rows) continue;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) dst[(size_t)(i * FN + j) * NT] = acc[i][j];
+    for (int j = 0; j < FN; ++j) {
+      const int col = !DUAL ? wn * WTN + j * 16 : (j < FH ? wn * (WTN / 2) + j * 16 : BN / 2 + wn * (WTN / 2) + (j - FH) * 16);
+      *reinterpret_cast<f32x4*>(base + (size_t)row * BN + col) = acc[i][j];
+    }
+  }
 }
 
 // One output tile (or one K part of it): the work of a workgroup once it knows its tile.
@@ -456,7 +470,7 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
   }
 
   if (part_slot >= 0) {
-    store_partial<FM, FN, NW * 64>(acc, partial, part_slot, tid);
+    store_partial<FM, FN, BM, BN, WTM, WTN, DUAL>(acc, partial, part_slot, m - m0, wm, wn, lane);
     return;
   }
   store_tile16<FM, FN, WTM, WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane);
@@ -473,11 +487,12 @@ __device__ __forceinline__ void gemm_pipe_body(const bf16* __restrict__ a, const
   gemm_pipe_loop<T, DUAL>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / T::WN, wn = wave % T::WN;
   if (part_slot >= 0) {
-    store_partial<T::FM, T::FN, 512>(acc, partial, part_slot, tid);
+    store_partial<T::FM, T::FN, T::BM, T::BN, T::WTM, T::WTN, DUAL>(acc, partial, part_slot, m - m0, wm, wn, lane);
     return;
   }
-  store_tile16<T::FM, T::FN, T::WTM, T::WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wave / T::WN, wave % T::WN, lane);
+  store_tile16<T::FM, T::FN, T::WTM, T::WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane);
 }
 
 // What the launch's grid does.  Workgroups [0, n_full_wgs) each own one of the first full_tiles output tiles
@@ -590,37 +605,126 @@ gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, cons
                          bw.k_end, bw.part_slot, partial);
 }
 
-// Sum of the K-split parts of the tail tiles (fixed order: part 0, 1, ...) followed by the epilogue.  One
-// workgroup per (tile, accumulator (i, j)); thread t owns the same (wavefront, lane) as thread t of the GEMM
-// kernel, so all reads of a part are coalesced.
-template <typename T, bool DUAL>
-__global__ void __launch_bounds__(T::NT)
-gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, TileOrder order, int full_tiles /* of `order` */,
-                  int split, const float* __restrict__ partial) {
-  constexpr int NT = T::NT, BM = T::BM, WTM = T::WTM, WTN = T::WTN, FM = T::FM, FN = T::FN;
-  constexpr int FN_OUT = DUAL ? FN / 2 : FN;
-  constexpr int BN_OUT = DUAL ? T::BN / 2 : T::BN;
-  constexpr int PER_TILE = FM * FN_OUT;
-  const int t = (int)blockIdx.x / PER_TILE;
-  const int rest = (int)blockIdx.x % PER_TILE;
-  const int j = rest % FN_OUT, i = rest / FN_OUT;
+// The parts of one product that are still to be added up: tiles [full, ...) of `order`, bm x bn, in `split` parts each.
+struct PartTiles { TileOrder order; int full, split, bm, bn; const float* partial; };
+
+// index of tile (tile_m, tile_n) in the order: the inverse of tile_of
+__device__ __host__ inline int tile_index(TileOrder o, int tile_m, int tile_n) {
+  const int base = o.tiles_m / o.bands, rem = o.tiles_m % o.bands;
+  const int tall = rem * (base + 1);
+  const bool in_tall = tile_m < tall;
+  const int h = in_tall ? base + 1 : base;
+  const int local = in_tall ? tile_m : tile_m - tall;
+  const int m_in = local % h;
+  return (tile_m - m_in) * o.tiles_n + tile_n * h + m_in;
+}
+
+// Sum of the K parts of the cut tiles (fixed order: part 0, 1, ...) followed by the epilogue.  A thread owns four columns of
+// a row, consecutive threads a row's next ones.
+template <bool DUAL>
+__global__ void __launch_bounds__(256)
+gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, PartTiles pt, int wgs_per_tile) {
+  const int bn_out = DUAL ? pt.bn / 2 : pt.bn, quads = bn_out / 4;
+  const int t = (int)blockIdx.x / wgs_per_tile;
+  const int item = ((int)blockIdx.x % wgs_per_tile) * 256 + (int)threadIdx.x;
+  const int r = item / quads, q = item - r * quads;
   int tile_m, tile_n;
-  tile_of(order, full_tiles + t, &tile_m, &tile_n);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / T::WN, wn = wave % T::WN;
-  // the sums land in a one-accumulator "tile" so that the epilogue code is the GEMM kernel's own
-  f32x4 one[1][DUAL ? 2 : 1];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { one[0][0][e] = 0.f; if (DUAL) one[0][DUAL ? 1 : 0][e] = 0.f; }
-  for (int p = 0; p < split; ++p) {
-    const f32x4* src = reinterpret_cast<const f32x4*>(partial) + (size_t)(t * split + p) * (FM * FN) * NT + tid;
-    one[0][0] += src[(size_t)(i * FN + j) * NT];
-    if (DUAL) one[0][DUAL ? 1 : 0] += src[(size_t)(i * FN + j + FN_OUT) * NT];
+  tile_of(pt.order, pt.full + t, &tile_m, &tile_n);
+  const int row = tile_m * pt.bm + r, col = tile_n * bn_out + 4 * q;
+  if (r >= pt.bm || row >= m || col >= n) return;
+  const size_t part = (size_t)pt.bm * pt.bn;
+  const float* src = pt.partial + (size_t)t * pt.split * part + (size_t)r * pt.bn + 4 * q;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f}, up = sum;
+#pragma unroll 4
+  for (int p = 0; p < pt.split; ++p) {
+    sum += *reinterpret_cast<const f32x4*>(src + p * part);
+    if (DUAL) up += *reinterpret_cast<const f32x4*>(src + p * part + bn_out);
   }
-  // row/column origin of accumulator (i, j) of this wavefront
-  const int m_org = tile_m * BM + wm * WTM + i * 16;
-  const int n_org = tile_n * BN_OUT + wn * (DUAL ? WTN / 2 : WTN) + j * 16;
-  store_tile16<1, DUAL ? 2 : 1, 16, DUAL ? 32 : 16, DUAL>(one, c, m, n, ldc, epi, m_org, n_org, 0, 0, lane);
+  const bool f32_out = !DUAL && (epi == EPI_STORE_F32 || epi == EPI_ADD_F32);
+  const bool vec_ok = (ldc & 3) == 0 && (reinterpret_cast<size_t>(c) & (f32_out ? 15 : 7)) == 0;
+  const size_t o = (size_t)row * ldc + col;
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = DUAL ? silu_mf(sum[e]) * up[e] : sum[e];
+  store_quad(c, o, v, epi, f32_out, vec_ok && col + 3 < n, n - col);
+}
+
+// The same for the residual add (h += the product), with the RMS norm of the finished rows behind it: a workgroup per row, the
+// row stays in registers.  Elements and sums are those of rmsnorm_kernel, whose thread t owns elements 4 (t + 256 u) + 0..3:
+// here 256 threads take UPT u's each, so that a row's parts are asked for by up to sixteen wavefronts at once (with the four of
+// rmsnorm_kernel a row of 16 parts took 21 us), and the squares are added up in its order.  Sum and norm in launches of their own
+// -> here: 62 rows in 8 and 16 parts 4.8-7.8 + 4.7 -> 6.2 us, 1639 rows 22 + 9.8 -> 24.7 us (125 MB: 5 TB/s).
+template <int UPT>
+__global__ void __launch_bounds__(1024)
+gemm_fixup_norm_kernel(float* __restrict__ h, const bf16* __restrict__ gain, bf16* __restrict__ out, int d, float eps, PartTiles pt) {
+  __shared__ float squares[8][256];
+  __shared__ float red[4];
+  const int r = blockIdx.x, tid = threadIdx.x, t = tid & 255, u0 = (tid >> 8) * UPT;
+  const int tile_m = r / pt.bm, rr = r - tile_m * pt.bm;
+  float* const x = h + (size_t)r * d;
+  const size_t part = (size_t)pt.bm * pt.bn;
+  const float* src[UPT];
+  size_t step[UPT];
+  f32x4 v[UPT], sum[UPT];
+  uint2 g[UPT];
+  bool cut[UPT];
+#pragma unroll
+  for (int i = 0; i < UPT; ++i) {
+    const int c = min((t + (u0 + i) * 256) * 4, d - 4);   // elements past the row repeat its last ones; no condition around a load
+    v[i] = *reinterpret_cast<const f32x4*>(x + c);
+    g[i] = *reinterpret_cast<const uint2*>(gain + c);
+    const int tile_n = c / pt.bn;
+    const int k = tile_m < pt.order.tiles_m ? tile_index(pt.order, tile_m, tile_n) - pt.full : -1;   // the thin row is never cut
+    cut[i] = k >= 0;
+    src[i] = pt.partial + (cut[i] ? (size_t)k * pt.split * part + (size_t)rr * pt.bn + (c - tile_n * pt.bn) : 0);
+    step[i] = cut[i] ? part : 0;   // whole tiles: the same line over and over
+    sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  constexpr int AHEAD = 8 / UPT;
+  for (int p0 = 0; p0 < pt.split; p0 += AHEAD) {
+    f32x4 q[AHEAD][UPT];
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p)
+#pragma unroll
+      for (int i = 0; i < UPT; ++i) q[p][i] = *reinterpret_cast<const f32x4*>(src[i] + min(p0 + p, pt.split - 1) * step[i]);
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p)
+      if (p0 + p < pt.split) {   // uniform
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) sum[i] += q[p][i];
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < UPT; ++i) {
+    const int c = (t + (u0 + i) * 256) * 4;
+    if (cut[i]) v[i] = sum[i] + v[i];
+    if (cut[i] && c < d) *reinterpret_cast<f32x4*>(x + c) = v[i];
+    squares[u0 + i][t] = c < d ? add_squares(0.f, make_float4(v[i][0], v[i][1], v[i][2], v[i][3])) : 0.f;
+  }
+  __syncthreads();
+  if (tid < 256) {
+    float ss = squares[0][t];
+    for (int u = 1; u * 1024 < d; ++u) ss += squares[u][t];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = ss;
+  }
+  __syncthreads();
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s += red[i];
+  const float inv = 1.0f / sqrtf(s / (float)d + eps);
+#pragma unroll
+  for (int i = 0; i < UPT; ++i) {
+    const int c = (t + (u0 + i) * 256) * 4;
+    if (c >= d) continue;
+    uint2 pk;
+    pk.x = (uint32_t)f32_to_bf16(v[i][0] * inv * __uint_as_float(g[i].x << 16)).v |
+           ((uint32_t)f32_to_bf16(v[i][1] * inv * __uint_as_float(g[i].x & 0xffff0000u)).v << 16);
+    pk.y = (uint32_t)f32_to_bf16(v[i][2] * inv * __uint_as_float(g[i].y << 16)).v |
+           ((uint32_t)f32_to_bf16(v[i][3] * inv * __uint_as_float(g[i].y & 0xffff0000u)).v << 16);
+    *reinterpret_cast<uint2*>(out + (size_t)r * d + c) = pk;
+  }
 }
 
 // ------------------------------------------------------------------ the K partition of a product
@@ -806,12 +910,10 @@ static GridPlan uniform_grid_plan(int m, int tiles_n, int bm, int ksteps, int sp
 }
 
 template <typename T, bool THIN>
-static hipError_t launch_dl(const GridPlan& plan, int n_blocks, int rem_tiles, const bf16* a, const bf16* w, const bf16* w2,
-                            const bf16* w3, int ns1, int ns2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
-                            float* partial, hipStream_t st, const int* m_live) {
-  constexpr int NT = T::NT;
+static hipError_t launch_dl(const GridPlan& plan, int n_blocks, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1,
+                            int ns2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
+                            const int* m_live) {
   const bool dual = epi == EPI_SWIGLU_T;
-  const int normal_full = plan.full_tiles - plan.n_thin;
   const dim3 grid((unsigned)n_blocks);
   constexpr size_t lds_bytes = T::LDS_BYTES;
   hipError_t e = hipSuccess;
@@ -820,22 +922,35 @@ static hipError_t launch_dl(const GridPlan& plan, int n_blocks, int rem_tiles, c
     static std::atomic<unsigned long long> told{0};
     e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
     if (e != hipSuccess) return e;
-    kern<<<grid, NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
-    if (rem_tiles > 0)
-      gemm_fixup_kernel<T, true><<<rem_tiles * T::FM * (T::FN / 2), NT, 0, st>>>(
-          c, m, n, ldc, (int)epi, plan.order, normal_full, plan.split, partial);
+    kern<<<grid, T::NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
     return hipGetLastError();
   }
-  {
-    auto kern = gemm_mfma_dl_kernel<T, false, THIN>;
-    static std::atomic<unsigned long long> told{0};
-    e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
-    if (e != hipSuccess) return e;
-    kern<<<grid, NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
-    if (rem_tiles > 0)
-      gemm_fixup_kernel<T, false><<<rem_tiles * T::FM * T::FN, NT, 0, st>>>(
-          c, m, n, ldc, (int)epi, plan.order, normal_full, plan.split, partial);
-  }
+  auto kern = gemm_mfma_dl_kernel<T, false, THIN>;
+  static std::atomic<unsigned long long> told{0};
+  e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
+  if (e != hipSuccess) return e;
+  kern<<<grid, T::NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
+  return hipGetLastError();
+}
+
+static PartTiles part_tiles(const GemmRest& r) {
+  return PartTiles{{r.tiles_m, r.tiles_n, r.bands}, r.full, r.split, r.bm, r.bn, r.partial};
+}
+
+static hipError_t launch_fixup(const GemmRest& r, void* c, int m, int n, int ldc, GemmEpilogue epi, hipStream_t st) {
+  const bool dual = epi == EPI_SWIGLU_T;
+  const int per_tile = (r.bm * ((dual ? r.bn / 2 : r.bn) / 4) + 255) / 256;
+  if (dual) gemm_fixup_kernel<true><<<r.tiles * per_tile, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile);
+  else gemm_fixup_kernel<false><<<r.tiles * per_tile, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile);
+  return hipGetLastError();
+}
+
+hipError_t launch_rest_rmsnorm(const GemmRest& rest, float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
+                               const int* m_live) {
+  if (rest.tiles == 0) return launch_rmsnorm(h, gain, out, rows, d, eps, st, m_live);
+  const int nu = (d + 1023) / 1024;   // at most eight: kRestNormMax
+  if (nu <= 4) gemm_fixup_norm_kernel<1><<<rows, 256 * nu, 0, st>>>(h, gain, out, d, eps, part_tiles(rest));
+  else gemm_fixup_norm_kernel<2><<<rows, 256 * ((nu + 1) / 2), 0, st>>>(h, gain, out, d, eps, part_tiles(rest));
   return hipGetLastError();
 }
 
@@ -863,7 +978,7 @@ static hipError_t launch_cfg(const bf16* a, const bf16* w, const bf16* w2, const
 }
 
 // The launch of a direct-to-LDS product: tile type (the codes of kTiles; 6: Tile128), grid, tiles that are summed in K parts.
-struct DlPlan { int type; GridPlan grid; int n_blocks, rem_tiles; };
+struct DlPlan { int type; GridPlan grid; int n_blocks, rem_tiles, bm, bn; };
 
 static bool parts_fit(int bm, int bn, int tiles, int split) { return (size_t)tiles * split * bm * bn <= kPartialFloats; }
 
@@ -890,7 +1005,7 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
       if (cost7 < std::min(cost5, cost6)) part = 7;
     }
   }
-  DlPlan p = {part, {}, 0, 0};
+  DlPlan p = {part, {}, 0, 0, 0, 0};
   int split = 1, kpp = ksteps;
   bool uniform = true;
   if (part != 6) {
@@ -917,6 +1032,9 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
   } else if (part == 6) {
     p.grid = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &p.n_blocks, &p.rem_tiles);
   }
+  p.bm = p.bn = 128;   // code 6
+  for (const TileInfo& t : kTiles)
+    if (t.code == p.type) { p.bm = t.bm; p.bn = t.bn; }
   return p;
 }
 
@@ -926,9 +1044,7 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
 // code; n_cus: CUs to plan for.
 int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool with_partial, int* n_blocks_out) {
   const DlPlan p = plan_dl(tile, m, n, k, dual, n_cus, with_partial, false, m);
-  int bm = 128, bn = 128;   // code 6
-  for (const TileInfo& t : kTiles)
-    if (t.code == p.type) { bm = t.bm; bn = t.bn; }
+  const int bm = p.bm, bn = p.bn;
   const int bn_out = dual ? bn / 2 : bn;
   const int tiles_m = (m + bm - 1) / bm, tiles_n = (n + bn_out - 1) / bn_out;
   if (n_blocks_out) *n_blocks_out = p.n_blocks;
@@ -958,17 +1074,24 @@ int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool wi
   for (size_t i = 0; i < slots.size(); ++i)
     if (slots[i] != (int)i) ++errors;
   if (!parts_fit(bm, bn, (int)slots.size(), 1)) ++errors;
+  for (int tm = 0; tm < p.grid.order.tiles_m; ++tm)
+    for (int tn = 0; tn < tiles_n; ++tn) {
+      int bm_i, bn_i;
+      tile_of(p.grid.order, tile_index(p.grid.order, tm, tn), &bm_i, &bn_i);
+      if (bm_i != tm || bn_i != tn) ++errors;   // the summing passes look tiles up by their place
+    }
   if (p.rem_tiles > 0 ? slots.size() != (size_t)p.rem_tiles * p.grid.split : !slots.empty()) ++errors;
   return errors;
 }
 
-// Direct-to-LDS kernels (K a multiple of 64).
+// Direct-to-LDS kernels (K a multiple of 64).  rest: see launch_gemm_bf16.
 static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
                               void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                              const int* m_live, int m_expected) {
+                              const int* m_live, int m_expected, GemmRest* rest) {
   const DlPlan p = plan_dl(tile, m, n, k, epi == EPI_SWIGLU_T, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
+  hipError_t e = hipErrorInvalidValue;
 #define RC_DL(CODE, THIN, ...) \
-  case CODE: return launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, p.rem_tiles, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live)
+  case CODE: e = launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live); break
   switch (p.type) {
     RC_DL(5, true, TilePipe<2, 4, 4, 4, 2, 2>);
     RC_DL(6, false, Tile128);
@@ -979,16 +1102,24 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
     RC_DL(11, false, TilePipe<4, 2, 2, 1, 4, 2>);
     RC_DL(12, false, TilePipe<2, 4, 2, 0, 1, 1, 3>);
     RC_DL(13, false, TilePipe<1, 8, 4, 0, 1, 1, 2>);
-    default: return hipErrorInvalidValue;
   }
 #undef RC_DL
+  if (e != hipSuccess || p.rem_tiles == 0) return e;
+  GemmRest r = {p.rem_tiles, p.grid.order.tiles_m, p.grid.order.tiles_n, p.grid.order.bands, p.grid.full_tiles - p.grid.n_thin,
+                p.grid.split, p.bm, p.bn, partial};
+  if (rest) {
+    *rest = r;
+    return e;
+  }
+  return launch_fixup(r, c, m, n, ldc, epi, st);
 }
 
 bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2) { return g_gemm_tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2); }
 
 static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c,
                            int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                           const int* m_live, int m_expected) {
+                           const int* m_live, int m_expected, GemmRest* rest = nullptr) {
+  if (rest) rest->tiles = 0;
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
   if (gemm_takes_few_rows(m, n, k, ns1, ns2))
@@ -996,7 +1127,7 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
   if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
   if ((tile == 0 || tile >= 5) && k % BK == 0)
     return dispatch_dl(tile, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live,
-                       m_live && m_expected > 0 ? std::min(m, m_expected) : m);
+                       m_live && m_expected > 0 ? std::min(m, m_expected) : m, rest);
   switch (tile) {   // the direct-load kernels need whole K steps
     case 1: return launch_cfg<128, 256, 2, 2, 2>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
     case 2: return launch_cfg<256, 256, 4, 2, 1>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
@@ -1005,8 +1136,8 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
 }
 
 hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc,
-                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected) {
-  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live, m_expected);
+                            GemmEpilogue epi, float* partial, hipStream_t st, const int* m_live, int m_expected, GemmRest* rest) {
+  return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live, m_expected, rest);
 }
 
 // q | k | v projections of the same rows as one GEMM over the concatenated output columns
