@@ -548,19 +548,21 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D, nq, nq + nkv);
       const bool normed = few && gemm_skinny_norm_fits(rows, D);
       if (!normed) RC_LAUNCH(PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
+      const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
+                            job.k_pre_pool ? (bf16*)job.k_pre_pool[l] : nullptr, gd.block_size};
+      bool rotated = few;
       if (few) {
-        const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
-                              job.k_pre_pool ? (bf16*)job.k_pre_pool[l] : nullptr, gd.block_size};
         RC_LAUNCH(PC_GEMM_QKV, launch_gemm_skinny_qkv_rope(w.a, normed ? norm : NormIn{}, (const bf16*)lw.wq, nq, (const bf16*)lw.wk,
                                                            (const bf16*)lw.wv, nkv, rows, D, rope, st, m_live));
       } else {
         RC_LAUNCH(PC_GEMM_QKV, launch_gemm_qkv_bf16(w.a, (const bf16*)lw.wq, nq, (const bf16*)lw.wk, (const bf16*)lw.wv, nkv,
-                                                    w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected));
-        // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
+                                                    w.qkv, rows, D, w.gemm_part, st, m_live, rows_expected, &rope, &rotated));
+      }
+      // rotary on q/k at the rows' absolute positions; fresh K/V written into the cache before anyone attends
+      if (!rotated)
         RC_LAUNCH(PC_ROPE_SCATTER, launch_rope_scatter<T>(w.qkv, rows, w.row_pos, w.row_req, w.tables + cur, w.rope_tab, (T*)w.q,
                                       (T*)job.dst->k_pool[l], (T*)job.dst->v_pool[l],
                                       job.k_pre_pool ? (T*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st));
-      }
     }
     // influence accumulation (decoding): the bf16 matrix-core attention kernel hands out its scores; the other
     // paths compute them in a pass of their own

@@ -355,9 +355,11 @@ hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* 
 constexpr int kRestNormMax = 8192;
 hipError_t launch_rest_rmsnorm(const GemmRest& rest, float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
                                const int* m_live);
-// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T
+// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T.  With rope (heads of 128), rotary and scatter are part of the product where that
+// can be (*rotated; C is not written then).
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                                int m, int k, float* partial, hipStream_t st, const int* m_live = nullptr, int m_expected = 0);
+                                int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected, const RopeOut* rope,
+                                bool* rotated);
 void set_gemm_xcd_remap(int on);
 int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool with_partial, int* n_blocks_out);
 void set_gemm_thin_tiles(int on);   // 1: a ragged last tile row of at most 64 rows goes to the thin tile body

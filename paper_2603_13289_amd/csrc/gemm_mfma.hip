@@ -272,11 +272,70 @@ __device__ __forceinline__ void store_quad(void* __restrict__ c, size_t o, const
   }
 }
 
-template <int FM, int FN, int WTM, int WTN, bool DUAL>
+// Four consecutive rotary pairs of a row of q|k|v, rotated and left where they belong: the work and the arithmetic of
+// rope_scatter_kernel.  lo / hi: the columns of the two halves of a head.  In the epilogue of the product it costs 5 us on 110
+// (2500 rows) or nothing (60 rows, inside the sum over the K parts); the launch it replaces wrote and read the product in floats:
+// 6 us at 60 rows, 12.7 at 1639, 37 at 5120.
+__device__ __forceinline__ void rope_quad(const RopeOut& o, int row, int pos, unsigned dst, int pair, const f32x4& lo, const f32x4& hi, int ns1,
+                                          int ns2) {
+  const int col = rope_column(pair, 0), i = pair & 63;
+  f32x4 a = lo, b = hi;
+  if (col < ns2) {
+    const float4 t01 = *reinterpret_cast<const float4*>(o.tab + (size_t)pos * 64 + i);       // (cos, sin) of pairs i, i+1
+    const float4 t23 = *reinterpret_cast<const float4*>(o.tab + (size_t)pos * 64 + i + 2);   // pairs i+2, i+3
+    const float c[4] = {t01.x, t01.z, t23.x, t23.z}, s[4] = {t01.y, t01.w, t23.y, t23.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a[e] = __builtin_fmaf(lo[e], c[e], -(hi[e] * s[e]));
+      b[e] = __builtin_fmaf(hi[e], c[e], lo[e] * s[e]);
+    }
+  }
+  auto put = [](bf16* p, const f32x4& v) {
+    uint2 pk;
+    pk.x = (uint32_t)f32_to_bf16(v[0]).v | ((uint32_t)f32_to_bf16(v[1]).v << 16);
+    pk.y = (uint32_t)f32_to_bf16(v[2]).v | ((uint32_t)f32_to_bf16(v[3]).v << 16);
+    *reinterpret_cast<uint2*>(p) = pk;
+  };
+  if (col < ns1) {
+    bf16* q = o.q + (size_t)row * ns1 + col;
+    put(q, a);
+    put(q + 64, b);
+    return;
+  }
+  if (dst == kRowNoDst) return;
+  const bool is_v = col >= ns2;
+  const size_t at = ((size_t)dst + (size_t)((col - (is_v ? ns2 : ns1)) >> 7) * o.block_size) * 128 + i;
+  bf16* pool = is_v ? o.v_pool : o.k_pool;
+  put(pool + at, a);
+  put(pool + at + 64, b);
+  if (!is_v && o.k_pre_pool) {
+    put(o.k_pre_pool + at, lo);
+    put(o.k_pre_pool + at + 64, hi);
+  }
+}
+
+template <int FM, int FN, int WTM, int WTN, int MODE>
 __device__ inline void store_tile16(const f32x4 (&acc)[FM][FN], void* __restrict__ c, int m, int n, int ldc, int epi,
-                                    int m0, int n0, int wm, int wn, int lane) {
+                                    int m0, int n0, int wm, int wn, int lane, int ns1, int ns2, const RopeOut& rope) {
+  constexpr bool DUAL = MODE == kDual;
   constexpr int FN_OUT = DUAL ? FN / 2 : FN;
   constexpr int WTN_OUT = DUAL ? WTN / 2 : WTN;
+  if constexpr (MODE == kRope) {
+    constexpr int FH = FN / 2;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int row = m0 + wm * WTM + i * 16 + (lane & 15);
+      if (row >= m) continue;
+      const int pos = rope.row_pos[row];
+      const unsigned dst = rope.row_dst[row];
+#pragma unroll
+      for (int j = 0; j < FH; ++j) {
+        const int pair = n0 + wn * (WTN / 2) + j * 16 + 4 * (lane >> 4);
+        if (pair < n) rope_quad(rope, row, pos, dst, pair, acc[i][j], acc[i][j + FH], ns1, ns2);
+      }
+    }
+    return;
+  }
   const bool f32_out = !DUAL && (epi == EPI_STORE_F32 || epi == EPI_ADD_F32);
   const bool vec_ok = (ldc & 3) == 0 && (reinterpret_cast<size_t>(c) & (f32_out ? 15 : 7)) == 0;
   if constexpr (!DUAL) {
@@ -317,9 +376,9 @@ __device__ inline void store_tile16(const f32x4 (&acc)[FM][FN], void* __restrict
   }
 }
 
-// The accumulators of a K part, as rows of BN floats (DUAL: the tile's gate columns, then its up columns) of the part's BM x BN
+// The accumulators of a K part, as rows of BN floats (PAIRED: the first columns of all pairs, then the second) of the part's BM x BN
 // block: whoever adds the parts up reads whole rows.  Rows past the product's last one are left out.
-template <int FM, int FN, int BM, int BN, int WTM, int WTN, bool DUAL>
+template <int FM, int FN, int BM, int BN, int WTM, int WTN, bool PAIRED>
 __device__ inline void store_partial(const f32x4 (&acc)[FM][FN], float* __restrict__ partial, int part_slot, int rows, int wm, int wn,
                                      int lane) {
   constexpr int FH = FN / 2;
@@ -330,18 +389,18 @@ __device__ inline void store_partial(const f32x4 (&acc)[FM][FN], float* __restri
     if (row >= rows) continue;
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-      const int col = !DUAL ? wn * WTN + j * 16 : (j < FH ? wn * (WTN / 2) + j * 16 : BN / 2 + wn * (WTN / 2) + (j - FH) * 16);
+      const int col = !PAIRED ? wn * WTN + j * 16 : (j < FH ? wn * (WTN / 2) + j * 16 : BN / 2 + wn * (WTN / 2) + (j - FH) * 16);
       *reinterpret_cast<f32x4*>(base + (size_t)row * BN + col) = acc[i][j];
     }
   }
 }
 
 // One output tile (or one K part of it): the work of a workgroup once it knows its tile.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool DUAL>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE>
 __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const bf16* __restrict__ w,
                                                const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
                                                void* __restrict__ c, int m, int n, int k, int ldc, int epi, int m0, int n0,
-                                               int k_begin, int k_end, int part_slot, float* __restrict__ partial) {
+                                               int k_begin, int k_end, int part_slot, float* __restrict__ partial, const RopeOut& rope) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int FM = WTM / 16, FN = WTN / 16, FH = FN / 2;
@@ -370,12 +429,14 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
     const int row = (wave + i * NW) * 8 + lrow;
     const int chunk = lslot ^ ((row >> 1) & 7);
     const bf16* src;
-    if (DUAL) {
+    if (MODE == kDual) {
       const int half = row >= BN / 2;
       const int col = min(n0 + row - half * (BN / 2), n - 1);
       src = (half ? w2 : w) + (size_t)col * k;
     } else {
-      const int col = min(n0 + row, n - 1);
+      const int half = MODE == kRope && row >= BN / 2 ? 1 : 0;
+      const int unit = min(n0 + row - half * (BN / 2), n - 1);
+      const int col = MODE == kRope ? rope_column(unit, half) : unit;
       src = col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k);
     }
     pb[i] = src + chunk * 8;
@@ -406,7 +467,7 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
   for (int i = 0; i < FM; ++i) arow[i] = wm * WTM + i * 16 + (lane & 15);
 #pragma unroll
   for (int j = 0; j < FN; ++j) {
-    if (DUAL) brow[j] = (j < FH ? wn * (WTN / 2) + j * 16 : BN / 2 + wn * (WTN / 2) + (j - FH) * 16) + (lane & 15);
+    if (MODE != kPlain) brow[j] = (j < FH ? wn * (WTN / 2) + j * 16 : BN / 2 + wn * (WTN / 2) + (j - FH) * 16) + (lane & 15);
     else brow[j] = wn * WTN + j * 16 + (lane & 15);
   }
   const int kq = lane >> 4;
@@ -470,29 +531,29 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
   }
 
   if (part_slot >= 0) {
-    store_partial<FM, FN, BM, BN, WTM, WTN, DUAL>(acc, partial, part_slot, m - m0, wm, wn, lane);
+    store_partial<FM, FN, BM, BN, WTM, WTN, MODE != kPlain>(acc, partial, part_slot, m - m0, wm, wn, lane);
     return;
   }
-  store_tile16<FM, FN, WTM, WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane);
+  store_tile16<FM, FN, WTM, WTN, MODE>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane, ns1, ns2, rope);
 }
 
 // The same on the pipelined main loop of gemm_pipe.h; partial sums in the layout of gemm_tile_body.
-template <typename T, bool DUAL>
+template <typename T, int MODE>
 __device__ __forceinline__ void gemm_pipe_body(const bf16* __restrict__ a, const bf16* __restrict__ w,
                                                const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
                                                void* __restrict__ c, int m, int n, int k, int ldc, int epi, int m0, int n0,
-                                               int k_begin, int k_end, int part_slot, float* __restrict__ partial) {
+                                               int k_begin, int k_end, int part_slot, float* __restrict__ partial, const RopeOut& rope) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   f32x4 acc[T::FM][T::FN];
-  gemm_pipe_loop<T, DUAL>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
+  gemm_pipe_loop<T, MODE>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
   if (part_slot >= 0) {
-    store_partial<T::FM, T::FN, T::BM, T::BN, T::WTM, T::WTN, DUAL>(acc, partial, part_slot, m - m0, wm, wn, lane);
+    store_partial<T::FM, T::FN, T::BM, T::BN, T::WTM, T::WTN, MODE != kPlain>(acc, partial, part_slot, m - m0, wm, wn, lane);
     return;
   }
-  store_tile16<T::FM, T::FN, T::WTM, T::WTN, DUAL>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane);
+  store_tile16<T::FM, T::FN, T::WTM, T::WTN, MODE>(acc, c, m, n, ldc, epi, m0, n0, wm, wn, lane, ns1, ns2, rope);
 }
 
 // What the launch's grid does.  Workgroups [0, n_full_wgs) each own one of the first full_tiles output tiles
@@ -558,25 +619,25 @@ struct Tile128 {
   static constexpr int LDS_BYTES = 2 * (BM + BN) * 128;
   static constexpr int OCC = 2, WAVES_PER_SIMD = 2;
   static constexpr bool DUAL_OK = true;
-  template <bool DUAL, typename... Args> static __device__ __forceinline__ void body(Args... args) {
-    gemm_tile_body<128, 128, 2, 2, DUAL>(args...);
+  template <int MODE, typename... Args> static __device__ __forceinline__ void body(const Args&... args) {
+    gemm_tile_body<128, 128, 2, 2, MODE>(args...);
   }
 };
 template <int WM_, int WN_, int FM0_, int FM1_, int FN0_, int FN1_, int OCC_ = 1>
 struct TilePipe : PipeTile<WM_, WN_, FM0_, FM1_, FN0_, FN1_> {
   static constexpr int NT = 512, OCC = OCC_, WAVES_PER_SIMD = 2 * OCC_;
   static constexpr bool DUAL_OK = FN0_ == FN1_;
-  template <bool DUAL, typename... Args> static __device__ __forceinline__ void body(Args... args) {
-    gemm_pipe_body<PipeTile<WM_, WN_, FM0_, FM1_, FN0_, FN1_>, DUAL>(args...);
+  template <int MODE, typename... Args> static __device__ __forceinline__ void body(const Args&... args) {
+    gemm_pipe_body<PipeTile<WM_, WN_, FM0_, FM1_, FN0_, FN1_>, MODE>(args...);
   }
 };
 
-template <typename T, bool DUAL, bool THIN>
-__global__ void __launch_bounds__(T::NT, T::WAVES_PER_SIMD)
-gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
-                    const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
-                    int epi, GridPlan plan, float* __restrict__ partial, const int* __restrict__ m_live) {
-  constexpr int BM = T::BM, BN = T::BN, BN_OUT = DUAL ? BN / 2 : BN;
+template <typename T, int MODE, bool THIN>
+__device__ __forceinline__ void gemm_dl_work(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
+                                             const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k,
+                                             int ldc, int epi, const GridPlan& plan, float* __restrict__ partial,
+                                             const int* __restrict__ m_live, const RopeOut& rope) {
+  constexpr int BM = T::BM, BN = T::BN, BN_OUT = MODE != kPlain ? BN / 2 : BN;
   BlockWork bw = {1, 0, 0, 0, k, -1};   // one call of the tile body for both cases: with two, its loop ran out of registers
   if (m_live) {
     // The row count lives on the device (rows selected by a threshold) and the host's m only sized the grid.  The
@@ -596,13 +657,30 @@ gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, cons
   }
   if constexpr (THIN) {
     if (bw.kind == 2) {
-      gemm_tile_body<64, BN, 1, T::NT / 64, DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
-                                                         bw.tile_n * BN_OUT, 0, k, -1, partial);
+      gemm_tile_body<64, BN, 1, T::NT / 64, MODE>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
+                                                         bw.tile_n * BN_OUT, 0, k, -1, partial, rope);
       return;
     }
   }
-  T::template body<DUAL>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM, bw.tile_n * BN_OUT, bw.k_begin,
-                         bw.k_end, bw.part_slot, partial);
+  T::template body<MODE>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM, bw.tile_n * BN_OUT, bw.k_begin,
+                         bw.k_end, bw.part_slot, partial, rope);
+}
+
+template <typename T, bool DUAL, bool THIN>
+__global__ void __launch_bounds__(T::NT, T::WAVES_PER_SIMD)
+gemm_mfma_dl_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
+                    const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
+                    int epi, GridPlan plan, float* __restrict__ partial, const int* __restrict__ m_live) {
+  gemm_dl_work<T, DUAL ? kDual : kPlain, THIN>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, plan, partial, m_live, RopeOut{});
+}
+
+// the q|k|v product with rotary and scatter; n: rotary pairs
+template <typename T, bool THIN>
+__global__ void __launch_bounds__(T::NT, T::WAVES_PER_SIMD)
+gemm_qkv_rope_kernel(const bf16* __restrict__ a, const bf16* __restrict__ wq, const bf16* __restrict__ wk, const bf16* __restrict__ wv,
+                     int ns1, int ns2, int m, int n, int k, GridPlan plan, float* __restrict__ partial, const int* __restrict__ m_live,
+                     RopeOut rope) {
+  gemm_dl_work<T, kRope, THIN>(a, wq, wk, wv, ns1, ns2, nullptr, m, n, k, 0, (int)EPI_STORE_T, plan, partial, m_live, rope);
 }
 
 // The parts of one product that are still to be added up: tiles [full, ...) of `order`, bm x bn, in `split` parts each.
@@ -621,10 +699,12 @@ __device__ __host__ inline int tile_index(TileOrder o, int tile_m, int tile_n) {
 
 // Sum of the K parts of the cut tiles (fixed order: part 0, 1, ...) followed by the epilogue.  A thread owns four columns of
 // a row, consecutive threads a row's next ones.
-template <bool DUAL>
+template <int MODE>
 __global__ void __launch_bounds__(256)
-gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, PartTiles pt, int wgs_per_tile) {
-  const int bn_out = DUAL ? pt.bn / 2 : pt.bn, quads = bn_out / 4;
+gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, PartTiles pt, int wgs_per_tile, int ns1,
+                  int ns2, RopeOut rope) {
+  constexpr bool PAIRED = MODE != kPlain, DUAL = MODE == kDual;
+  const int bn_out = PAIRED ? pt.bn / 2 : pt.bn, quads = bn_out / 4;
   const int t = (int)blockIdx.x / wgs_per_tile;
   const int item = ((int)blockIdx.x % wgs_per_tile) * 256 + (int)threadIdx.x;
   const int r = item / quads, q = item - r * quads;
@@ -638,7 +718,11 @@ gemm_fixup_kernel(void* __restrict__ c, int m, int n, int ldc, int epi, PartTile
 #pragma unroll 4
   for (int p = 0; p < pt.split; ++p) {
     sum += *reinterpret_cast<const f32x4*>(src + p * part);
-    if (DUAL) up += *reinterpret_cast<const f32x4*>(src + p * part + bn_out);
+    if (PAIRED) up += *reinterpret_cast<const f32x4*>(src + p * part + bn_out);
+  }
+  if constexpr (MODE == kRope) {
+    rope_quad(rope, row, rope.row_pos[row], rope.row_dst[row], col, sum, up, ns1, ns2);
+    return;
   }
   const bool f32_out = !DUAL && (epi == EPI_STORE_F32 || epi == EPI_ADD_F32);
   const bool vec_ok = (ldc & 3) == 0 && (reinterpret_cast<size_t>(c) & (f32_out ? 15 : 7)) == 0;
@@ -861,11 +945,12 @@ static GridPlan make_grid_plan(int m, int tiles_n, int bm, int ksteps, int slots
 // workgroups to a compute unit, were 2.9 % (16 %, 32 %) behind: gate/up of 200 x 27648 x 5120 167 us for 133,
 // 777 x 6144 x 4096 65 for 51.
 // 256x192 at 1.08 and not the fit's 1.11: 192-row tiles that cover as much in the one round are then not preferred to it
-// (2500 x 4096 x 14336 244 -> 239 us, 2039 x 5120 x 27648 466 -> 453; 1801 x 5120 x 27648 loses 441 -> 451).
+// (2500 x 4096 x 14336 244 -> 239 us, 2039 x 5120 x 27648 466 -> 453; 1801 x 5120 x 27648 loses 441 -> 451).  192x256 with
+// wavefronts of 96 x 64 instead of 48 x 128 outputs (a tenth fewer LDS reads) is 2 % faster over 40 shapes: 1.01 for 1.03.
 struct TileInfo { int code, bm, bn, occ; bool dual; float step_lo, step_hi, fixed; };
 static constexpr TileInfo kTiles[] = {
     {5, 256, 256, 1, true, 1.01f, 1.23f, 5.34f},  {7, 256, 192, 1, false, 0.70f, 1.08f, 2.44f},
-    {8, 192, 256, 1, true, 0.99f, 1.03f, 2.60f},  {11, 192, 192, 1, false, 0.78f, 0.89f, 2.12f},
+    {8, 192, 256, 1, true, 0.99f, 1.01f, 2.60f},  {11, 192, 192, 1, false, 0.78f, 0.89f, 2.12f},
     {9, 128, 256, 1, true, 0.69f, 0.85f, 1.60f},  {10, 128, 128, 2, true, 0.07f, 1.12f, 2.03f},
     {12, 64, 128, 3, true, 0.03f, 1.27f, 0.68f},  {13, 64, 256, 2, true, 0.02f, 1.46f, 2.05f},
 };
@@ -912,36 +997,39 @@ static GridPlan uniform_grid_plan(int m, int tiles_n, int bm, int ksteps, int sp
 template <typename T, bool THIN>
 static hipError_t launch_dl(const GridPlan& plan, int n_blocks, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1,
                             int ns2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                            const int* m_live) {
-  const bool dual = epi == EPI_SWIGLU_T;
-  const dim3 grid((unsigned)n_blocks);
+                            const int* m_live, const RopeOut* rope) {
   constexpr size_t lds_bytes = T::LDS_BYTES;
-  hipError_t e = hipSuccess;
-  if constexpr (T::DUAL_OK) if (dual) {
-    auto kern = gemm_mfma_dl_kernel<T, true, THIN>;
-    static std::atomic<unsigned long long> told{0};
-    e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
+  const dim3 grid((unsigned)n_blocks);
+  static std::atomic<unsigned long long> told[3] = {};
+  if (rope) {
+    auto kern = gemm_qkv_rope_kernel<T, THIN>;
+    const hipError_t e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told[2]);
+    if (e != hipSuccess) return e;
+    kern<<<grid, T::NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, m, n / 2, k, plan, partial, m_live, *rope);
+    return hipGetLastError();
+  }
+  auto go = [&](auto kern, std::atomic<unsigned long long>& done) {
+    const hipError_t e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, done);
     if (e != hipSuccess) return e;
     kern<<<grid, T::NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
     return hipGetLastError();
-  }
-  auto kern = gemm_mfma_dl_kernel<T, false, THIN>;
-  static std::atomic<unsigned long long> told{0};
-  e = allow_dynamic_lds((const void*)kern, (int)lds_bytes, told);
-  if (e != hipSuccess) return e;
-  kern<<<grid, T::NT, lds_bytes, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, plan, partial, m_live);
-  return hipGetLastError();
+  };
+  if constexpr (T::DUAL_OK) if (epi == EPI_SWIGLU_T) return go(gemm_mfma_dl_kernel<T, true, THIN>, told[1]);
+  return go(gemm_mfma_dl_kernel<T, false, THIN>, told[0]);
 }
 
 static PartTiles part_tiles(const GemmRest& r) {
   return PartTiles{{r.tiles_m, r.tiles_n, r.bands}, r.full, r.split, r.bm, r.bn, r.partial};
 }
 
-static hipError_t launch_fixup(const GemmRest& r, void* c, int m, int n, int ldc, GemmEpilogue epi, hipStream_t st) {
-  const bool dual = epi == EPI_SWIGLU_T;
-  const int per_tile = (r.bm * ((dual ? r.bn / 2 : r.bn) / 4) + 255) / 256;
-  if (dual) gemm_fixup_kernel<true><<<r.tiles * per_tile, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile);
-  else gemm_fixup_kernel<false><<<r.tiles * per_tile, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile);
+static hipError_t launch_fixup(const GemmRest& r, void* c, int m, int n, int ldc, GemmEpilogue epi, hipStream_t st, int ns1, int ns2,
+                               const RopeOut* rope) {
+  const bool paired = rope || epi == EPI_SWIGLU_T;
+  const int per_tile = (r.bm * ((paired ? r.bn / 2 : r.bn) / 4) + 255) / 256;
+  const dim3 grid((unsigned)(r.tiles * per_tile));
+  if (rope) gemm_fixup_kernel<kRope><<<grid, 256, 0, st>>>(c, m, n / 2, ldc, (int)epi, part_tiles(r), per_tile, ns1, ns2, *rope);
+  else if (paired) gemm_fixup_kernel<kDual><<<grid, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile, ns1, ns2, RopeOut{});
+  else gemm_fixup_kernel<kPlain><<<grid, 256, 0, st>>>(c, m, n, ldc, (int)epi, part_tiles(r), per_tile, ns1, ns2, RopeOut{});
   return hipGetLastError();
 }
 
@@ -978,7 +1066,7 @@ static hipError_t launch_cfg(const bf16* a, const bf16* w, const bf16* w2, const
 }
 
 // The launch of a direct-to-LDS product: tile type (the codes of kTiles; 6: Tile128), grid, tiles that are summed in K parts.
-struct DlPlan { int type; GridPlan grid; int n_blocks, rem_tiles, bm, bn; };
+struct DlPlan { int type; GridPlan grid; int n_blocks, rem_tiles, bm, bn; bool uniform; /* summed the same way everywhere */ };
 
 static bool parts_fit(int bm, int bn, int tiles, int split) { return (size_t)tiles * split * bm * bn <= kPartialFloats; }
 
@@ -1005,7 +1093,7 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
       if (cost7 < std::min(cost5, cost6)) part = 7;
     }
   }
-  DlPlan p = {part, {}, 0, 0, 0, 0};
+  DlPlan p = {part, {}, 0, 0, 0, 0, true};
   int split = 1, kpp = ksteps;
   bool uniform = true;
   if (part != 6) {
@@ -1032,6 +1120,7 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
   } else if (part == 6) {
     p.grid = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &p.n_blocks, &p.rem_tiles);
   }
+  p.uniform = uniform;
   p.bm = p.bn = 128;   // code 6
   for (const TileInfo& t : kTiles)
     if (t.code == p.type) { p.bm = t.bm; p.bn = t.bn; }
@@ -1087,16 +1176,16 @@ int check_grid_plan(int m, int n, int k, bool dual, int tile, int n_cus, bool wi
 // Direct-to-LDS kernels (K a multiple of 64).  rest: see launch_gemm_bf16.
 static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
                               void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
-                              const int* m_live, int m_expected, GemmRest* rest) {
+                              const int* m_live, int m_expected, GemmRest* rest, const RopeOut* rope = nullptr) {
   const DlPlan p = plan_dl(tile, m, n, k, epi == EPI_SWIGLU_T, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
   hipError_t e = hipErrorInvalidValue;
 #define RC_DL(CODE, THIN, ...) \
-  case CODE: e = launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live); break
+  case CODE: e = launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live, rope); break
   switch (p.type) {
     RC_DL(5, true, TilePipe<2, 4, 4, 4, 2, 2>);
     RC_DL(6, false, Tile128);
-    RC_DL(7, false, TilePipe<2, 4, 4, 4, 2, 1>);
-    RC_DL(8, false, TilePipe<4, 2, 2, 1, 4, 4>);
+    RC_DL(7, false, TilePipe<4, 2, 2, 2, 4, 2>);
+    RC_DL(8, false, TilePipe<2, 4, 4, 2, 2, 2>);
     RC_DL(9, false, TilePipe<2, 4, 2, 2, 2, 2>);
     RC_DL(10, false, TilePipe<2, 4, 2, 2, 1, 1, 2>);
     RC_DL(11, false, TilePipe<4, 2, 2, 1, 4, 2>);
@@ -1111,7 +1200,7 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
     *rest = r;
     return e;
   }
-  return launch_fixup(r, c, m, n, ldc, epi, st);
+  return launch_fixup(r, c, m, n, ldc, epi, st, ns1, ns2, rope);
 }
 
 bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2) { return g_gemm_tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2); }
@@ -1140,10 +1229,22 @@ hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* 
   return dispatch(a, w, w2, nullptr, n, n, c, m, n, k, ldc, epi, partial, st, m_live, m_expected, rest);
 }
 
-// q | k | v projections of the same rows as one GEMM over the concatenated output columns
+// q | k | v projections of the same rows as one GEMM over the concatenated output columns.  Rotary and scatter are part of it where
+// rotary partners can sit in one wavefront: a tile of pairs covers the columns of the tile it stands for, which matters where
+// whole and cut tiles are mixed, when its width is a multiple of a head (256, not 192).
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
-                                int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected) {
-  const int n = nq + 2 * nkv;
+                                int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected, const RopeOut* rope,
+                                bool* rotated) {
+  const int n = nq + 2 * nkv, tile = g_gemm_tile;
+  *rotated = false;
+  if (rope && m > 0 && (tile == 0 || tile >= 5) && k % BK == 0 && !gemm_takes_few_rows(m, n, k, nq, nq + nkv)) {
+    if (m_live) partial = nullptr;
+    m_expected = m_live && m_expected > 0 ? std::min(m, m_expected) : m;
+    const DlPlan p = plan_dl(tile, m, n, k, false, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
+    *rotated = p.uniform || p.type != 7;
+    if (*rotated)
+      return dispatch_dl(tile, a, wq, wk, wv, nq, nq + nkv, nullptr, m, n, k, n, EPI_STORE_T, partial, st, m_live, m_expected, nullptr, rope);
+  }
   return dispatch(a, wq, wk, wv, nq, nq + nkv, c, m, n, k, n, EPI_STORE_F32, partial, st, m_live, m_expected);
 }
 

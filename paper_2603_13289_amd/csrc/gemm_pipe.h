@@ -45,16 +45,22 @@ struct PipeTile {
   static_assert(A_BYTES <= 32768 && B_BYTES <= 32768, "LDS read offsets are 16-bit");
 };
 
-// A loads [k_begin, k_end) of rows m0.. of a (clamped to the last row) and columns n0.. of the weights; weight rows of
-// the output columns below ns1 come from w, below ns2 from w2, the rest from w3 (boundaries are multiples of 8).  DUAL:
-// column half 0 of every wavefront is the gate (w), half 1 the up projection (w2) of the same BN / 2 output columns.
+// What the columns of a tile are.  kPlain: BN neighbours.  The paired modes give every wavefront both members of BN / 2 / WN pairs,
+// in column blocks j and j + FN / 2.  kDual: gate (w) and up projection (w2) of an output column.  kRope: rotary partners, columns
+// i and i + 64 of a head of 128; pair p is column i = p % 64 of head p / 64.
+enum GemmMode : int { kPlain = 0, kDual = 1, kRope = 2 };
+__device__ __host__ inline int rope_column(int pair, int second) { return (pair >> 6) * 128 + (pair & 63) + 64 * second; }
+
+// A loads [k_begin, k_end) of rows m0.. of a (clamped to the last row) and columns (paired modes: pairs) n0.. of the weights, of
+// which there are n; weight rows of the output columns below ns1 come from w, below ns2 from w2, the rest from w3
+// (boundaries are multiples of 8).
 // acc (i, j): rows wm * WTM + 16 i + lane % 16, columns 16 j + 4 (lane / 16) + 0..3 of the wavefront's sub-tile.
-template <typename T, bool DUAL>
+template <typename T, int MODE>
 __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const bf16* __restrict__ w,
                                                const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
                                                int m, int n, int k, int m0, int n0, int k_begin, int k_end,
                                                unsigned char* lds, pipe_f32x4 (&acc)[T::FM][T::FN]) {
-  static_assert(!DUAL || T::FN0 == T::FN1, "gate and up halves");
+  static_assert(MODE == kPlain || T::FN % 2 == 0, "blocks of pairs");
   constexpr int FM0 = T::FM0, FM1 = T::FM1, FN0 = T::FN0, FN1 = T::FN1, FMX = FM0 > FM1 ? FM0 : FM1, FNX = FN0 > FN1 ? FN0 : FN1;
   constexpr int LAX = T::LA0 > T::LA1 ? T::LA0 : T::LA1, LBX = T::LB0 > T::LB1 ? T::LB0 : T::LB1;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -80,13 +86,15 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
       const int per = 2 * (h ? FN1 : FN0), blk = wave + 8 * i;
       const int wn_i = blk / per, rr = (blk % per) * 8;
       const int r = wn_i * T::WTN + h * FN0 * 16 + rr;
-      const int col = DUAL ? n0 + wn_i * FN0 * 16 + rr : n0 + r;
-      const int c0 = min(col, n - 1);
+      constexpr int FH = T::FN / 2;
+      const int j = h * FN0 + rr / 16, second = j >= FH ? 1 : 0;
+      const int unit = MODE == kPlain ? n0 + r : n0 + wn_i * FH * 16 + (j - second * FH) * 16 + rr % 16;   // column or pair
+      const int u0 = min(unit, n - 1), c0 = MODE == kRope ? rope_column(min(unit, n - 8), second) : u0;
       const bf16* src;
-      if (DUAL) src = (h ? w2 : w) + (size_t)c0 * k;
+      if (MODE == kDual) src = (second ? w2 : w) + (size_t)c0 * k;
       else src = c0 < ns1 ? w + (size_t)c0 * k : (c0 < ns2 ? w2 + (size_t)(c0 - ns1) * k : w3 + (size_t)(c0 - ns2) * k);
       pb[h][i] = src;
-      vb[h][i] = (min(col + lrow, n - 1) - c0) * k * 2 + ((lslot ^ (((r + lrow) >> 1) & 7)) << 4);
+      vb[h][i] = (MODE == kRope ? lrow : min(unit + lrow, n - 1) - u0) * k * 2 + ((lslot ^ (((r + lrow) >> 1) & 7)) << 4);
       lb[h][i] = 2 * T::A_BYTES + r * 128;
     }
   }
@@ -168,15 +176,15 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
   read_a(0, 0, 0, 2 * FM0);
   read_b(0, 0, 0, 0, 2 * FN0);
 
-  // One K step on buffer P; the weights' half 0 is in register slot P.  MODE 0: in the loop; 1: last but one step; 2: last.
-  auto step = [&](auto P_, auto MODE_, int k0) {
-    constexpr int P = decltype(P_)::value, MODE = decltype(MODE_)::value, Q = 1 - P;
+  // One K step on buffer P; the weights' half 0 is in register slot P.  STAGE 0: in the loop; 1: last but one step; 2: last.
+  auto step = [&](auto P_, auto STAGE_, int k0) {
+    constexpr int P = decltype(P_)::value, STAGE = decltype(STAGE_)::value, Q = 1 - P;
     constexpr int M00 = 2 * FM0 * FN0, M01 = 2 * FM0 * FN1, M11 = 2 * FM1 * FN1, M10 = 2 * FM1 * FN0;
     // phase 0: A0 * B0; reads B1 of this step; refills A0
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(MODE == 2 ? 0 : LALL) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(STAGE == 2 ? 0 : LALL) : "memory");
     tie_a(0); tie_b(P, 0);
     RC_FENCE; __builtin_amdgcn_s_barrier(); RC_FENCE;
-    if constexpr (MODE == 0) load_a(0, P, k0 + 128);
+    if constexpr (STAGE == 0) load_a(0, P, k0 + 128);
 #pragma unroll
     for (int r = 0; r < FN1; ++r) {
       read_b(Q, 1, P, 2 * r, 2 * r + 2);
@@ -186,7 +194,7 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     tie_b(Q, 1);
     RC_FENCE;
-    if constexpr (MODE == 0) load_b(0, P, k0 + 128);
+    if constexpr (STAGE == 0) load_b(0, P, k0 + 128);
     RC_FENCE;
     constexpr int RA1 = FM1 > 0 ? FM1 : 1;            // pairs of reads
 #pragma unroll
@@ -195,27 +203,27 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
       RC_FENCE; multiply(0, Q, 1, r * M01 / (2 * RA1), r + 1 == RA1 ? M01 : (r + 1) * M01 / (2 * RA1)); RC_FENCE;
     }
     // phase 2: A1 * B1; reads most of A0 of the next step; refills B1
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(MODE == 2 ? 63 : MODE == 1 ? L23 : LALL) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(STAGE == 2 ? 63 : STAGE == 1 ? L23 : LALL) : "memory");
     tie_a(1);
     RC_FENCE;
-    if constexpr (MODE != 2) __builtin_amdgcn_s_barrier();
+    if constexpr (STAGE != 2) __builtin_amdgcn_s_barrier();
     RC_FENCE;
-    if constexpr (MODE == 0) load_b(1, P, k0 + 128);
+    if constexpr (STAGE == 0) load_b(1, P, k0 + 128);
     RC_FENCE;
     constexpr int RA2 = (2 * FM0 * 3 / 4 + 1) / 2;   // pairs of reads in phase 2
 #pragma unroll
     for (int r = 0; r < RA2; ++r) {
-      if constexpr (MODE != 2) read_a(0, Q, 2 * r, 2 * r + 2);
+      if constexpr (STAGE != 2) read_a(0, Q, 2 * r, 2 * r + 2);
       RC_FENCE; multiply(1, Q, 1, r * M11 / (2 * RA2), r + 1 == RA2 ? M11 : (r + 1) * M11 / (2 * RA2)); RC_FENCE;
     }
     // phase 3: A1 * B0; reads the rest of A0 and B0 of the next step (into B1's registers); refills A1
-    if constexpr (MODE == 0) load_a(1, P, k0 + 128);
+    if constexpr (STAGE == 0) load_a(1, P, k0 + 128);
     RC_FENCE;
-    if constexpr (MODE != 2) read_a(0, Q, 2 * RA2, 2 * FM0);
+    if constexpr (STAGE != 2) read_a(0, Q, 2 * RA2, 2 * FM0);
     RC_FENCE; multiply(1, P, 0, 0, 2); RC_FENCE;
 #pragma unroll
     for (int r = 0; r < FN0; ++r) {
-      if constexpr (MODE != 2) read_b(Q, 0, Q, 2 * r, 2 * r + 2);
+      if constexpr (STAGE != 2) read_b(Q, 0, Q, 2 * r, 2 * r + 2);
       RC_FENCE; multiply(1, P, 0, 2 + 4 * r, r + 1 == FN0 ? M10 : 6 + 4 * r); RC_FENCE;
     }
   };
