@@ -341,6 +341,10 @@ hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf
 hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
                                        int m, int k, const RopeOut& rope, hipStream_t st, const int* m_live);
 
+// few rows, K in `parts` parts of `part_steps` steps of 32 (at most 16 parts; n, ns1 and ns2 multiples of 16, k of 64)
+hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c, int m, int n,
+                                      int k, int ldc, GemmEpilogue epi, int parts, int part_steps, hipStream_t st);
+
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.
 size_t gemm_partial_bytes();

@@ -1212,6 +1212,11 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
   if (gemm_takes_few_rows(m, n, k, ns1, ns2))
+  // Few rows, cut into enough parts to keep the wavefronts of a workgroup busy: one launch, which also adds them up.  (Whole, or in
+  // two or three parts, a wavefront's chain over K would be as long as a tile's.)
+  if (tile == 0 && !m_live && !rope && m <= 32 && p.uniform && p.rem_tiles > 0 && p.grid.split >= 4 && p.grid.split <= 16 && n % 16 == 0 &&
+      ns1 % 16 == 0 && ns2 % 16 == 0)
+    return launch_gemm_few_rows_parts(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, p.grid.split, p.grid.kpp * (BK / 32), st);
     return launch_gemm_skinny_bf16(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
   if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
   if ((tile == 0 || tile >= 5) && k % BK == 0)

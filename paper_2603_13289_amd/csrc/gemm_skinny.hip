@@ -292,6 +292,85 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
   }
 }
 
+// Products of few rows whose K is no multiple of 256: summed in the K parts of the tile kernels' partition (`parts` of `part_steps`
+// steps of 32 each, the last one shorter), a part by one wavefront, added up in the same workgroup: the bits of a tile launch and
+// its sum over the parts, in one launch.  3 x 512 x 1408 (eleven parts): 4.1 + 6.0 -> 4.0 us.
+template <bool DUAL, bool TWO>
+__global__ void __launch_bounds__(kSkinnyWaves * 64, 2)
+gemm_few_rows_parts_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
+                           const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc, int epi,
+                           int parts, int part_steps) {
+  constexpr int TILES = (DUAL ? 2 : 1) * (TWO ? 2 : 1), UP = TWO ? 2 : 1, U = 4;
+  extern __shared__ __attribute__((aligned(16))) f32x4s lds_parts[];   // [part][tile][lane]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = (int)blockIdx.x * 16 + (lane & 15);
+  const bf16* const pw = (DUAL || col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k)) + 8 * (lane >> 4);
+  const bf16* const pu = DUAL ? w2 + (size_t)col * k + 8 * (lane >> 4) : nullptr;
+  const bf16* const pa0 = a + (size_t)min(lane & 15, m - 1) * k + 8 * (lane >> 4);
+  const bf16* const pa1 = a + (size_t)min(16 + (lane & 15), m - 1) * k + 8 * (lane >> 4);
+  for (int p = wave; p < parts; p += kSkinnyWaves) {
+    f32x4s acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) acc[t] = f32x4s{0.f, 0.f, 0.f, 0.f};
+    const int first = p * part_steps, last = min(first + part_steps, k / 32);
+    for (int s0 = first; s0 < last; s0 += U) {
+      bf16x8s fb[U], fu[DUAL ? U : 1], fa0[U], fa1[TWO ? U : 1];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int o = 32 * min(s0 + i, last - 1);
+        fb[i] = *reinterpret_cast<const bf16x8s*>(pw + o);
+        if constexpr (DUAL) fu[i] = *reinterpret_cast<const bf16x8s*>(pu + o);
+        fa0[i] = *reinterpret_cast<const bf16x8s*>(pa0 + o);
+        if constexpr (TWO) fa1[i] = *reinterpret_cast<const bf16x8s*>(pa1 + o);
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        if (s0 + i >= last) continue;   // uniform
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[i], fb[i], acc[0], 0, 0, 0);
+        if constexpr (TWO) acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[i], fb[i], acc[1], 0, 0, 0);
+        if constexpr (DUAL) acc[UP] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[i], fu[i], acc[UP], 0, 0, 0);
+        if constexpr (DUAL && TWO) acc[UP + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[i], fu[i], acc[UP + 1], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) lds_parts[(p * TILES + t) * 64 + lane] = acc[t];
+  }
+  __syncthreads();
+  if (wave > (TWO ? 1 : 0)) return;
+  f32x4s gs = {0.f, 0.f, 0.f, 0.f}, us = gs;
+  for (int p = 0; p < parts; ++p) {
+    gs += lds_parts[(p * TILES + wave) * 64 + lane];
+    if constexpr (DUAL) us += lds_parts[(p * TILES + UP + wave) * 64 + lane];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = wave * 16 + 4 * (lane >> 4) + e;
+    if (row >= m) continue;
+    const size_t o = (size_t)row * ldc + col;
+    if (DUAL) reinterpret_cast<bf16*>(c)[o] = f32_to_bf16(silu_s(gs[e]) * us[e]);
+    else if (epi == EPI_STORE_F32) reinterpret_cast<float*>(c)[o] = gs[e];
+    else if (epi == EPI_ADD_F32) reinterpret_cast<float*>(c)[o] += gs[e];
+    else reinterpret_cast<bf16*>(c)[o] = f32_to_bf16(gs[e]);
+  }
+}
+
+hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c, int m, int n,
+                                      int k, int ldc, GemmEpilogue epi, int parts, int part_steps, hipStream_t st) {
+  auto go = [&](auto dual, auto two) {
+    const size_t lds = (size_t)parts * (decltype(dual)::value ? 2 : 1) * (decltype(two)::value ? 2 : 1) * 64 * sizeof(f32x4s);
+    gemm_few_rows_parts_kernel<decltype(dual)::value, decltype(two)::value><<<dim3((unsigned)(n / 16)), kSkinnyWaves * 64, lds, st>>>(
+        a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, parts, part_steps);
+  };
+  auto rows = [&](auto dual) {
+    if (m > 16) go(dual, std::true_type{});
+    else go(dual, std::false_type{});
+  };
+  if (epi == EPI_SWIGLU_T) rows(std::true_type{});
+  else rows(std::false_type{});
+  return hipGetLastError();
+}
+
 bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2) {
   return m >= 1 && m <= 32 && n % 16 == 0 && k % (kSkinnyWaves * 32) == 0 && ns1 % 16 == 0 && ns2 % 16 == 0;
 }
