@@ -342,11 +342,12 @@ template <typename T>
 hipError_t attention_dispatch(const T* q, const int* row_pos, const int* row_req, const ReqTable* table,
                               int total_rows, int total_tiles, const T* k_pool, const T* v_pool, KvGeom g,
                               int n_q_heads, T* out, AttnSplit sp, float* part, hipStream_t st, float* scores,
-                              int scores_len, int merge_rows, bool one_row);
+                              int scores_len, int merge_rows, bool one_row, const InfluencePtrs* inf, bool* inf_done);
 template <>
 hipError_t attention_dispatch<float>(const float* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                      int total_rows, int total_tiles, const float* k_pool, const float* v_pool,
-                                     KvGeom g, int n_q_heads, float* out, AttnSplit, float*, hipStream_t st, float*, int, int, bool) {
+                                     KvGeom g, int n_q_heads, float* out, AttnSplit, float*, hipStream_t st, float*, int, int, bool,
+                                     const InfluencePtrs*, bool*) {
   return launch_attention<float>(q, row_pos, row_req, table, 0, total_rows, total_tiles, k_pool, v_pool, g,
                                  n_q_heads, out, st);
 }
@@ -354,9 +355,10 @@ template <>
 hipError_t attention_dispatch<bf16>(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                     int total_rows, int total_tiles, const bf16* k_pool, const bf16* v_pool,
                                     KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part, hipStream_t st,
-                                    float* scores, int scores_len, int merge_rows, bool one_row) {
+                                    float* scores, int scores_len, int merge_rows, bool one_row, const InfluencePtrs* inf,
+                                    bool* inf_done) {
   return launch_attention_bf16(q, row_pos, row_req, table, 0, total_rows, total_tiles, k_pool, v_pool, g, n_q_heads,
-                               out, sp, part, st, scores, scores_len, merge_rows, one_row);
+                               out, sp, part, st, scores, scores_len, merge_rows, one_row, inf, inf_done);
 }
 
 template <typename T>
@@ -573,9 +575,11 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
                                                          w.inf_scratch, st));
     RC_LAUNCH(PC_ATTENTION, attention_dispatch<T>((const T*)w.q, w.row_pos, w.row_req, w.tables + cur, rows,
                                  tabs[cur].total_items, (const T*)job.dst->k_pool[l],
+    bool inf_done = false;
                                  (const T*)job.dst->v_pool[l], gd, d.n_q_heads, (T*)w.o, splits[cur], w.attn_part, st,
-                                 scores_from_attention ? w.inf_scratch : nullptr, job.score_len(), tabs[cur].total_merge_rows, one_row[cur]));
-    if (job.any_inf)
+                                 scores_from_attention ? w.inf_scratch : nullptr, job.score_len(), tabs[cur].total_merge_rows, one_row[cur],
+                                 job.any_inf ? &job.inf : nullptr, &inf_done));
+    if (job.any_inf && !inf_done)
       RC_LAUNCH(PC_INFLUENCE, launch_influence_finish(w.row_pos, w.row_req, rows, d.n_q_heads, job.score_len(), job.inf,
                                                       w.inf_scratch, scores_from_attention, st));
     rest.tiles = 0;

@@ -468,11 +468,9 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
 // Merge of the KV chunks of one (row, head): one wavefront each, two head-dim elements per lane.
 // Only rows of split tiles take part; chunk c holds keys for a row iff its first key position is <=
 // the row's position.
-__global__ void __launch_bounds__(256)
-attn_merge_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_req, const ReqTable* __restrict__ table,
-                  int total_rows, int n_q_heads, AttnSplit sp, const float* __restrict__ part_o,
-                  const float2* __restrict__ part_ml, bf16* __restrict__ out, float2* __restrict__ score_ml) {
-  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void merge_item(int item, const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows,
+                                           int n_q_heads, const AttnSplit& sp, const float* __restrict__ part_o,
+                                           const float2* __restrict__ part_ml, bf16* __restrict__ out, float2* __restrict__ score_ml) {
   const int lane = threadIdx.x & 63;
   int r, head, split_tile, ql, part_base = 0, tile_last_row;
   if (table) {
@@ -544,6 +542,97 @@ attn_merge_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_r
   *reinterpret_cast<uint32_t*>(out + ((size_t)r * n_q_heads + head) * DH + 2 * lane) = pk;
 }
 
+__global__ void __launch_bounds__(256)
+attn_merge_kernel(const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows, int n_q_heads, AttnSplit sp,
+                  const float* __restrict__ part_o, const float2* __restrict__ part_ml, bf16* __restrict__ out,
+                  float2* __restrict__ score_ml) {
+  merge_item((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, score_ml);
+}
+
+// A decoding step with influence sums, its KV ranges split: workgroups below `merge_wgs` merge, the others add the rows' weights to
+// the influence vectors, 64 keys each (influence_add_kernel), and for that work the heads' merged exponents and sums out for
+// themselves.  Both hang on the same partial results, so one launch does for two: 6.0 + 4.6 -> 6.8 us (32 heads x 5k keys).
+// Four wavefronts share the heads; the weights of a key are added up head by head in ascending order.
+static constexpr int kInfMaxHeads = 64;   // of a model that takes this path (LDS)
+__global__ void __launch_bounds__(256)
+attn_merge_influence_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_req, const ReqTable* __restrict__ table,
+                            int total_rows, int n_q_heads, AttnSplit sp, const float* __restrict__ part_o,
+                            const float2* __restrict__ part_ml, bf16* __restrict__ out, const float* __restrict__ scores, int scores_len,
+                            const float2* __restrict__ score_ml, InfluencePtrs inf, int merge_wgs, int wgs_per_row) {
+  __shared__ float weight[kInfMaxHeads][64];
+  __shared__ float2 pair[kInfMaxHeads];
+  if ((int)blockIdx.x < merge_wgs) {
+    merge_item((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, nullptr);
+    return;
+  }
+  const int row = ((int)blockIdx.x - merge_wgs) / wgs_per_row;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = (((int)blockIdx.x - merge_wgs) % wgs_per_row) * 64 + lane;
+  const int pos = row_pos[row];
+  if (j - lane > pos) return;   // uniform
+  const int req = row_req[row] & kRowReqMask;
+  float* const dst = inf.s_inf[req];
+  if (dst == nullptr) return;   // uniform
+  const ReqDev& rq = table->r[req];
+  const bool is_split = rq.long_tile_start == 0 && pos / BKV + 1 > sp.long_thr;
+  const int nc = is_split ? min(sp.n_chunks, pos / (sp.chunk_tiles * BKV) + 1) : 0;
+  const size_t slot0 = (size_t)rq.part_base * n_q_heads * BQ, cstride = (size_t)n_q_heads * BQ;
+  const float old = wave == 0 && j <= pos ? dst[j] : 0.f;
+  const float* s = scores + (size_t)row * n_q_heads * scores_len + min(j, pos);
+  float v[kInfMaxHeads / 4];
+#pragma unroll
+  for (int i = 0; i < kInfMaxHeads / 4; ++i) v[i] = s[(size_t)min(wave + 4 * i, n_q_heads - 1) * scores_len];
+  // Merged pair of a head: eight lanes, lane c & 7 reads chunk c, eight of its chunks at a time; the sum runs in chunk order.
+  for (int h0 = 0; h0 < n_q_heads; h0 += 32) {
+    const int h = h0 + (tid >> 3), cl = tid & 7;
+    float m = -INFINITY, l = 0.f;
+    if (is_split) {   // uniform
+      const float2* ml = part_ml + slot0 + (size_t)min(h, n_q_heads - 1) * BQ;
+      float2 t[8];
+      auto load = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = ml[min(c0 + 8 * i + cl, nc - 1) * cstride];
+      };
+      for (int c0 = 0; c0 < nc; c0 += 64) {
+        load(c0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = fmaxf(m, t[i].x);   // past the last chunk: the last one again
+      }
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+      for (int c0 = 0; c0 < nc; c0 += 64) {
+        if (nc > 64) load(c0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (c0 + 8 * i >= nc) continue;   // uniform
+          const float w = t[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t[i].x - m);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const float tk = __shfl(t[i].y, (lane & 56) + k, 64), wk = __shfl(w, (lane & 56) + k, 64);
+            if (c0 + 8 * i + k < nc) l = __builtin_fmaf(tk, wk, l);
+          }
+        }
+      }
+    } else if (h < n_q_heads) {   // one workgroup had the whole range and left the pair
+      const float2 p = score_ml[(size_t)row * n_q_heads + h];
+      m = p.x;
+      l = p.y;
+    }
+    if (cl == 0 && h < n_q_heads) pair[h] = make_float2(m, l);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kInfMaxHeads / 4; ++i) {
+    const int h = wave + 4 * i;
+    if (h < n_q_heads) weight[h][lane] = __builtin_amdgcn_exp2f(v[i] * 1.4426950408889634f - pair[h].x) / pair[h].y;
+  }
+  __syncthreads();
+  if (wave > 0 || j > pos) return;
+  float acc = 0.f;
+  for (int h = 0; h < n_q_heads; ++h) acc += weight[h][lane];
+  dst[j] = old + acc;
+}
+
 static int g_force_chunk_tiles = 0;   // 0: by shape; > 0: this many KV tiles per chunk
 void set_attention_chunk_tiles(int t) { g_force_chunk_tiles = t; }
 int attention_forced_chunk_tiles() { return g_force_chunk_tiles; }
@@ -584,7 +673,8 @@ static hipError_t launch_g(const bf16* q, const int* row_pos, const ReqTable* ta
 hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* row_req, const ReqTable* table,
                                  int fixed_seq, int total_rows, int total_tiles, const bf16* k_pool,
                                  const bf16* v_pool, KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part,
-                                 hipStream_t st, float* scores, int scores_len, int merge_rows, bool one_row) {
+                                 hipStream_t st, float* scores, int scores_len, int merge_rows, bool one_row,
+                                 const InfluencePtrs* inf, bool* inf_done) {
   if (total_rows <= 0) return hipSuccess;
   const int G = n_q_heads / g.n_kv_heads;
   if (!part || sp.total_slots <= 0) sp = attention_no_split();
@@ -614,8 +704,17 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
   // with a table, merge_rows (the rows of the tiles that may be split, or an upper bound) sizes the merge grid
   const int items = (table ? merge_rows : total_rows) * n_q_heads;
   if (items <= 0) return hipSuccess;
-  attn_merge_kernel<<<(items + 3) / 4, 256, 0, st>>>(row_pos, row_req, table, total_rows, n_q_heads, sp, part, part_ml,
-                                                     out, scores ? influence_pairs(scores, total_rows, n_q_heads, scores_len) : nullptr);
+  const int merge_wgs = (items + 3) / 4;
+  if (inf && scores && table && one_row && G <= 8 && n_q_heads <= kInfMaxHeads) {
+    const int wgs_per_row = (scores_len + 63) / 64;
+    attn_merge_influence_kernel<<<merge_wgs + total_rows * wgs_per_row, 256, 0, st>>>(
+        row_pos, row_req, table, total_rows, n_q_heads, sp, part, part_ml, out, scores, scores_len,
+        influence_pairs(scores, total_rows, n_q_heads, scores_len), *inf, merge_wgs, wgs_per_row);
+    *inf_done = true;
+    return hipGetLastError();
+  }
+  attn_merge_kernel<<<merge_wgs, 256, 0, st>>>(row_pos, table, total_rows, n_q_heads, sp, part, part_ml, out,
+                                               scores ? influence_pairs(scores, total_rows, n_q_heads, scores_len) : nullptr);
   return hipGetLastError();
 }
 

@@ -386,6 +386,9 @@ hipError_t launch_attention_simt(const bf16* q, const int* row_pos, const int* r
                                  int n_q_heads, bf16* out, hipStream_t st);
 int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads);  // query rows per attention tile
 
+// per-request influence vectors (Eq. 6), passed to the accumulation kernel by value; nullptr: not tracked
+struct InfluencePtrs { float* s_inf[RC_MAX_REQ]; };
+
 // bf16 attention with an optional split of every query tile's KV range into chunks (partial results
 // in `part`, merged by a second kernel).  part == nullptr: no split.
 // With a table, total_tiles is the number of work items of the launch (ReqTable::total_items as assign_split_slots
@@ -393,7 +396,8 @@ int attention_tile_rows(int dtype, int n_q_heads, int n_kv_heads);  // query row
 // A query tile whose KV range spans more than long_thr tiles is cut into chunks of chunk_tiles tiles;
 // n_chunks is the grid's chunk dimension (1: no split at all), total_slots the (tile, chunk) slots of
 // partial results the plan may touch.
-// one_row (with a table whose counts the host knows): no request has more than one live row.
+// one_row (with a table whose counts the host knows): no request has more than one live row.  inf: the influence vectors that the
+// scores are for; *inf_done is set where the merge has added them up as well.
 struct AttnSplit { int n_chunks, chunk_tiles, long_thr, total_slots; };
 inline AttnSplit attention_no_split() { AttnSplit sp = {1, 1 << 24, 1 << 24, 0}; return sp; }
 int attention_forced_chunk_tiles();
@@ -403,7 +407,7 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
                                  int fixed_seq, int total_rows, int total_tiles, const bf16* k_pool,
                                  const bf16* v_pool, KvGeom g, int n_q_heads, bf16* out, AttnSplit sp, float* part,
                                  hipStream_t st, float* scores = nullptr, int scores_len = 0, int merge_rows = 0,
-                                 bool one_row = false);
+                                 bool one_row = false, const InfluencePtrs* inf = nullptr, bool* inf_done = nullptr);
 
 template <typename T>
 hipError_t launch_vdev_score(const T* v_fresh, int fresh_row_stride, const T* v_pool, KvGeom g,
@@ -426,8 +430,6 @@ hipError_t launch_finalize_tables(ReqTable* tabs, const int* sel_cnt, int tile_r
                                   int chunks_c, int cap_c, int thr_d, int chunks_d, int cap_d, hipStream_t st);
 hipError_t launch_threshold_select(const float* score, int n, float tau, int* idx_out, int* count_out,
                                    hipStream_t st);
-// per-request influence vectors (Eq. 6), passed to the accumulation kernel by value; nullptr: not tracked
-struct InfluencePtrs { float* s_inf[RC_MAX_REQ]; };
 size_t influence_scratch_floats(int n_rows, int n_q_heads, int max_len);
 // scratch holds the scores [rows][Hq][max_len] (q.k / sqrt(dh)) followed by one (reference exponent in log2 units,
 // sum of exp2(score * log2(e) - reference)) pair per (row, head).  The scores are written by launch_influence_scores

@@ -76,3 +76,37 @@ def test_row_alone_and_with_another(group, page, chunk, ramp, scores):
                     assert torch.equal(one, two), (p, l, which)
         if scores:   # weights of every head and layer add up to one
             assert abs(float(s_inf[b].double().sum()) - LAYERS * sh.n_q_heads) <= 1e-4 * LAYERS * sh.n_q_heads
+
+
+@pytest.mark.parametrize("group,chunk", [(4, 1), (4, 3), (8, 2), (1, 4)])
+def test_influence_added_by_the_merge(group, chunk):
+    """One model layer; KV ranges in one piece (a launch of its own adds the weights up) and in chunks (the merge does)."""
+    from paper_2603_13289_amd import binding as rc
+    g = torch.Generator(device="cuda")
+    g.manual_seed(group + chunk)
+    sh, model = _model(rc, g, group)
+    n = len(POSITIONS)
+    table = torch.randperm(n * 64, generator=g, device="cuda").to(torch.int32).view(n, 64).contiguous()
+    k, v = (torch.empty((LAYERS, n * 64, NKV, 16, DH), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    x = torch.empty((n, D), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    got = []
+    for c in (1000, chunk):
+        kk, vv = k.clone(), v.clone()
+        cache = rc.PagedKV.from_pools(list(kk.unbind(0)), list(vv.unbind(0)), table, rc.RC_BF16)
+        s_inf = [torch.full((p + 1,), 0.5, dtype=torch.float32, device="cuda") for p in POSITIONS]
+        # every third request keeps no influence vector
+        reqs = [rc.DecodeReq(x[b], p, b, None, s_inf[b] if b % 3 else None) for b, p in enumerate(POSITIONS)]
+        rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, c)
+        try:
+            rc.rc_decode_step(model, reqs, cache, torch.zeros((n, 256), dtype=torch.float32, device="cuda"),
+                              rc.alloc_workspace(rc.rc_decode_workspace_bytes(model, reqs)))
+        finally:
+            rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, 0)
+        torch.cuda.synchronize()
+        got.append(s_inf)
+    for b in range(n):
+        if b % 3 == 0:
+            assert float((got[1][b] - 0.5).abs().max()) == 0
+            continue
+        # the layers behind the first see attention outputs rounded to bf16 from other partial sums
+        assert rel_err(to_np(got[1][b]), to_np(got[0][b])) <= 1e-2, POSITIONS[b]
