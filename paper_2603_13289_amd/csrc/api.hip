@@ -424,7 +424,9 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
   int hbuf = 0;
   // Row counts of the phase: exact on the host, or (threshold selector, from the sparse phase on) an upper bound
   // that sizes the grids while the kernels read the live counts from the device table.
-  auto live = [&](int ph) -> const int* { return on_device[ph] ? &(w.tables + ph)->total_rows : nullptr; };
+  // (Behind the sparse phase no row of a segment but its last one is live, whatever was selected: the host's count is exact.)
+  auto counted = [&](int ph) { return on_device[ph] && ph != PH_D; };
+  auto live = [&](int ph) -> const int* { return counted(ph) ? &(w.tables + ph)->total_rows : nullptr; };
   int expected_rows[PH_COUNT] = {0, 0, 0, 0};   // of a phase whose count is on the device: what the GEMM tiles are chosen for
   auto enter_phase = [&](Phase ph) -> rc_status {
     if (!on_device[ph]) {
@@ -573,9 +575,9 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       RC_LAUNCH(PC_INFLUENCE, launch_influence_scores<T>((const T*)w.q, w.row_pos, w.row_req, w.tables + cur, rows,
                                                          (const T*)job.dst->k_pool[l], gd, d.n_q_heads, job.score_len(),
                                                          w.inf_scratch, st));
+    bool inf_done = false;
     RC_LAUNCH(PC_ATTENTION, attention_dispatch<T>((const T*)w.q, w.row_pos, w.row_req, w.tables + cur, rows,
                                  tabs[cur].total_items, (const T*)job.dst->k_pool[l],
-    bool inf_done = false;
                                  (const T*)job.dst->v_pool[l], gd, d.n_q_heads, (T*)w.o, splits[cur], w.attn_part, st,
                                  scores_from_attention ? w.inf_scratch : nullptr, job.score_len(), tabs[cur].total_merge_rows, one_row[cur],
                                  job.any_inf ? &job.inf : nullptr, &inf_done));
@@ -612,7 +614,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     return RC_OK;
   } else {
     // the host knows where the last rows are unless they are rows of a phase counted on the device
-    if (!on_device[cur] && gemm_takes_few_rows(n_req, d.vocab, D, d.vocab, d.vocab) && gemm_skinny_norm_fits(n_req, D)) {
+    if (!counted(cur) && gemm_takes_few_rows(n_req, d.vocab, D, d.vocab, d.vocab) && gemm_skinny_norm_fits(n_req, D)) {
       NormIn norm = {w.h[hbuf], (const bf16*)job.m->g_final, d.rms_eps, {0, 0, 0, 0}};
       for (int b = 0; b < n_req; ++b) norm.row[b] = tabs[cur].r[b].n_rows > 0 ? tabs[cur].r[b].row_base + tabs[cur].r[b].n_rows - 1 : -1;
       RC_LAUNCH(PC_GEMM_LM_HEAD, launch_gemm_skinny_normed(norm, (const bf16*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, EPI_STORE_F32, st, nullptr));
