@@ -538,15 +538,16 @@ __device__ __forceinline__ void gemm_tile_body(const bf16* __restrict__ a, const
 }
 
 // The same on the pipelined main loop of gemm_pipe.h; partial sums in the layout of gemm_tile_body.
-template <typename T, int MODE>
+template <typename T, int MODE, bool LANE_ID = false>
 __device__ __forceinline__ void gemm_pipe_body(const bf16* __restrict__ a, const bf16* __restrict__ w,
                                                const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
                                                void* __restrict__ c, int m, int n, int k, int ldc, int epi, int m0, int n0,
                                                int k_begin, int k_end, int part_slot, float* __restrict__ partial, const RopeOut& rope) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   f32x4 acc[T::FM][T::FN];
-  gemm_pipe_loop<T, MODE>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
-  const int tid = threadIdx.x, lane = tid & 63;
+  gemm_pipe_loop<T, MODE, LANE_ID>(a, w, w2, w3, ns1, ns2, m, n, k, m0, n0, k_begin, k_end, lds, acc);
+  const int tid = threadIdx.x;
+  const int lane = LANE_ID ? __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
   if (part_slot >= 0) {
@@ -562,8 +563,8 @@ __device__ __forceinline__ void gemm_pipe_body(const bf16* __restrict__ a, const
 // accumulators in `partial`; gemm_fixup_kernel adds the parts in a fixed order and applies the epilogue.
 //
 // Thin tiles: when the last tile row has at most 64 live rows (a prompt whose live rows are a multiple of the tile
-// height plus a few: the last reused token, a short suffix), its n_thin tiles are multiplied by a 64-row body whose
-// eight wavefronts sit side by side, which costs about a third of a full tile; `order` then describes the tile rows
+// height plus a few: the last reused token, a short suffix), its n_thin tiles are multiplied by a 64 x 256 body (the tile of
+// code 13), which costs about a third of a full tile; `order` then describes the tile rows
 // above it only.  The thin tiles are always whole-K tiles and are dealt out evenly over the XCDs' queues, at
 // the tail of each, where they fill the last round.  (A 128-row body for up to 128 live rows was measured
 // as well: no gain.)
@@ -656,9 +657,10 @@ __device__ __forceinline__ void gemm_dl_work(const bf16* __restrict__ a, const b
     if (bw.kind == 0) return;
   }
   if constexpr (THIN) {
+    static_assert(BN == 256 && T::NT == 512, "the thin body covers a tile's columns");
     if (bw.kind == 2) {
-      gemm_tile_body<64, BN, 1, T::NT / 64, MODE>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
-                                                         bw.tile_n * BN_OUT, 0, k, -1, partial, rope);
+      gemm_pipe_body<PipeTile<1, 8, 4, 0, 1, 1>, MODE, true>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, bw.tile_m * BM,
+                                                       bw.tile_n * BN_OUT, 0, k, -1, partial, rope);
       return;
     }
   }
@@ -994,6 +996,33 @@ static GridPlan uniform_grid_plan(int m, int tiles_n, int bm, int ksteps, int sp
   return g;
 }
 
+// 256x256 tiles, all whole, with a ragged last tile row of at most kThinRows rows on the thin body, whose tiles come last and fill
+// what the last round of the others leaves idle: 1025 x 28672 x 4096 232 us on 192x256 tiles, 203 like this (233 with the thin body
+// on the older loop).
+static GridPlan thin_grid_plan(int m, int tiles_n, int ksteps, int* n_blocks) {
+  GridPlan g = {};
+  const int tiles_m = (m + 255) / 256;
+  g.order = make_tile_order(tiles_m - 1, tiles_n);
+  g.full_tiles = tiles_m * tiles_n;
+  g.per_xcd = (g.full_tiles + XCDS - 1) / XCDS;
+  g.n_full_wgs = g.per_xcd * XCDS;
+  g.split = 1;
+  g.kpp = ksteps;
+  g.n_thin = tiles_n;
+  *n_blocks = g.n_full_wgs;
+  if (!g_xcd_remap) g.per_xcd = 0;
+  return g;
+}
+static float thin_cost(int m, int tiles_n, int ksteps, int n_cus) {
+  const TileInfo& t = kTiles[0];
+  const int tiles_m = (m + 255) / 256, normal = (tiles_m - 1) * tiles_n;
+  if (!g_thin_tiles || m - (tiles_m - 1) * 256 > kThinRows || normal < n_cus) return 1e30f;   // at least one full round of the others
+  const int rounds = normal / n_cus, last = normal % n_cus, idle = n_cus - last;
+  const float full = ksteps * step_us(t, n_cus, n_cus, tiles_m) + t.fixed;
+  const float others = rounds * full + (last > 0 ? ksteps * step_us(t, last, n_cus, tiles_m) + t.fixed : 0.f);
+  return std::max(others, rounds * full + (float)((tiles_n + idle - 1) / idle) * kThinCost * full);
+}
+
 template <typename T, bool THIN>
 static hipError_t launch_dl(const GridPlan& plan, int n_blocks, const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1,
                             int ns2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
@@ -1117,6 +1146,11 @@ static DlPlan plan_dl(int tile, int m, int n, int k, bool dual, int cus, bool wi
     }
     for (const TileInfo& t : kTiles)
       if (t.code == p.type) p.grid = uniform_grid_plan(m, cols(t.bn), t.bm, ksteps, split, kpp, &p.n_blocks, &p.rem_tiles);
+    if (tile == 0 && split == 1 && !device_rows && thin_cost(m, cols(256), ksteps, cus) < best) {
+      p.type = 5;
+      p.grid = thin_grid_plan(m, cols(256), ksteps, &p.n_blocks);
+      p.rem_tiles = 0;
+    }
   } else if (part == 6) {
     p.grid = uniform_grid_plan(m, cols(128), 128, ksteps, 1, ksteps, &p.n_blocks, &p.rem_tiles);
   }
@@ -1178,6 +1212,11 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
                               void* c, int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
                               const int* m_live, int m_expected, GemmRest* rest, const RopeOut* rope = nullptr) {
   const DlPlan p = plan_dl(tile, m, n, k, epi == EPI_SWIGLU_T, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
+  // Few rows, cut into enough parts to keep the wavefronts of a workgroup busy: one launch, which also adds them up.  (Whole, or in
+  // two or three parts, a wavefront's chain over K would be as long as a tile's.)
+  if (tile == 0 && !m_live && !rope && m <= 32 && p.uniform && p.rem_tiles > 0 && p.grid.split >= 4 && p.grid.split <= 16 && n % 16 == 0 &&
+      ns1 % 16 == 0 && ns2 % 16 == 0)
+    return launch_gemm_few_rows_parts(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, p.grid.split, p.grid.kpp * (BK / 32), st);
   hipError_t e = hipErrorInvalidValue;
 #define RC_DL(CODE, THIN, ...) \
   case CODE: e = launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live, rope); break
@@ -1212,11 +1251,6 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
   if (gemm_takes_few_rows(m, n, k, ns1, ns2))
-  // Few rows, cut into enough parts to keep the wavefronts of a workgroup busy: one launch, which also adds them up.  (Whole, or in
-  // two or three parts, a wavefront's chain over K would be as long as a tile's.)
-  if (tile == 0 && !m_live && !rope && m <= 32 && p.uniform && p.rem_tiles > 0 && p.grid.split >= 4 && p.grid.split <= 16 && n % 16 == 0 &&
-      ns1 % 16 == 0 && ns2 % 16 == 0)
-    return launch_gemm_few_rows_parts(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, p.grid.split, p.grid.kpp * (BK / 32), st);
     return launch_gemm_skinny_bf16(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
   if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
   if ((tile == 0 || tile >= 5) && k % BK == 0)

@@ -55,7 +55,9 @@ __device__ __host__ inline int rope_column(int pair, int second) { return (pair 
 // which there are n; weight rows of the output columns below ns1 come from w, below ns2 from w2, the rest from w3
 // (boundaries are multiples of 8).
 // acc (i, j): rows wm * WTM + 16 i + lane % 16, columns 16 j + 4 (lane / 16) + 0..3 of the wavefront's sub-tile.
-template <typename T, int MODE>
+// LANE_ID: the lane number is worked out in another way, so that a kernel with two such loops shares no value between them that
+// would stay in registers.
+template <typename T, int MODE, bool LANE_ID = false>
 __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const bf16* __restrict__ w,
                                                const bf16* __restrict__ w2, const bf16* __restrict__ w3, int ns1, int ns2,
                                                int m, int n, int k, int m0, int n0, int k_begin, int k_end,
@@ -63,7 +65,8 @@ __device__ __forceinline__ void gemm_pipe_loop(const bf16* __restrict__ a, const
   static_assert(MODE == kPlain || T::FN % 2 == 0, "blocks of pairs");
   constexpr int FM0 = T::FM0, FM1 = T::FM1, FN0 = T::FN0, FN1 = T::FN1, FMX = FM0 > FM1 ? FM0 : FM1, FNX = FN0 > FN1 ? FN0 : FN1;
   constexpr int LAX = T::LA0 > T::LA1 ? T::LA0 : T::LA1, LBX = T::LB0 > T::LB1 ? T::LB0 : T::LB1;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
+  const int lane = LANE_ID ? __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
   const int lrow = lane >> 3, lslot = lane & 7;

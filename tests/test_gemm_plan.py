@@ -72,3 +72,12 @@ def test_bad_arguments():
     assert rc.rc_gemm_plan_check(0, 64, 64, False, 5)[0] == -1
     assert rc.rc_gemm_plan_check(64, 64, 100, False, 5)[0] == -1
     assert rc.rc_gemm_plan_check(64, 64, 64, False, 4)[0] == -1
+
+
+def test_coverage_of_the_schedules_the_library_chooses():
+    """Tile type by shape, among them a thin last tile row behind whole tiles."""
+    for n, k, swiglu in ((28672 // 2, 4096, True), (16384, 128, False), (4096, 14336, False), (6144, 4096, False), (5120, 27648, False)):
+        for m in list(range(33, 700, 31)) + [768, 769, 1024, 1025, 1088, 1089, 1639, 2050, 2112, 2113, 5121]:
+            for ws in (True, False):
+                err, nb = rc.rc_gemm_plan_check(m, n, k, swiglu, 0, 256, ws)
+                assert err == 0 and nb > 0, (m, n, k, swiglu, ws)
