@@ -683,10 +683,10 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
     const unsigned grid = (unsigned)total_tiles * (unsigned)g.n_kv_heads;
     float2* part_ml = reinterpret_cast<float2*>(part + (size_t)sp.total_slots * n_q_heads * BQ * PROW);
     if (scores)
-      attn_decode_kernel<true><<<grid, 128, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, scores,
+      attn_decode_kernel<true><<<grid, 256, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, scores,
                                                      scores_len, influence_pairs(scores, total_rows, n_q_heads, scores_len));
     else
-      attn_decode_kernel<false><<<grid, 128, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, nullptr, 0, nullptr);
+      attn_decode_kernel<false><<<grid, 256, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, nullptr, 0, nullptr);
     e = hipGetLastError();
   } else switch (G) {
 #define RC_ATTN_CASE(GG) \
