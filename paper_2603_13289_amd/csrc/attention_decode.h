@@ -34,9 +34,7 @@ attn_decode_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, 
   const int kvh = (int)blockIdx.x % g.n_kv_heads;
   const int item = (int)blockIdx.x / g.n_kv_heads;
   if (item >= table->total_items) return;
-  int b = table->n_req - 1;                 // item_base is 0 for the last request and grows towards the first
-  while (b > 0 && item >= table->r[b - 1].item_base) --b;
-  const ReqDev& rq = table->r[b];
+  const ReqDev& rq = table->r[request_of_item(table, item)];
   if (rq.n_rows <= 0) return;
   const int row = rq.row_base, seq = rq.dst_seq, part_base = rq.part_base;
   const int chunk = item - rq.item_base;

@@ -52,6 +52,22 @@ __device__ inline float pair_max32(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Request of a work item / of a merge row: the bases fall (rise) with the request, so the lanes compare one request each and the
+// wavefront counts, instead of a chain of table loads from request to request (16 decoding requests: merge 8.8 -> 5.3 us, attention 81.5 -> 80).
+static_assert(RC_MAX_REQ <= 64, "a lane per request");
+__device__ __forceinline__ int request_of_item(const ReqTable* table, int item) {
+  const int n = table->n_req, lane = threadIdx.x & 63;
+  if (n == 1) return 0;
+  const unsigned long long at = __ballot(lane < n && item >= table->r[min(lane, n - 1)].item_base);
+  return __builtin_amdgcn_readfirstlane(__ffsll((long long)at) - 1);
+}
+__device__ __forceinline__ int request_of_merge_row(const ReqTable* table, int mr) {
+  const int n = table->n_req, lane = threadIdx.x & 63;
+  if (n == 1) return 0;
+  const unsigned long long at = __ballot(lane < n && mr >= table->r[min(lane, n - 1)].merge_base);
+  return __builtin_amdgcn_readfirstlane(__popcll(at) - 1);
+}
+
 // SCORES: additionally write every visible score q.k / sqrt(dh) of every valid row to
 // scores[(row * n_q_heads + head) * scores_len + key] (the decode-side influence accumulation reads them), and
 // the row's reference exponent and sum, score_ml[row * n_q_heads + head], unless the tile's KV range is split
@@ -91,9 +107,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     // tile and KV chunk), then the whole tiles, late ones first.  The host's counts may be upper bounds
     // (rows selected on the device): the table has the live ones.
     if (item >= table->total_items) return;
-    int b = table->n_req - 1;                              // item_base is 0 for the last request and grows towards the first
-    while (b > 0 && item >= table->r[b - 1].item_base) --b;
-    const ReqDev& rq = table->r[b];
+    const ReqDev& rq = table->r[request_of_item(table, item)];   // item_base is 0 for the last request and grows towards the first
     const int tiles = (rq.n_rows + BQ - 1) / BQ;
     const int start = min(rq.long_tile_start, tiles);
     const int j = item - rq.item_base;
@@ -478,9 +492,7 @@ __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row
     const int mr = item / n_q_heads;
     head = item - mr * n_q_heads;
     if (mr >= table->total_merge_rows) return;
-    int b = 0;
-    while (b + 1 < table->n_req && mr >= table->r[b + 1].merge_base) ++b;
-    const ReqDev& rq = table->r[b];
+    const ReqDev& rq = table->r[request_of_merge_row(table, mr)];
     const int local = min(rq.long_tile_start, 1 << 20) * BQ + (mr - rq.merge_base);     // row inside the request
     if (local >= rq.n_rows) return;
     r = rq.row_base + local;
