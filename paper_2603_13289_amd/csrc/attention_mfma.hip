@@ -479,18 +479,25 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
 
 #include "attention_decode.h"
 
-// Merge of the KV chunks of one (row, head): one wavefront each, two head-dim elements per lane.
-// Only rows of split tiles take part; chunk c holds keys for a row iff its first key position is <=
-// the row's position.
+// Merge of the KV chunks: a wavefront takes 2 PAIRS heads of a row, 32 lanes with four head-dim elements each per head.  Only rows of
+// split tiles take part; chunk c holds keys for a row iff its first key position is <= the row's position.
+// The bytes are few (1476 rows x 32 heads: 75 MB); what bounds it is a chain of dependent reads (table, positions, exponents,
+// outputs) per wavefront, so a wavefront has 16 rows of outputs under way behind one walk of that chain, requested before the
+// exponents are reduced: four heads by four chunks where rows are many, two by eight in a decoding step, where wavefronts are few and
+// chunks many.  One head per wavefront before: 1476 rows x 32 heads 31.9 -> 16.9 us, 1639 rows over 17k keys 47.9 -> 32.8, sixteen
+// decoding rows 5.3 -> 4.8; four heads by four chunks for the decoding rows as well: 5.6, and the launch below 6.7 -> 7.6 instead of 6.6.
+template <int PAIRS, int AHEAD>
 __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows,
                                            int n_q_heads, const AttnSplit& sp, const float* __restrict__ part_o,
                                            const float2* __restrict__ part_ml, bf16* __restrict__ out, float2* __restrict__ score_ml) {
-  const int lane = threadIdx.x & 63;
-  int r, head, split_tile, ql, part_base = 0, tile_last_row;
+  const int lane = threadIdx.x & 63, e = lane & 31;
+  const int groups = (n_q_heads + 2 * PAIRS - 1) / (2 * PAIRS);
+  item = __builtin_amdgcn_readfirstlane(item);
+  int r, split_tile, ql, part_base = 0, tile_last_row;
+  const int mr = item / groups;
+  const int head0 = (item - mr * groups) * (2 * PAIRS) + (lane >> 5);   // and head0 + 2
   if (table) {
     // items run over the rows of the tiles that may be split only (the late tiles of every request)
-    const int mr = item / n_q_heads;
-    head = item - mr * n_q_heads;
     if (mr >= table->total_merge_rows) return;
     const ReqDev& rq = table->r[request_of_merge_row(table, mr)];
     const int local = min(rq.long_tile_start, 1 << 20) * BQ + (mr - rq.merge_base);     // row inside the request
@@ -502,9 +509,8 @@ __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row
     part_base = rq.part_base;
     tile_last_row = min(rq.row_base + (lt + 1) * BQ, rq.row_base + rq.n_rows) - 1;
   } else {
-    if (item >= total_rows * n_q_heads) return;
-    r = item / n_q_heads;
-    head = item - r * n_q_heads;
+    if (mr >= total_rows) return;
+    r = mr;
     split_tile = r / BQ;
     ql = r % BQ;
     tile_last_row = min((split_tile + 1) * BQ, total_rows) - 1;
@@ -512,58 +518,80 @@ __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row
   const int n_kv_tiles = row_pos[tile_last_row] / BKV + 1;
   if (split_tile < 0 || n_kv_tiles <= sp.long_thr) return;   // this row's tile was done by one workgroup
   const int nc = min(sp.n_chunks, row_pos[r] / (sp.chunk_tiles * BKV) + 1);
-  const size_t slot0 = ((size_t)(part_base + split_tile * sp.n_chunks) * n_q_heads + head) * BQ + ql;
   const size_t cstride = (size_t)n_q_heads * BQ;
-  // Pass 1, one chunk per lane (64 at a time): the common reference exponent.  Pass 2: every lane needs every
-  // chunk's weight, so the (m, l) pairs are read again (they are cached) and the partial outputs of four chunks are
-  // requested before the first is used.  The sums run in chunk order.
-  float m = -INFINITY;
-  for (int c = lane; c < nc; c += 64) m = fmaxf(m, part_ml[slot0 + c * cstride].x);
+  size_t slot0[PAIRS];
+  float4 o[PAIRS][AHEAD], acc[PAIRS];
+  float2 ml[PAIRS][AHEAD];
+  float m[PAIRS], l[PAIRS];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  float l = 0.f, o0 = 0.f, o1 = 0.f;
-  int c = 0;
-  for (; c + 4 <= nc; c += 4) {
-    float2 ml[4], o[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const size_t slot = slot0 + (c + u) * cstride;
-      ml[u] = part_ml[slot];
-      o[u] = *reinterpret_cast<const float2*>(part_o + slot * PROW + 2 * lane);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float wgt = (ml[u].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m);
-      l += ml[u].y * wgt;
-      o0 += o[u].x * wgt;
-      o1 += o[u].y * wgt;
-    }
+  for (int p = 0; p < PAIRS; ++p) {
+    slot0[p] = ((size_t)(part_base + split_tile * sp.n_chunks) * n_q_heads + min(head0 + 2 * p, n_q_heads - 1)) * BQ + ql;
+    acc[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+    l[p] = 0.f;
   }
-  for (; c < nc; ++c) {
-    const size_t slot = slot0 + c * cstride;
-    const float2 ml = part_ml[slot];
-    const float wgt = (ml.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml.x - m);
-    l += ml.y * wgt;
-    const float2 o = *reinterpret_cast<const float2*>(part_o + slot * PROW + 2 * lane);
-    o0 += o.x * wgt;
-    o1 += o.y * wgt;
+  auto fetch = [&](int c) {   // the chunks c .. c + AHEAD - 1, the last one again behind it
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const size_t slot = slot0[p] + min(c + u, nc - 1) * cstride;
+        ml[p][u] = part_ml[slot];
+        o[p][u] = *reinterpret_cast<const float4*>(part_o + slot * PROW + 4 * e);
+      }
+  };
+  // The common reference exponent (one chunk per lane, 32 at a time), then the sums in chunk order.
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) m[p] = part_ml[slot0[p] + min(e, nc - 1) * cstride].x;
+  fetch(0);
+  for (int c = e + 32; c < nc; c += 32)
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) m[p] = fmaxf(m[p], part_ml[slot0[p] + c * cstride].x);
+#pragma unroll
+  for (int s = 16; s > 0; s >>= 1)
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) m[p] = fmaxf(m[p], __shfl_xor(m[p], s, 64));
+  for (int c = 0;;) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      if (c + u >= nc) break;   // uniform
+#pragma unroll
+      for (int p = 0; p < PAIRS; ++p) {
+        const float wgt = (ml[p][u].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[p][u].x - m[p]);
+        l[p] += ml[p][u].y * wgt;
+        acc[p].x += o[p][u].x * wgt;
+        acc[p].y += o[p][u].y * wgt;
+        acc[p].z += o[p][u].z * wgt;
+        acc[p].w += o[p][u].w * wgt;
+      }
+    }
+    c += AHEAD;
+    if (c >= nc) break;
+    fetch(c);
   }
-  if (score_ml && lane == 0) score_ml[(size_t)r * n_q_heads + head] = make_float2(m, l);
-  const float inv = 1.0f / l;
-  const uint32_t pk = (uint32_t)f32_to_bf16(o0 * inv).v | ((uint32_t)f32_to_bf16(o1 * inv).v << 16);
-  *reinterpret_cast<uint32_t*>(out + ((size_t)r * n_q_heads + head) * DH + 2 * lane) = pk;
+#pragma unroll
+  for (int p = 0; p < PAIRS; ++p) {
+    const int head = head0 + 2 * p;
+    if (head >= n_q_heads) continue;
+    if (score_ml && e == 0) score_ml[(size_t)r * n_q_heads + head] = make_float2(m[p], l[p]);
+    const float inv = 1.0f / l[p];
+    uint2 pk;
+    pk.x = (uint32_t)f32_to_bf16(acc[p].x * inv).v | ((uint32_t)f32_to_bf16(acc[p].y * inv).v << 16);
+    pk.y = (uint32_t)f32_to_bf16(acc[p].z * inv).v | ((uint32_t)f32_to_bf16(acc[p].w * inv).v << 16);
+    *reinterpret_cast<uint2*>(out + ((size_t)r * n_q_heads + head) * DH + 4 * e) = pk;
+  }
 }
 
+template <int PAIRS, int AHEAD>
 __global__ void __launch_bounds__(256)
 attn_merge_kernel(const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows, int n_q_heads, AttnSplit sp,
                   const float* __restrict__ part_o, const float2* __restrict__ part_ml, bf16* __restrict__ out,
                   float2* __restrict__ score_ml) {
-  merge_item((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, score_ml);
+  merge_item<PAIRS, AHEAD>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, score_ml);
 }
 
 // A decoding step with influence sums, its KV ranges split: workgroups below `merge_wgs` merge, the others add the rows' weights to
 // the influence vectors, 64 keys each (influence_add_kernel), and for that work the heads' merged exponents and sums out for
-// themselves.  Both hang on the same partial results, so one launch does for two: 6.0 + 4.6 -> 6.8 us (32 heads x 5k keys).
+// themselves.  Both hang on the same partial results, so one launch does for two: 6.0 + 4.6 -> 6.6 us (32 heads x 5k keys).
 // Four wavefronts share the heads; the weights of a key are added up head by head in ascending order.
 static constexpr int kInfMaxHeads = 64;   // of a model that takes this path (LDS)
 __global__ void __launch_bounds__(256)
@@ -574,7 +602,7 @@ attn_merge_influence_kernel(const int* __restrict__ row_pos, const int* __restri
   __shared__ float weight[kInfMaxHeads][64];
   __shared__ float2 pair[kInfMaxHeads];
   if ((int)blockIdx.x < merge_wgs) {
-    merge_item((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, nullptr);
+    merge_item<1, 8>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, nullptr);
     return;
   }
   const int row = ((int)blockIdx.x - merge_wgs) / wgs_per_row;
@@ -714,7 +742,8 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
   if (e != hipSuccess || sp.n_chunks == 1) return e;
   const float2* part_ml = reinterpret_cast<const float2*>(part + (size_t)sp.total_slots * n_q_heads * BQ * PROW);
   // with a table, merge_rows (the rows of the tiles that may be split, or an upper bound) sizes the merge grid
-  const int items = (table ? merge_rows : total_rows) * n_q_heads;
+  const int heads = one_row ? 2 : 4;   // per wavefront
+  const int items = (table ? merge_rows : total_rows) * ((n_q_heads + heads - 1) / heads);
   if (items <= 0) return hipSuccess;
   const int merge_wgs = (items + 3) / 4;
   if (inf && scores && table && one_row && G <= 8 && n_q_heads <= kInfMaxHeads) {
@@ -725,8 +754,9 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
     *inf_done = true;
     return hipGetLastError();
   }
-  attn_merge_kernel<<<merge_wgs, 256, 0, st>>>(row_pos, table, total_rows, n_q_heads, sp, part, part_ml, out,
-                                               scores ? influence_pairs(scores, total_rows, n_q_heads, scores_len) : nullptr);
+  (one_row ? attn_merge_kernel<1, 8> : attn_merge_kernel<2, 4>)<<<merge_wgs, 256, 0, st>>>(
+      row_pos, table, total_rows, n_q_heads, sp, part, part_ml, out,
+      scores ? influence_pairs(scores, total_rows, n_q_heads, scores_len) : nullptr);
   return hipGetLastError();
 }
 
