@@ -16,12 +16,15 @@
 // bits: it does not depend on which of the two kernels computed it.
 //
 // Per launch, tile kernel -> two wavefronts doing both halves in turn -> this one (32 query heads, 8 KV heads): one sequence of 5k
-// keys with its scores written 18.7 -> 10.7 -> 10.5 us; sixteen of 1.3k to 10k keys 112 -> 97 -> 82 us (394 MB, 4.8 TB/s); three of 150 to 700
+// keys with its scores written 18.7 -> 10.7 -> 10.5 us; sixteen of 1.3k to 10k keys 112 -> 97 -> 80 us (394 MB, 4.9 TB/s); three of 150 to 700
 // keys on 2 KV heads 14.3 -> 10.2 -> 8.2.
 #pragma once
 
 static constexpr int kDecodeSets = 4;   // register sets of a tile's K or V
 
+// SCORES: additionally write every visible score q.k / sqrt(dh) to scores[(row * n_q_heads + head) * scores_len + key] (the
+// influence sums read them), and the row's reference exponent and sum, score_ml[row * n_q_heads + head], unless the KV range is
+// split (then the merge has the pair).
 template <bool SCORES>
 __global__ void __launch_bounds__(256, 2)
 attn_decode_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, const ReqTable* __restrict__ table,

@@ -68,17 +68,12 @@ __device__ __forceinline__ int request_of_merge_row(const ReqTable* table, int m
   return __builtin_amdgcn_readfirstlane(__popcll(at) - 1);
 }
 
-// SCORES: additionally write every visible score q.k / sqrt(dh) of every valid row to
-// scores[(row * n_q_heads + head) * scores_len + key] (the decode-side influence accumulation reads them), and
-// the row's reference exponent and sum, score_ml[row * n_q_heads + head], unless the tile's KV range is split
-// (then attn_merge_kernel writes the merged pair).
-template <int G, bool SCORES>
+template <int G>
 __global__ void __launch_bounds__(64 * (G < 4 ? 4 : G), (G <= 4 ? 2 : 1))
 attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, const ReqTable* __restrict__ table,
                  int fixed_seq, int total_rows, int total_tiles, const bf16* __restrict__ k_pool,
                  const bf16* __restrict__ v_pool, KvGeom g, bf16* __restrict__ out, AttnSplit sp,
-                 float* __restrict__ part_o, float2* __restrict__ part_ml, float* __restrict__ scores,
-                 int scores_len, float2* __restrict__ score_ml) {
+                 float* __restrict__ part_o, float2* __restrict__ part_ml) {
   // A workgroup has at least four wavefronts: with fewer, each thread would stage so much of a K/V tile that the
   // kernel runs out of registers.  In a group of one to three query heads the wavefronts beyond the group only take
   // their share of the staging; they multiply zeros for head 0 of the group and write nothing.
@@ -378,19 +373,6 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
           if (key > my_pos) acc_s[b][e] = -INFINITY;
         }
     }
-    if (SCORES) {
-      if (q_ok) {
-        float* srow = scores + ((size_t)my_row * n_q_heads + head) * scores_len;
-        const float inv_sqrt = 1.0f / sqrtf((float)DH);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int key = kv0 + 32 * b + 8 * (e >> 2) + 4 * half + (e & 3);
-            if (key <= my_pos) srow[key] = acc_s[b][e] * inv_sqrt;
-          }
-      }
-    }
     float mx = acc_s[0][0];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -461,7 +443,6 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     return;
   }
   if (q_ok) {
-    if (SCORES && half == 0) score_ml[(size_t)my_row * n_q_heads + head] = make_float2(m_run, l_tot);
     const float inv = 1.0f / l_tot;
     bf16* orow = out + ((size_t)my_row * n_q_heads + head) * DH;
 #pragma unroll
@@ -689,24 +670,18 @@ size_t attention_partial_floats(int total_slots, int n_q_heads) {
 template <int G>
 static hipError_t launch_g(const bf16* q, const int* row_pos, const ReqTable* table, int fixed_seq, int total_rows,
                            int total_tiles, const bf16* k_pool, const bf16* v_pool, KvGeom g, bf16* out,
-                           AttnSplit sp, float* part, float* scores, int scores_len, hipStream_t st) {
+                           AttnSplit sp, float* part, hipStream_t st) {
   // with a table, total_tiles is the phase's number of work items (ReqTable::total_items, or an upper bound of it)
   const long items = table ? (long)total_tiles : (long)total_tiles * sp.n_chunks;
   dim3 grid((unsigned)(items * g.n_kv_heads));
   float* part_o = part;
   float2* part_ml = reinterpret_cast<float2*>(part + (size_t)sp.total_slots * g.n_kv_heads * G * BQ * PROW);
   // more than the 64 KB a kernel gets without asking
-  static std::atomic<unsigned long long> told_scores{0}, told_plain{0};
-  hipError_t e = scores ? allow_dynamic_lds((const void*)attn_mfma_kernel<G, true>, ATTN_LDS_BYTES, told_scores)
-                        : allow_dynamic_lds((const void*)attn_mfma_kernel<G, false>, ATTN_LDS_BYTES, told_plain);
+  static std::atomic<unsigned long long> told{0};
+  hipError_t e = allow_dynamic_lds((const void*)attn_mfma_kernel<G>, ATTN_LDS_BYTES, told);
   if (e != hipSuccess) return e;
-  if (scores)
-    attn_mfma_kernel<G, true><<<grid, 64 * (G < 4 ? 4 : G), ATTN_LDS_BYTES, st>>>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool,
-                                                                    v_pool, g, out, sp, part_o, part_ml, scores, scores_len,
-                                                                    influence_pairs(scores, total_rows, g.n_kv_heads * G, scores_len));
-  else
-    attn_mfma_kernel<G, false><<<grid, 64 * (G < 4 ? 4 : G), ATTN_LDS_BYTES, st>>>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool,
-                                                                     v_pool, g, out, sp, part_o, part_ml, nullptr, 0, nullptr);
+  attn_mfma_kernel<G><<<grid, 64 * (G < 4 ? 4 : G), ATTN_LDS_BYTES, st>>>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool, v_pool,
+                                                                          g, out, sp, part_o, part_ml);
   return hipGetLastError();
 }
 
@@ -728,14 +703,15 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
     else
       attn_decode_kernel<false><<<grid, 256, 0, st>>>(q, row_pos, table, k_pool, v_pool, g, G, out, sp, part, part_ml, nullptr, 0, nullptr);
     e = hipGetLastError();
+  } else if (scores) {   // only one live row per request has scores written, by the kernel above
+    return hipErrorInvalidValue;
   } else switch (G) {
 #define RC_ATTN_CASE(GG) \
-    case GG: e = launch_g<GG>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool, v_pool, g, out, sp, part, scores, scores_len, st); break;
+    case GG: e = launch_g<GG>(q, row_pos, table, fixed_seq, total_rows, total_tiles, k_pool, v_pool, g, out, sp, part, st); break;
     RC_ATTN_CASE(1) RC_ATTN_CASE(2) RC_ATTN_CASE(3) RC_ATTN_CASE(4)
     RC_ATTN_CASE(5) RC_ATTN_CASE(6) RC_ATTN_CASE(7) RC_ATTN_CASE(8)
 #undef RC_ATTN_CASE
     default:  // wider groups: one wavefront per (row, head) on the vector ALUs
-      if (scores) return hipErrorInvalidValue;
       return launch_attention_simt(q, row_pos, row_req, table, fixed_seq, total_rows, k_pool, v_pool, g,
                                          n_q_heads, out, st);
   }
