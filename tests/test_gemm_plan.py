@@ -4,6 +4,8 @@ import itertools
 import pytest
 
 from paper_2603_13289_amd import binding as rc
+from tests import test_gpu_gemm_whole_calls as whole_calls
+from tests import test_gpu_qkv_rope as qkv_rope
 
 
 def test_every_tile_is_covered_exactly_once_on_the_workload_shapes():
@@ -81,3 +83,37 @@ def test_coverage_of_the_schedules_the_library_chooses():
             for ws in (True, False):
                 err, nb = rc.rc_gemm_plan_check(m, n, k, swiglu, 0, 256, ws)
                 assert err == 0 and nb > 0, (m, n, k, swiglu, ws)
+
+
+def _blocks(m, n, k, swiglu, workspace, thin=1):
+    rc.rc_tune_set(rc.RC_TUNE_GEMM_THIN_TILES, thin)
+    try:
+        return rc.rc_gemm_plan_check(m, n, k, swiglu, 0, 256, workspace)[1]
+    finally:
+        rc.rc_tune_set(rc.RC_TUNE_GEMM_THIN_TILES, 1)
+
+
+@pytest.mark.parametrize("m,n,k,epilogue,workspace", [(*c, True) for c in whole_calls.THIN] + [(*c, False) for c in whole_calls.THIN_WHOLE])
+def test_shapes_that_take_the_thin_body(m, n, k, epilogue, workspace):
+    swiglu = epilogue == "swiglu"
+    tiles = -(-m // 256) * -(-n // (128 if swiglu else 256))
+    assert _blocks(m, n, k, swiglu, workspace) == -(-tiles // 8) * 8 != _blocks(m, n, k, swiglu, workspace, thin=0)
+
+
+def test_shapes_of_few_rows_that_are_cut_in_parts():
+    most = 0
+    for m, n, k, epilogue in whole_calls.FEW:
+        swiglu = epilogue == "swiglu"
+        blocks, tiles = _blocks(m, n, k, swiglu, True), -(-n // (64 if swiglu else 128))   # tiles of 64 rows by 128 weight rows
+        assert k % 256 and n % 16 == 0 and blocks != _blocks(m, n, k, swiglu, False)
+        assert blocks % tiles == 0 and 4 <= blocks // tiles <= 16, (m, n, k)
+        most = max(most, blocks // tiles * (2 if swiglu else 1) * (2 if m > 16 else 1))
+    assert most == 64   # accumulator tiles of 1 KB: all the LDS that a launch gets without asking
+
+
+@pytest.mark.parametrize("m,d,nq,nkv,page,tile", qkv_rope.THIN)
+def test_shapes_of_qkv_with_a_thin_row_and_cut_tiles(m, d, nq, nkv, page, tile):
+    n = (nq + 2 * nkv) * 128
+    blocks = _blocks(m, n, d, False, True)
+    assert blocks != _blocks(m, n, d, False, True, thin=0)      # thin tiles, which are never cut
+    assert blocks > -(-(-(-m // 256) * -(-n // 256)) // 8) * 8  # more workgroups than tiles: others are
