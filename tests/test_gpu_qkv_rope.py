@@ -11,7 +11,10 @@ pytestmark = pytest.mark.gpu
 # rows; model width; heads; page; forced tile type (0: by shape)
 CASES = [(33, 512, 8, 2, 0, 0), (100, 4096, 32, 8, 16, 0), (257, 5120, 40, 8, 16, 0), (1025, 4096, 32, 8, 0, 0), (1639, 4096, 32, 8, 16, 0),
          (2500, 4096, 32, 8, 0, 0), (5120, 1024, 32, 8, 16, 0), (300, 1024, 7, 1, 3, 0)]
-CASES += [(m, 640, 6, 2, 16, t) for m in (40, 197) for t in (7, 8, 9, 10, 11, 12, 13)]
+CASES += [(m, 640, 6, 2, 16, t) for m in (40, 197) for t in (5, 6, 7, 8, 9, 10, 11, 12, 13)]
+# 256x256 tiles, some of them cut along K, and a thin last tile row: all three ends of the product in one launch (test_gemm_plan.py)
+THIN = [(2817, 4096, 32, 8, 16, 0), (3073, 4096, 32, 8, 0, 0), (2305, 5120, 40, 8, 16, 0)]
+CASES += THIN
 
 
 @pytest.mark.parametrize("m,d,nq,nkv,page,tile", CASES)
@@ -42,7 +45,8 @@ def test_product_and_scatter(m, d, nq, nkv, page, tile):
     logits = torch.zeros((1, 256), dtype=torch.float32, device="cuda")
     rc.rc_tune_set(rc.RC_TUNE_GEMM_TILE, tile)
     try:
-        rc.rc_prefill(model, [x], [0], cache, logits, rc.alloc_workspace(rc.rc_prefill_workspace_bytes(model, [m])), k_pre=record)
+        ws_call = rc.alloc_workspace(rc.rc_prefill_workspace_bytes(model, [m]))
+        rc.rc_prefill(model, [x], [0], cache, logits, ws_call, k_pre=record)
         # the same product into floats, then the scatter stage
         r = np.float32(1) / np.sqrt(np.float32(1) + np.float32(1e-5))
         a = (x.float() * float(r)).to(torch.bfloat16)
@@ -62,3 +66,7 @@ def test_product_and_scatter(m, d, nq, nkv, page, tile):
     assert torch.equal(k1, k2) and torch.equal(v1, v2)
     want = qkv[:, nq * 128:(nq + nkv) * 128].to(torch.bfloat16).view(m, nkv, 128)
     assert torch.equal(record.read("k", 0, 0, m).view(m, nkv, 128), want)
+    # the rotated queries of the one layer are still in the call's workspace, at a multiple of 256 bytes
+    held, q = ws_call.view(torch.int16), q.view(torch.int16).flatten()
+    at = (held[:held.numel() // 128 * 128].view(-1, 128) == q[:128]).all(1).nonzero().flatten().tolist()
+    assert any(torch.equal(held[128 * i:128 * i + q.numel()], q) for i in at)
