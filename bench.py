@@ -374,8 +374,9 @@ def main() -> int:
     rc.rc_profile_enable(False)
     stages = {name: {"ms_per_step": ms / args.steps, "launches_per_step": n // args.steps}
               for name, (ms, n) in prof.items() if n}
+    # a launch that adds K parts up counts with its product, also where it does the next norm as well (a stage of its own)
     gemm_ms = sum(v["ms_per_step"] for n, v in stages.items() if n.startswith("gemm"))
-    gemm_launches = sum(v["launches_per_step"] for n, v in stages.items() if n.startswith("gemm"))
+    gemm_launches = sum(v["launches_per_step"] for n, v in stages.items() if n.startswith("gemm") and n != "gemm_parts_norm")
     fl, row_layers = gemm_flops_batch(w, lens, ks)
     achieved = fl / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
 
@@ -430,6 +431,10 @@ def main() -> int:
                       "frac": (attn_flops / (attn_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS) if attn_ms > 0 else 0.0,
                       "algorithmic_gflop_per_step": attn_flops / 1e9, "ms_per_step": attn_ms},
     }
+    # stages that did not run (rotary + scatter inside the products), and norms of which others did a share, have no rate
+    if "gemm_parts_norm" in stages:
+        del stage_rooflines["rmsnorm"]
+    stage_rooflines = {n: r for n, r in stage_rooflines.items() if r["ms_per_step"] > 0}
 
     full_ms = None
     if not args.no_full_prefill:

@@ -32,11 +32,14 @@ namespace {
 // ---------------------------------------------------------------- optional per-class GPU timing
 enum ProfClass : int {
   PC_REROTATE = 0, PC_ROWS, PC_RMSNORM, PC_GEMM_QKV, PC_GEMM_O, PC_GEMM_GATE_UP, PC_GEMM_DOWN, PC_GEMM_VFRESH,
-  PC_GEMM_LM_HEAD, PC_ROPE_SCATTER, PC_ATTENTION, PC_SCORE, PC_SELECT, PC_TABLES, PC_INFLUENCE, PC_COUNT
+  PC_GEMM_LM_HEAD, PC_ROPE_SCATTER, PC_ATTENTION, PC_SCORE, PC_SELECT, PC_TABLES, PC_INFLUENCE,
+  PC_GEMM_PARTS_NORM,   // K parts of a product added up by the norm that follows
+  PC_COUNT
 };
 const char* const kProfNames[PC_COUNT] = {"rope_rerotate", "row_bookkeeping", "rmsnorm", "gemm_qkv", "gemm_o",
                                           "gemm_gate_up", "gemm_down", "gemm_vfresh", "gemm_lm_head",
-                                          "rope_scatter", "attention", "vdev_score", "select", "tables", "influence"};
+                                          "rope_scatter", "attention", "vdev_score", "select", "tables", "influence",
+                                          "gemm_parts_norm"};
 struct ProfRec { int cls; hipEvent_t a, b; };
 struct Profiler {
   bool on = false;
@@ -551,7 +554,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       const NormIn norm = {h, (const bf16*)lw.g_attn, d.rms_eps, {0, 1, 2, 3}};
       const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D, nq, nq + nkv);
       const bool normed = few && gemm_skinny_norm_fits(rows, D);
-      if (!normed) RC_LAUNCH(PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
+      if (!normed) RC_LAUNCH(rest.tiles > 0 ? PC_GEMM_PARTS_NORM : PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
       const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
                             job.k_pre_pool ? (bf16*)job.k_pre_pool[l] : nullptr, gd.block_size};
       bool rotated = few;
@@ -596,7 +599,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
         const NormIn norm = {h, (const bf16*)lw.g_ffn, d.rms_eps, {0, 1, 2, 3}};
         RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_skinny_normed(norm, (const bf16*)lw.w_gate, (const bf16*)lw.w_up, w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
       } else {
-        RC_LAUNCH(PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
+        RC_LAUNCH(rest.tiles > 0 ? PC_GEMM_PARTS_NORM : PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_ffn, w.a, rows, D, d.rms_eps, st, m_live));
         RC_LAUNCH(PC_GEMM_GATE_UP, gemm_any<T>((const T*)w.a, (const T*)lw.w_gate, (const T*)lw.w_up, w.act, rows, F, D, F, EPI_SWIGLU_T, w.gemm_part, st, m_live, rows_expected));
       }
     }
