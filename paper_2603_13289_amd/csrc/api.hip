@@ -380,17 +380,18 @@ hipError_t gemm_any<bf16>(const bf16* a, const bf16* wt, const bf16* wt2, void* 
 // Partial-attention slots the sparse phase (and the phase after it) may use when the threshold selector decides the
 // row counts on the device: planned for a nominal selection of a fifth of every segment, with room for twice that;
 // a selection that needs more attends unsplit.
-struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int cap[PH_COUNT]; int rows[PH_COUNT]; };
+struct ThresholdSplit { AttnSplit sp[PH_COUNT]; int cap[PH_COUNT]; int sparse_rows; };
 ThresholdSplit plan_threshold_split(const ReqTable& base, int n_kv_heads, int n_q_heads, int tile_rows, int max_pos, bool bf16_model) {
   ThresholdSplit ts;
-  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.cap[p] = 0; ts.rows[p] = 0; }
+  for (int p = 0; p < PH_COUNT; ++p) { ts.sp[p] = attention_no_split(); ts.cap[p] = 0; }
+  ts.sparse_rows = 0;
   if (!bf16_model) return ts;
   for (int p = PH_C; p <= PH_D; ++p) {
     ReqTable t = base;
     for (int b = 0; b < t.n_req; ++b)
       if (t.r[b].k > 0) t.r[b].k = std::max(1, t.r[b].S / 5);
     fill_phase_table(&t, p, nullptr, tile_rows);
-    ts.rows[p] = t.total_rows;
+    if (p == PH_C) ts.sparse_rows = t.total_rows;
     AttnSplit sp = choose_phase_split(&t, n_kv_heads, n_q_heads, tile_rows, max_pos);
     if (sp.n_chunks <= 1) continue;
     for (int b = 0; b < t.n_req; ++b)
@@ -430,7 +431,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
   // (Behind the sparse phase no row of a segment but its last one is live, whatever was selected: the host's count is exact.)
   auto counted = [&](int ph) { return on_device[ph] && ph != PH_D; };
   auto live = [&](int ph) -> const int* { return counted(ph) ? &(w.tables + ph)->total_rows : nullptr; };
-  int expected_rows[PH_COUNT] = {0, 0, 0, 0};   // of a phase whose count is on the device: what the GEMM tiles are chosen for
+  int sparse_rows = 0;   // of the sparse phase when its count is on the device: what the GEMM tiles are chosen for
   auto enter_phase = [&](Phase ph) -> rc_status {
     if (!on_device[ph]) {
       fill_phase_table(&tabs[ph], ph, cur >= 0 ? &tabs[cur] : nullptr, tile_rows);
@@ -509,11 +510,11 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
           // one-thread kernel rewrites their counts, row offsets and attention slots from sel_cnt: nothing comes
           // back to the host, the call stays asynchronous.
           const ThresholdSplit ts = plan_threshold_split(job.base, d.n_kv_heads, d.n_q_heads, tile_rows, job.max_pos, d.dtype == RC_BF16);
+          sparse_rows = ts.sparse_rows;
           int phase_before = cur;
           for (int p = PH_C; p <= PH_D; ++p) {
             fill_phase_table(&tabs[p], p, &tabs[phase_before], tile_rows);
             splits[p] = ts.sp[p];
-            expected_rows[p] = ts.rows[p];
             if (attention_partial_floats(splits[p].total_slots, d.n_q_heads) > w.attn_part_floats) splits[p] = attention_no_split();
             // work items of the attention grid, as an upper bound over every possible selection: all tiles whole, or
             // the tiles that stay whole plus as many (tile, chunk) pairs as there are slots
@@ -541,7 +542,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     const int rows = tabs[cur].total_rows;
     if (rows == 0) continue;
     const int* m_live = live(cur);
-    const int rows_expected = m_live ? expected_rows[cur] : rows;
+    const int rows_expected = m_live ? sparse_rows : rows;
     if (l == job.capture_layer) RC_LAUNCH(PC_ROWS, launch_capture_rows<T>(w.tables + cur, rows, w.h[hbuf], w.row_req, D, st));
 
     float* h = w.h[hbuf];
@@ -552,7 +553,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
                                                       job.k_pre_pool ? (float*)job.k_pre_pool[l] : nullptr, gd, d.n_q_heads, st, m_live));
     } else {
       const NormIn norm = {h, (const bf16*)lw.g_attn, d.rms_eps, {0, 1, 2, 3}};
-      const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D, nq, nq + nkv);
+      const bool few = gemm_takes_few_rows(rows, nq + 2 * nkv, D);
       const bool normed = few && gemm_skinny_norm_fits(rows, D);
       if (!normed) RC_LAUNCH(rest.tiles > 0 ? PC_GEMM_PARTS_NORM : PC_RMSNORM, launch_rest_rmsnorm(rest, h, (const bf16*)lw.g_attn, w.a, rows, D, d.rms_eps, st, m_live));
       const RopeOut rope = {w.row_pos, w.row_dst, w.rope_tab, (bf16*)w.q, (bf16*)job.dst->k_pool[l], (bf16*)job.dst->v_pool[l],
@@ -595,7 +596,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
       RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_f32_normed(h, (const float*)lw.g_ffn, d.rms_eps, nullptr, (const float*)lw.w_gate,
                                                         (const float*)lw.w_up, (float*)w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
     } else {
-      if (gemm_takes_few_rows(rows, F, D, F, F) && gemm_skinny_norm_fits(rows, D)) {
+      if (gemm_takes_few_rows(rows, F, D) && gemm_skinny_norm_fits(rows, D)) {
         const NormIn norm = {h, (const bf16*)lw.g_ffn, d.rms_eps, {0, 1, 2, 3}};
         RC_LAUNCH(PC_GEMM_GATE_UP, launch_gemm_skinny_normed(norm, (const bf16*)lw.w_gate, (const bf16*)lw.w_up, w.act, rows, F, D, EPI_SWIGLU_T, st, m_live));
       } else {
@@ -617,7 +618,7 @@ rc_status run_job(Job& job, Workspace& w, hipStream_t st) {
     return RC_OK;
   } else {
     // the host knows where the last rows are unless they are rows of a phase counted on the device
-    if (!counted(cur) && gemm_takes_few_rows(n_req, d.vocab, D, d.vocab, d.vocab) && gemm_skinny_norm_fits(n_req, D)) {
+    if (!counted(cur) && gemm_takes_few_rows(n_req, d.vocab, D) && gemm_skinny_norm_fits(n_req, D)) {
       NormIn norm = {w.h[hbuf], (const bf16*)job.m->g_final, d.rms_eps, {0, 0, 0, 0}};
       for (int b = 0; b < n_req; ++b) norm.row[b] = tabs[cur].r[b].n_rows > 0 ? tabs[cur].r[b].row_base + tabs[cur].r[b].n_rows - 1 : -1;
       RC_LAUNCH(PC_GEMM_LM_HEAD, launch_gemm_skinny_normed(norm, (const bf16*)job.m->w_lm, nullptr, job.logits, n_req, d.vocab, D, EPI_STORE_F32, st, nullptr));

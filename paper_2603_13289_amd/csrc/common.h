@@ -327,13 +327,12 @@ struct NormIn { const float* h; const bf16* gain; float eps; int row[kNormRows];
 constexpr unsigned kRowNoDst = 0xffffffffu;   // a row that leaves the cache writes to its twin
 struct RopeOut { const int* row_pos; const unsigned* row_dst; const float2* tab; bf16 *q, *k_pool, *v_pool, *k_pre_pool; int block_size; };
 
-// few-row variant (M <= 32, weights streamed once); columns < ns1 come from w, < ns2 from w2, the rest from w3
-bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2);
-hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
-                                   void* c, int m, int n, int k, int ldc, GemmEpilogue epi, hipStream_t st,
-                                   const int* m_live = nullptr);
+// few-row variant (M <= 32, weights streamed once); w2: the up weights of EPI_SWIGLU_T
+bool gemm_skinny_applies(int m, int n, int k);
+hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
+                                   hipStream_t st, const int* m_live = nullptr);
 
-bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2);   // as above, and no tile type is forced
+bool gemm_takes_few_rows(int m, int n, int k);   // as above, and no tile type is forced
 // the same with the RMS norm of the rows inside (gemm_skinny_norm_fits), and the q|k|v product (heads of 128) with rotary and scatter
 bool gemm_skinny_norm_fits(int m, int k);
 hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf16* w2, void* c, int m, int n, int k,
@@ -341,9 +340,9 @@ hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf
 hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv,
                                        int m, int k, const RopeOut& rope, hipStream_t st, const int* m_live);
 
-// few rows, K in `parts` parts of `part_steps` steps of 32 (at most 16 parts; n, ns1 and ns2 multiples of 16, k of 64)
-hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c, int m, int n,
-                                      int k, int ldc, GemmEpilogue epi, int parts, int part_steps, hipStream_t st);
+// few rows, K in `parts` parts of `part_steps` steps of 32 (at most 16 parts; n a multiple of 16, k of 64)
+hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
+                                      int parts, int part_steps, hipStream_t st);
 
 // bf16 GEMMs with a scratch buffer (gemm_partial_bytes()) for the K-split tail of the tile schedule;
 // partial == nullptr: every tile is done by one workgroup.
@@ -359,8 +358,8 @@ hipError_t launch_gemm_bf16(const bf16* a, const bf16* w, const bf16* w2, void* 
 constexpr int kRestNormMax = 8192;
 hipError_t launch_rest_rmsnorm(const GemmRest& rest, float* h, const bf16* gain, bf16* out, int rows, int d, float eps, hipStream_t st,
                                const int* m_live);
-// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T.  With rope (heads of 128), rotary and scatter are part of the product where that
-// can be (*rotated; C is not written then).
+// C[M][nq + 2 nkv] (float) = A * [wq; wk; wv]^T, of more rows than the few-row kernel takes.  With rope (heads of 128), rotary and
+// scatter are part of the product where that can be (*rotated; C is not written then).
 hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf16* wk, const bf16* wv, int nkv, float* c,
                                 int m, int k, float* partial, hipStream_t st, const int* m_live, int m_expected, const RopeOut* rope,
                                 bool* rotated);

@@ -1214,9 +1214,8 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
   const DlPlan p = plan_dl(tile, m, n, k, epi == EPI_SWIGLU_T, num_cus(), partial != nullptr, m_live != nullptr, m_expected);
   // Few rows, cut into enough parts to keep the wavefronts of a workgroup busy: one launch, which also adds them up.  (Whole, or in
   // two or three parts, a wavefront's chain over K would be as long as a tile's.)
-  if (tile == 0 && !m_live && !rope && m <= 32 && p.uniform && p.rem_tiles > 0 && p.grid.split >= 4 && p.grid.split <= 16 && n % 16 == 0 &&
-      ns1 % 16 == 0 && ns2 % 16 == 0)
-    return launch_gemm_few_rows_parts(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, p.grid.split, p.grid.kpp * (BK / 32), st);
+  if (tile == 0 && !m_live && !w3 && m <= 32 && p.uniform && p.rem_tiles > 0 && p.grid.split >= 4 && p.grid.split <= 16 && n % 16 == 0)
+    return launch_gemm_few_rows_parts(a, w, w2, c, m, n, k, ldc, epi, p.grid.split, p.grid.kpp * (BK / 32), st);
   hipError_t e = hipErrorInvalidValue;
 #define RC_DL(CODE, THIN, ...) \
   case CODE: e = launch_dl<__VA_ARGS__, THIN>(p.grid, p.n_blocks, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live, rope); break
@@ -1242,7 +1241,7 @@ static hipError_t dispatch_dl(int tile, const bf16* a, const bf16* w, const bf16
   return launch_fixup(r, c, m, n, ldc, epi, st, ns1, ns2, rope);
 }
 
-bool gemm_takes_few_rows(int m, int n, int k, int ns1, int ns2) { return g_gemm_tile == 0 && gemm_skinny_applies(m, n, k, ns1, ns2); }
+bool gemm_takes_few_rows(int m, int n, int k) { return g_gemm_tile == 0 && gemm_skinny_applies(m, n, k); }
 
 static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c,
                            int m, int n, int k, int ldc, GemmEpilogue epi, float* partial, hipStream_t st,
@@ -1250,8 +1249,7 @@ static hipError_t dispatch(const bf16* a, const bf16* w, const bf16* w2, const b
   if (rest) rest->tiles = 0;
   if (m <= 0 || n <= 0) return hipSuccess;
   int tile = g_gemm_tile;
-  if (gemm_takes_few_rows(m, n, k, ns1, ns2))
-    return launch_gemm_skinny_bf16(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, st, m_live);
+  if (!w3 && gemm_takes_few_rows(m, n, k)) return launch_gemm_skinny_bf16(a, w, w2, c, m, n, k, ldc, epi, st, m_live);
   if (m_live) partial = nullptr;   // live row count on the device: every output summed whole
   if ((tile == 0 || tile >= 5) && k % BK == 0)
     return dispatch_dl(tile, a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, partial, st, m_live,
@@ -1276,7 +1274,7 @@ hipError_t launch_gemm_qkv_bf16(const bf16* a, const bf16* wq, int nq, const bf1
                                 bool* rotated) {
   const int n = nq + 2 * nkv, tile = g_gemm_tile;
   *rotated = false;
-  if (rope && m > 0 && (tile == 0 || tile >= 5) && k % BK == 0 && !gemm_takes_few_rows(m, n, k, nq, nq + nkv)) {
+  if (rope && m > 0 && (tile == 0 || tile >= 5) && k % BK == 0) {
     if (m_live) partial = nullptr;
     m_expected = m_live && m_expected > 0 ? std::min(m, m_expected) : m;
     const DlPlan p = plan_dl(tile, m, n, k, false, num_cus(), partial != nullptr, m_live != nullptr, m_expected);

@@ -42,13 +42,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 __device__ inline float silu_s(float x) { return x / (1.0f + __expf(-x)); }
 
-// DUAL: gate and up weights of the same columns.  TWO: more than 16 rows.  U: K steps of a register set.
+// DUAL: gate (w) and up weights (w2) of the same columns.  TWO: more than 16 rows.  U: K steps of a register set.
 // NORM: the rows, at most 2 NORM of them, are RMS-normalised on the way in (NormIn), in the order of rmsnorm_kernel, so that the
 // operand has the same bits.  Every workgroup does it for itself, into LDS, while its first weights are on their way: what a row of
 // 4096 costs (16 KB from the L2, a reduction) hides behind them and the launch of the norm kernel goes.
 // One row, K = 4096: q|k|v 12.0 + norm 4.7 + rotary 5.5 -> 14.3 us, gate/up 42.2 + 4.7 -> 43.0, LM head (32768) 43 + norm and
 // gather 10.3 -> 46.3.  More than four rows keep the norm's own launch: every workgroup would read and hold them all.
-// ROPE: the columns are q, k and v heads of 128 (RopeOut); a workgroup has columns 8 j .. 8 j + 7 of both halves of a head, i.e.
+// ROPE: the columns are q, k and v heads of 128 (RopeOut), below ns1 of w, below ns2 of w2, the rest of w3; a workgroup has columns 8 j .. 8 j + 7 of both halves of a head, i.e.
 // eight whole rotary pairs, and its epilogue does what rope_scatter_kernel does with a row, in the same arithmetic.
 template <bool DUAL, bool TWO, int U, int NORM, bool ROPE>
 __global__ void __launch_bounds__(kSkinnyWaves * 64, U == 8 || (DUAL && TWO) ? 2 : 4)
@@ -75,12 +75,9 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
   const size_t koff = (size_t)wave * kw + 8 * (lane >> 4);
   const bf16* pw;
   const bf16* pu = nullptr;
-  if (DUAL) {
-    pw = w + (size_t)col * k + koff;
-    pu = w2 + (size_t)col * k + koff;
-  } else {
-    pw = (col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k)) + koff;
-  }
+  if constexpr (ROPE) pw = (col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k)) + koff;
+  else pw = w + (size_t)col * k + koff;
+  if constexpr (DUAL) pu = w2 + (size_t)col * k + koff;
   const bf16* pa0 = a + (size_t)min(lane & 15, m - 1) * k + koff;
   const bf16* pa1 = a + (size_t)min(16 + (lane & 15), m - 1) * k + koff;
   const unsigned char* la0 = lds_rows + (size_t)min(lane & 15, m - 1) * norm_pitch(k) + 2 * koff;
@@ -306,15 +303,14 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
 // its sum over the parts, in one launch.  3 x 512 x 1408 (eleven parts): 4.1 + 6.0 -> 4.0 us.
 template <bool DUAL, bool TWO>
 __global__ void __launch_bounds__(kSkinnyWaves * 64, 2)
-gemm_few_rows_parts_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
-                           const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc, int epi,
-                           int parts, int part_steps) {
+gemm_few_rows_parts_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2, void* __restrict__ c, int m,
+                           int n, int k, int ldc, int epi, int parts, int part_steps) {
   constexpr int TILES = (DUAL ? 2 : 1) * (TWO ? 2 : 1), UP = TWO ? 2 : 1, U = 4;
   extern __shared__ __attribute__((aligned(16))) f32x4s lds_parts[];   // [part][tile][lane]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = (int)blockIdx.x * 16 + (lane & 15);
-  const bf16* const pw = (DUAL || col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k)) + 8 * (lane >> 4);
+  const bf16* const pw = w + (size_t)col * k + 8 * (lane >> 4);
   const bf16* const pu = DUAL ? w2 + (size_t)col * k + 8 * (lane >> 4) : nullptr;
   const bf16* const pa0 = a + (size_t)min(lane & 15, m - 1) * k + 8 * (lane >> 4);
   const bf16* const pa1 = a + (size_t)min(16 + (lane & 15), m - 1) * k + 8 * (lane >> 4);
@@ -364,12 +360,12 @@ gemm_few_rows_parts_kernel(const bf16* __restrict__ a, const bf16* __restrict__ 
   }
 }
 
-hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2, void* c, int m, int n,
-                                      int k, int ldc, GemmEpilogue epi, int parts, int part_steps, hipStream_t st) {
+hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
+                                      int parts, int part_steps, hipStream_t st) {
   auto go = [&](auto dual, auto two) {
     const size_t lds = (size_t)parts * (decltype(dual)::value ? 2 : 1) * (decltype(two)::value ? 2 : 1) * 64 * sizeof(f32x4s);
     gemm_few_rows_parts_kernel<decltype(dual)::value, decltype(two)::value><<<dim3((unsigned)(n / 16)), kSkinnyWaves * 64, lds, st>>>(
-        a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, parts, part_steps);
+        a, w, w2, c, m, n, k, ldc, (int)epi, parts, part_steps);
   };
   auto rows = [&](auto dual) {
     if (m > 16) go(dual, std::true_type{});
@@ -380,17 +376,14 @@ hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* 
   return hipGetLastError();
 }
 
-bool gemm_skinny_applies(int m, int n, int k, int ns1, int ns2) {
-  return m >= 1 && m <= 32 && n % 16 == 0 && k % (kSkinnyWaves * 32) == 0 && ns1 % 16 == 0 && ns2 % 16 == 0;
-}
+bool gemm_skinny_applies(int m, int n, int k) { return m >= 1 && m <= 32 && n % 16 == 0 && k % (kSkinnyWaves * 32) == 0; }
 
-hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, const bf16* w3, int ns1, int ns2,
-                                   void* c, int m, int n, int k, int ldc, GemmEpilogue epi, hipStream_t st,
-                                   const int* m_live) {
+hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
+                                   hipStream_t st, const int* m_live) {
   const dim3 grid((unsigned)(n / 16));
   auto go = [&](auto dual, auto two, auto u) {
     gemm_skinny_kernel<decltype(dual)::value, decltype(two)::value, decltype(u)::value, 0, false>
-        <<<grid, kSkinnyWaves * 64, 0, st>>>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, (int)epi, m_live, NormIn{}, RopeOut{});
+        <<<grid, kSkinnyWaves * 64, 0, st>>>(a, w, w2, nullptr, 0, 0, c, m, n, k, ldc, (int)epi, m_live, NormIn{}, RopeOut{});
   };
   auto rows = [&](auto dual, auto u) {
     if (m > 16) go(dual, std::true_type{}, u);
@@ -409,7 +402,7 @@ hipError_t launch_gemm_skinny_normed(const NormIn& norm, const bf16* w, const bf
   const dim3 grid((unsigned)(n / 16));
   auto go = [&](auto dual, auto passes) {
     gemm_skinny_kernel<decltype(dual)::value, false, 4, decltype(passes)::value, false>
-        <<<grid, kSkinnyWaves * 64, (size_t)m * norm_pitch(k), st>>>(nullptr, w, w2, nullptr, n, n, c, m, n, k, n, (int)epi, m_live, norm,
+        <<<grid, kSkinnyWaves * 64, (size_t)m * norm_pitch(k), st>>>(nullptr, w, w2, nullptr, 0, 0, c, m, n, k, n, (int)epi, m_live, norm,
                                                                     RopeOut{});
   };
   auto rows = [&](auto dual) {
