@@ -12,8 +12,9 @@
 //                                               d = 64 w + 2 (row) + j
 // The scores of a tile run one ahead of its softmax, so that a tile costs the longer of the two halves and not their sum.  K and V
 // go from memory straight to registers, four tiles ahead (128 KB in flight per work item); one barrier per tile, which waits for
-// no load.  Products, key tiles, chunks and the order of every sum are those of the tile kernel, so a row's result has the same
-// bits: it does not depend on which of the two kernels computed it.
+// no load.  Products, key tiles, chunks and the order of every sum are those of the tile kernel.  A row gets the bits that the tile
+// kernel gives a row alone in its tile.  In company it may not: there one row whose maximum outgrows the slack moves the reference
+// exponents of all rows of the tile, here those of its own head only; the weights are then rounded to bf16 at another scale.
 //
 // Per launch, tile kernel -> two wavefronts doing both halves in turn -> this one (32 query heads, 8 KV heads): one sequence of 5k
 // keys with its scores written 18.7 -> 10.7 -> 10.5 us; sixteen of 1.3k to 10k keys 112 -> 97 -> 80 us (394 MB, 4.9 TB/s); three of 150 to 700

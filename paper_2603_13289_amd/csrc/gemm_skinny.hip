@@ -28,8 +28,11 @@ static constexpr int kSkinnyWaves = 8;
 // sequence on the 7B shape 4.23 ms, of sixteen 7.97; as it is 4.17 and 7.88).
 static constexpr int kSkinnyDeepGroups = 256;
 
-// Rows that a workgroup normalises for itself: at most four, of at most 5120 elements (registers), in at most 48 KB of LDS (with
-// the partial tiles two workgroups fit a compute unit).
+// Rows that a workgroup normalises for itself: at most four, in at most 48 KB of LDS (with the partial tiles two workgroups fit a
+// compute unit), of at most 5120 elements.  A thread keeps its share of up to two rows and of the gains in registers, 1024 elements
+// of a row at a time whatever its width: at 5120 gate/up of four rows needs 121 of the 128 registers that two workgroups leave, at
+// 6144 it goes through scratch memory (16 bytes a lane), at 8192 q|k|v does as well.  One or two rows would fit up to 8192 (116
+// registers for 100): not built, wider models have a norm launch of their own instead (4.7 us).
 static constexpr int kNormRowMax = 5120;
 static constexpr size_t kNormLds = 48 * 1024;
 __device__ __host__ inline int norm_pitch(int k) { return 2 * k + 16; }   // bytes; rows start in different LDS banks
@@ -300,7 +303,7 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
 
 // Products of few rows whose K is no multiple of 256: summed in the K parts of the tile kernels' partition (`parts` of `part_steps`
 // steps of 32 each, the last one shorter), a part by one wavefront, added up in the same workgroup: the bits of a tile launch and
-// its sum over the parts, in one launch.  3 x 512 x 1408 (eleven parts): 4.1 + 6.0 -> 4.0 us.
+// its sum over the parts, in one launch.  3 x 512 x 1408 (eleven parts) in a decoding step: 4.1 + 6.0 -> 4.9 us.
 template <bool DUAL, bool TWO>
 __global__ void __launch_bounds__(kSkinnyWaves * 64, 2)
 gemm_few_rows_parts_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2, void* __restrict__ c, int m,
