@@ -247,6 +247,15 @@ gemm_mfma_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const b
 // four consecutive output columns per lane, stored with one 16-byte (f32) or 8-byte (bf16) access.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// Four bf16 outputs as one number.  Of a struct of two or four the compiler stores the parts one by one wherever another branch ends
+// in a store of the same part, as the ragged end of a row does: the gate/up epilogue wrote nearly every group of four with three
+// stores.  Gate/up products with one store instead: 1639 x 28672 x 4096 341 -> 323 us, 5120 rows 915 -> 884, 1025 rows 208 -> 198, 900 x
+// 2816 x 512 9.5 -> 8.0.
+__device__ __forceinline__ unsigned long long pack_bf16(float a, float b, float c, float d) {
+  return (unsigned long long)f32_to_bf16(a).v | ((unsigned long long)f32_to_bf16(b).v << 16) | ((unsigned long long)f32_to_bf16(c).v << 32) |
+         ((unsigned long long)f32_to_bf16(d).v << 48);
+}
+
 // four consecutive outputs at element o of C, `left` of them inside the row
 __device__ __forceinline__ void store_quad(void* __restrict__ c, size_t o, const float (&v)[4], int epi, bool f32_out, bool vec, int left) {
   if (vec) {
@@ -256,10 +265,7 @@ __device__ __forceinline__ void store_quad(void* __restrict__ c, size_t o, const
       if (epi == EPI_ADD_F32) { const float4 old = *dst; t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w; }
       *dst = t;
     } else {
-      union { bf16 h[4]; uint2 u; } pk;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) pk.h[e] = f32_to_bf16(v[e]);
-      *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(c) + o) = pk.u;
+      *reinterpret_cast<unsigned long long*>(reinterpret_cast<bf16*>(c) + o) = pack_bf16(v[0], v[1], v[2], v[3]);
     }
   } else {
 #pragma unroll
@@ -290,12 +296,7 @@ __device__ __forceinline__ void rope_quad(const RopeOut& o, int row, int pos, un
       b[e] = __builtin_fmaf(hi[e], c[e], lo[e] * s[e]);
     }
   }
-  auto put = [](bf16* p, const f32x4& v) {
-    uint2 pk;
-    pk.x = (uint32_t)f32_to_bf16(v[0]).v | ((uint32_t)f32_to_bf16(v[1]).v << 16);
-    pk.y = (uint32_t)f32_to_bf16(v[2]).v | ((uint32_t)f32_to_bf16(v[3]).v << 16);
-    *reinterpret_cast<uint2*>(p) = pk;
-  };
+  auto put = [](bf16* p, const f32x4& v) { *reinterpret_cast<unsigned long long*>(p) = pack_bf16(v[0], v[1], v[2], v[3]); };
   if (col < ns1) {
     bf16* q = o.q + (size_t)row * ns1 + col;
     put(q, a);

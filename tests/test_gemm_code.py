@@ -86,3 +86,13 @@ def test_nothing_touches_a_fragment_before_the_wait(kernels):
 def test_nothing_is_spilled(kernels):
     for name, lines in kernels.items():
         assert not [l for l in lines if re.match(r"\s+scratch_", l)], name
+
+
+def test_gate_up_outputs_are_stored_eight_bytes_at_a_time(kernels):
+    """One by one at the ragged end of a row, else four bf16 outputs with one store; K parts 16 bytes at a time."""
+    gate_up = {name: lines for name, lines in kernels.items() if re.search(r"EELb1ELb[01]E", name)}
+    assert len(gate_up) == 6
+    for name, lines in gate_up.items():
+        stores = [m[1] for l in lines if (m := re.match(r"\s+(global_store_\w+)", l))]
+        assert set(stores) == {"global_store_short", "global_store_dwordx2", "global_store_dwordx4"}, name
+        assert stores.count("global_store_short") == 4 * stores.count("global_store_dwordx2"), name

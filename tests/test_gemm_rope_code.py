@@ -24,3 +24,4 @@ def test_no_fragment_is_touched_early_or_spilled(tmp_path):
         assert sum(in_asm and op == "ds_read_b128" for _, b in blocks for op, _, in_asm in b) >= 32, name
         assert not _touched_in_flight(blocks), name
         assert not [l for l in lines if re.match(r"\s+scratch_", l)], name
+        assert {m[1] for l in lines if (m := re.match(r"\s+(global_store_\w+)", l))} == {"global_store_dwordx2", "global_store_dwordx4"}, name
