@@ -8,9 +8,11 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-# model widths of one to six 1024-element passes, whole and ragged; rows that cut all tiles, some tiles (1639) and leave a thin row
-@pytest.mark.parametrize("d,rows", [(512, 40), (1152, 100), (2048, 257), (4096, 70), (4096, 1025), (4096, 1639), (5120, 300), (5376, 65)])
-def test_norm_adds_the_parts(d, rows):
+# model widths of one to six 1024-element passes, whole and ragged; rows that cut all tiles, some tiles (1639) and leave a thin row;
+# every width of a tile (192 columns change places in blocks of 64, the others of 128)
+@pytest.mark.parametrize("d,rows,tile", [(512, 40, 0), (1152, 100, 0), (2048, 257, 0), (4096, 70, 0), (4096, 1025, 0), (4096, 1639, 0),
+                                         (5120, 300, 0), (5376, 65, 0)] + [(1152, 100, t) for t in range(7, 14)])
+def test_norm_adds_the_parts(d, rows, tile):
     from paper_2603_13289_amd import binding as rc
     g = torch.Generator(device="cuda")
     g.manual_seed(d + rows)
@@ -35,8 +37,12 @@ def test_norm_adds_the_parts(d, rows):
         torch.cuda.synchronize()
         return k, v, logits, h
 
-    k1, v1, logits1, _ = run(False)
-    k2, v2, logits2, h = run(True)
+    rc.rc_tune_set(rc.RC_TUNE_GEMM_TILE, tile)
+    try:
+        k1, v1, logits1, _ = run(False)
+        k2, v2, logits2, h = run(True)
+    finally:
+        rc.rc_tune_set(rc.RC_TUNE_GEMM_TILE, 0)
     for a, b in ((k1, k2), (v1, v2), (logits1, logits2)):
         assert torch.equal(a, b)
     # the second layer's values against 64 bits, from the kept rows (bf16): operands rounded twice, the result once
