@@ -182,9 +182,9 @@ int est_row_pos(const ReqDev& r, int i) {
 // Measured on the 2048 + 16384-token workload: its sparse layers (1639 selected rows, up to 288 KV tiles each) take
 // 520 us unsplit and 182 + 33 us with chunks of 32; the dense layer and the short prefix-only layers are best left whole.
 // A decoding step (one row per sequence, 8 KV heads, 80 KV tiles) gets chunks of 4: 160 workgroups instead of 40.
-// All of this is measured on the tile kernel (attn_mfma_kernel).  Phases whose requests have one row each run attn_decode_kernel,
-// whose tile steps are several times shorter, and are priced in the same units: the chunks they get are the ones it was
-// measured with, not the best of a fit of its own.
+// All of this is measured on the tile kernel (attn_mfma_kernel).  Phases whose requests have one row each run attn_decode_kernel
+// (0.87 us a tile step and about six of them fixed, over 40 to 320 tiles of one sequence) and are priced by the same constants:
+// the chunks they get are the ones it was measured with, not the best of a fit of its own.
 constexpr float kWgFixedSteps = 4.f;       // fixed cost of a workgroup
 constexpr float kMergeFixedSteps = 3.5f;   // launch of the merge kernel
 constexpr float kMergeBytesPerStep = 8.8e6f;

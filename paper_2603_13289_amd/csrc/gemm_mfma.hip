@@ -279,7 +279,7 @@ __device__ __forceinline__ void store_quad(void* __restrict__ c, size_t o, const
 }
 
 // Four consecutive rotary pairs of a row of q|k|v, rotated and left where they belong: the work and the arithmetic of
-// rope_scatter_kernel.  lo / hi: the columns of the two halves of a head.  In the epilogue of the product it costs 5 us on 110
+// rope_scatter_kernel.  lo / hi: the columns of the two halves of a head.  In the epilogue of the product it costs 2 us of 109
 // (2500 rows) or nothing (60 rows, inside the sum over the K parts); the launch it replaces wrote and read the product in floats:
 // 6 us at 60 rows, 12.7 at 1639, 37 at 5120.
 __device__ __forceinline__ void rope_quad(const RopeOut& o, int row, int pos, unsigned dst, int pair, const f32x4& lo, const f32x4& hi, int ns1,
