@@ -1,4 +1,4 @@
-"""The benchmark script end to end: one JSON line with the fields the harness reads."""
+"""The benchmark script end to end: one JSON line with the fields its readers rely on, and the stages that it adds up."""
 import json
 import os
 import subprocess
