@@ -13,10 +13,17 @@
 // each group of 16.  V is transposed while it is written to LDS, with that same permutation applied,
 // so each operand is one 16-byte LDS read.
 //
-// LDS rows are padded by 16 bytes (K: 272, V^T: 144 bytes apart) so that operand fetches are free of
-// bank conflicts and all LDS addresses are constants off a per-thread base.  K/V rows come from the paged
-// cache through the block table, one tile ahead in registers and one tile ahead in a second pair of LDS
-// buffers, so a tile costs one barrier.
+// LDS rows of K are padded by 16 bytes (272 apart), 16-byte pieces of V^T rows change places by the row, so that operand fetches
+// and writes are free of bank conflicts.  K/V rows come from the paged cache through the block table, one tile ahead in registers
+// and one tile ahead in a second pair of LDS buffers, so a tile costs one barrier.
+//
+// What bounds it: a tile step is a chain of S^T, softmax and O^T in which the LDS reads of the products, the LDS writes of the staging and
+// the loads of the tile two on each keep a unit busy for about 500 cycles of the four wavefronts together.  Side by side with
+// another's instructions they are hidden: the staging writes run under the exponentials (K's before, V's between them), the loads between the
+// matrix instructions of O^T, in a main loop without conditions.  In a bunch, with the staging between the products of S^T, the loads behind
+// it and a table look-up of its own in front of each load, a step took 4000 cycles alone on a compute unit and 5600 with two workgroups; now
+// 2900 and 3350.  Per launch, 4096 queries over 8000 keys, 32 heads on 8: 16-token pages 558 -> 426 us (938 TFLOP/s), contiguous 476 -> 473
+// (at 1.7 GHz: the power limit); 40 heads on 8 739 -> 581, 8 on 8 458 -> 337; pages of 8 522 -> 471.  100 queries over 264 keys 15.9 -> 12.8.
 // KV tiles entirely above the tile's last query position are skipped; the causal mask is applied
 // only in tiles that reach above the tile's first query position.  Workgroups are issued longest
 // first over the whole launch (KV head fastest, query tiles by decreasing KV range).
@@ -34,11 +41,11 @@ static constexpr int BQ = 32;    // query rows per workgroup
 static constexpr int BKV = 64;   // keys per tile
 static constexpr int DH = 128;
 static constexpr int KROW = DH * 2 + 16;   // bytes between K rows in LDS
-static constexpr int VROW = BKV * 2 + 16;  // bytes between V^T rows in LDS
+static constexpr int VROW = BKV * 2;       // bytes between V^T rows in LDS
 static constexpr int K_TILE_BYTES = BKV * KROW;
 static constexpr int V_TILE_BYTES = DH * VROW;
 static constexpr int kLdsTableEntries = 2048;   // block-table entries of the workgroup's KV range kept in LDS (paged caches)
-static constexpr int ATTN_LDS_BYTES = 2 * (K_TILE_BYTES + V_TILE_BYTES) + kLdsTableEntries * 4;
+static constexpr int ATTN_LDS_BYTES = 2 * (K_TILE_BYTES + V_TILE_BYTES);
 static constexpr int PROW = DH + 16;         // floats between the rows of a partial result (see attention_partial_floats)
 static constexpr int kFragAhead = 4;       // LDS operand fragments in flight ahead of the MFMA that uses them
 static constexpr float kRescaleSlack = 8.f;   // log2 units the running maximum may lead the reference exponent
@@ -78,15 +85,12 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   // kernel runs out of registers.  In a group of one to three query heads the wavefronts beyond the group only take
   // their share of the staging; they multiply zeros for head 0 of the group and write nothing.
   constexpr int NW = G < 4 ? 4 : G;
-  constexpr int NT = 64 * NW;
-  // K rows are 256 + 16 bytes, V^T rows 128 + 16 bytes apart.  With 64 banks of 4 bytes, the 16 lanes
-  // that fetch the same 16-byte chunk of 16 consecutive rows then hit every bank exactly once, and every
-  // LDS address in the main loop is a per-thread base plus a compile-time constant.
+  // K rows are 256 + 16 bytes apart.  With 64 banks of 4 bytes, the 16 lanes that fetch the same 16-byte chunk of 16 consecutive rows
+  // then hit every bank exactly once, and every LDS address of K is a per-thread base plus a compile-time constant.
   // Two K and two V^T buffers: tile t lives in buffer t % 2 and tile t + 1 is staged while tile t is multiplied,
   // so one barrier per tile suffices.
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_attn[];
-  unsigned char* const lds_k = lds_attn;                         // [2][BKV * KROW]
-  unsigned char* const lds_vt = lds_attn + 2 * K_TILE_BYTES;     // [2][DH * VROW]
+  unsigned char* const lds_k = lds_attn;                         // [2][BKV * KROW], behind it V^T, [2][DH * VROW]
 
   // late tiles see the most keys: start them first.  With sp.n_chunks > 1 the KV range of a long query
   // tile is cut into chunks of sp.chunk_tiles tiles, one workgroup each, whose partial results are merged
@@ -136,7 +140,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   }
   if (n_valid <= 0) return;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ql = lane & 31, half = lane >> 5;
   const bool active = G >= 4 || wave < G;   // wave-uniform
   const int head = kvh * G + (active ? wave : 0);
@@ -165,168 +169,146 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   float m_run = -INFINITY, l_run = 0.f;
   const float c_scale = 1.4426950408889634f / sqrtf((float)DH);   // log2(e) / sqrt(dh)
 
-  // K/V tile staging: every thread owns KPER 16-byte chunks of the K tile (rows krow0 + i*KSTEP, chunk
-  // tid%16) and VPER blocks of the V tile (4 consecutive keys x 8 d).  The next tile is fetched into
-  // registers while the current one is multiplied.
-  constexpr int KSTEP = NT / 16;
-  constexpr int KPER = (BKV + KSTEP - 1) / KSTEP;
-  constexpr int VPER = (16 + KSTEP - 1) / KSTEP;
+  // K/V tile staging, by the first NS threads: every one owns KPER 16-byte chunks of the K tile (rows krow0 + i*KSTEP, chunk
+  // tid%16), the first 256 one block of the V tile each (4 consecutive keys x 8 d).  Neighbouring lanes have neighbouring chunks of a
+  // row, in both: with neighbouring lanes in different rows of V a load touched 64 cache lines and the eight loads of a tile took 750 to
+  // 1900 cycles to issue.  The next tile is fetched into registers while the current one is multiplied.
+  constexpr int NS = G == 8 ? 512 : 256, KSTEP = NS / 16, KPER = BKV / KSTEP;
+  const bool stages_k = NW * 64 == NS || wave * 64 < NS, stages_v = NW == 4 || wave < 4;   // wave-uniform
   const int krow0 = tid >> 4, kch = tid & 15;      // K: row, 16-byte chunk
-  const int vdch0 = tid >> 4, vquad = tid & 15;    // V: chunk of 8 d, quad of 4 keys
-  const bool contig = g.max_blocks == 1;           // one block per sequence: rows are a linear function of pos
-  const bf16 *kbase = nullptr, *vbase = nullptr;
-  if (contig) {
-    const size_t o = kv_row_offset(g, seq, 0, kvh);
-    kbase = k_pool + o + kch * 8;
-    vbase = v_pool + o;
-  }
-  // Paged cache with power-of-two blocks: the block ids of this workgroup's KV range are copied into LDS once
-  // (lds_tab, filled below when the range is known), so that a row's address costs one LDS read instead of a
-  // block-table load from memory in front of every K/V load (a dependent pair of global loads has twice the
-  // latency the one-tile look-ahead of the fetches has to cover).  Ranges with more blocks than fit, and block
-  // sizes that are no power of two, take the general path.
-  int* const lds_tab = reinterpret_cast<int*>(lds_attn + 2 * (K_TILE_BYTES + V_TILE_BYTES));
-  bool tab_in_lds = false;
-  int tab_first = 0;                               // block index of lds_tab[0]
-  // lds_tab[i] = block id * n_kv_heads + this workgroup's KV head: the pool row of a position is then a shift and an or
-  auto row_offset = [&](int pos) -> size_t {
-    if (!tab_in_lds) return kv_row_offset(g, seq, pos, kvh);
-    const unsigned e = (unsigned)lds_tab[(pos >> g.bs_shift) - tab_first];
-    return ((((size_t)e) << g.bs_shift) | (unsigned)(pos & (g.block_size - 1))) * (size_t)DH;
-  };
+  const int vquad = tid >> 4, vdch = tid & 15;     // V: quad of 4 keys, chunk of 8 d
   // the tile fetched during step t is staged during step t + 1 and multiplied in step t + 2
-  uint4 rk[KPER], rv[VPER][4];
-  // contiguous cache: this thread's first K chunk and V block of KV tile 0; a full tile is then fetched at constant
-  // offsets from one pointer per operand, without per-row position arithmetic or predicates
-  const bf16* const kthread = contig ? kbase + (size_t)krow0 * DH : nullptr;
-  const bf16* const vthread = contig ? vbase + (size_t)(vquad * 4) * DH + vdch0 * 8 : nullptr;
-  // only where every thread owns whole rows / blocks of the tile and registers allow (groups of four query heads; for
-  // a group of five the same short-cut gained 4 % on dense layers and lost 3 % on sparse ones)
-  constexpr bool kFastFetch = G >= 4 && KPER * KSTEP == BKV && VPER * KSTEP == 16;
-  auto fetch_k = [&](int kv0) {
-    const bool full = kv0 + BKV - 1 <= last_pos;   // uniform: only a query tile's last KV tile can be ragged
-    if (kFastFetch && contig && full) {
-      const bf16* kp = kthread + (size_t)kv0 * DH;
-#pragma unroll
-      for (int i = 0; i < KPER; ++i) rk[i] = *reinterpret_cast<const uint4*>(kp + (size_t)i * KSTEP * DH);
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < KPER; ++i) {
-      const int row = krow0 + i * KSTEP;
-      const int pos = kv0 + row;
-      rk[i] = make_uint4(0, 0, 0, 0);
-      if (row < BKV && (full || pos <= last_pos)) {
-        const bf16* src = contig ? kbase + (size_t)pos * DH : k_pool + row_offset(pos) + kch * 8;
-        rk[i] = *reinterpret_cast<const uint4*>(src);
-      }
-    }
+  uint4 rk[KPER], rv[4];
+  // A lane looks up the pool row (of DH elements) of one key of a tile.  In blocks of a multiple of 16 slots the 16 keys of a group lie
+  // one behind the other: lane i looks up group i % 4, and loads go to the scalar row of their group and a constant lane offset.
+  // Other block sizes, and a query tile's last KV tile where it is ragged: key kv0 + lane, rows handed around.  Past the last
+  // position that is the last row again, whose weight there is 0 (the mask sets the score).
+  const bool contig = g.max_blocks == 1;           // one block per sequence
+  const unsigned crow = contig ? (unsigned)(kv_row_offset(g, seq, 0, kvh) / DH) : 0u;
+  const bool by_group = contig || g.bs_shift >= 4;
+  const unsigned k_lane = (unsigned)((krow0 & 15) * DH + kch * 8) * 2, v_lane = (unsigned)((vquad & 3) * 4 * DH + vdch * 8) * 2;
+  auto grouped = [&](int kv0) __attribute__((always_inline)) { return by_group && kv0 + BKV - 1 <= last_pos; };   // uniform
+  auto look_up = [&](int kv0) __attribute__((always_inline)) -> unsigned {
+    const int pos = grouped(kv0) ? kv0 + 16 * (lane & 3) : min(kv0 + lane, last_pos);
+    if (contig) return crow + (unsigned)pos;
+    return (unsigned)(kv_row_offset(g, seq, pos, kvh) / DH);
   };
-  auto fetch_v = [&](int kv0) {
-    const bool full = kv0 + BKV - 1 <= last_pos;
-    if (kFastFetch && contig && full) {
-      const bf16* vp = vthread + (size_t)kv0 * DH;
-#pragma unroll
-      for (int i = 0; i < VPER; ++i)
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) rv[i][kk] = *reinterpret_cast<const uint4*>(vp + (size_t)i * KSTEP * 8 + (size_t)kk * DH);
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < VPER; ++i) {
-      const int dch = vdch0 + i * KSTEP;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int pos = kv0 + vquad * 4 + kk;
-        rv[i][kk] = make_uint4(0, 0, 0, 0);
-        if (dch < 16 && (full || pos <= last_pos)) {
-          const bf16* src = contig ? vbase + (size_t)pos * DH + dch * 8 : v_pool + row_offset(pos) + dch * 8;
-          rv[i][kk] = *reinterpret_cast<const uint4*>(src);
+  auto rsrc_of = [](const void* p) __attribute__((always_inline)) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000); };
+  // the same in two halves, for the main loop: the block of lane i's group is asked for early and not waited for
+  const int tab_shift = contig ? 31 : g.bs_shift;
+  const unsigned tab_mask = contig ? 0x7fffffffu : (unsigned)(g.block_size - 1);
+  const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
+  auto ask_block = [&](int kv0) __attribute__((always_inline)) {
+    return (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(seq_table), 4 * min((kv0 + 16 * (lane & 3)) >> tab_shift, g.max_blocks - 1), 0, 0);
+  };
+  auto group_row = [&](int kv0, int blk) __attribute__((always_inline)) -> unsigned {
+    return (unsigned)(min(max(blk, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * (unsigned)g.block_size + ((unsigned)(kv0 + 16 * (lane & 3)) & tab_mask);
+  };
+  auto group_at = [&](const bf16* pool, unsigned row, int grp) __attribute__((always_inline)) {   // scalar
+    return rsrc_of(pool + (size_t)(unsigned)__builtin_amdgcn_readlane((int)row, grp) * DH);
+  };
+  auto k_chunk = [&](unsigned row, int i) __attribute__((always_inline)) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(k_pool, row, i * (KSTEP / 16) + (NS == 512 ? wave >> 2 : 0)), k_lane, 0, 0));
+  };
+  auto v_chunk_of = [&](unsigned row, int kk) __attribute__((always_inline)) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(v_pool, row, wave & 3), v_lane, kk * DH * 2, 0));
+  };
+  auto fetch = [&](int kv0, unsigned row) __attribute__((always_inline)) {
+    const unsigned char* const kp = reinterpret_cast<const unsigned char*>(k_pool);
+    const unsigned char* const vp = reinterpret_cast<const unsigned char*>(v_pool);
+    if (grouped(kv0)) {
+      if (stages_k) {
+        rk[0] = k_chunk(row, 0);
+        rk[1] = k_chunk(row, 1);
+        if constexpr (KPER == 4) {
+          rk[2] = k_chunk(row, 2);
+          rk[3] = k_chunk(row, 3);
         }
       }
+      if (stages_v) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) rv[kk] = v_chunk_of(row, kk);
+      }
+      return;
+    }
+    int th = tid;
+    asm volatile("" : "+v"(th));   // lane numbers worked out here each time: kept over the main loop they took its registers
+    if (stages_k) {
+#pragma unroll
+      for (int i = 0; i < KPER; ++i)
+        rk[i] = *reinterpret_cast<const uint4*>(kp + (size_t)(unsigned)__shfl((int)row, (th >> 4) + i * KSTEP, 64) * (DH * 2) + (th & 15) * 16);
+    }
+    if (stages_v) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        rv[kk] = *reinterpret_cast<const uint4*>(vp + (size_t)(unsigned)__shfl((int)row, ((th >> 4) * 4 + kk) & 63, 64) * (DH * 2) + (th & 15) * 16);
     }
   };
-  // V transposed: key = 16 grp + 8 a + 4 h + c goes to column 16 grp + 8 h + 4 a + c; a quad shares (grp, a, h)
-  const int vkey0 = vquad * 4;
-  const int vcol = (vkey0 & ~15) + 8 * ((vkey0 >> 2) & 1) + 4 * ((vkey0 >> 3) & 1);
+  // V transposed: key = 16 grp + 8 a + 4 h + c goes to column 16 grp + 8 h + 4 a + c; a quad shares (grp, a, h).
+  // In LDS, 16-byte chunk c of V^T row d is chunk c ^ (d/2 & 7) ^ (d/16) of row d ^ (d/8 & 1): the sixteen rows of an operand fetch
+  // then meet all banks once, and so do the writes of a wavefront, which has four quads of sixteen d / 8.
+  // Row pair (2 m, 2 m + 1) of a thread's eight d: chunk v_chunk ^ m; odd d / 8 have the two rows exchanged.
+  const int vgrp = vquad >> 2, v_odd = vdch & 1;
+  const int v_chunk = (2 * vgrp + (vquad & 1)) ^ (4 * v_odd) ^ (vdch >> 1);
   unsigned char* const k_wr = lds_k + krow0 * KROW + kch * 16;
-  unsigned char* const v_wr = lds_vt + vdch0 * 8 * VROW + vcol * 2;
-  auto stage_k = [&](auto buf) {
+  const unsigned v_wr = 2 * K_TILE_BYTES + vdch * 8 * VROW + 16 * v_chunk + 8 * ((vquad >> 1) & 1);   // chunk ^ m: bits 4-6 of the address
+  // byte select: the low halves of two words (even d) or the high ones, for a thread's first and second row of a pair
+  const uint32_t v_sel0 = v_odd ? 0x07060302u : 0x05040100u, v_sel1 = v_odd ? 0x05040100u : 0x07060302u;
+  auto stage_k = [&](auto buf) __attribute__((always_inline)) {
     constexpr int KOFF = decltype(buf)::value * K_TILE_BYTES;
+    if (!stages_k) return;
 #pragma unroll
-    for (int i = 0; i < KPER; ++i)
-      if (krow0 + i * KSTEP < BKV) *reinterpret_cast<uint4*>(k_wr + KOFF + i * KSTEP * KROW) = rk[i];
+    for (int i = 0; i < KPER; ++i) *reinterpret_cast<uint4*>(k_wr + KOFF + i * KSTEP * KROW) = rk[i];
   };
   // V^T rows e_begin .. e_end - 1 (of the 8 head-dim elements a thread's block covers)
-  auto stage_v = [&](auto buf, int e_begin, int e_end) {
+  auto stage_v = [&](auto buf, int e_begin, int e_end) __attribute__((always_inline)) {
     constexpr int VOFF = decltype(buf)::value * V_TILE_BYTES;
+    if (!stages_v) return;
+    const uint32_t w[4][4] = {{rv[0].x, rv[0].y, rv[0].z, rv[0].w},
+                              {rv[1].x, rv[1].y, rv[1].z, rv[1].w},
+                              {rv[2].x, rv[2].y, rv[2].z, rv[2].w},
+                              {rv[3].x, rv[3].y, rv[3].z, rv[3].w}};
 #pragma unroll
-    for (int i = 0; i < VPER; ++i) {
-      if (vdch0 + i * KSTEP >= 16) continue;
-      const uint32_t w[4][4] = {{rv[i][0].x, rv[i][0].y, rv[i][0].z, rv[i][0].w},
-                                {rv[i][1].x, rv[i][1].y, rv[i][1].z, rv[i][1].w},
-                                {rv[i][2].x, rv[i][2].y, rv[i][2].z, rv[i][2].w},
-                                {rv[i][3].x, rv[i][3].y, rv[i][3].z, rv[i][3].w}};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (e < e_begin || e >= e_end) continue;
-        const int wi = e >> 1;
-        // byte select: even e packs the low halves of two words, odd e the high halves
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-        uint2 pk;
-        pk.x = __builtin_amdgcn_perm(w[1][wi], w[0][wi], sel);
-        pk.y = __builtin_amdgcn_perm(w[3][wi], w[2][wi], sel);
-        *reinterpret_cast<uint2*>(v_wr + VOFF + (i * KSTEP * 8 + e) * VROW) = pk;
-      }
+    for (int e = 0; e < 8; ++e) {
+      if (e < e_begin || e >= e_end) continue;
+      const int m = e >> 1;
+      const uint32_t sel = (e & 1) ? v_sel1 : v_sel0;
+      uint2 pk;
+      pk.x = __builtin_amdgcn_perm(w[1][m], w[0][m], sel);
+      pk.y = __builtin_amdgcn_perm(w[3][m], w[2][m], sel);
+      *reinterpret_cast<uint2*>(lds_attn + (v_wr ^ (16 * m)) + VOFF + e * VROW) = pk;
     }
   };
-  // operand fetch addresses: K block b, dh step s -> k_rd + b*32*KROW + s*32 ; V^T block db, key step tt
+  // operand fetch addresses: K block b, dh step s -> k_rd + b*32*KROW + s*32 ; V^T block db, key step tt -> (v_rd ^ 32 (tt ^ db)) + db*32*VROW
   const unsigned char* const k_rd = lds_k + ql * KROW + half * 16;
-  const unsigned char* const v_rd = lds_vt + ql * VROW + half * 16;
+  const unsigned v_rd = 2 * K_TILE_BYTES + (ql ^ ((ql >> 3) & 1)) * VROW + 16 * (half ^ ((ql >> 1) & 7) ^ (ql >> 4));
 
   const int n_kv_tiles = last_pos / BKV + 1;
   const bool is_split = sp.n_chunks > 1 && split_tile >= 0 && n_kv_tiles > sp.long_thr;
   const int t_begin = is_split ? chunk * sp.chunk_tiles : 0;
   const int t_end = is_split ? min(n_kv_tiles, t_begin + sp.chunk_tiles) : n_kv_tiles;
   if (t_begin >= t_end || (!is_split && chunk != 0)) return;   // nothing for this workgroup (uniform)
-  if (!contig && g.bs_shift >= 0) {
-    tab_first = (t_begin * BKV) >> g.bs_shift;
-    const int n_blk = min(((t_end * BKV - 1) >> g.bs_shift), g.max_blocks - 1) - tab_first + 1;
-    if (n_blk <= kLdsTableEntries) {   // uniform
-      for (int i = tid; i < n_blk; i += NT) {
-        const int blk = g.block_table[(size_t)seq * g.max_blocks + tab_first + i];
-        lds_tab[i] = min(max(blk, 0), g.n_blocks - 1) * g.n_kv_heads + kvh;
-      }
-      tab_in_lds = true;
-      __syncthreads();
-    }
-  }
   const std::integral_constant<int, 0> buf0;
   const std::integral_constant<int, 1> buf1;
   // prologue: the first tile goes to buffer 0, the second one is on its way in registers
-  fetch_k(t_begin * BKV);
-  fetch_v(t_begin * BKV);
+  fetch(t_begin * BKV, look_up(t_begin * BKV));
   stage_k(buf0);
   stage_v(buf0, 0, 8);
-  if (t_begin + 1 < t_end) {
-    fetch_k((t_begin + 1) * BKV);
-    fetch_v((t_begin + 1) * BKV);
-  }
+  if (t_begin + 1 < t_end) fetch((t_begin + 1) * BKV, look_up((t_begin + 1) * BKV));
   __syncthreads();
   // step i (tile t = t_begin + i) multiplies buffer i % 2; meanwhile it stages tile t + 1 into the other buffer
-  // (free since the barrier that ended step i - 1) and starts the loads of tile t + 2.  That staging is vector-ALU
-  // and LDS-write work, which is dealt out between the MFMAs of S^T so that it runs while the matrix pipe is busy.
-  auto tile_step = [&](int t, auto buf) {
+  // (free since the barrier that ended step i - 1) and starts the loads of tile t + 2.  how: 1 in the main loop, where there are such
+  // tiles, whole ones; 2 the same for wavefronts beyond the fourth, which stage no V (and no K but in groups of eight); 0 anywhere.
+  auto tile_step = [&](int t, auto buf, auto how) __attribute__((always_inline)) {
+    constexpr bool steady = decltype(how)::value > 0, K_TOO = decltype(how)::value == 1 || G == 8, V_TOO = decltype(how)::value == 1;
     constexpr int KOFF = decltype(buf)::value * K_TILE_BYTES, VOFF = decltype(buf)::value * V_TILE_BYTES;
     const std::integral_constant<int, 1 - decltype(buf)::value> other;
     const int kv0 = t * BKV;
     const bool has_next = t + 1 < t_end, has_next2 = t + 2 < t_end;
-    auto staging_slice = [&](int i) {   // i-th of the 16 gaps between the MFMAs of S^T
-      if (!has_next) return;
-      if (i == 0) stage_k(other);
-      else if (i >= 1 && i <= 4) stage_v(other, 2 * (i - 1), 2 * i);
-    };
-
+    unsigned row2 = 0;   // of the tile two on: asked for here, used behind the first product
+    int blk2 = 0;
+    if constexpr (!steady) row2 = look_up(kv0 + 2 * BKV);
+    else if constexpr (K_TOO) blk2 = ask_block(kv0 + 2 * BKV);
     // S^T = K Q^T : two blocks of 32 keys.  The two accumulator chains alternate and the K fragments are read
     // kFragAhead MFMAs ahead of their use, so that neither the LDS latency nor the MFMA dependency is exposed.
     f32x16 acc_s[2];
@@ -345,21 +327,30 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
       for (int i = 0; i < 16; ++i) {
         acc_s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i % kFragAhead], qf[i >> 1], i < 2 ? zero : acc_s[i & 1], 0, 0, 0);
         if (i + kFragAhead < 16) kf[i % kFragAhead] = k_frag(i + kFragAhead);
-        staging_slice(i);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (has_next2) {
-      fetch_k(kv0 + 2 * BKV);
-      fetch_v(kv0 + 2 * BKV);
-    }
     // the first V^T fragments do not depend on the softmax: their LDS reads run under it
     auto v_frag = [&](int i) {     // step i: head-dim block i & 3, key step i >> 2
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(v_rd + VOFF + (i & 3) * 32 * VROW + (i >> 2) * 32));
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds_attn + (v_rd ^ (32 * ((i & 3) ^ (i >> 2)))) + VOFF + (i & 3) * 32 * VROW));
     };
     bf16x8 vf[kFragAhead];
 #pragma unroll
     for (int i = 0; i < kFragAhead; ++i) vf[i] = v_frag(i);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (steady) {
+      if constexpr (K_TOO) {
+        stage_k(other);
+        row2 = group_row(kv0 + 2 * BKV, blk2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      if (has_next) {
+        stage_k(other);
+        stage_v(other, 0, 8);
+      }
+      if (has_next2) fetch(kv0 + 2 * BKV, row2);
+    }
     // running softmax on raw scores; the 1/sqrt(dh) * log2(e) factor is folded into the exponent.
     // Element e of block b is key kv0 + 32 b + 8 (e/4) + 4 half + e%4.  Only tiles that reach above the
     // tile's first query position need the causal mask.
@@ -410,6 +401,12 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
           psum += p[j];
         }
         pf[2 * b + u] = __builtin_convertvector(p, bf16x8);
+        asm volatile("" : "+v"(psum));   // added up here: put off, the 32 weights stayed in registers over the second product
+        if constexpr (V_TOO) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (b == 0) stage_v(other, 4 * u, 4 * u + 4);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     l_run += psum;
     // O^T += V^T P : four accumulator chains alternate, fragments read kFragAhead MFMAs ahead
@@ -417,12 +414,29 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     for (int i = 0; i < 16; ++i) {
       acc_o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % kFragAhead], pf[i >> 2], acc_o[i & 3], 0, 0, 0);
       if (i + kFragAhead < 16) vf[i % kFragAhead] = v_frag(i + kFragAhead);
+      if constexpr (steady) {
+        if constexpr (K_TOO)
+          if (i % 2 == 0 && i < 2 * KPER) rk[i / 2] = k_chunk(row2, i / 2);
+        if constexpr (V_TOO)
+          if (i % 2 == 0 && i >= 2 * KPER && i < 2 * KPER + 8) rv[i / 2 - KPER] = v_chunk_of(row2, i / 2 - KPER);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     __syncthreads();   // tile t fully consumed, tile t + 1 fully staged
   };
-  for (int t = t_begin; t < t_end; t += 2) {
-    tile_step(t, buf0);
-    if (t + 1 < t_end) tile_step(t + 1, buf1);
+  int t = t_begin;
+  auto steady_tiles = [&](auto how) __attribute__((always_inline)) {
+    for (; t + 3 < t_end && grouped((t + 3) * BKV); t += 2) {
+      tile_step(t, buf0, how);
+      tile_step(t + 1, buf1, how);
+    }
+  };
+  if (stages_v) steady_tiles(std::integral_constant<int, 1>{});
+  else steady_tiles(std::integral_constant<int, 2>{});
+  const std::integral_constant<int, 0> general;
+  for (; t < t_end; t += 2) {
+    tile_step(t, buf0, general);
+    if (t + 1 < t_end) tile_step(t + 1, buf1, general);
   }
 
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
