@@ -148,7 +148,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   const int my_row = r0 + (q_ok ? ql : 0);
   const int my_pos = q_ok ? row_pos[my_row] : 0;
   const int first_pos = row_pos[r0];
-  const int last_pos = row_pos[r0 + n_valid - 1];
+  const int last_pos = max((int)min((long)row_pos[r0 + n_valid - 1], (long)g.max_blocks * g.block_size - 1), 0);   // never past the cache
 
   // Q as B operands: lane (q, half) holds Q[q][16 s + 8 half .. +7], s = 0..7
   bf16x8 qf[8];
