@@ -6,10 +6,12 @@
 // Per key block a wavefront computes
 //   S^T[key][q] = K[key][:] . Q[q][:]      lane holds query lane % 16, keys 4 (lane / 16) + 0..3
 //   O^T[d][q]  += V^T[d][key] P[key][q]    P's operand is S^T's result register as it stands
-// Bound by latency: float models have a few hundred keys, so the chain of one wavefront is a handful of blocks; the next
-// block's keys are requested before the current one is used.  Measured in a call, 384 rows x 4 heads of 64 x up to 384
-// keys: 146 us with one wavefront per (row, head) on the vector ALUs, 15.7 us now.
+// Bound by latency: float models have a few hundred keys, so the chain of one wavefront is a handful of blocks; the next block's keys
+// and values are requested before the current one's softmax, and the page they are on a block before that, so that no load waits
+// for a look-up.  Measured in a call, 384 rows x 4 heads of 64 x up to 384 keys: 146 us with one wavefront per (row, head) on the
+// vector ALUs, 15.1 with values and their pages looked up in the block that uses them, 12.2 now (188 rows: 15.3 -> 12.8).
 #include <climits>
+#include <type_traits>
 
 #include "common.h"
 
@@ -25,7 +27,7 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
   constexpr int NB = DH / 16, NW = DH == 64 ? 8 : 4;   // wavefronts: what 32 KB of partial results allow
   __shared__ float lds_o[NW][DH][16];
   __shared__ float2 lds_ml[NW][16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, qi = lane & 15, kq = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), qi = lane & 15, kq = lane >> 4;
   const int head = blockIdx.y, kvh = head / (n_q_heads / g.n_kv_heads);
   int r0 = blockIdx.x * 16, n_valid, seq = fixed_seq;
   if (table) {   // the tile-th group of 16 rows, counted request by request
@@ -53,27 +55,52 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
   const float scale = 1.4426950408889634f / sqrtf((float)DH);   // scores in log2 units
   const float* qrow = q + ((size_t)(r0 + (q_ok ? qi : 0)) * n_q_heads + head) * DH;
   f32x4a fq[NB], fk[NB], acc[NB];
+  float fv[2][NB][4];   // V[key 4 kq + c][d]: the operand of instruction c, of this block and the next
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
     fq[t] = q_ok ? *reinterpret_cast<const f32x4a*>(qrow + 16 * t + 4 * kq) * scale : f32x4a{0.f, 0.f, 0.f, 0.f};
     acc[t] = f32x4a{0.f, 0.f, 0.f, 0.f};
   }
   float m_run = -INFINITY, l_run = 0.f;
+  last_pos = max((int)min((long)__builtin_amdgcn_readfirstlane(last_pos), (long)g.max_blocks * g.block_size - 1), 0);   // never past the cache
   const int n_blocks = last_pos / 16 + 1;
-  auto fetch_k = [&](int kb) {
-    const float* krow = k_pool + kv_row_offset(g, seq, min(kb * 16 + qi, last_pos), kvh);
+  // Pages of a multiple of 16 slots hold a block's keys one behind the other: its page is one scalar read, a block ahead of the loads
+  // that hang on it.  Other page sizes look every key up.  Keys past the last position repeat it.
+  const bool contig = g.max_blocks == 1, grouped = contig || g.bs_shift >= 4;
+  const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
+  auto page_of = [&](int kb) {
+    return grouped ? seq_table[contig ? 0 : min(min(kb, n_blocks - 1) * 16 >> g.bs_shift, g.max_blocks - 1)] : 0;
+  };
+  auto offset_of = [&](int kb, int j, int page) -> size_t {   // of key j of the block
+    if (!grouped) return kv_row_offset(g, seq, min(kb * 16 + j, last_pos), kvh);
+    const int first = contig ? kb * 16 : kb * 16 & (g.block_size - 1);
+    return (((size_t)min(max(page, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * g.block_size + first + min(j, last_pos - kb * 16)) * DH;
+  };
+  auto fetch_k = [&](int kb, int page) {
+    const float* krow = k_pool + offset_of(kb, qi, page);
 #pragma unroll
     for (int t = 0; t < NB; ++t) fk[t] = *reinterpret_cast<const f32x4a*>(krow + 16 * t + 4 * kq);
   };
-  if (wave < n_blocks) fetch_k(wave);
-  for (int kb = wave; kb < n_blocks; kb += NW) {
-    float fv[NB][4];   // V[key 4 kq + c][d]: the operand of instruction c
+  auto fetch_v = [&](auto buf, int kb, int page) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const float* vrow = v_pool + kv_row_offset(g, seq, min(kb * 16 + 4 * kq + c, last_pos), kvh) + qi;
+      const float* vrow = v_pool + offset_of(kb, 4 * kq + c, page) + qi;
 #pragma unroll
-      for (int t = 0; t < NB; ++t) fv[t][c] = vrow[16 * t];
+      for (int t = 0; t < NB; ++t) fv[decltype(buf)::value][t][c] = vrow[16 * t];
     }
+  };
+  int page = 0;   // of the wavefront's next block
+  const std::integral_constant<int, 0> buf0;
+  const std::integral_constant<int, 1> buf1;
+  if (wave < n_blocks) {
+    const int first = page_of(wave);
+    page = page_of(wave + NW);
+    fetch_k(wave, first);
+    fetch_v(buf0, wave, first);
+  }
+  auto block = [&](auto buf, auto other, int kb) {
+    constexpr int B = decltype(buf)::value;
+    const int page2 = page_of(kb + 2 * NW);
     f32x4a s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
     for (int t = 0; t < NB; t += 2)
@@ -82,7 +109,11 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
         s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(fk[t][c], fq[t][c], s0, 0, 0, 0);
         s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(fk[t + 1][c], fq[t + 1][c], s1, 0, 0, 0);
       }
-    if (kb + NW < n_blocks) fetch_k(kb + NW);
+    if (kb + NW < n_blocks) {
+      fetch_k(kb + NW, page);
+      fetch_v(other, kb + NW, page);
+    }
+    page = page2;
     s0 += s1;
     float mx = -INFINITY;
 #pragma unroll
@@ -111,20 +142,20 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
 #pragma unroll
       for (int t = 0; t < NB; ++t)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) z = fmaf(fv[t][c], 0.f, z);
+        for (int c = 0; c < 4; ++c) z = fmaf(fv[B][t][c], 0.f, z);
       odd = __any(z != z);
       if (odd) {
 #pragma unroll
         for (int t = 0; t < NB; ++t)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) fv[t][c] = isfinite(fv[t][c]) ? fv[t][c] : 0.f;
+          for (int c = 0; c < 4; ++c) fv[B][t][c] = isfinite(fv[B][t][c]) ? fv[B][t][c] : 0.f;
       }
     }
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       acc[t] *= corr;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[t][c], s0[c], acc[t], 0, 0, 0);
+      for (int c = 0; c < 4; ++c) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[B][t][c], s0[c], acc[t], 0, 0, 0);
     }
     if (odd) {
 #pragma unroll 1
@@ -141,6 +172,10 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
             if (!isfinite(vrow[16 * t + e])) acc[t][e] += p * vrow[16 * t + e];
       }
     }
+  };
+  for (int kb = wave; kb < n_blocks; kb += 2 * NW) {
+    block(buf0, buf1, kb);
+    if (kb + NW < n_blocks) block(buf1, buf0, kb + NW);
   }
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
