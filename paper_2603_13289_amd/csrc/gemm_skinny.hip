@@ -53,26 +53,28 @@ __device__ inline float silu_s(float x) { return x / (1.0f + __expf(-x)); }
 // gather 10.3 -> 46.3.  More than four rows keep the norm's own launch: every workgroup would read and hold them all.
 // ROPE: the columns are q, k and v heads of 128 (RopeOut), below ns1 of w, below ns2 of w2, the rest of w3; a workgroup has columns 8 j .. 8 j + 7 of both halves of a head, i.e.
 // eight whole rotary pairs, and its epilogue does what rope_scatter_kernel does with a row, in the same arithmetic.
-template <bool DUAL, bool TWO, int U, int NORM, bool ROPE>
-__global__ void __launch_bounds__(kSkinnyWaves * 64, U == 8 || (DUAL && TWO) ? 2 : 4)
-gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
-                   const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
-                   int epi, const int* __restrict__ m_live, NormIn norm, RopeOut rope) {
-  static_assert(!(NORM > 0 && TWO) && !(DUAL && ROPE), "");
-  constexpr int TILES = (DUAL ? 2 : 1) * (TWO ? 2 : 1), UP = TWO ? 2 : 1;   // tiles: gate rows 0-15 (16-31), up rows 0-15 (16-31)
+// WIDE: a workgroup owns 32 columns, as two sets of 16 (takes_wide).
+template <bool DUAL, bool TWO, int U, int NORM, bool ROPE, bool WIDE>
+__device__ __forceinline__ void few_rows_body(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
+                                              const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
+                                              int epi, const int* __restrict__ m_live, const NormIn& norm, const RopeOut& rope) {
+  static_assert(!(NORM > 0 && (TWO || WIDE)) && !(DUAL && (ROPE || WIDE)), "");
+  constexpr bool SETS = DUAL || WIDE;   // two sets of 16 weight rows: gate and up, or neighbouring columns
+  constexpr int TILES = (SETS ? 2 : 1) * (TWO ? 2 : 1), UP = TWO ? 2 : 1;   // tiles: first set rows 0-15 (16-31), second set rows 0-15 (16-31)
+  constexpr int PAIRS = WIDE ? 16 : 8;   // ROPE: rotary pairs of a workgroup
   __shared__ float part[kSkinnyWaves][TILES][64][4];   // [wave][tile][lane][e]
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_rows[];   // NORM: [m][k] bf16, rows norm_pitch(k) bytes apart
   __shared__ float norm_red[NORM > 0 ? NORM : 1][kSkinnyWaves];
-  __shared__ float2 lds_cs[ROPE ? 32 : 1][8];
+  __shared__ float2 lds_cs[ROPE ? 32 : 1][PAIRS];
   __shared__ unsigned lds_dst[ROPE ? 32 : 1];
   m = live_count(m, m_live);
   if (m <= 0) return;
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = (int)blockIdx.x * 16;
-  // ROPE: columns 0-7 and 8-15 of the tile are partners, half a head apart
-  const int head = (int)blockIdx.x >> 3;
-  int dim = ((int)blockIdx.x & 7) * 8 + (lane & 7) + 64 * ((lane >> 3) & 1);
+  const int n0 = (int)blockIdx.x * (WIDE ? 32 : 16);
+  // ROPE: columns 0-7 and 8-15 of a set are partners, half a head apart; WIDE: the second set is the next eight pairs
+  const int head = n0 >> 7, pair0 = (n0 & 127) >> 1;
+  int dim = pair0 + (lane & 7) + 64 * ((lane >> 3) & 1);
   int col = ROPE ? head * 128 + dim : n0 + (lane & 15);
   const int kw = k / kSkinnyWaves;
   const size_t koff = (size_t)wave * kw + 8 * (lane >> 4);
@@ -81,11 +83,12 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
   if constexpr (ROPE) pw = (col < ns1 ? w + (size_t)col * k : (col < ns2 ? w2 + (size_t)(col - ns1) * k : w3 + (size_t)(col - ns2) * k)) + koff;
   else pw = w + (size_t)col * k + koff;
   if constexpr (DUAL) pu = w2 + (size_t)col * k + koff;
+  else if constexpr (WIDE) pu = pw + (size_t)(ROPE ? 8 : 16) * k;   // of the same matrix: its columns are whole heads
   const bf16* pa0 = a + (size_t)min(lane & 15, m - 1) * k + koff;
   const bf16* pa1 = a + (size_t)min(16 + (lane & 15), m - 1) * k + koff;
   const unsigned char* la0 = lds_rows + (size_t)min(lane & 15, m - 1) * norm_pitch(k) + 2 * koff;
   f32x4s g0 = {0.f, 0.f, 0.f, 0.f}, g1 = g0, u0 = g0, u1 = g0;
-  bf16x8s fb[2][U], fu[2][DUAL ? U : 1], fa0[2][NORM > 0 ? 1 : U], fa1[2][TWO ? U : 1];
+  bf16x8s fb[2][U], fu[2][SETS ? U : 1], fa0[2][NORM > 0 ? 1 : U], fa1[2][TWO ? U : 1];
   const int steps = kw / 32;
   auto load = [&](auto set, int first, auto ragged) {   // ragged: some steps of the set may lie past the last one
     constexpr int S = decltype(set)::value;
@@ -94,7 +97,7 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
       if (decltype(ragged)::value && first + i >= steps) continue;
       const int o = 32 * (first + i);
       fb[S][i] = *reinterpret_cast<const bf16x8s*>(pw + o);
-      if constexpr (DUAL) fu[S][i] = *reinterpret_cast<const bf16x8s*>(pu + o);
+      if constexpr (SETS) fu[S][i] = *reinterpret_cast<const bf16x8s*>(pu + o);
       if constexpr (NORM == 0) fa0[S][i] = *reinterpret_cast<const bf16x8s*>(pa0 + o);
       if constexpr (TWO) fa1[S][i] = *reinterpret_cast<const bf16x8s*>(pa1 + o);
     }
@@ -109,7 +112,7 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
       else f = fa0[S][i];
       g0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, fb[S][i], g0, 0, 0, 0);
       if constexpr (TWO) g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[S][i], fb[S][i], g1, 0, 0, 0);
-      if constexpr (DUAL) {
+      if constexpr (SETS) {
         u0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, fu[S][i], u0, 0, 0, 0);
         if constexpr (TWO) u1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[S][i], fu[S][i], u1, 0, 0, 0);
       }
@@ -172,20 +175,20 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
     }
     lds_barrier();
   };
-  // ROPE: thread 8 r + p fetches the angle of pair p of the tile for row r, and the row's place in the cache; they wait in LDS for
+  // ROPE: thread PAIRS r + p fetches the angle of pair p of the tile for row r, and the row's place in the cache; they wait in LDS for
   // the epilogue.  Every wavefront asks: a load that only some have in flight would make the compiler wait for all.
   int rope_pos;
   unsigned rope_dst;
   float2 rope_cs;
   auto rope_load = [&]() {
     if constexpr (ROPE) {
-      const int r = min(tid >> 3, m - 1);
+      const int r = min(tid / PAIRS, m - 1);
       rope_pos = rope.row_pos[r];
       rope_dst = rope.row_dst[r];
     }
   };
   auto rope_angles = [&]() {
-    if constexpr (ROPE) rope_cs = rope.tab[(size_t)rope_pos * 64 + ((int)blockIdx.x & 7) * 8 + (tid & 7)];
+    if constexpr (ROPE) rope_cs = rope.tab[(size_t)rope_pos * 64 + pair0 + tid % PAIRS];
   };
 
   const std::integral_constant<int, 0> s0;
@@ -236,29 +239,34 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
     // went through scratch memory (q|k|v of 20 rows of 4096 in a decoding step: 21.0 us with and 20.9 without, of 32 rows 24.9)
     lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     tid = 64 * wave + lane;
-    dim = ((int)blockIdx.x & 7) * 8 + (lane & 7) + 64 * ((lane >> 3) & 1);
+    dim = pair0 + (lane & 7) + 64 * ((lane >> 3) & 1);
     col = head * 128 + dim;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     part[wave][0][lane][e] = g0[e];
     if constexpr (TWO) part[wave][1][lane][e] = g1[e];
-    if constexpr (DUAL) part[wave][UP][lane][e] = u0[e];
-    if constexpr (DUAL && TWO) part[wave][UP + 1][lane][e] = u1[e];
+    if constexpr (SETS) part[wave][UP][lane][e] = u0[e];
+    if constexpr (SETS && TWO) part[wave][UP + 1][lane][e] = u1[e];
   }
   if constexpr (ROPE) {
     if constexpr (!kRopeEarly) {
       rope_load();
       rope_angles();
     }
-    if (tid < 256) {
-      lds_cs[tid >> 3][tid & 7] = rope_cs;
-      if ((tid & 7) == 0) lds_dst[tid >> 3] = rope_dst;
+    if (tid < 32 * PAIRS) {
+      lds_cs[tid / PAIRS][tid % PAIRS] = rope_cs;
+      if (tid % PAIRS == 0) lds_dst[tid / PAIRS] = rope_dst;
     }
   }
   __syncthreads();
-  // wavefront 0 finishes rows 0-15, wavefront 1 rows 16-31
-  if (wave > (TWO ? 1 : 0)) return;
+  // wavefront 0 finishes rows 0-15, wavefront 1 rows 16-31; WIDE: of the first set, the next ones those of the second
+  if (wave >= UP * (WIDE ? 2 : 1)) return;
+  const int rows16 = WIDE ? wave % UP : wave, second = WIDE ? wave / UP : 0;
+  if constexpr (WIDE) {
+    dim += 8 * second;
+    col += (ROPE ? 8 : 16) * second;
+  }
   float gs[4] = {0.f, 0.f, 0.f, 0.f}, us[4] = {0.f, 0.f, 0.f, 0.f};
   for (int p = 0; p < kSkinnyWaves; ++p) {
 #pragma unroll
@@ -272,9 +280,9 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float other = __shfl_xor(gs[e], 8, 64);
-      const int row = wave * 16 + 4 * (lane >> 4) + e;
+      const int row = rows16 * 16 + 4 * (lane >> 4) + e;
       if (row >= m) continue;
-      const float2 cs = lds_cs[row][lane & 7];
+      const float2 cs = lds_cs[row][8 * second + (lane & 7)];
       const unsigned dst = lds_dst[row];
       float v = gs[e];
       if (!is_v) v = dim < 64 ? fmaf(v, cs.x, -(other * cs.y)) : fmaf(v, cs.x, other * cs.y);
@@ -291,7 +299,7 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int row = wave * 16 + 4 * (lane >> 4) + e;
+    const int row = rows16 * 16 + 4 * (lane >> 4) + e;
     if (row >= m) continue;
     const size_t o = (size_t)row * ldc + col;
     if (DUAL) reinterpret_cast<bf16*>(c)[o] = f32_to_bf16(silu_s(gs[e]) * us[e]);
@@ -299,6 +307,22 @@ gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const
     else if (epi == EPI_ADD_F32) reinterpret_cast<float*>(c)[o] += gs[e];
     else reinterpret_cast<bf16*>(c)[o] = f32_to_bf16(gs[e]);
   }
+}
+
+template <bool DUAL, bool TWO, int U, int NORM, bool ROPE>
+__global__ void __launch_bounds__(kSkinnyWaves * 64, U == 8 || (DUAL && TWO) ? 2 : 4)
+gemm_skinny_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2,
+                   const bf16* __restrict__ w3, int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc,
+                   int epi, const int* __restrict__ m_live, NormIn norm, RopeOut rope) {
+  few_rows_body<DUAL, TWO, U, NORM, ROPE, false>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, m_live, norm, rope);
+}
+
+template <bool TWO, bool ROPE>
+__global__ void __launch_bounds__(kSkinnyWaves * 64, 2)
+gemm_wide_few_rows_kernel(const bf16* __restrict__ a, const bf16* __restrict__ w, const bf16* __restrict__ w2, const bf16* __restrict__ w3,
+                          int ns1, int ns2, void* __restrict__ c, int m, int n, int k, int ldc, int epi, const int* __restrict__ m_live,
+                          RopeOut rope) {
+  few_rows_body<false, TWO, TWO ? 4 : 8, 0, ROPE, true>(a, w, w2, w3, ns1, ns2, c, m, n, k, ldc, epi, m_live, NormIn{}, rope);
 }
 
 // Products of few rows whose K is no multiple of 256: summed in the K parts of the tile kernels' partition (`parts` of `part_steps`
@@ -381,6 +405,18 @@ hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* 
 
 bool gemm_skinny_applies(int m, int n, int k) { return m >= 1 && m <= 32 && n % 16 == 0 && k % (kSkinnyWaves * 32) == 0; }
 
+// Workgroups of 32 columns.  Every workgroup reads all rows of activations, from the L2; half as many workgroups read half as much, but
+// have half the wavefronts to keep weights coming.  Where 16 columns each make more than one workgroup but fewer than two to a
+// compute unit, some units have twice the work of others, and the uneven round goes as well: from five rows on, with K = 4096 from twelve
+// (5120 x 27648, 5 / 16 / 32 rows: 73.0 / 98.5 / 146 -> 64.6 / 78.2 / 99.3 us; 7168 x 5120 17.7 / 23.0 / 32.6 -> 16.3 / 18.9 /
+// 23.6; 6144 x 4096, 10 / 16 / 32 rows: 15.2 / 17.2 / 23.8 -> 15.2 / 15.7 / 17.7).  Two even rounds or more: from 24 rows on (32768 x 4096,
+// 17 / 24 / 32 rows: 69.7 / 78.3 / 88.0 -> 71.9 / 74.0 / 75.5).  Fewer than 160 would leave the chip idle (4096 x 14336, 16 rows: 29.8 -> 41.8).
+static bool takes_wide(int m, int n, int k) {
+  const int wgs = n / 32;
+  if (n % 32 != 0 || k < kSkinnyWaves * 32 * 16 || wgs < 160) return false;
+  return m >= (wgs < kSkinnyDeepGroups ? (k > 4096 ? 5 : 12) : 24);
+}
+
 hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2, void* c, int m, int n, int k, int ldc, GemmEpilogue epi,
                                    hipStream_t st, const int* m_live) {
   const dim3 grid((unsigned)(n / 16));
@@ -394,6 +430,11 @@ hipError_t launch_gemm_skinny_bf16(const bf16* a, const bf16* w, const bf16* w2,
   };
   const std::integral_constant<int, 4> u4;
   const std::integral_constant<int, 8> u8;
+  if (epi != EPI_SWIGLU_T && takes_wide(m, n, k)) {
+    (m > 16 ? gemm_wide_few_rows_kernel<true, false> : gemm_wide_few_rows_kernel<false, false>)<<<dim3((unsigned)(n / 32)), kSkinnyWaves * 64, 0, st>>>(
+        a, w, w2, nullptr, 0, 0, c, m, n, k, ldc, (int)epi, m_live, RopeOut{});
+    return hipGetLastError();
+  }
   if (epi == EPI_SWIGLU_T) rows(std::true_type{}, u4);
   else if (n <= 16 * kSkinnyDeepGroups && k >= kSkinnyWaves * 32 * 16) rows(std::false_type{}, u8);
   else rows(std::false_type{}, u4);
@@ -426,6 +467,11 @@ hipError_t launch_gemm_skinny_qkv_rope(const bf16* a, const NormIn& norm, const 
         <<<grid, kSkinnyWaves * 64, norm.h ? (size_t)m * norm_pitch(k) : 0, st>>>(a, wq, wk, wv, nq, nq + nkv, nullptr, m, n, k, n,
                                                                                  (int)EPI_STORE_T, m_live, norm, rope);
   };
+  if (!norm.h && takes_wide(m, n, k)) {   // q, k and v are whole heads of 128 columns
+    (m > 16 ? gemm_wide_few_rows_kernel<true, true> : gemm_wide_few_rows_kernel<false, true>)<<<dim3((unsigned)(n / 32)), kSkinnyWaves * 64, 0, st>>>(
+        a, wq, wk, wv, nq, nq + nkv, nullptr, m, n, k, n, (int)EPI_STORE_T, m_live, rope);
+    return hipGetLastError();
+  }
   if (norm.h && m > 2) go(std::false_type{}, std::integral_constant<int, 2>{});
   else if (norm.h) go(std::false_type{}, std::integral_constant<int, 1>{});
   else if (m > 16) go(std::true_type{}, std::integral_constant<int, 0>{});
