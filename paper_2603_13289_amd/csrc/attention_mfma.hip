@@ -23,7 +23,8 @@
 // matrix instructions of O^T, in a main loop without conditions.  In a bunch, with the staging between the products of S^T, the loads behind
 // it and a table look-up of its own in front of each load, a step took 4000 cycles alone on a compute unit and 5600 with two workgroups; now
 // 2900 and 3350.  Per launch, 4096 queries over 8000 keys, 32 heads on 8: 16-token pages 558 -> 426 us (938 TFLOP/s), contiguous 476 -> 473
-// (at 1.7 GHz: the power limit); 40 heads on 8 739 -> 581, 8 on 8 458 -> 337; pages of 8 522 -> 471.  100 queries over 264 keys 15.9 -> 12.8.
+// (at 1.7 GHz: the power limit); 40 heads on 8 739 -> 581, 8 on 8 458 -> 337; pages of 8 522 -> 471, of 24
+// 32 queries over 4096 keys 209 -> 104 (look-ups waited for where they are made: 109).  100 queries over 264 keys 15.9 -> 12.3, 61 over 61 10.3 -> 10.9.
 // KV tiles entirely above the tile's last query position are skipped; the causal mask is applied
 // only in tiles that reach above the tile's first query position.  Workgroups are issued longest
 // first over the whole launch (KV head fastest, query tiles by decreasing KV range).
@@ -183,27 +184,33 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   // one behind the other: lane i looks up group i % 4, and loads go to the scalar row of their group and a constant lane offset.
   // Other block sizes, and a query tile's last KV tile where it is ragged: key kv0 + lane, rows handed around.  Past the last
   // position that is the last row again, whose weight there is 0 (the mask sets the score).
+  // A look-up comes in two halves, so that the block of a tile two on is asked for early and not waited for.
   const bool contig = g.max_blocks == 1;           // one block per sequence
-  const unsigned crow = contig ? (unsigned)(kv_row_offset(g, seq, 0, kvh) / DH) : 0u;
   const bool by_group = contig || g.bs_shift >= 4;
   const unsigned k_lane = (unsigned)((krow0 & 15) * DH + kch * 8) * 2, v_lane = (unsigned)((vquad & 3) * 4 * DH + vdch * 8) * 2;
   auto grouped = [&](int kv0) __attribute__((always_inline)) { return by_group && kv0 + BKV - 1 <= last_pos; };   // uniform
-  auto look_up = [&](int kv0) __attribute__((always_inline)) -> unsigned {
-    const int pos = grouped(kv0) ? kv0 + 16 * (lane & 3) : min(kv0 + lane, last_pos);
-    if (contig) return crow + (unsigned)pos;
-    return (unsigned)(kv_row_offset(g, seq, pos, kvh) / DH);
-  };
   auto rsrc_of = [](const void* p) __attribute__((always_inline)) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000); };
-  // the same in two halves, for the main loop: the block of lane i's group is asked for early and not waited for
   const int tab_shift = contig ? 31 : g.bs_shift;
   const unsigned tab_mask = contig ? 0x7fffffffu : (unsigned)(g.block_size - 1);
   const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
-  auto ask_block = [&](int kv0) __attribute__((always_inline)) {
-    return (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(seq_table), 4 * min((kv0 + 16 * (lane & 3)) >> tab_shift, g.max_blocks - 1), 0, 0);
+  struct Asked { int block; unsigned slot; };
+  auto ask = [&](int pos) __attribute__((always_inline)) -> Asked {
+    int at;
+    unsigned slot;
+    if (tab_shift >= 0) {
+      at = pos >> tab_shift;
+      slot = (unsigned)pos & tab_mask;
+    } else {
+      at = pos / g.block_size;
+      slot = (unsigned)(pos - at * g.block_size);
+    }
+    return {(int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(seq_table), 4 * min(at, g.max_blocks - 1), 0, 0), slot};
   };
-  auto group_row = [&](int kv0, int blk) __attribute__((always_inline)) -> unsigned {
-    return (unsigned)(min(max(blk, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * (unsigned)g.block_size + ((unsigned)(kv0 + 16 * (lane & 3)) & tab_mask);
+  auto row_of = [&](Asked q) __attribute__((always_inline)) -> unsigned {
+    return (unsigned)(min(max(q.block, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * (unsigned)g.block_size + q.slot;
   };
+  auto group_pos = [&](int kv0) __attribute__((always_inline)) { return kv0 + 16 * (lane & 3); };
+  auto ask_tile = [&](int kv0) __attribute__((always_inline)) { return ask(grouped(kv0) ? group_pos(kv0) : min(kv0 + lane, last_pos)); };
   auto group_at = [&](const bf16* pool, unsigned row, int grp) __attribute__((always_inline)) {   // scalar
     return rsrc_of(pool + (size_t)(unsigned)__builtin_amdgcn_readlane((int)row, grp) * DH);
   };
@@ -213,7 +220,8 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   auto v_chunk_of = [&](unsigned row, int kk) __attribute__((always_inline)) {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(v_pool, row, wave & 3), v_lane, kk * DH * 2, 0));
   };
-  auto fetch = [&](int kv0, unsigned row) __attribute__((always_inline)) {
+  auto fetch = [&](int kv0, Asked asked) __attribute__((always_inline)) {
+    const unsigned row = row_of(asked);
     const unsigned char* const kp = reinterpret_cast<const unsigned char*>(k_pool);
     const unsigned char* const vp = reinterpret_cast<const unsigned char*>(v_pool);
     if (grouped(kv0)) {
@@ -290,11 +298,12 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   if (t_begin >= t_end || (!is_split && chunk != 0)) return;   // nothing for this workgroup (uniform)
   const std::integral_constant<int, 0> buf0;
   const std::integral_constant<int, 1> buf1;
+  const Asked first_tile = ask_tile(t_begin * BKV), second_tile = ask_tile((t_begin + 1) * BKV);
   // prologue: the first tile goes to buffer 0, the second one is on its way in registers
-  fetch(t_begin * BKV, look_up(t_begin * BKV));
+  fetch(t_begin * BKV, first_tile);
   stage_k(buf0);
   stage_v(buf0, 0, 8);
-  if (t_begin + 1 < t_end) fetch((t_begin + 1) * BKV, look_up((t_begin + 1) * BKV));
+  if (t_begin + 1 < t_end) fetch((t_begin + 1) * BKV, second_tile);
   __syncthreads();
   // step i (tile t = t_begin + i) multiplies buffer i % 2; meanwhile it stages tile t + 1 into the other buffer
   // (free since the barrier that ended step i - 1) and starts the loads of tile t + 2.  how: 1 in the main loop, where there are such
@@ -305,10 +314,13 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     const std::integral_constant<int, 1 - decltype(buf)::value> other;
     const int kv0 = t * BKV;
     const bool has_next = t + 1 < t_end, has_next2 = t + 2 < t_end;
-    unsigned row2 = 0;   // of the tile two on: asked for here, used behind the first product
-    int blk2 = 0;
-    if constexpr (!steady) row2 = look_up(kv0 + 2 * BKV);
-    else if constexpr (K_TOO) blk2 = ask_block(kv0 + 2 * BKV);
+    Asked asked = {};   // for the tile two on
+    if constexpr (!steady) {
+      if (has_next2) asked = ask_tile(kv0 + 2 * BKV);
+    } else if constexpr (K_TOO) {
+      asked = ask(group_pos(kv0 + 2 * BKV));
+    }
+    unsigned row2 = 0;
     // S^T = K Q^T : two blocks of 32 keys.  The two accumulator chains alternate and the K fragments are read
     // kFragAhead MFMAs ahead of their use, so that neither the LDS latency nor the MFMA dependency is exposed.
     f32x16 acc_s[2];
@@ -341,7 +353,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     if constexpr (steady) {
       if constexpr (K_TOO) {
         stage_k(other);
-        row2 = group_row(kv0 + 2 * BKV, blk2);
+        row2 = row_of(asked);
       }
       __builtin_amdgcn_sched_barrier(0);
     } else {
@@ -349,7 +361,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
         stage_k(other);
         stage_v(other, 0, 8);
       }
-      if (has_next2) fetch(kv0 + 2 * BKV, row2);
+      if (has_next2) fetch(kv0 + 2 * BKV, asked);
     }
     // running softmax on raw scores; the 1/sqrt(dh) * log2(e) factor is folded into the exponent.
     // Element e of block b is key kv0 + 32 b + 8 (e/4) + 4 half + e%4.  Only tiles that reach above the
