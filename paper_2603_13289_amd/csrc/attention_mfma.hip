@@ -45,7 +45,7 @@ static constexpr int KROW = DH * 2 + 16;   // bytes between K rows in LDS
 static constexpr int VROW = BKV * 2;       // bytes between V^T rows in LDS
 static constexpr int K_TILE_BYTES = BKV * KROW;
 static constexpr int V_TILE_BYTES = DH * VROW;
-static constexpr int kLdsTableEntries = 2048;   // block-table entries of the workgroup's KV range kept in LDS (paged caches)
+static constexpr int kLdsTableEntries = 2048;   // block-table entries of the workgroup's KV range kept in LDS (attn_decode_kernel, paged caches)
 static constexpr int ATTN_LDS_BYTES = 2 * (K_TILE_BYTES + V_TILE_BYTES);
 static constexpr int PROW = DH + 16;         // floats between the rows of a partial result (see attention_partial_floats)
 static constexpr int kFragAhead = 4;       // LDS operand fragments in flight ahead of the MFMA that uses them
