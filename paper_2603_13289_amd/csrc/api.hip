@@ -2,6 +2,7 @@
 // launch sequence.  All device work is done by the kernels in the sibling files; this file only
 // decides which rows are active in which layer and enqueues launches.
 #include <algorithm>
+#include <climits>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -97,6 +98,7 @@ KvGeom geom_of(const rc_paged_kv& kv, const rc_model_desc& d) {
   g.n_kv_heads = d.n_kv_heads;
   g.head_dim = d.head_dim;
   g.bs_shift = log2_if_pow2(kv.block_size);
+  g.last_pos = (int)std::min((long)kv.max_blocks_per_seq * kv.block_size - 1, (long)INT_MAX);
   return g;
 }
 
@@ -109,6 +111,7 @@ KvGeom geom_of(const rc_kv_layer& kv) {
   g.n_kv_heads = kv.n_kv_heads;
   g.head_dim = kv.head_dim;
   g.bs_shift = log2_if_pow2(kv.block_size);
+  g.last_pos = (int)std::min((long)kv.max_blocks_per_seq * kv.block_size - 1, (long)INT_MAX);
   return g;
 }
 

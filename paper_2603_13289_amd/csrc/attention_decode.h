@@ -42,7 +42,7 @@ attn_decode_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, 
   if (rq.n_rows <= 0) return;
   const int row = rq.row_base, seq = rq.dst_seq, part_base = rq.part_base;
   const int chunk = item - rq.item_base;
-  const int pos = row_pos[row];
+  const int pos = pos_in_cache(row_pos[row], g.last_pos);
   const int n_kv_tiles = pos / BKV + 1;
   const bool is_split = sp.n_chunks > 1 && rq.long_tile_start == 0 && n_kv_tiles > sp.long_thr;
   const int t_begin = is_split ? chunk * sp.chunk_tiles : 0;

@@ -149,7 +149,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   const int my_row = r0 + (q_ok ? ql : 0);
   const int my_pos = q_ok ? row_pos[my_row] : 0;
   const int first_pos = row_pos[r0];
-  const int last_pos = max((int)min((long)row_pos[r0 + n_valid - 1], (long)g.max_blocks * g.block_size - 1), 0);   // never past the cache
+  const int last_pos = pos_in_cache(row_pos[r0 + n_valid - 1], g.last_pos);
 
   // Q as B operands: lane (q, half) holds Q[q][16 s + 8 half .. +7], s = 0..7
   bf16x8 qf[8];
@@ -495,7 +495,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
 // decoding rows 5.3 -> 4.8; four heads by four chunks for the decoding rows as well: 5.6, and the launch below 6.7 -> 7.6 instead of 6.6.
 template <int PAIRS, int AHEAD>
 __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows,
-                                           int n_q_heads, const AttnSplit& sp, const float* __restrict__ part_o,
+                                           int n_q_heads, const AttnSplit& sp, int cache_last, const float* __restrict__ part_o,
                                            const float2* __restrict__ part_ml, bf16* __restrict__ out, float2* __restrict__ score_ml) {
   const int lane = threadIdx.x & 63, e = lane & 31;
   const int groups = (n_q_heads + 2 * PAIRS - 1) / (2 * PAIRS);
@@ -522,9 +522,9 @@ __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row
     ql = r % BQ;
     tile_last_row = min((split_tile + 1) * BQ, total_rows) - 1;
   }
-  const int n_kv_tiles = row_pos[tile_last_row] / BKV + 1;
+  const int n_kv_tiles = pos_in_cache(row_pos[tile_last_row], cache_last) / BKV + 1;
   if (split_tile < 0 || n_kv_tiles <= sp.long_thr) return;   // this row's tile was done by one workgroup
-  const int nc = min(sp.n_chunks, row_pos[r] / (sp.chunk_tiles * BKV) + 1);
+  const int nc = min(sp.n_chunks, pos_in_cache(row_pos[r], cache_last) / (sp.chunk_tiles * BKV) + 1);
   const size_t cstride = (size_t)n_q_heads * BQ;
   size_t slot0[PAIRS];
   float4 o[PAIRS][AHEAD], acc[PAIRS];
@@ -591,9 +591,9 @@ __device__ __forceinline__ void merge_item(int item, const int* __restrict__ row
 template <int PAIRS, int AHEAD>
 __global__ void __launch_bounds__(256)
 attn_merge_kernel(const int* __restrict__ row_pos, const ReqTable* __restrict__ table, int total_rows, int n_q_heads, AttnSplit sp,
-                  const float* __restrict__ part_o, const float2* __restrict__ part_ml, bf16* __restrict__ out,
+                  int cache_last, const float* __restrict__ part_o, const float2* __restrict__ part_ml, bf16* __restrict__ out,
                   float2* __restrict__ score_ml) {
-  merge_item<PAIRS, AHEAD>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, score_ml);
+  merge_item<PAIRS, AHEAD>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, cache_last, part_o, part_ml, out, score_ml);
 }
 
 // A decoding step with influence sums, its KV ranges split: workgroups below `merge_wgs` merge, the others add the rows' weights to
@@ -603,19 +603,19 @@ attn_merge_kernel(const int* __restrict__ row_pos, const ReqTable* __restrict__ 
 static constexpr int kInfMaxHeads = 64;   // of a model that takes this path (LDS)
 __global__ void __launch_bounds__(256)
 attn_merge_influence_kernel(const int* __restrict__ row_pos, const int* __restrict__ row_req, const ReqTable* __restrict__ table,
-                            int total_rows, int n_q_heads, AttnSplit sp, const float* __restrict__ part_o,
+                            int total_rows, int n_q_heads, AttnSplit sp, int cache_last, const float* __restrict__ part_o,
                             const float2* __restrict__ part_ml, bf16* __restrict__ out, const float* __restrict__ scores, int scores_len,
                             const float2* __restrict__ score_ml, InfluencePtrs inf, int merge_wgs, int wgs_per_row) {
   __shared__ float weight[kInfMaxHeads][64];
   __shared__ float2 pair[kInfMaxHeads];
   if ((int)blockIdx.x < merge_wgs) {
-    merge_item<1, 8>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, part_o, part_ml, out, nullptr);
+    merge_item<1, 8>((int)blockIdx.x * 4 + (threadIdx.x >> 6), row_pos, table, total_rows, n_q_heads, sp, cache_last, part_o, part_ml, out, nullptr);
     return;
   }
   const int row = ((int)blockIdx.x - merge_wgs) / wgs_per_row;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = (((int)blockIdx.x - merge_wgs) % wgs_per_row) * 64 + lane;
-  const int pos = row_pos[row];
+  const int pos = pos_in_cache(row_pos[row], cache_last);
   if (j - lane > pos) return;   // uniform
   const int req = row_req[row] & kRowReqMask;
   float* const dst = inf.s_inf[req];
@@ -751,13 +751,13 @@ hipError_t launch_attention_bf16(const bf16* q, const int* row_pos, const int* r
   if (inf && scores && table && one_row && G <= 8 && n_q_heads <= kInfMaxHeads) {
     const int wgs_per_row = (scores_len + 63) / 64;
     attn_merge_influence_kernel<<<merge_wgs + total_rows * wgs_per_row, 256, 0, st>>>(
-        row_pos, row_req, table, total_rows, n_q_heads, sp, part, part_ml, out, scores, scores_len,
+        row_pos, row_req, table, total_rows, n_q_heads, sp, g.last_pos, part, part_ml, out, scores, scores_len,
         influence_pairs(scores, total_rows, n_q_heads, scores_len), *inf, merge_wgs, wgs_per_row);
     *inf_done = true;
     return hipGetLastError();
   }
   (one_row ? attn_merge_kernel<1, 8> : attn_merge_kernel<2, 4>)<<<merge_wgs, 256, 0, st>>>(
-      row_pos, table, total_rows, n_q_heads, sp, part, part_ml, out,
+      row_pos, table, total_rows, n_q_heads, sp, g.last_pos, part, part_ml, out,
       scores ? influence_pairs(scores, total_rows, n_q_heads, scores_len) : nullptr);
   return hipGetLastError();
 }

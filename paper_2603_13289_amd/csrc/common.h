@@ -93,7 +93,12 @@ struct KvGeom {
   int max_blocks;
   int n_kv_heads, head_dim;
   int bs_shift;  // log2(block_size) when it is a power of two, else -1
+  int last_pos;  // the last position that a sequence has room for
 };
+
+// A row's position as attention takes it.  Every kernel that counts key tiles or chunks asks here: the ones that write partial results
+// and the ones that merge them have to agree where a position from device memory lies outside the cache.
+__device__ inline int pos_in_cache(int pos, int last_pos) { return min(max(pos, 0), last_pos); }
 
 inline int log2_if_pow2(int x) {
   if (x <= 0 || (x & (x - 1))) return -1;
