@@ -45,7 +45,7 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
     n_valid = min(16, total_rows - r0);
   }
   const bool q_ok = qi < n_valid;
-  const int my_pos = q_ok ? row_pos[r0 + qi] : -1;
+  const int my_pos = q_ok ? pos_in_cache(row_pos[r0 + qi], g.last_pos) : -1;
   int last_pos = my_pos, first_pos = q_ok ? my_pos : INT_MAX;   // the group's largest and smallest position
 #pragma unroll
   for (int o = 1; o < 16; o <<= 1) {
@@ -62,7 +62,7 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
     acc[t] = f32x4a{0.f, 0.f, 0.f, 0.f};
   }
   float m_run = -INFINITY, l_run = 0.f;
-  last_pos = max((int)min((long)__builtin_amdgcn_readfirstlane(last_pos), (long)g.max_blocks * g.block_size - 1), 0);   // never past the cache
+  last_pos = __builtin_amdgcn_readfirstlane(last_pos);
   const int n_blocks = last_pos / 16 + 1;
   // Pages of a multiple of 16 slots hold a block's keys one behind the other: its page is one scalar read, a block ahead of the loads
   // that hang on it.  Other page sizes look every key up.  Keys past the last position repeat it.

@@ -147,8 +147,8 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   const int head = kvh * G + (active ? wave : 0);
   const bool q_ok = active && ql < n_valid;
   const int my_row = r0 + (q_ok ? ql : 0);
-  const int my_pos = q_ok ? row_pos[my_row] : 0;
-  const int first_pos = row_pos[r0];
+  const int my_pos = q_ok ? pos_in_cache(row_pos[my_row], g.last_pos) : 0;
+  const int first_pos = pos_in_cache(row_pos[r0], g.last_pos);
   const int last_pos = pos_in_cache(row_pos[r0 + n_valid - 1], g.last_pos);
 
   // Q as B operands: lane (q, half) holds Q[q][16 s + 8 half .. +7], s = 0..7

@@ -17,7 +17,7 @@ attn_simt_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   if (table && r >= table->total_rows) return;   // the grid may be sized for an upper bound of the row count
   const int kvh = hq / (n_q_heads / g.n_kv_heads);
   const int dh = g.head_dim;
-  const int pos = row_pos[r];
+  const int pos = pos_in_cache(row_pos[r], g.last_pos);
   const int seq = table ? table->r[row_req[r] & kRowReqMask].dst_seq : fixed_seq;
   const bf16* qrow = q + ((size_t)r * n_q_heads + hq) * dh;
   for (int c = lane; c < dh; c += 64) q_s[c] = to_f32(qrow[c]);

@@ -40,3 +40,15 @@ def test_kernel_and_merge_agree_on_the_key_range(page, capacity, n):
     """16 key tiles fit, the positions ask for more than the 24 from which on a range is cut into chunks; 2000 keys are cut anyway."""
     got, want = _rows(NKV, 4, 128, torch.bfloat16, page, capacity, True, [capacity + 900, 2 * capacity], n)
     assert torch.equal(got[:n - 2], want[:n - 2])
+
+
+@pytest.mark.parametrize("page,capacity", [(0, 1024), (0, 1000), (16, 1008), (24, 1008), (16, 2000), (0, 5)])
+@pytest.mark.parametrize("group,DH,td", [(1, 128, torch.bfloat16), (4, 128, torch.bfloat16), (5, 128, torch.bfloat16), (8, 128, torch.bfloat16),
+                                         (16, 128, torch.bfloat16), (2, 64, torch.float32), (2, 128, torch.float32)])
+@pytest.mark.parametrize("workspace", [False, True])
+def test_a_row_outside_counts_as_the_last_one(page, capacity, group, DH, td, workspace):
+    if workspace and td == torch.float32:
+        pytest.skip("only the bf16 kernel splits ranges")
+    for n, outside in ((40, [capacity, capacity + 900, 2 * capacity]), (1, [capacity + 17])):
+        got, want = _rows(NKV, group, DH, td, page, capacity, workspace, outside, n)
+        assert torch.equal(got, want), n
