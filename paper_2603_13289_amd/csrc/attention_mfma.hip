@@ -183,7 +183,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   // A lane looks up the pool row (of DH elements) of one key of a tile.  In blocks of a multiple of 16 slots the 16 keys of a group lie
   // one behind the other: lane i looks up group i % 4, and loads go to the scalar row of their group and a constant lane offset.
   // Other block sizes, and a query tile's last KV tile where it is ragged: key kv0 + lane, rows handed around.  Past the last
-  // position that is the last row again, whose weight there is 0 (the mask sets the score).
+  // position that is the last row again: the mask sets its score, and its values are staged as zeros (clear_v).
   // A look-up comes in two halves, so that the block of a tile two on is asked for early and not waited for.
   const bool contig = g.max_blocks == 1;           // one block per sequence
   const bool by_group = contig || g.bs_shift >= 4;
@@ -252,6 +252,15 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
         rv[kk] = *reinterpret_cast<const uint4*>(vp + (size_t)(unsigned)__shfl((int)row, ((th >> 4) * 4 + kk) & 63, 64) * (DH * 2) + (th & 15) * 16);
     }
   };
+  // Values behind the last position: zeros, so that an infinity of the last row is not multiplied by their weight of 0.
+  auto clear_v = [&](int kv0) __attribute__((always_inline)) {
+    if (kv0 + BKV - 1 <= last_pos || !stages_v) return;   // uniform
+    int th = tid;
+    asm volatile("" : "+v"(th));
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      if (kv0 + (th >> 4) * 4 + kk > last_pos) rv[kk] = make_uint4(0, 0, 0, 0);
+  };
   // V transposed: key = 16 grp + 8 a + 4 h + c goes to column 16 grp + 8 h + 4 a + c; a quad shares (grp, a, h).
   // In LDS, 16-byte chunk c of V^T row d is chunk c ^ (d/2 & 7) ^ (d/16) of row d ^ (d/8 & 1): the sixteen rows of an operand fetch
   // then meet all banks once, and so do the writes of a wavefront, which has four quads of sixteen d / 8.
@@ -302,6 +311,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   // prologue: the first tile goes to buffer 0, the second one is on its way in registers
   fetch(t_begin * BKV, first_tile);
   stage_k(buf0);
+  clear_v(t_begin * BKV);
   stage_v(buf0, 0, 8);
   if (t_begin + 1 < t_end) fetch((t_begin + 1) * BKV, second_tile);
   __syncthreads();
@@ -359,6 +369,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     } else {
       if (has_next) {
         stage_k(other);
+        clear_v(kv0 + BKV);
         stage_v(other, 0, 8);
       }
       if (has_next2) fetch(kv0 + 2 * BKV, asked);
