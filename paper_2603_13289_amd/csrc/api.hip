@@ -99,6 +99,7 @@ KvGeom geom_of(const rc_paged_kv& kv, const rc_model_desc& d) {
   g.head_dim = d.head_dim;
   g.bs_shift = log2_if_pow2(kv.block_size);
   g.last_pos = (int)std::min((long)kv.max_blocks_per_seq * kv.block_size - 1, (long)INT_MAX);
+  set_block_division(&g);
   return g;
 }
 
@@ -112,6 +113,7 @@ KvGeom geom_of(const rc_kv_layer& kv) {
   g.head_dim = kv.head_dim;
   g.bs_shift = log2_if_pow2(kv.block_size);
   g.last_pos = (int)std::min((long)kv.max_blocks_per_seq * kv.block_size - 1, (long)INT_MAX);
+  set_block_division(&g);
   return g;
 }
 

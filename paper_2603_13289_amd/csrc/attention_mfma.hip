@@ -22,9 +22,12 @@
 // another's instructions they are hidden: the staging writes run under the exponentials (K's before, V's between them), the loads between the
 // matrix instructions of O^T, in a main loop without conditions.  In a bunch, with the staging between the products of S^T, the loads behind
 // it and a table look-up of its own in front of each load, a step took 4000 cycles alone on a compute unit and 5600 with two workgroups; now
-// 2900 and 3350.  Per launch, 4096 queries over 8000 keys, 32 heads on 8: 16-token pages 558 -> 426 us (938 TFLOP/s), contiguous 476 -> 473
-// (at 1.7 GHz: the power limit); 40 heads on 8 739 -> 581, 8 on 8 458 -> 337; pages of 8 522 -> 471, of 24
-// 32 queries over 4096 keys 209 -> 104 (look-ups waited for where they are made: 109).  100 queries over 264 keys 15.9 -> 12.3, 61 over 61 10.3 -> 10.9.
+// 2900 and 3350.  Per launch in a train of twenty, before that loop -> now, all on one card: 4096 queries over 8000 keys, 32 heads on 8: 16-token
+// pages 494 -> 387 us (1030 TFLOP/s), contiguous 389 -> 387, pages of 24 791 -> 437; 40 heads on 8: 809 -> 567 and 738 -> 566 contiguous.
+// 32 queries over 4096 keys 135 -> 75 (pages of 24: 211 -> 102), 100 over 264 15.8 -> 11.6 (contiguous 12.3 -> 11.6).
+// Ranges of a tile or two are bound by the chain to the first product and by instructions that are fetched for the first time, so what runs before it
+// has few branches (look-ups by a multiplication, every lane loads a row of Q) and few links: the first block look-ups do not hang on the rows'
+// positions, Q is asked for behind K and V.  61 queries over 61 keys: 16-token pages 7.70 -> 6.74, contiguous 6.84 -> 6.61 (7.10 without those).
 // KV tiles entirely above the tile's last query position are skipped; the causal mask is applied
 // only in tiles that reach above the tile's first query position.  Workgroups are issued longest
 // first over the whole launch (KV head fastest, query tiles by decreasing KV range).
@@ -142,25 +145,26 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   if (n_valid <= 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Block of a position and slot in it; past the cache a slot of its last block.
+  auto rsrc_of = [](const void* p) __attribute__((always_inline)) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000); };
+  const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
+  struct Asked { int block; unsigned slot; };
+  auto ask = [&](int pos) __attribute__((always_inline)) -> Asked {
+    const int at = block_of(g, pos);
+    return {(int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(seq_table), 4 * min(at, g.max_blocks - 1), 0, 0), (unsigned)(pos - at * g.block_size)};
+  };
+  // Key kv0 + lane of the first two tiles: that does not hang on the rows' positions, which are asked for beside it.
+  auto ask_tile = [&](int kv0) __attribute__((always_inline)) { return ask(kv0 + lane); };
+  const int t_first = chunk * sp.chunk_tiles;   // 0 where the range is not cut
+  const Asked first_tile = ask_tile(t_first * BKV), second_tile = ask_tile((t_first + 1) * BKV);
   const int ql = lane & 31, half = lane >> 5;
   const bool active = G >= 4 || wave < G;   // wave-uniform
   const int head = kvh * G + (active ? wave : 0);
   const bool q_ok = active && ql < n_valid;
   const int my_row = r0 + (q_ok ? ql : 0);
-  const int my_pos = q_ok ? pos_in_cache(row_pos[my_row], g.last_pos) : 0;
+  const int my_pos = pos_in_cache(row_pos[my_row], g.last_pos);   // of every lane: under a condition it is waited for at once
   const int first_pos = pos_in_cache(row_pos[r0], g.last_pos);
   const int last_pos = pos_in_cache(row_pos[r0 + n_valid - 1], g.last_pos);
-
-  // Q as B operands: lane (q, half) holds Q[q][16 s + 8 half .. +7], s = 0..7
-  bf16x8 qf[8];
-  {
-    const bf16* qrow = q + ((size_t)my_row * n_q_heads + head) * DH + 8 * half;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      uint4 v = q_ok ? *reinterpret_cast<const uint4*>(qrow + 16 * s) : make_uint4(0, 0, 0, 0);
-      qf[s] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
 
   f32x16 acc_o[4];
 #pragma unroll
@@ -180,45 +184,26 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   const int vquad = tid >> 4, vdch = tid & 15;     // V: quad of 4 keys, chunk of 8 d
   // the tile fetched during step t is staged during step t + 1 and multiplied in step t + 2
   uint4 rk[KPER], rv[4];
-  // A lane looks up the pool row (of DH elements) of one key of a tile.  In blocks of a multiple of 16 slots the 16 keys of a group lie
-  // one behind the other: lane i looks up group i % 4, and loads go to the scalar row of their group and a constant lane offset.
-  // Other block sizes, and a query tile's last KV tile where it is ragged: key kv0 + lane, rows handed around.  Past the last
-  // position that is the last row again: the mask sets its score, and its values are staged as zeros (clear_v).
+  // A lane looks up the pool row (of DH elements) of one key of a tile.  In blocks of 16, 32, 64, ... slots the 16 keys of a group lie
+  // one behind the other, and loads go to the scalar row of their group and a constant lane offset: in the main loop lane i looks up group
+  // i % 4, elsewhere key kv0 + i.  Other block sizes, and a query tile's last KV tile where it is ragged: rows handed around.  Past the last
+  // position that is whatever row the cache has there: the mask sets its score, and its values are staged as zeros (sel_of).
   // A look-up comes in two halves, so that the block of a tile two on is asked for early and not waited for.
-  const bool contig = g.max_blocks == 1;           // one block per sequence
-  const bool by_group = contig || g.bs_shift >= 4;
+  const bool by_group = g.max_blocks == 1 || g.bs_shift >= 4;   // one block per sequence, or blocks of 16, 32, ...
   const unsigned k_lane = (unsigned)((krow0 & 15) * DH + kch * 8) * 2, v_lane = (unsigned)((vquad & 3) * 4 * DH + vdch * 8) * 2;
   auto grouped = [&](int kv0) __attribute__((always_inline)) { return by_group && kv0 + BKV - 1 <= last_pos; };   // uniform
-  auto rsrc_of = [](const void* p) __attribute__((always_inline)) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000); };
-  const int tab_shift = contig ? 31 : g.bs_shift;
-  const unsigned tab_mask = contig ? 0x7fffffffu : (unsigned)(g.block_size - 1);
-  const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
-  struct Asked { int block; unsigned slot; };
-  auto ask = [&](int pos) __attribute__((always_inline)) -> Asked {
-    int at;
-    unsigned slot;
-    if (tab_shift >= 0) {
-      at = pos >> tab_shift;
-      slot = (unsigned)pos & tab_mask;
-    } else {
-      at = pos / g.block_size;
-      slot = (unsigned)(pos - at * g.block_size);
-    }
-    return {(int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(seq_table), 4 * min(at, g.max_blocks - 1), 0, 0), slot};
-  };
   auto row_of = [&](Asked q) __attribute__((always_inline)) -> unsigned {
     return (unsigned)(min(max(q.block, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * (unsigned)g.block_size + q.slot;
   };
   auto group_pos = [&](int kv0) __attribute__((always_inline)) { return kv0 + 16 * (lane & 3); };
-  auto ask_tile = [&](int kv0) __attribute__((always_inline)) { return ask(grouped(kv0) ? group_pos(kv0) : min(kv0 + lane, last_pos)); };
-  auto group_at = [&](const bf16* pool, unsigned row, int grp) __attribute__((always_inline)) {   // scalar
-    return rsrc_of(pool + (size_t)(unsigned)__builtin_amdgcn_readlane((int)row, grp) * DH);
+  auto group_at = [&](const bf16* pool, unsigned row, int from) __attribute__((always_inline)) {   // scalar
+    return rsrc_of(pool + (size_t)(unsigned)__builtin_amdgcn_readlane((int)row, from) * DH);
   };
-  auto k_chunk = [&](unsigned row, int i) __attribute__((always_inline)) {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(k_pool, row, i * (KSTEP / 16) + (NS == 512 ? wave >> 2 : 0)), k_lane, 0, 0));
+  auto k_chunk = [&](unsigned row, int i, int lanes) __attribute__((always_inline)) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(k_pool, row, lanes * (i * (KSTEP / 16) + (NS == 512 ? wave >> 2 : 0))), k_lane, 0, 0));
   };
-  auto v_chunk_of = [&](unsigned row, int kk) __attribute__((always_inline)) {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(v_pool, row, wave & 3), v_lane, kk * DH * 2, 0));
+  auto v_chunk_of = [&](unsigned row, int kk, int lanes) __attribute__((always_inline)) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(group_at(v_pool, row, lanes * (wave & 3)), v_lane, kk * DH * 2, 0));
   };
   auto fetch = [&](int kv0, Asked asked) __attribute__((always_inline)) {
     const unsigned row = row_of(asked);
@@ -226,16 +211,16 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     const unsigned char* const vp = reinterpret_cast<const unsigned char*>(v_pool);
     if (grouped(kv0)) {
       if (stages_k) {
-        rk[0] = k_chunk(row, 0);
-        rk[1] = k_chunk(row, 1);
+        rk[0] = k_chunk(row, 0, 16);
+        rk[1] = k_chunk(row, 1, 16);
         if constexpr (KPER == 4) {
-          rk[2] = k_chunk(row, 2);
-          rk[3] = k_chunk(row, 3);
+          rk[2] = k_chunk(row, 2, 16);
+          rk[3] = k_chunk(row, 3, 16);
         }
       }
       if (stages_v) {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) rv[kk] = v_chunk_of(row, kk);
+        for (int kk = 0; kk < 4; ++kk) rv[kk] = v_chunk_of(row, kk, 16);
       }
       return;
     }
@@ -252,15 +237,6 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
         rv[kk] = *reinterpret_cast<const uint4*>(vp + (size_t)(unsigned)__shfl((int)row, ((th >> 4) * 4 + kk) & 63, 64) * (DH * 2) + (th & 15) * 16);
     }
   };
-  // Values behind the last position: zeros, so that an infinity of the last row is not multiplied by their weight of 0.
-  auto clear_v = [&](int kv0) __attribute__((always_inline)) {
-    if (kv0 + BKV - 1 <= last_pos || !stages_v) return;   // uniform
-    int th = tid;
-    asm volatile("" : "+v"(th));
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      if (kv0 + (th >> 4) * 4 + kk > last_pos) rv[kk] = make_uint4(0, 0, 0, 0);
-  };
   // V transposed: key = 16 grp + 8 a + 4 h + c goes to column 16 grp + 8 h + 4 a + c; a quad shares (grp, a, h).
   // In LDS, 16-byte chunk c of V^T row d is chunk c ^ (d/2 & 7) ^ (d/16) of row d ^ (d/8 & 1): the sixteen rows of an operand fetch
   // then meet all banks once, and so do the writes of a wavefront, which has four quads of sixteen d / 8.
@@ -271,6 +247,21 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   const unsigned v_wr = 2 * K_TILE_BYTES + vdch * 8 * VROW + 16 * v_chunk + 8 * ((vquad >> 1) & 1);   // chunk ^ m: bits 4-6 of the address
   // byte select: the low halves of two words (even d) or the high ones, for a thread's first and second row of a pair
   const uint32_t v_sel0 = v_odd ? 0x07060302u : 0x05040100u, v_sel1 = v_odd ? 0x05040100u : 0x07060302u;
+  // The selects of a thread's keys 0, 1 and 2, 3.  Values behind the last position become zeros (byte select 12): what lies there may be no
+  // finite number, and is not to be multiplied by a weight of 0.
+  struct Sel { uint32_t lo0, lo1, hi0, hi1; };
+  const Sel whole = {v_sel0, v_sel1, v_sel0, v_sel1};
+  auto sel_of = [&](int kv0) __attribute__((always_inline)) -> Sel {
+    Sel s = whole;
+    if (kv0 + BKV - 1 > last_pos) {   // uniform
+      int th = tid;
+      asm volatile("" : "+v"(th));
+      const int n = last_pos - kv0 - (th >> 4) * 4;   // keys 0 .. n
+      const uint32_t lo = n < 0 ? 0u : (n < 1 ? 0xffffu : ~0u), hi = n < 2 ? 0u : (n < 3 ? 0xffffu : ~0u);
+      s = {(s.lo0 & lo) | (0x0c0c0c0cu & ~lo), (s.lo1 & lo) | (0x0c0c0c0cu & ~lo), (s.hi0 & hi) | (0x0c0c0c0cu & ~hi), (s.hi1 & hi) | (0x0c0c0c0cu & ~hi)};
+    }
+    return s;
+  };
   auto stage_k = [&](auto buf) __attribute__((always_inline)) {
     constexpr int KOFF = decltype(buf)::value * K_TILE_BYTES;
     if (!stages_k) return;
@@ -278,7 +269,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     for (int i = 0; i < KPER; ++i) *reinterpret_cast<uint4*>(k_wr + KOFF + i * KSTEP * KROW) = rk[i];
   };
   // V^T rows e_begin .. e_end - 1 (of the 8 head-dim elements a thread's block covers)
-  auto stage_v = [&](auto buf, int e_begin, int e_end) __attribute__((always_inline)) {
+  auto stage_v = [&](auto buf, int e_begin, int e_end, Sel sel) __attribute__((always_inline)) {
     constexpr int VOFF = decltype(buf)::value * V_TILE_BYTES;
     if (!stages_v) return;
     const uint32_t w[4][4] = {{rv[0].x, rv[0].y, rv[0].z, rv[0].w},
@@ -289,10 +280,9 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     for (int e = 0; e < 8; ++e) {
       if (e < e_begin || e >= e_end) continue;
       const int m = e >> 1;
-      const uint32_t sel = (e & 1) ? v_sel1 : v_sel0;
       uint2 pk;
-      pk.x = __builtin_amdgcn_perm(w[1][m], w[0][m], sel);
-      pk.y = __builtin_amdgcn_perm(w[3][m], w[2][m], sel);
+      pk.x = __builtin_amdgcn_perm(w[1][m], w[0][m], (e & 1) ? sel.lo1 : sel.lo0);
+      pk.y = __builtin_amdgcn_perm(w[3][m], w[2][m], (e & 1) ? sel.hi1 : sel.hi0);
       *reinterpret_cast<uint2*>(lds_attn + (v_wr ^ (16 * m)) + VOFF + e * VROW) = pk;
     }
   };
@@ -302,17 +292,26 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
 
   const int n_kv_tiles = last_pos / BKV + 1;
   const bool is_split = sp.n_chunks > 1 && split_tile >= 0 && n_kv_tiles > sp.long_thr;
-  const int t_begin = is_split ? chunk * sp.chunk_tiles : 0;
+  const int t_begin = is_split ? t_first : 0;
   const int t_end = is_split ? min(n_kv_tiles, t_begin + sp.chunk_tiles) : n_kv_tiles;
   if (t_begin >= t_end || (!is_split && chunk != 0)) return;   // nothing for this workgroup (uniform)
   const std::integral_constant<int, 0> buf0;
   const std::integral_constant<int, 1> buf1;
-  const Asked first_tile = ask_tile(t_begin * BKV), second_tile = ask_tile((t_begin + 1) * BKV);
   // prologue: the first tile goes to buffer 0, the second one is on its way in registers
   fetch(t_begin * BKV, first_tile);
+  // Q as B operands: lane (q, half) holds Q[q][16 s + 8 half .. +7], s = 0..7.  Lanes without a row of their own repeat the tile's first and
+  // are not written out.
+  bf16x8 qf[8];
+  {
+    const bf16* qrow = q + ((size_t)my_row * n_q_heads + head) * DH + 8 * half;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + 16 * s));
+    }
+  }
+
   stage_k(buf0);
-  clear_v(t_begin * BKV);
-  stage_v(buf0, 0, 8);
+  stage_v(buf0, 0, 8, sel_of(t_begin * BKV));
   if (t_begin + 1 < t_end) fetch((t_begin + 1) * BKV, second_tile);
   __syncthreads();
   // step i (tile t = t_begin + i) multiplies buffer i % 2; meanwhile it stages tile t + 1 into the other buffer
@@ -369,8 +368,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     } else {
       if (has_next) {
         stage_k(other);
-        clear_v(kv0 + BKV);
-        stage_v(other, 0, 8);
+        stage_v(other, 0, 8, sel_of(kv0 + BKV));
       }
       if (has_next2) fetch(kv0 + 2 * BKV, asked);
     }
@@ -427,7 +425,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
         asm volatile("" : "+v"(psum));   // added up here: put off, the 32 weights stayed in registers over the second product
         if constexpr (V_TOO) {
           __builtin_amdgcn_sched_barrier(0);
-          if (b == 0) stage_v(other, 4 * u, 4 * u + 4);
+          if (b == 0) stage_v(other, 4 * u, 4 * u + 4, whole);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -439,17 +437,18 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
       if (i + kFragAhead < 16) vf[i % kFragAhead] = v_frag(i + kFragAhead);
       if constexpr (steady) {
         if constexpr (K_TOO)
-          if (i % 2 == 0 && i < 2 * KPER) rk[i / 2] = k_chunk(row2, i / 2);
+          if (i % 2 == 0 && i < 2 * KPER) rk[i / 2] = k_chunk(row2, i / 2, 1);
         if constexpr (V_TOO)
-          if (i % 2 == 0 && i >= 2 * KPER && i < 2 * KPER + 8) rv[i / 2 - KPER] = v_chunk_of(row2, i / 2 - KPER);
+          if (i % 2 == 0 && i >= 2 * KPER && i < 2 * KPER + 8) rv[i / 2 - KPER] = v_chunk_of(row2, i / 2 - KPER, 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     __syncthreads();   // tile t fully consumed, tile t + 1 fully staged
   };
   int t = t_begin;
+  const int t_whole = by_group ? min(t_end, (last_pos + 1) / BKV) : 0;   // tiles before it are whole ones
   auto steady_tiles = [&](auto how) __attribute__((always_inline)) {
-    for (; t + 3 < t_end && grouped((t + 3) * BKV); t += 2) {
+    for (; t + 3 < t_whole; t += 2) {
       tile_step(t, buf0, how);
       tile_step(t + 1, buf1, how);
     }

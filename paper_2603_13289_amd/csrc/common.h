@@ -94,7 +94,18 @@ struct KvGeom {
   int n_kv_heads, head_dim;
   int bs_shift;  // log2(block_size) when it is a power of two, else -1
   int last_pos;  // the last position that a sequence has room for
+  unsigned div_mul;   // position / block_size for positions of 31 bits: block_of
+  int div_shift;
 };
+
+// With l = div_shift = ceil(log2(block_size)) and div_mul = ceil(2^(31 + l) / block_size) = (2^(31 + l) + e) / block_size, e < block_size <= 2^l,
+// a position below 2^31 times div_mul over 2^(31 + l) is the quotient plus less than e / (block_size 2^l) < 1 / block_size: its floor is exact.
+inline void set_block_division(KvGeom* g) {
+  g->div_shift = 0;
+  while ((1ll << g->div_shift) < g->block_size) ++g->div_shift;
+  g->div_mul = (unsigned)(((1ull << (31 + g->div_shift)) + g->block_size - 1) / g->block_size);
+}
+__host__ __device__ inline int block_of(const KvGeom& g, int pos) { return (int)(((unsigned long long)(2u * (unsigned)pos) * g.div_mul) >> 32 >> g.div_shift); }
 
 // A row's position as attention takes it.  Every kernel that counts key tiles or chunks asks here: the ones that write partial results
 // and the ones that merge them have to agree where a position from device memory lies outside the cache.
