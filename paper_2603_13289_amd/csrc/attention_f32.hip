@@ -10,6 +10,10 @@
 // and values are requested before the current one's softmax, and the page they are on a block before that, so that no load waits
 // for a look-up.  Measured in a call, 384 rows x 4 heads of 64 x up to 384 keys: 146 us with one wavefront per (row, head) on the
 // vector ALUs, 15.1 with values and their pages looked up in the block that uses them, 12.2 now (188 rows: 15.3 -> 12.8).
+// GROUPED: a contiguous cache, or pages of 16, 32, 64, ... slots: the keys of a block lie one behind the other and its page is one scalar read.
+// Other pages look up every key.  Two look-ups a block, one between the products and the softmax for the next keys and one ahead of the
+// products for the values, are then the better chain: with both in one place 500 rows over 1000 keys on pages of 24 took 27.7 us instead
+// of 25.9 (heads of 128: 53.5 instead of 41.1).  GROUPED there: 19.1 (29.0); one block of 16 keys 6.4 -> 6.0 since the kernels are two.
 #include <climits>
 #include <type_traits>
 
@@ -19,7 +23,7 @@ namespace rc {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4a;
 
-template <int DH>
+template <int DH, bool GROUPED>
 __global__ void __launch_bounds__(DH == 64 ? 512 : 256, DH == 64 ? 4 : 2)
 attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, const ReqTable* __restrict__ table,
                 int fixed_seq, int total_rows, const float* __restrict__ k_pool, const float* __restrict__ v_pool, KvGeom g,
@@ -45,7 +49,8 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
     n_valid = min(16, total_rows - r0);
   }
   const bool q_ok = qi < n_valid;
-  const int my_pos = q_ok ? pos_in_cache(row_pos[r0 + qi], g.last_pos) : -1;
+  const int own_pos = pos_in_cache(row_pos[r0 + min(qi, n_valid - 1)], g.last_pos);   // of every lane: under a condition it is waited for at once
+  const int my_pos = q_ok ? own_pos : -1;
   int last_pos = my_pos, first_pos = q_ok ? my_pos : INT_MAX;   // the group's largest and smallest position
 #pragma unroll
   for (int o = 1; o < 16; o <<= 1) {
@@ -55,7 +60,7 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
   const float scale = 1.4426950408889634f / sqrtf((float)DH);   // scores in log2 units
   const float* qrow = q + ((size_t)(r0 + (q_ok ? qi : 0)) * n_q_heads + head) * DH;
   f32x4a fq[NB], fk[NB], acc[NB];
-  float fv[2][NB][4];   // V[key 4 kq + c][d]: the operand of instruction c, of this block and the next
+  float fv[GROUPED ? 2 : 1][NB][4];   // V[key 4 kq + c][d]: the operand of instruction c, of this block and the next
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
     fq[t] = q_ok ? *reinterpret_cast<const f32x4a*>(qrow + 16 * t + 4 * kq) * scale : f32x4a{0.f, 0.f, 0.f, 0.f};
@@ -64,15 +69,14 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
   float m_run = -INFINITY, l_run = 0.f;
   last_pos = __builtin_amdgcn_readfirstlane(last_pos);
   const int n_blocks = last_pos / 16 + 1;
-  // Pages of a multiple of 16 slots hold a block's keys one behind the other: its page is one scalar read, a block ahead of the loads
-  // that hang on it.  Other page sizes look every key up.  Keys past the last position repeat it.
-  const bool contig = g.max_blocks == 1, grouped = contig || g.bs_shift >= 4;
+  // Keys past the last position repeat it.  A block's page is read a block ahead of the loads that hang on it.
+  const bool contig = g.max_blocks == 1;
   const int32_t* const seq_table = g.block_table + (size_t)seq * g.max_blocks;
   auto page_of = [&](int kb) {
-    return grouped ? seq_table[contig ? 0 : min(min(kb, n_blocks - 1) * 16 >> g.bs_shift, g.max_blocks - 1)] : 0;
+    return GROUPED ? seq_table[contig ? 0 : min(min(kb, n_blocks - 1) * 16 >> g.bs_shift, g.max_blocks - 1)] : 0;
   };
   auto offset_of = [&](int kb, int j, int page) -> size_t {   // of key j of the block
-    if (!grouped) return kv_row_offset(g, seq, min(kb * 16 + j, last_pos), kvh);
+    if (!GROUPED) return kv_row_offset(g, seq, min(kb * 16 + j, last_pos), kvh);
     const int first = contig ? kb * 16 : kb * 16 & (g.block_size - 1);
     return (((size_t)min(max(page, 0), g.n_blocks - 1) * g.n_kv_heads + kvh) * g.block_size + first + min(j, last_pos - kb * 16)) * DH;
   };
@@ -96,11 +100,12 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
     const int first = page_of(wave);
     page = page_of(wave + NW);
     fetch_k(wave, first);
-    fetch_v(buf0, wave, first);
+    if constexpr (GROUPED) fetch_v(buf0, wave, first);
   }
   auto block = [&](auto buf, auto other, int kb) {
     constexpr int B = decltype(buf)::value;
     const int page2 = page_of(kb + 2 * NW);
+    if constexpr (!GROUPED) fetch_v(buf, kb, 0);
     f32x4a s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
     for (int t = 0; t < NB; t += 2)
@@ -111,7 +116,7 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
       }
     if (kb + NW < n_blocks) {
       fetch_k(kb + NW, page);
-      fetch_v(other, kb + NW, page);
+      if constexpr (GROUPED) fetch_v(other, kb + NW, page);
     }
     page = page2;
     s0 += s1;
@@ -173,9 +178,13 @@ attn_f32_kernel(const float* __restrict__ q, const int* __restrict__ row_pos, co
       }
     }
   };
-  for (int kb = wave; kb < n_blocks; kb += 2 * NW) {
-    block(buf0, buf1, kb);
-    if (kb + NW < n_blocks) block(buf1, buf0, kb + NW);
+  if constexpr (GROUPED) {
+    for (int kb = wave; kb < n_blocks; kb += 2 * NW) {
+      block(buf0, buf1, kb);
+      if (kb + NW < n_blocks) block(buf1, buf0, kb + NW);
+    }
+  } else {
+    for (int kb = wave; kb < n_blocks; kb += NW) block(buf0, buf0, kb);
   }
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
@@ -217,8 +226,10 @@ hipError_t launch_attention<float>(const float* q, const int* row_pos, const int
   // 16-row groups: at most two per query tile (32 rows) of the table
   const unsigned groups = table ? (unsigned)(2 * total_tiles) : (unsigned)((total_rows + 15) / 16);
   const dim3 grid(groups, (unsigned)n_q_heads);
-  if (g.head_dim == 64) attn_f32_kernel<64><<<grid, 512, 0, st>>>(q, row_pos, table, fixed_seq, total_rows, k_pool, v_pool, g, n_q_heads, out);
-  else attn_f32_kernel<128><<<grid, 256, 0, st>>>(q, row_pos, table, fixed_seq, total_rows, k_pool, v_pool, g, n_q_heads, out);
+  const bool grouped = g.max_blocks == 1 || g.bs_shift >= 4;   // measured both ways at the kernel
+  auto* const kernel = g.head_dim == 64 ? (grouped ? attn_f32_kernel<64, true> : attn_f32_kernel<64, false>)
+                                        : (grouped ? attn_f32_kernel<128, true> : attn_f32_kernel<128, false>);
+  kernel<<<grid, g.head_dim == 64 ? 512 : 256, 0, st>>>(q, row_pos, table, fixed_seq, total_rows, k_pool, v_pool, g, n_q_heads, out);
   return hipGetLastError();
 }
 
