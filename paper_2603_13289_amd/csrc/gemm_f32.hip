@@ -154,6 +154,10 @@ struct F32Rope {
   int n_q_heads;
 };
 
+// EARLY: where the row goes and its angles, a chain of three reads, are asked for ahead of the operands and behind them and not behind
+// the product: 7.4 -> 6.8 us a launch of 384 x 512 x 256.  They hold twelve registers over it (108 instead of 96), which costs the fifth
+// workgroup of a compute unit: takes_early.
+template <bool EARLY>
 __global__ void __launch_bounds__(256)
 gemm_f32_rope_kernel(F32Gemm g, F32Rope p) {
   const int m = live_count(g.m, g.m_live), m0 = blockIdx.y * 16;
@@ -163,17 +167,16 @@ gemm_f32_rope_kernel(F32Gemm g, F32Rope p) {
   const int head = (int)blockIdx.x / per_head, c0 = ((int)blockIdx.x % per_head) * 16;
   f32x4m lo, hi;
   const int row = m0 + r, i = c0 + 4 * (lane >> 4), n_kv = p.geom.n_kv_heads;
-  // Where the row goes and its angles, for the wavefront that finishes: asked for ahead of the operands and behind them, not behind
-  // the product (a chain of three reads): 7.4 -> 6.8 us a launch of 384 x 512 x 256.
-  int pos = 0, rr = 0;
   const bool finishes = wave == 0 && row < m;
-  if (finishes) {
-    pos = p.row_pos[row];
-    rr = p.row_req[row];
-  }
+  int pos = 0, rr = 0;
   size_t off = 0;
   f32x4m cs01 = {0.f, 0.f, 0.f, 0.f}, cs23 = cs01;
-  f32_block<true>(g, f32_a_row(g, m0 + r, m), f32_w_row(g, head * dh + c0 + r), f32_w_row(g, head * dh + half + c0 + r), &lo, &hi, [&] {
+  auto find_row = [&] {
+    if (!finishes) return;
+    pos = p.row_pos[row];
+    rr = p.row_req[row];
+  };
+  auto find_place = [&] {
     if (!finishes) return;
     if (head < p.n_q_heads + n_kv) {
       const f32x4m* cs = reinterpret_cast<const f32x4m*>(p.rope_tab + (size_t)pos * half + i);
@@ -182,7 +185,15 @@ gemm_f32_rope_kernel(F32Gemm g, F32Rope p) {
     }
     if (head >= p.n_q_heads)
       off = kv_row_offset(p.geom, p.table->r[rr & kRowReqMask].dst_seq, pos, head < p.n_q_heads + n_kv ? head - p.n_q_heads : head - p.n_q_heads - n_kv);
+  };
+  if constexpr (EARLY) find_row();
+  f32_block<true>(g, f32_a_row(g, m0 + r, m), f32_w_row(g, head * dh + c0 + r), f32_w_row(g, head * dh + half + c0 + r), &lo, &hi, [&] {
+    if constexpr (EARLY) find_place();
   });
+  if constexpr (!EARLY) {
+    find_row();
+    find_place();
+  }
   if (!finishes) return;
   const bool write_cache = (rr & kRowNoCacheWrite) == 0;
   if (head >= p.n_q_heads && !write_cache) return;
@@ -326,6 +337,11 @@ hipError_t launch_gemm_f32_normed(const float* h, const float* gain, float eps, 
   return launch_f32(F32Gemm{h, w, w2, nullptr, n, n, gain, eps, last_of, c, m, n, k, n, (int)epi, m_live}, st);
 }
 
+// The chain shows where the chip has room for all workgroups at once (four each to 256 compute units).  In a fuller launch other workgroups hide it
+// and the fifth counts, the more the shorter the product: 512 columns of K = 256, 2048 / 4096 rows 20.6 / 35.2 us early, 19.2 / 31.0 late; 1024 of
+// K = 512 54.9 / 101.6 and 54.0 / 100.2; 1536 of K = 1024 144.3 / 281.9 and 144.7 / 282.5, so long products stay with the early form.
+static bool takes_early(long workgroups, int k) { return workgroups <= 1024 || k >= 1024; }
+
 hipError_t launch_gemm_f32_qkv_rope(const float* h, const float* gain, float eps, const float* wq, const float* wk,
                                     const float* wv, int m, int k, const int* row_pos, const int* row_req,
                                     const ReqTable* table, const float2* rope_tab, float* q_out, float* k_pool, float* v_pool,
@@ -334,7 +350,8 @@ hipError_t launch_gemm_f32_qkv_rope(const float* h, const float* gain, float eps
   const int nq = n_q_heads * geom.head_dim, nkv = geom.n_kv_heads * geom.head_dim, n = nq + 2 * nkv;
   const F32Gemm g = {h, wq, wk, wv, nq, nq + nkv, gain, eps, nullptr, nullptr, m, n, k, n, EPI_STORE_F32, m_live};
   const F32Rope p = {row_pos, row_req, table, rope_tab, q_out, k_pool, v_pool, k_pre_pool, geom, n_q_heads};
-  gemm_f32_rope_kernel<<<dim3((unsigned)(n / 32), (unsigned)((m + 15) / 16)), 256, 0, st>>>(g, p);
+  const dim3 grid((unsigned)(n / 32), (unsigned)((m + 15) / 16));
+  (takes_early((long)grid.x * grid.y, k) ? gemm_f32_rope_kernel<true> : gemm_f32_rope_kernel<false>)<<<grid, 256, 0, st>>>(g, p);
   return hipGetLastError();
 }
 
