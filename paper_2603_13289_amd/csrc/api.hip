@@ -183,15 +183,15 @@ int est_row_pos(const ReqDev& r, int i) {
 // split when its range is longer than one chunk) are priced by a list-scheduling estimate: the busier of "the longest
 // workgroup" and "all work spread over the slots", plus half a longest workgroup for the ragged end of a launch with
 // more workgroups than slots,
-// plus the merge pass over the partial results of the split rows.  Units: one KV tile step of one slot (~2.2 us).
+// plus the merge pass over the partial results of the split rows.  Units: one KV tile step of one slot, which took 2.2 us in the tile kernel
+// that the constants were fitted to.
 // Measured on the 2048 + 16384-token workload: its sparse layers (1639 selected rows, up to 288 KV tiles each) take
 // 520 us unsplit and 182 + 33 us with chunks of 32; the dense layer and the short prefix-only layers are best left whole.
 // A decoding step (one row per sequence, 8 KV heads, 80 KV tiles) gets chunks of 4: 160 workgroups instead of 40.
-// All of this is measured on the tile kernel (attn_mfma_kernel), at the 2.2 us a step that it took then (1.3 alone on a compute unit and 2.0
-// beside another workgroup now).  The prices stay: another chunk length rounds the weights of a row at other scales, which over 32
-// layers moves the outputs by 0.7 to 1.9 % (2500 prompt rows: 80.3 us + 16.6 of merge in chunks of 16, 72.5 whole).
-// Phases whose requests have one row each run attn_decode_kernel (0.87 us a tile step and about six of them fixed, over 40 to 320 tiles of one sequence) and are priced by the same constants:
-// the chunks they get are the ones it was measured with, not the best of a fit of its own.
+// The tile kernel has become faster since (a step takes 1.3 us alone on a compute unit and 2.0 beside another workgroup), so that these prices cut
+// some ranges that would be faster whole (2500 prompt rows: 80.3 us + 16.6 of merge in chunks of 16, 72.5 whole).  They stay: another
+// chunk length rounds the weights of a row at other scales, which over 32 layers moves the outputs by 0.7 to 1.9 %.  Phases whose requests have one
+// row each run attn_decode_kernel (0.87 us a tile step and about six of them fixed) and are priced by the same constants.
 constexpr float kWgFixedSteps = 4.f;       // fixed cost of a workgroup
 constexpr float kMergeFixedSteps = 3.5f;   // launch of the merge kernel
 constexpr float kMergeBytesPerStep = 8.8e6f;

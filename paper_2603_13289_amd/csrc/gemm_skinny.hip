@@ -406,11 +406,14 @@ hipError_t launch_gemm_few_rows_parts(const bf16* a, const bf16* w, const bf16* 
 bool gemm_skinny_applies(int m, int n, int k) { return m >= 1 && m <= 32 && n % 16 == 0 && k % (kSkinnyWaves * 32) == 0; }
 
 // Workgroups of 32 columns.  Every workgroup reads all rows of activations, from the L2; half as many workgroups read half as much, but
-// have half the wavefronts to keep weights coming.  Where 16 columns each make more than one workgroup but fewer than two to a
-// compute unit, some units have twice the work of others, and the uneven round goes as well: from five rows on, with K = 4096 from twelve
-// (5120 x 27648, 5 / 16 / 32 rows: 73.0 / 98.5 / 146 -> 64.6 / 78.2 / 99.3 us; 7168 x 5120 17.7 / 23.0 / 32.6 -> 16.3 / 18.9 /
-// 23.6; 6144 x 4096, 10 / 16 / 32 rows: 15.2 / 17.2 / 23.8 -> 15.2 / 15.7 / 17.7).  Two even rounds or more: from 24 rows on (32768 x 4096,
-// 17 / 24 / 32 rows: 69.7 / 78.3 / 88.0 -> 71.9 / 74.0 / 75.5).  Fewer than 160 would leave the chip idle (4096 x 14336, 16 rows: 29.8 -> 41.8).
+// have half the wavefronts to keep weights coming.  Gain over 16 columns each, weights from HBM, K = 4096 to 14336:
+//   up to 4096 columns (one round of 16-column workgroups)    0.62 to 0.84x: half the chip idle
+//   4608 (144 wide workgroups)                                1.07 to 1.46x from 5 rows on; left to the old form
+//   5120 to 7168 (a second, uneven round of narrow ones)      from 5 rows on 1.003 to 1.46x with K > 4096, with K = 4096 0.999 to 1.13x at 5 rows,
+//                                                             1.14x and more from 12 on
+//   8192 to 32768 (at least 256 wide ones, rounds of either   at 5 rows 0.75 to 1.03x; at 24 and 32 rows 1.02 to 1.40x, the least of it at 9216 to
+//   form even or not)                                         12288 (1.02 to 1.11x), where the last round of both is uneven
+// 5120 x 27648, 5 / 16 / 32 rows: 73.0 / 98.5 / 146 -> 64.6 / 78.2 / 99.3 us.  The line lies where no size of these lost.
 static bool takes_wide(int m, int n, int k) {
   const int wgs = n / 32;
   if (n % 32 != 0 || k < kSkinnyWaves * 32 * 16 || wgs < 160) return false;

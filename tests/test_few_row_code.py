@@ -1,5 +1,6 @@
-"""The generated code of the kernels that live on loads in flight, the few-row GEMM and decode attention (no GPU): nothing goes through
-scratch memory, and their main loops never wait for all the loads they have under way."""
+"""The generated code of the kernels that live on loads in flight, the few-row GEMMs and decode attention (no GPU): nothing goes through
+scratch memory, and their main loops never wait for all the loads they have under way.  The other attention kernels and the float q|k|v
+product: nothing through scratch memory."""
 import os
 import re
 import subprocess
@@ -41,6 +42,7 @@ def _main_loops(lines):
 
 
 @pytest.mark.parametrize("source,name,count,loops", [("gemm_skinny.hip", "gemm_skinny_kernel", 14, 1),
+                                                     ("gemm_skinny.hip", "gemm_wide_few_rows_kernel", 4, 1),
                                                      ("attention_mfma.hip", "attn_decode_kernel", 2, 2)])
 def test_loads_stay_in_flight(tmp_path, source, name, count, loops):
     kernels = _kernels(tmp_path, source, name)
@@ -52,7 +54,10 @@ def test_loads_stay_in_flight(tmp_path, source, name, count, loops):
         assert all(waits and min(waits) > 0 for waits in found), (k, found)
 
 
-def test_parts_kernel_has_no_scratch(tmp_path):
-    kernels = _kernels(tmp_path, "gemm_skinny.hip", "gemm_few_rows_parts_kernel")
-    assert len(kernels) == 4
+@pytest.mark.parametrize("source,name,count", [("gemm_skinny.hip", "gemm_few_rows_parts_kernel", 4), ("attention_mfma.hip", "attn_mfma_kernel", 8),
+                                               ("attention_mfma.hip", "attn_merge_kernel", 2), ("attention_f32.hip", "attn_f32_kernel", 4),
+                                               ("gemm_f32.hip", "gemm_f32_rope_kernel", 2)])
+def test_no_scratch(tmp_path, source, name, count):
+    kernels = _kernels(tmp_path, source, name)
+    assert len(kernels) == count
     assert all(scratch == 0 for _, scratch in kernels.values())

@@ -18,13 +18,19 @@ def test_page_sizes_give_the_same_bits(group, keys):
     _same_bits(group, keys, 128, torch.bfloat16, 1e-2)   # weights and outputs rounded to bf16, as in the stage test
 
 
+@pytest.mark.parametrize("group", [1, 4, 5, 8])
+@pytest.mark.parametrize("keys", [1601, 2048])   # more than 24 key tiles: late rows in chunks of four tiles, merged
+def test_page_sizes_give_the_same_bits_in_chunks(group, keys):
+    _same_bits(group, keys, 128, torch.bfloat16, 1e-2, workspace=True)
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("keys", [5, 16, 17, 64, 65, 128, 129, 256, 257, 300, 1000])
 def test_page_sizes_give_the_same_bits_f32(dh, keys):
     _same_bits(2, keys, dh, torch.float32, 2e-5)   # as in the stage test
 
 
-def _same_bits(group, keys, DH, td, tol):
+def _same_bits(group, keys, DH, td, tol, workspace=False):
     from paper_2603_13289_amd import binding as rc
     g = torch.Generator(device="cuda")
     g.manual_seed(100 * group + keys)
@@ -51,7 +57,8 @@ def _same_bits(group, keys, DH, td, tol):
             table = torch.zeros((1, 1), dtype=torch.int32, device="cuda")
         cache = rc.PagedKV.from_pools([pools[0]], [pools[1]], table, rc.RC_BF16 if td == torch.bfloat16 else rc.RC_F32)
         out = torch.zeros((n, nq, DH), dtype=td, device="cuda")
-        rc.rc_sparse_attention(q, pos.cuda(), n, nq, cache.layer(0), 0, out, None)
+        ws = rc.alloc_workspace(rc.rc_sparse_attention_workspace_bytes(n, nq, cache.layer(0))) if workspace else None
+        rc.rc_sparse_attention(q, pos.cuda(), n, nq, cache.layer(0), 0, out, ws)
         torch.cuda.synchronize()
         outs.append(out)
     for page, out in zip(PAGES[1:], outs[1:]):

@@ -110,3 +110,36 @@ def test_influence_added_by_the_merge(group, chunk):
             continue
         # the layers behind the first see attention outputs rounded to bf16 from other partial sums
         assert rel_err(to_np(got[1][b]), to_np(got[0][b])) <= 1e-2, POSITIONS[b]
+
+
+@pytest.mark.parametrize("scores", [False, True])
+def test_more_blocks_than_the_lds_table_holds(scores):
+    """Pages of one slot, a range in one piece: 2049 and more blocks are looked up in memory, fewer are kept in LDS, the same bits."""
+    from paper_2603_13289_amd import binding as rc
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2048)
+    sh, model = _model(rc, g, 4)
+    positions, size = [2047, 2048, 2300, 40], 2304
+    n = len(positions)
+    k, v = (torch.empty((LAYERS, n, NKV, size, DH), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    x = torch.empty((n, D), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    outs = []
+    for page in (16, 1):
+        table = torch.randperm(n * size // page, generator=g, device="cuda").to(torch.int32).view(n, size // page).contiguous()
+        pools = [torch.empty((LAYERS, n * size // page, NKV, page, DH), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        for pool, rows in zip(pools, (k, v)):
+            pool[:, table.flatten().long()] = rows.view(LAYERS, n, NKV, size // page, page, DH).transpose(2, 3).reshape(LAYERS, -1, NKV, page, DH)
+        cache = rc.PagedKV.from_pools(list(pools[0].unbind(0)), list(pools[1].unbind(0)), table, rc.RC_BF16)
+        s_inf = [torch.zeros(p + 1, dtype=torch.float32, device="cuda") for p in positions]
+        reqs = [rc.DecodeReq(x[b], p, b, None, s_inf[b] if scores else None) for b, p in enumerate(positions)]
+        logits = torch.zeros((n, 256), dtype=torch.float32, device="cuda")
+        rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, 1000)
+        try:
+            rc.rc_decode_step(model, reqs, cache, logits, rc.alloc_workspace(rc.rc_decode_workspace_bytes(model, reqs)))
+        finally:
+            rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, 0)
+        torch.cuda.synchronize()
+        outs.append([logits] + s_inf + [cache.read(w, l, b, 1, start=p) for w in ("k", "v") for l in range(LAYERS) for b, p in enumerate(positions)])
+    assert bool(torch.isfinite(outs[0][0]).all())
+    for one, two in zip(*outs):
+        assert torch.equal(one, two)

@@ -263,9 +263,8 @@ def test_sparse_attention_wide_score_range(case, split):
 
 @pytest.mark.parametrize("split", [False, True])
 def test_sparse_attention_over_more_blocks_than_the_lds_table_holds(split):
-    """A paged cache whose sequence spans 2063 blocks of 16 tokens.  A workgroup keeps the block-table slice of its KV
-    range in LDS when it has at most 2048 entries; an unsplit query tile near the end of this sequence needs more and
-    looks its blocks up in global memory instead.  With a workspace the range is cut into chunks whose slices fit."""
+    """A paged cache whose sequence spans 2063 blocks of 16 tokens, whole and cut into chunks.  The tile kernel, which this call runs, looks the
+    blocks of a tile up as it goes; the decode kernel, which keeps up to 2048 of them in LDS, is in test_gpu_decode_attention.py."""
     rc = _rc()
     hq, hkv, dh, T = 8, 2, 128, 33001
     cache, ks, vs = _cache("bf16", hkv, dh, [5, T], 16, "att_long")

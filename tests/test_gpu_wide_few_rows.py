@@ -36,22 +36,24 @@ def test_rows_in_company_have_the_bits_of_four_rows(n, k, rows, epilogue):
 
 @pytest.mark.parametrize("n", [12, 17, 32])
 def test_rotated_and_scattered_rows(n):
-    """q|k|v of 6144 columns in a decoding step: the first layer's rows in the cache, and the logits behind one layer."""
+    """q|k|v of 6144 columns in a decoding step: the first layer's rows in the cache, bit for bit, and the second layer's: with O the identity, no
+    feed-forward sum and KV ranges in one piece its inputs are the embeddings and the first layer's attention, which shows every rotated query."""
     from paper_2603_13289_amd import binding as rc
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     d, ffn, nq, nkv, page = 4096, 256, 32, 8, 16
     rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
     ones = torch.ones(d, dtype=torch.bfloat16, device="cuda")
-    sh = SimpleNamespace(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ffn=ffn, vocab=256, rope_base=1e6,
+    sh = SimpleNamespace(n_layers=2, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ffn=ffn, vocab=256, rope_base=1e6,
                          rms_eps=1e-5, dtype="bf16")
-    layer = dict(wq=rnd(nq * 128, d), wk=rnd(nkv * 128, d), wv=rnd(nkv * 128, d), wo=rnd(d, nq * 128), w_gate=rnd(ffn, d),
-                 w_up=rnd(ffn, d), w_down=rnd(d, ffn), g_attn=ones, g_ffn=ones)
-    model = rc.Model(sh, [layer], ones, rnd(256, d))
+    layers = [dict(wq=rnd(nq * 128, d), wk=rnd(nkv * 128, d), wv=rnd(nkv * 128, d), wo=torch.eye(d, dtype=torch.bfloat16, device="cuda"),
+                   w_gate=rnd(ffn, d), w_up=rnd(ffn, d), w_down=torch.zeros((d, ffn), dtype=torch.bfloat16, device="cuda"), g_attn=ones,
+                   g_ffn=ones) for _ in range(2)]
+    model = rc.Model(sh, layers, ones, rnd(256, d))
     rows = [1 + 7 * b for b in range(n)]
     need = max(rows) // page + 1
     table = torch.randperm(n * need, generator=g, device="cuda").to(torch.int32).view(n, need).contiguous()
-    k, v = (torch.empty((1, n * need, nkv, page, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    k, v = (torch.empty((2, n * need, nkv, page, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
     x = torch.empty((n, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
 
     def step(groups):
@@ -67,8 +69,12 @@ def test_rotated_and_scattered_rows(n):
         torch.cuda.synchronize()
         return kk, vv, pre, logits
 
-    together, four = step(n), step(4)
+    rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, 1000)
+    try:
+        together, four = step(n), step(4)
+    finally:
+        rc.rc_tune_set(rc.RC_TUNE_ATTN_CHUNK_TILES, 0)
     for a, b in zip(together[:3], four[:3]):
         assert torch.equal(a, b)
-    assert not torch.equal(together[0], k)
+    assert not torch.equal(together[0][0], k[0]) and not torch.equal(together[0][1], k[1])
     assert rel_err(to_np(together[3]), to_np(four[3])) <= 2e-2
