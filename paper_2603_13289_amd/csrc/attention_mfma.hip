@@ -14,7 +14,8 @@
 // so each operand is one 16-byte LDS read.
 //
 // LDS rows of K are padded by 16 bytes (272 apart), 16-byte pieces of V^T rows change places by the row, so that operand fetches
-// and writes are free of bank conflicts.  K/V rows come from the paged cache through the block table, one tile ahead in registers
+// and writes are free of bank conflicts (SQ_LDS_BANK_CONFLICT 0; with pieces exchanged by pairs of rows it was 14 % of the LDS cycles, 4096 queries over
+// 8000 keys 407 us instead of 401).  K/V rows come from the paged cache through the block table, one tile ahead in registers
 // and one tile ahead in a second pair of LDS buffers, so a tile costs one barrier.
 //
 // What bounds it: a tile step is a chain of S^T, softmax and O^T in which the LDS reads of the products, the LDS writes of the staging and
@@ -89,8 +90,8 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   // kernel runs out of registers.  In a group of one to three query heads the wavefronts beyond the group only take
   // their share of the staging; they multiply zeros for head 0 of the group and write nothing.
   constexpr int NW = G < 4 ? 4 : G;
-  // K rows are 256 + 16 bytes apart.  With 64 banks of 4 bytes, the 16 lanes that fetch the same 16-byte chunk of 16 consecutive rows
-  // then hit every bank exactly once, and every LDS address of K is a per-thread base plus a compile-time constant.
+  // K rows are 256 + 16 bytes apart.  Eight lanes (a cycle: 128 bytes) that fetch the same 16-byte chunk of consecutive rows then hit
+  // every bank exactly once, and every LDS address of K is a per-thread base plus a compile-time constant.
   // Two K and two V^T buffers: tile t lives in buffer t % 2 and tile t + 1 is staged while tile t is multiplied,
   // so one barrier per tile suffices.
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_attn[];
@@ -181,7 +182,11 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
   constexpr int NS = G == 8 ? 512 : 256, KSTEP = NS / 16, KPER = BKV / KSTEP;
   const bool stages_k = NW * 64 == NS || wave * 64 < NS, stages_v = NW == 4 || wave < 4;   // wave-uniform
   const int krow0 = tid >> 4, kch = tid & 15;      // K: row, 16-byte chunk
-  const int vquad = tid >> 4, vdch = tid & 15;     // V: quad of 4 keys, chunk of 8 d
+  // V: quad of 4 keys, chunk of 8 d.  Eight neighbouring lanes have 128 bytes of a row; sixteen, in two quads 8 keys apart, write half a
+  // row of V^T each in 128 different bytes (below).
+  auto quad_of = [](int th) __attribute__((always_inline)) { return (th >> 6) * 4 + ((th >> 5) & 1) + ((th >> 2) & 2); };
+  auto dch_of = [](int th) __attribute__((always_inline)) { return (th & 7) + ((th >> 1) & 8); };
+  const int vquad = quad_of(tid), vdch = dch_of(tid);
   // the tile fetched during step t is staged during step t + 1 and multiplied in step t + 2
   uint4 rk[KPER], rv[4];
   // A lane looks up the pool row (of DH elements) of one key of a tile.  In blocks of 16, 32, 64, ... slots the 16 keys of a group lie
@@ -234,29 +239,26 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     if (stages_v) {
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
-        rv[kk] = *reinterpret_cast<const uint4*>(vp + (size_t)(unsigned)__shfl((int)row, ((th >> 4) * 4 + kk) & 63, 64) * (DH * 2) + (th & 15) * 16);
+        rv[kk] = *reinterpret_cast<const uint4*>(vp + (size_t)(unsigned)__shfl((int)row, (quad_of(th) * 4 + kk) & 63, 64) * (DH * 2) + dch_of(th) * 16);
     }
   };
   // V transposed: key = 16 grp + 8 a + 4 h + c goes to column 16 grp + 8 h + 4 a + c; a quad shares (grp, a, h).
-  // In LDS, 16-byte chunk c of V^T row d is chunk c ^ (d/2 & 7) ^ (d/16) of row d ^ (d/8 & 1): the sixteen rows of an operand fetch
-  // then meet all banks once, and so do the writes of a wavefront, which has four quads of sixteen d / 8.
-  // Row pair (2 m, 2 m + 1) of a thread's eight d: chunk v_chunk ^ m; odd d / 8 have the two rows exchanged.
-  const int vgrp = vquad >> 2, v_odd = vdch & 1;
-  const int v_chunk = (2 * vgrp + (vquad & 1)) ^ (4 * v_odd) ^ (vdch >> 1);
+  // In LDS, 16-byte chunk c of V^T row d is chunk c ^ (d & 7) ^ (d/8 & 7): eight rows of an operand fetch then meet all 128 bytes of a cycle
+  // once, and so do sixteen lanes that write.
+  const int vgrp = vquad >> 2;
+  const int v_chunk = (2 * vgrp + (vquad & 1)) ^ (vdch & 7);
   unsigned char* const k_wr = lds_k + krow0 * KROW + kch * 16;
-  const unsigned v_wr = 2 * K_TILE_BYTES + vdch * 8 * VROW + 16 * v_chunk + 8 * ((vquad >> 1) & 1);   // chunk ^ m: bits 4-6 of the address
-  // byte select: the low halves of two words (even d) or the high ones, for a thread's first and second row of a pair
-  const uint32_t v_sel0 = v_odd ? 0x07060302u : 0x05040100u, v_sel1 = v_odd ? 0x05040100u : 0x07060302u;
+  const unsigned v_wr = 2 * K_TILE_BYTES + vdch * 8 * VROW + 16 * v_chunk + 8 * ((vquad >> 1) & 1);   // chunk ^ e: bits 4-6 of the address
   // The selects of a thread's keys 0, 1 and 2, 3.  Values behind the last position become zeros (byte select 12): what lies there may be no
   // finite number, and is not to be multiplied by a weight of 0.
-  struct Sel { uint32_t lo0, lo1, hi0, hi1; };
-  const Sel whole = {v_sel0, v_sel1, v_sel0, v_sel1};
+  struct Sel { uint32_t lo0, lo1, hi0, hi1; };   // byte selects: the low halves of two words (even d) or the high ones
+  const Sel whole = {0x05040100u, 0x07060302u, 0x05040100u, 0x07060302u};
   auto sel_of = [&](int kv0) __attribute__((always_inline)) -> Sel {
     Sel s = whole;
     if (kv0 + BKV - 1 > last_pos) {   // uniform
       int th = tid;
       asm volatile("" : "+v"(th));
-      const int n = last_pos - kv0 - (th >> 4) * 4;   // keys 0 .. n
+      const int n = last_pos - kv0 - quad_of(th) * 4;   // keys 0 .. n
       const uint32_t lo = n < 0 ? 0u : (n < 1 ? 0xffffu : ~0u), hi = n < 2 ? 0u : (n < 3 ? 0xffffu : ~0u);
       s = {(s.lo0 & lo) | (0x0c0c0c0cu & ~lo), (s.lo1 & lo) | (0x0c0c0c0cu & ~lo), (s.hi0 & hi) | (0x0c0c0c0cu & ~hi), (s.hi1 & hi) | (0x0c0c0c0cu & ~hi)};
     }
@@ -283,12 +285,12 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
       uint2 pk;
       pk.x = __builtin_amdgcn_perm(w[1][m], w[0][m], (e & 1) ? sel.lo1 : sel.lo0);
       pk.y = __builtin_amdgcn_perm(w[3][m], w[2][m], (e & 1) ? sel.hi1 : sel.hi0);
-      *reinterpret_cast<uint2*>(lds_attn + (v_wr ^ (16 * m)) + VOFF + e * VROW) = pk;
+      *reinterpret_cast<uint2*>(lds_attn + (v_wr ^ (16 * e)) + VOFF + e * VROW) = pk;
     }
   };
-  // operand fetch addresses: K block b, dh step s -> k_rd + b*32*KROW + s*32 ; V^T block db, key step tt -> (v_rd ^ 32 (tt ^ db)) + db*32*VROW
+  // operand fetch addresses: K block b, dh step s -> k_rd + b*32*KROW + s*32 ; V^T block db, key step tt -> (v_rd ^ 32 (tt ^ 2 db)) + db*32*VROW
   const unsigned char* const k_rd = lds_k + ql * KROW + half * 16;
-  const unsigned v_rd = 2 * K_TILE_BYTES + (ql ^ ((ql >> 3) & 1)) * VROW + 16 * (half ^ ((ql >> 1) & 7) ^ (ql >> 4));
+  const unsigned v_rd = 2 * K_TILE_BYTES + ql * VROW + 16 * (half ^ (ql & 7) ^ (ql >> 3));
 
   const int n_kv_tiles = last_pos / BKV + 1;
   const bool is_split = sp.n_chunks > 1 && split_tile >= 0 && n_kv_tiles > sp.long_thr;
@@ -353,7 +355,7 @@ attn_mfma_kernel(const bf16* __restrict__ q, const int* __restrict__ row_pos, co
     }
     // the first V^T fragments do not depend on the softmax: their LDS reads run under it
     auto v_frag = [&](int i) {     // step i: head-dim block i & 3, key step i >> 2
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds_attn + (v_rd ^ (32 * ((i & 3) ^ (i >> 2)))) + VOFF + (i & 3) * 32 * VROW));
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds_attn + (v_rd ^ (32 * ((2 * (i & 1)) ^ (i >> 2)))) + VOFF + (i & 3) * 32 * VROW));
     };
     bf16x8 vf[kFragAhead];
 #pragma unroll
