@@ -24,11 +24,11 @@
 // matrix instructions of O^T, in a main loop without conditions.  In a bunch, with the staging between the products of S^T, the loads behind
 // it and a table look-up of its own in front of each load, a step took 4000 cycles alone on a compute unit and 5600 with two workgroups; now
 // 2900 and 3350.  Per launch in a train of twenty, before that loop -> now, all on one card: 4096 queries over 8000 keys, 32 heads on 8: 16-token
-// pages 494 -> 387 us (1030 TFLOP/s), contiguous 389 -> 387, pages of 24 791 -> 437; 40 heads on 8: 809 -> 567 and 738 -> 566 contiguous.
-// 32 queries over 4096 keys 135 -> 75 (pages of 24: 211 -> 102), 100 over 264 15.8 -> 11.6 (contiguous 12.3 -> 11.6).
+// pages 515 -> 407 us (980 TFLOP/s), contiguous 417 -> 407, pages of 24 791 -> 463; 40 heads on 8: 810 -> 587 and 739 -> 589 contiguous.
+// 32 queries over 4096 keys 135 -> 76 (pages of 24: 209 -> 105), 100 over 264 15.8 -> 11.8 (contiguous 12.3 -> 11.8).
 // Ranges of a tile or two are bound by the chain to the first product and by instructions that are fetched for the first time, so what runs before it
 // has few branches (look-ups by a multiplication, every lane loads a row of Q) and few links: the first block look-ups do not hang on the rows'
-// positions, Q is asked for behind K and V.  61 queries over 61 keys: 16-token pages 7.70 -> 6.74, contiguous 6.84 -> 6.61 (7.10 without those).
+// positions, Q is asked for behind K and V.  61 queries over 61 keys: 16-token pages 7.68 -> 6.83, contiguous 6.84 -> 6.73 (7.11 without those).
 // KV tiles entirely above the tile's last query position are skipped; the causal mask is applied
 // only in tiles that reach above the tile's first query position.  Workgroups are issued longest
 // first over the whole launch (KV head fastest, query tiles by decreasing KV range).
