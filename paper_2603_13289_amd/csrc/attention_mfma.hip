@@ -14,8 +14,8 @@
 // so each operand is one 16-byte LDS read.
 //
 // LDS rows of K are padded by 16 bytes (272 apart), 16-byte pieces of V^T rows change places by the row, so that operand fetches
-// and writes are free of bank conflicts (SQ_LDS_BANK_CONFLICT 0; with pieces exchanged by pairs of rows it was 14 % of the LDS cycles, 4096 queries over
-// 8000 keys 407 us instead of 401).  K/V rows come from the paged cache through the block table, one tile ahead in registers
+// and writes are free of bank conflicts (SQ_LDS_BANK_CONFLICT 0; with pieces exchanged by pairs of rows it was 14 % of the LDS cycles and
+// 4096 queries over 8000 keys took 1.4 % longer).  K/V rows come from the paged cache through the block table, one tile ahead in registers
 // and one tile ahead in a second pair of LDS buffers, so a tile costs one barrier.
 //
 // What bounds it: a tile step is a chain of S^T, softmax and O^T in which the LDS reads of the products, the LDS writes of the staging and
